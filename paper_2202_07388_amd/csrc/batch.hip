@@ -52,51 +52,49 @@ struct Group {
     double* sc;                             // nr * B_SIZE
     int* fl;                                // nr * F_SIZE (inside one array for all groups)
     double* part;                           // nr * kPartStride
+    unsigned* tick;                         // nr * kTicketWords
     hipStream_t s;
 };
 
 // ---------------------------------------------------------------- batched map / finalise
 
 template <class F>
-__global__ __launch_bounds__(256) void bmap_kernel(long nunits, int Vh, F f, double* partials,
+__global__ __launch_bounds__(256) void bmap_kernel(Runs runs, F f, double* partials, unsigned* tickets,
+                                                   double* sc, int off, int fin, int k,
                                                    const int* fl, int gate)
 {
     const int r = blockIdx.y;
     if (gate >= 0 && !fl[r * F_SIZE + gate]) return;
     double acc[F::NS > 0 ? F::NS : 1];
 #pragma unroll
-    for (int k = 0; k < (F::NS > 0 ? F::NS : 1); ++k) acc[k] = 0.0;
-    for (long u = (long)blockIdx.x * blockDim.x + threadIdx.x; u < nunits;
-         u += (long)gridDim.x * blockDim.x)
-        f(unit_of(u, Vh), acc, r);
+    for (int j = 0; j < (F::NS > 0 ? F::NS : 1); ++j) acc[j] = 0.0;
+    for (unsigned n = blockIdx.x * 4 + (threadIdx.x >> 6); n < runs.nw; n += gridDim.x * 4) {
+        const Unit u = runs.unit(n);
+        if (runs.holds(u)) f(u, acc, r);
+    }
     if constexpr (F::NS > 0)
-        block_reduce_store<F::NS>(acc, partials + r * kPartStride + (long)blockIdx.x * F::NS);
-}
-
-__global__ __launch_bounds__(256) void bfinalize_kernel(const double* partials, int nblk, int ns,
-                                                        double* sc, int off, int op, int k,
-                                                        const int* fl, int gate)
-{
-    const int r = blockIdx.x;
-    if (gate >= 0 && !fl[r * F_SIZE + gate]) return;
-    finalize_body(partials + r * kPartStride, nblk, ns, sc + (long)r * B_SIZE + off, op, k);
+        grid_sums<F::NS>(acc, {partials + r * kPartStride, tickets + (long)r * kTicketWords,
+                               sc + (long)r * B_SIZE + off, fin, k},
+                         blockIdx.x, gridDim.x);
 }
 
 // launch f over every right-hand side of group G (gate: flag that must be set, or -1);
 // with F::NS > 0 the sums go through scalar program fin into sc[r][off ...]
 template <class F>
 int brun(const Group& G, const F& f, int gate, hipStream_t st, int off = 0, int fin = FIN_STORE,
-         int k = 0)
+         int k = 0, bool back = false)
 {
-    const long nunits = 3L * G.op->g.V;
-    const int nb = map_blocks(nunits);
-    bmap_kernel<F><<<dim3(nb, G.nr), 256, 0, st>>>(nunits, G.op->g.Vh, f, G.part, G.fl, gate);
+    const Runs runs = runs_of(G.op->g, false, back);
+    bmap_kernel<F><<<dim3(map_blocks<F::NS>(runs.nw), G.nr), 256, 0, st>>>(
+        runs, f, G.part, G.tick, G.sc, off, fin, k, G.fl, gate);
     QDW_LAUNCH_CHECK();
-    if constexpr (F::NS > 0) {
-        bfinalize_kernel<<<G.nr, 256, 0, st>>>(G.part, nb, F::NS, G.sc, off, fin, k, G.fl, gate);
-        QDW_LAUNCH_CHECK();
-    }
     return QDW_OK;
+}
+
+// the arrival counters of a group's reductions, zero before its first one
+__global__ void zero_tickets_kernel(unsigned* t, int n)
+{
+    for (int q = blockIdx.x * blockDim.x + threadIdx.x; q < n; q += gridDim.x * blockDim.x) t[q] = 0u;
 }
 
 // ---------------------------------------------------------------- functors (right-hand side r)
@@ -111,14 +109,13 @@ struct Fld {
 struct Init {
     static constexpr int NS = 1;
     Fld eta, x, rho;
-    int Vh;
     __device__ void operator()(const Unit& u, double* acc, int r) const
     {
         cx<double> e[4];
         const cx<double> z[4] = {{0, 0}, {0, 0}, {0, 0}, {0, 0}};
-        ld4<F64, double>(eta.at(r), Vh, u.par, u.g, u.i, e);
-        st4<F64, double>(x.at(r), Vh, u.par, u.g, u.i, z);
-        st4<F64, double>(rho.at(r), Vh, u.par, u.g, u.i, e);
+        ld4<F64, double>(eta.at(r), u, e);
+        st4<F64, double>(x.at(r), u, z);
+        st4<F64, double>(rho.at(r), u, e);
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc[0] += e[j].re * e[j].re + e[j].im * e[j].im;
     }
@@ -136,17 +133,17 @@ struct SapIn {
     static constexpr int NS = 0;
     Fld rho, rs, psis;
     const double* sc;
-    int Vh, V;
+    int V;
     __device__ void operator()(const Unit& u, double*, int r) const
     {
         const double s = sap_scale(sc + (long)r * B_SIZE, V);
         cx<double> v[4];
         const cx<double> z[4] = {{0, 0}, {0, 0}, {0, 0}, {0, 0}};
-        ld4<F64, double>(rho.at(r), Vh, u.par, u.g, u.i, v);
+        ld4<F64, double>(rho.at(r), u, v);
 #pragma unroll
         for (int j = 0; j < 4; ++j) v[j] = scale(v[j], s);
-        st4<SP, double>(rs.at(r), Vh, u.par, u.g, u.i, v);
-        st4<SP, double>(psis.at(r), Vh, u.par, u.g, u.i, z);
+        st4<SP, double>(rs.at(r), u, v);
+        st4<SP, double>(psis.at(r), u, z);
     }
 };
 
@@ -156,15 +153,15 @@ struct SapOut {
     static constexpr int NS = 0;
     Fld psis, phi;
     const double* sc;
-    int Vh, V;
+    int V;
     __device__ void operator()(const Unit& u, double*, int r) const
     {
         const float a = (float)(1.0 / sap_scale(sc + (long)r * B_SIZE, V));
         cx<float> v[4];
-        ld4<SP, float>(psis.at(r), Vh, u.par, u.g, u.i, v);
+        ld4<SP, float>(psis.at(r), u, v);
 #pragma unroll
         for (int j = 0; j < 4; ++j) v[j] = scale(v[j], a);
-        st4<F64, float>(phi.at(r), Vh, u.par, u.g, u.i, v);
+        st4<F64, float>(phi.at(r), u, v);
     }
 };
 
@@ -172,12 +169,11 @@ struct SapOut {
 struct Copy {
     static constexpr int NS = 0;
     Fld src, dst;
-    int Vh;
     __device__ void operator()(const Unit& u, double*, int r) const
     {
         cx<double> v[4];
-        ld4<F64, double>(src.at(r), Vh, u.par, u.g, u.i, v);
-        st4<F64, double>(dst.at(r), Vh, u.par, u.g, u.i, v);
+        ld4<F64, double>(src.at(r), u, v);
+        st4<F64, double>(dst.at(r), u, v);
     }
 };
 
@@ -186,15 +182,15 @@ template <int K>
 struct BMultiDot {
     static constexpr int NS = 2 * K;
     Fld chi;  // chi_l for right-hand side r at base + (l nr + r) stride
-    int nr, k, Vh;
+    int nr, k;
     __device__ void operator()(const Unit& u, double* acc, int r) const
     {
         cx<double> vv[4];
-        ld4<F64, double>(chi.at(k * nr + r), Vh, u.par, u.g, u.i, vv);
+        ld4<F64, double>(chi.at(k * nr + r), u, vv);
 #pragma unroll
         for (int l = 0; l < K; ++l) {
             cx<double> c[4];
-            ld4<F64, double>(chi.at(l * nr + r), Vh, u.par, u.g, u.i, c);
+            ld4<F64, double>(chi.at(l * nr + r), u, c);
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const cx<double> z = cmul_conj(c[j], vv[j]);
@@ -211,23 +207,23 @@ struct BGsUpdate {
     static constexpr int NS = 3;
     Fld chi, rho;
     const double* sc;
-    int nr, Vh;
+    int nr;
     __device__ void operator()(const Unit& u, double* acc, int r) const
     {
         const double* a = sc + (long)r * B_SIZE + G_A + 2 * kMaxKv * K;
         void* v = chi.at(K * nr + r);
         cx<double> vv[4], rr[4];
-        ld4<F64, double>(v, Vh, u.par, u.g, u.i, vv);
+        ld4<F64, double>(v, u, vv);
 #pragma unroll
         for (int l = 0; l < K; ++l) {
             const cx<double> al = {a[2 * l], a[2 * l + 1]};
             cx<double> c[4];
-            ld4<F64, double>(chi.at(l * nr + r), Vh, u.par, u.g, u.i, c);
+            ld4<F64, double>(chi.at(l * nr + r), u, c);
 #pragma unroll
             for (int j = 0; j < 4; ++j) vv[j] = vv[j] - al * c[j];
         }
-        if (K > 0) st4<F64, double>(v, Vh, u.par, u.g, u.i, vv);
-        ld4<F64, double>(rho.at(r), Vh, u.par, u.g, u.i, rr);
+        if (K > 0) st4<F64, double>(v, u, vv);
+        ld4<F64, double>(rho.at(r), u, rr);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             acc[0] += vv[j].re * vv[j].re + vv[j].im * vv[j].im;
@@ -243,7 +239,7 @@ struct BGcrUpdate {
     static constexpr int NS = 1;
     Fld chi, rho;
     const double* sc;
-    int nr, k, Vh;
+    int nr, k;
     __device__ void operator()(const Unit& u, double* acc, int r) const
     {
         const double* coef = sc + (long)r * B_SIZE + G_COEF;
@@ -251,16 +247,16 @@ struct BGcrUpdate {
         const cx<double> cb = {coef[1], coef[2]};
         void* v = chi.at(k * nr + r);
         cx<double> vv[4], rr[4];
-        ld4<F64, double>(v, Vh, u.par, u.g, u.i, vv);
-        ld4<F64, double>(rho.at(r), Vh, u.par, u.g, u.i, rr);
+        ld4<F64, double>(v, u, vv);
+        ld4<F64, double>(rho.at(r), u, rr);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             rr[j] = rr[j] - cb * vv[j];
             vv[j] = scale(vv[j], ib);
             acc[0] += rr[j].re * rr[j].re + rr[j].im * rr[j].im;
         }
-        st4<F64, double>(v, Vh, u.par, u.g, u.i, vv);
-        st4<F64, double>(rho.at(r), Vh, u.par, u.g, u.i, rr);
+        st4<F64, double>(v, u, vv);
+        st4<F64, double>(rho.at(r), u, rr);
     }
 };
 
@@ -270,21 +266,21 @@ struct BMultiAxpy {
     Fld x, phi;
     const double* sc;
     const int* fl;
-    int nr, Vh;
+    int nr;
     __device__ void operator()(const Unit& u, double*, int r) const
     {
         const double* al = sc + (long)r * B_SIZE + B_ALPHA;
         const int kk = fl[r * F_SIZE + F_KDONE];
         cx<double> p[4];
-        ld4<F64, double>(x.at(r), Vh, u.par, u.g, u.i, p);
+        ld4<F64, double>(x.at(r), u, p);
         for (int l = 0; l < kk; ++l) {
             const cx<double> a = {al[2 * l], al[2 * l + 1]};
             cx<double> f[4];
-            ld4<F64, double>(phi.at(l * nr + r), Vh, u.par, u.g, u.i, f);
+            ld4<F64, double>(phi.at(l * nr + r), u, f);
 #pragma unroll
             for (int j = 0; j < 4; ++j) p[j] = p[j] + a * f[j];
         }
-        st4<F64, double>(x.at(r), Vh, u.par, u.g, u.i, p);
+        st4<F64, double>(x.at(r), u, p);
     }
 };
 
@@ -292,18 +288,17 @@ struct BMultiAxpy {
 struct BResidual {
     static constexpr int NS = 1;
     Fld eta, t, rho;
-    int Vh;
     __device__ void operator()(const Unit& u, double* acc, int r) const
     {
         cx<double> ve[4], vt[4];
-        ld4<F64, double>(eta.at(r), Vh, u.par, u.g, u.i, ve);
-        ld4<F64, double>(t.at(r), Vh, u.par, u.g, u.i, vt);
+        ld4<F64, double>(eta.at(r), u, ve);
+        ld4<F64, double>(t.at(r), u, vt);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             ve[j] = ve[j] - vt[j];
             acc[0] += ve[j].re * ve[j].re + ve[j].im * ve[j].im;
         }
-        st4<F64, double>(rho.at(r), Vh, u.par, u.g, u.i, ve);
+        st4<F64, double>(rho.at(r), u, ve);
     }
 };
 
@@ -425,9 +420,9 @@ inline bool sap_precond(const qdw_sap_gcr_params& p)
 template <int SP>
 int precondition(const Group& G, const qdw_sap_gcr_params& p, void* phi_k, hipStream_t st)
 {
-    const int Vh = G.op->g.Vh, V = G.op->g.V;
+    const int V = G.op->g.V;
     int rc;
-    if ((rc = brun(G, SapIn<SP>{{G.rho, G.fb}, {G.rs, G.fbs}, {G.psis, G.fbs}, G.sc, Vh, V},
+    if ((rc = brun(G, SapIn<SP>{{G.rho, G.fb}, {G.rs, G.fbs}, {G.psis, G.fbs}, G.sc, V},
                    F_INCYCLE, st)))
         return rc;
     RhsStride bat;
@@ -437,12 +432,12 @@ int precondition(const Group& G, const qdw_sap_gcr_params& p, void* phi_k, hipSt
     if ((rc = sap_cycles(G.op, G.B, SP, p.ncy, p.nmr, G.rs, G.psis, G.delta, bat, G.nr, st,
                          p.precond == QDW_PRECOND_SAP_EO)))
         return rc;
-    return brun(G, SapOut<SP>{{G.psis, G.fbs}, {(char*)phi_k, G.fb}, G.sc, Vh, V}, F_INCYCLE, st);
+    return brun(G, SapOut<SP>{{G.psis, G.fbs}, {(char*)phi_k, G.fb}, G.sc, V}, F_INCYCLE, st);
 }
 
 int cycle(const Group& G, const qdw_sap_gcr_params& p, hipStream_t st)
 {
-    const int Vh = G.op->g.Vh, nr = G.nr;
+    const int nr = G.nr;
     const bool sap = sap_precond(p);
     const void* in[kMaxRhs];
     void* out[kMaxRhs];
@@ -457,7 +452,7 @@ int cycle(const Group& G, const qdw_sap_gcr_params& p, hipStream_t st)
             default: rc = precondition<BF16S>(G, p, phik, st); break;
             }
         } else {
-            rc = brun(G, Copy{{G.rho, G.fb}, {phik, G.fb}, Vh}, F_INCYCLE, st);
+            rc = brun(G, Copy{{G.rho, G.fb}, {phik, G.fb}}, F_INCYCLE, st);
         }
         if (rc) return rc;
         for (int r = 0; r < nr; ++r) {
@@ -470,7 +465,6 @@ int cycle(const Group& G, const qdw_sap_gcr_params& p, hipStream_t st)
                 f.chi = {G.chi, G.fb};
                 f.nr = nr;
                 f.k = k;
-                f.Vh = Vh;
                 return brun(G, f, F_INCYCLE, st, G_A + 2 * kMaxKv * k);
             })))
             return rc;
@@ -479,11 +473,10 @@ int cycle(const Group& G, const qdw_sap_gcr_params& p, hipStream_t st)
                 f.rho = {G.rho, G.fb};
                 f.sc = G.sc;
                 f.nr = nr;
-                f.Vh = Vh;
-                return brun(G, f, F_INCYCLE, st, 0, FIN_GCR_NORM, k);
+                return brun(G, f, F_INCYCLE, st, 0, FIN_GCR_NORM, k, true);
             })))
             return rc;
-        if ((rc = brun(G, BGcrUpdate{{G.chi, G.fb}, {G.rho, G.fb}, G.sc, nr, k, Vh}, F_INCYCLE, st,
+        if ((rc = brun(G, BGcrUpdate{{G.chi, G.fb}, {G.rho, G.fb}, G.sc, nr, k}, F_INCYCLE, st,
                        G_NORM)))
             return rc;
         step_ctrl_kernel<<<1, 64, 0, st>>>(G.fl, G.sc, nr, p.nmx);
@@ -492,7 +485,7 @@ int cycle(const Group& G, const qdw_sap_gcr_params& p, hipStream_t st)
     // restart step: x += sum alpha_l phi_l ; rho = eta - D x
     tri_kernel<<<1, 64, 0, st>>>(G.fl, G.sc, nr);
     QDW_LAUNCH_CHECK();
-    if ((rc = brun(G, BMultiAxpy{{G.x, G.fb}, {G.phi, G.fb}, G.sc, G.fl, nr, Vh}, F_ACTIVE, st)))
+    if ((rc = brun(G, BMultiAxpy{{G.x, G.fb}, {G.phi, G.fb}, G.sc, G.fl, nr}, F_ACTIVE, st)))
         return rc;
     for (int r = 0; r < nr; ++r) {
         in[r] = G.x + r * G.fb;
@@ -500,7 +493,7 @@ int cycle(const Group& G, const qdw_sap_gcr_params& p, hipStream_t st)
     }
     if ((rc = dw_launch_multi(G.op, in, out, nr, F64, false, G.fl + F_ACTIVE, F_SIZE, st)))
         return rc;
-    if ((rc = brun(G, BResidual{{G.eta, G.fb}, {G.tmp, G.fb}, {G.rho, G.fb}, Vh}, F_ACTIVE, st,
+    if ((rc = brun(G, BResidual{{G.eta, G.fb}, {G.tmp, G.fb}, {G.rho, G.fb}}, F_ACTIVE, st,
                    G_NORM)))
         return rc;
     restart_ctrl_kernel<<<1, 64, 0, st>>>(G.fl, G.sc, nr, p.nmx);
@@ -565,6 +558,7 @@ int plan(qdw_op* const* ops, int n, const qdw_sap_gcr_params& p, char* base,
         G.delta = sap ? take((size_t)G.fbs * G.nr) : nullptr;
         G.sc = (double*)take(sizeof(double) * B_SIZE * G.nr);
         G.part = (double*)take(sizeof(double) * kPartStride * G.nr);
+        G.tick = (unsigned*)take(sizeof(unsigned) * kTicketWords * G.nr);
         G.fl = flags ? flags + fo : nullptr;
         fo += G.nr * F_SIZE;
         G.s = nullptr;
@@ -720,12 +714,13 @@ extern "C" int qdw_batch_solve(qdw_batch* b, const void* const* etas, void* cons
     hipStream_t st = (hipStream_t)stream;
     // set-up: gather the sources, x = 0, rho = eta, |eta|^2, tolerances and flags
     for (const Group& G : b->gs) {
+        zero_tickets_kernel<<<1, 256, 0, st>>>(G.tick, kTicketWords * G.nr);
+        QDW_LAUNCH_CHECK();
         for (int r = 0; r < G.nr; ++r)
-            if ((rc = run_map(G.op, Axpby<F64, F64>{etas[G.prob[r]], G.eta + r * G.fb, 1.0, 0.0,
-                                                    G.op->g.Vh},
+            if ((rc = run_map(G.op, Axpby<F64, F64>{etas[G.prob[r]], G.eta + r * G.fb, 1.0, 0.0},
                               st)))
                 return rc;
-        if ((rc = brun(G, Init{{G.eta, G.fb}, {G.x, G.fb}, {G.rho, G.fb}, G.op->g.Vh}, -1, st,
+        if ((rc = brun(G, Init{{G.eta, G.fb}, {G.x, G.fb}, {G.rho, G.fb}}, -1, st,
                        B_ETA2)))
             return rc;
         init_ctrl_kernel<<<1, 64, 0, st>>>(G.fl, G.sc, G.nr, b->p.res);
@@ -752,8 +747,7 @@ extern "C" int qdw_batch_solve(qdw_batch* b, const void* const* etas, void* cons
     std::vector<double> hsc;
     for (const Group& G : b->gs) {
         for (int r = 0; r < G.nr; ++r)
-            if ((rc = run_map(G.op, Axpby<F64, F64>{G.x + r * G.fb, psis[G.prob[r]], 1.0, 0.0,
-                                                    G.op->g.Vh},
+            if ((rc = run_map(G.op, Axpby<F64, F64>{G.x + r * G.fb, psis[G.prob[r]], 1.0, 0.0},
                               st)))
                 return rc;
     }

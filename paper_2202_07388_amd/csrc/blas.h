@@ -3,12 +3,12 @@
 // The paper (Sec. 2.1) keeps every reduction variable in binary64 whatever the working
 // type of the vectors; here every lane accumulates its products in FP64 and the partial
 // sums are combined across the wavefront (shuffles), the workgroup (LDS) and the grid
-// (a second single-workgroup pass) in a fixed order, so results are bitwise
+// (by the workgroup that finishes last) in a fixed order, so results are bitwise
 // reproducible run to run.
 //
-// Unit of work: 4 complex numbers of one site, (parity, group g in 0..2, site i). Fields
-// of different storage precisions are addressed by the same unit, so mixed-precision
-// kernels (FP32 solution, FP16 residual) pair the same lattice components.
+// Unit of work: 4 complex numbers of one site. Fields of different storage precisions are
+// addressed by the same unit, so mixed-precision kernels (FP32 solution, FP16 residual)
+// pair the same lattice components.
 #pragma once
 
 #include "qdw_host.h"
@@ -17,15 +17,22 @@ namespace qdw {
 
 // ---------------------------------------------------------------- unit load / store
 
+// Unit of a map: run w of 64 sites, w = (parity * blocks of 64 sites + block) * 3 + group,
+// and the site within it. A field stores the chunks of one such run contiguously, in the
+// order of w, so a wavefront walks every field linearly whatever its precision, with no
+// division by the lattice size (chunk_at with chunk = group * NCH + k).
+struct Unit { unsigned w; int lane; };
+
 template <int P, typename R>
-__device__ __forceinline__ void ld4(const void* f, int Vh, int par, int g, int i, cx<R> v[4])
+__device__ __forceinline__ void ld4(const void* f, const Unit& u, cx<R> v[4])
 {
     using T = Traits<P>;
     constexpr int CPC = T::PER_CHUNK / 2;        // complex per chunk
     constexpr int NCH = 4 / CPC;                 // chunks per unit
+    const long at = (long)u.w * (NCH * kSB) + u.lane;
 #pragma unroll
     for (int k = 0; k < NCH; ++k) {
-        Chunk<P> c = load_chunk_cached<P>(f, chunk_at(Vh, T::SPIN_CHUNKS, par, g * NCH + k, i));
+        Chunk<P> c = load_chunk_cached<P>(f, at + k * kSB);
 #pragma unroll
         for (int j = 0; j < CPC; ++j)
             v[k * CPC + j] = {(R)to_real<P>(c.v[2 * j]), (R)to_real<P>(c.v[2 * j + 1])};
@@ -33,12 +40,13 @@ __device__ __forceinline__ void ld4(const void* f, int Vh, int par, int g, int i
 }
 
 template <int P, typename R>
-__device__ __forceinline__ void st4(void* f, int Vh, int par, int g, int i, const cx<R> v[4])
+__device__ __forceinline__ void st4(void* f, const Unit& u, const cx<R> v[4])
 {
     using T = Traits<P>;
     using RT = typename T::real;
     constexpr int CPC = T::PER_CHUNK / 2;
     constexpr int NCH = 4 / CPC;
+    const long at = (long)u.w * (NCH * kSB) + u.lane;
 #pragma unroll
     for (int k = 0; k < NCH; ++k) {
         Chunk<P> c;
@@ -47,60 +55,35 @@ __device__ __forceinline__ void st4(void* f, int Vh, int par, int g, int i, cons
             c.v[2 * j] = to_store<P>((RT)v[k * CPC + j].re);
             c.v[2 * j + 1] = to_store<P>((RT)v[k * CPC + j].im);
         }
-        const long at = chunk_at(Vh, T::SPIN_CHUNKS, par, g * NCH + k, i);
         uint4 raw;
         __builtin_memcpy(&raw, &c, 16);
-        ((uint4*)f)[at] = raw;
+        ((uint4*)f)[at + k * kSB] = raw;
     }
 }
 
-struct Unit { int par, g, i; };
-
-__device__ __forceinline__ Unit unit_of(long u, int Vh)
-{
-    const long per = 3L * Vh;
-    Unit r;
-    r.par = (int)(u / per);
-    const long rem = u - (long)r.par * per;
-    r.g = (int)(rem / Vh);
-    r.i = (int)(rem - (long)r.g * Vh);
-    return r;
-}
-
-// ---------------------------------------------------------------- reductions
-
-template <int NS>
-__device__ __forceinline__ void block_reduce_store(double acc[NS], double* partial)
-{
-    __shared__ double red[4][NS > 0 ? NS : 1];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-    for (int k = 0; k < NS; ++k) {
-        double v = acc[k];
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-        if (lane == 0) red[wave][k] = v;
+// The runs of a map launch: nw of them (both parities, or the even half), nb blocks of 64
+// sites per parity, tail = sites of a parity's last block (64 when it is full). The padding
+// positions of a ragged last block are left alone and never summed.
+// `back` walks the runs from the last to the first: a map that reads the fields which the
+// map before it has just read starts on the ones still in the 256 MB last-level cache.
+struct Runs {
+    unsigned nw;
+    int nb, tail;
+    bool back;
+    __device__ __forceinline__ Unit unit(unsigned n) const
+    {
+        return {back ? nw - 1 - n : n, (int)(threadIdx.x & 63)};
     }
-    __syncthreads();
-    if (threadIdx.x < NS) {
-        const int k = threadIdx.x;
-        partial[k] = ((red[0][k] + red[1][k]) + red[2][k]) + red[3][k];
+    __device__ __forceinline__ bool holds(const Unit& u) const
+    {
+        return tail == kSB || u.lane < tail || (int)((u.w / 3) % (unsigned)nb) != nb - 1;
     }
-}
+};
 
-// grid-stride map over units; F::NS doubles reduced per workgroup into partials
-template <class F>
-__global__ __launch_bounds__(256) void map_kernel(long nunits, int Vh, F f, double* partials)
+inline Runs runs_of(const Geom& g, bool even_half, bool back)
 {
-    double acc[F::NS > 0 ? F::NS : 1];
-#pragma unroll
-    for (int k = 0; k < (F::NS > 0 ? F::NS : 1); ++k) acc[k] = 0.0;
-    for (long u = (long)blockIdx.x * blockDim.x + threadIdx.x; u < nunits;
-         u += (long)gridDim.x * blockDim.x) {
-        const Unit w = unit_of(u, Vh);
-        f(w, acc);
-    }
-    if constexpr (F::NS > 0) block_reduce_store<F::NS>(acc, partials + (long)blockIdx.x * F::NS);
+    const int nb = padded(g.Vh) / kSB;
+    return {(unsigned)(3 * nb) * (even_half ? 1u : 2u), nb, g.Vh - (nb - 1) * kSB, back};
 }
 
 // scalar programs run by the finalising workgroup after the sums are formed
@@ -121,27 +104,9 @@ enum { G_A = 0, G_B = 2 * kMaxKv * kMaxKv, G_C = G_B + kMaxKv, G_COEF = G_C + 2 
 // scalar slots of the CG solver
 enum { S_RR = 0, S_PAP = 1, S_ALPHA = 2, S_RRNEW = 3, S_BETA = 4, S_TMP = 8 };
 
-// Body of the finalising pass (one workgroup of 256 lanes): sums the per-workgroup
-// partials in a fixed order (strided per lane, then a fixed tree), then runs the scalar
-// program `op`.
-__device__ inline void finalize_body(const double* partials, int nblk, int ns, double* out,
-                                     int op, int k)
+// the scalar program `op` on the grid's sums (one lane)
+__device__ inline void scalar_program(const double* sums, int ns, double* out, int op, int k)
 {
-    __shared__ double red[256];
-    __shared__ double sums[kMaxScalars];
-    for (int j = 0; j < ns; ++j) {
-        double s = 0.0;
-        for (int b = threadIdx.x; b < nblk; b += 256) s += partials[(long)b * ns + j];
-        red[threadIdx.x] = s;
-        __syncthreads();
-        for (int w = 128; w > 0; w >>= 1) {
-            if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) sums[j] = red[0];
-        __syncthreads();
-    }
-    if (threadIdx.x != 0) return;
     switch (op) {
     case FIN_STORE:
         for (int j = 0; j < ns; ++j) out[j] = sums[j];
@@ -171,36 +136,186 @@ __device__ inline void finalize_body(const double* partials, int nblk, int ns, d
     }
 }
 
-__global__ void finalize_kernel(const double* partials, int nblk, int ns, double* out, int op,
-                                int k);
+// ---------------------------------------------------------------- reductions over the grid
+//
+// Every workgroup leaves its partial sums in memory; the one that arrives last adds them
+// up, in an order fixed by the workgroup index, and runs the scalar program. That saves the
+// launch of a second kernel and the idle machine around it. Partial sums and arrival
+// counters are agent-scope atomics: each XCD has its own L2, and such accesses are coherent
+// between them without writing back or invalidating a whole cache. A workgroup's counter is
+// bumped only after its stores have completed (the wait below).
 
-struct Reducer {
-    int nblk;   // workgroups of the map launch (fixed per field size: deterministic)
+struct Sums {
+    double* partials;   // sum j of workgroup b at [j * workgroups + b]
+    unsigned* ticket;   // kTicketWords, zero between launches
+    double* out;        // scalar program's block
+    int fin, k;
 };
 
-inline int map_blocks(long nunits)
+__device__ __forceinline__ double agent_load(const double* p)
 {
-    long b = (nunits + 256 * 8 - 1) / (256 * 8);
-    if (b > kMaxPartials) b = kMaxPartials;
-    if (b < 1) b = 1;
-    return (int)b;
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void agent_store(double* p, double v)
+{
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// launch F over all 3V units of op's lattice, or over the first nu units when nu > 0
-// (3 Vh: the even half), and (if F::NS > 0) finalise into scalars
+// one lane per workgroup; true for the last of nblk (the counters are zero again then)
+__device__ __forceinline__ bool last_arrival(unsigned* ticket, unsigned blk, unsigned nblk)
+{
+    const unsigned ng = nblk < (unsigned)kTickets ? nblk : (unsigned)kTickets;
+    const unsigned gr = blk % ng, in_group = (nblk - gr + ng - 1) / ng;
+    unsigned* mine = ticket + 32 * (1 + gr);
+    if (__hip_atomic_fetch_add(mine, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != in_group - 1)
+        return false;
+    __hip_atomic_store(mine, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (__hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != ng - 1)
+        return false;
+    __hip_atomic_store(ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return true;
+}
+
+__device__ __forceinline__ double wave_sum(double v)
+{
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    return v;
+}
+
+constexpr int pow2_at_least(int n)
+{
+    int p = 1;
+    while (p < n) p *= 2;
+    return p;
+}
+
+// The sums over a wavefront of N values per lane, to dst[0 .. N). At each exchange a lane
+// keeps one half of its values and hands over the other, so N values take about N + 6
+// exchanges instead of 6 N (the 30 sums of a late Gram-Schmidt step cost more than the
+// loads they follow otherwise).
+template <int N>
+__device__ __forceinline__ void wave_sums(const double* acc, int lane, double* dst)
+{
+    constexpr int P = pow2_at_least(N);
+    static_assert(P <= 64, "one value per lane at most");
+    double v[P];
+#pragma unroll
+    for (int j = 0; j < P; ++j) v[j] = j < N ? acc[j] : 0.0;
+    int o = 32;
+#pragma unroll
+    for (int h = P / 2; h > 0; h /= 2, o /= 2) {
+        const bool up = lane & o;
+#pragma unroll
+        for (int j = 0; j < h; ++j) {
+            const double keep = up ? v[j + h] : v[j], send = up ? v[j] : v[j + h];
+            v[j] = keep + __shfl_xor(send, o, 64);
+        }
+    }
+    for (; o > 0; o /= 2) v[0] += __shfl_xor(v[0], o, 64);
+    constexpr int L = 64 / P;  // lanes that hold the same sum
+    if (lane % L == 0 && lane / L < N) dst[lane / L] = v[0];
+}
+
+// p[first] + p[first + step] + ... below n, eight loads in flight at a time
+__device__ __forceinline__ double sum_strided(const double* p, unsigned first, unsigned step, unsigned n)
+{
+    double v = 0.0;
+    for (unsigned b = first; b < n; b += 8 * step) {
+        double t[8];
+#pragma unroll
+        for (unsigned q = 0; q < 8; ++q) {
+            const unsigned at = b + q * step;
+            t[q] = agent_load(p + (at < n ? at : b));
+        }
+#pragma unroll
+        for (unsigned q = 0; q < 8; ++q) v += b + q * step < n ? t[q] : 0.0;
+    }
+    return v;
+}
+
+// Sums acc[NS] of every lane of the grid (whole workgroups of at most 256 lanes, all of
+// whose lanes call this; workgroup blk of nblk) into s.out through s.fin.
+template <int NS>
+__device__ __forceinline__ void grid_sums(const double* acc, const Sums& s, unsigned blk, unsigned nblk)
+{
+    __shared__ double red[4][NS];
+    __shared__ double sums[NS];
+    __shared__ int last;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwv = blockDim.x >> 6;
+    wave_sums<NS>(acc, lane, red[wave]);
+    __syncthreads();
+    if (wave == 0) {
+        if (lane < NS) {
+            double v = red[0][lane];
+            for (int w = 1; w < nwv; ++w) v += red[w][lane];
+            agent_store(s.partials + (long)lane * nblk + blk, v);
+        }
+        // the workgroup's partial sums are in memory before its arrival is counted
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if (lane == 0) last = last_arrival(s.ticket, blk, nblk);
+    }
+    __syncthreads();
+    if (!last) return;
+    if constexpr (NS <= 3) {
+        // few sums over possibly many workgroups: every lane takes part in each
+        double v[NS];
+#pragma unroll
+        for (int j = 0; j < NS; ++j)
+            v[j] = sum_strided(s.partials + (long)j * nblk, threadIdx.x, blockDim.x, nblk);
+        wave_sums<NS>(v, lane, red[wave]);
+        __syncthreads();
+        if (threadIdx.x < NS) {
+            double t = red[0][threadIdx.x];
+            for (int w = 1; w < nwv; ++w) t += red[w][threadIdx.x];
+            sums[threadIdx.x] = t;
+        }
+    } else {
+        // many sums: a wavefront each, side by side
+        for (int j = wave; j < NS; j += nwv) {
+            const double v = wave_sum(sum_strided(s.partials + (long)j * nblk, lane, 64, nblk));
+            if (lane == 0) sums[j] = v;
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) scalar_program(sums, NS, s.out, s.fin, s.k);
+}
+
+// map over the runs of a field, a wavefront per run; F::NS doubles are summed over the grid
+template <class F>
+__global__ __launch_bounds__(256) void map_kernel(Runs runs, F f, Sums s)
+{
+    double acc[F::NS > 0 ? F::NS : 1];
+#pragma unroll
+    for (int k = 0; k < (F::NS > 0 ? F::NS : 1); ++k) acc[k] = 0.0;
+    for (unsigned n = blockIdx.x * 4 + (threadIdx.x >> 6); n < runs.nw; n += gridDim.x * 4) {
+        const Unit u = runs.unit(n);
+        if (runs.holds(u)) f(u, acc);
+    }
+    if constexpr (F::NS > 0) grid_sums<F::NS>(acc, s, blockIdx.x, gridDim.x);
+}
+
+// Workgroups of a map: one run per wavefront until the machine is full (a small lattice then
+// spreads over all CUs: 16^3 x 32 has 3072 workgroups' worth of runs), at most kMaxPartials;
+// with many sums at most 512, two workgroups per CU, whose partial sums the last one reads
+// with one batch of loads per sum.
+template <int NS>
+inline int map_blocks(unsigned nw)
+{
+    const unsigned cap = NS > 3 ? 512 : kMaxPartials, b = (nw + 3) / 4;
+    return (int)(b < cap ? b : cap);
+}
+
+// launch F over op's lattice, or over its even half, and (if F::NS > 0) run the scalar
+// program fin on its sums
 template <class F>
 int run_map(const qdw_op* op, const F& f, hipStream_t st, double* out = nullptr,
-            int fin = FIN_STORE, int k = 0, long nu = 0)
+            int fin = FIN_STORE, int k = 0, bool even_half = false, bool back = false)
 {
-    const long nunits = nu > 0 ? nu : 3L * op->g.V;
-    const int nb = map_blocks(nunits);
-    map_kernel<F><<<nb, 256, 0, st>>>(nunits, op->g.Vh, f, op->partials);
+    const Runs r = runs_of(op->g, even_half, back);
+    const Sums s = {op->partials, op->tickets, out ? out : op->scalars, fin, k};
+    map_kernel<F><<<map_blocks<F::NS>(r.nw), 256, 0, st>>>(r, f, s);
     QDW_LAUNCH_CHECK();
-    if constexpr (F::NS > 0) {
-        finalize_kernel<<<1, 256, 0, st>>>(op->partials, nb, F::NS, out ? out : op->scalars,
-                                           fin, k);
-        QDW_LAUNCH_CHECK();
-    }
     return QDW_OK;
 }
 
@@ -210,11 +325,10 @@ template <int P>
 struct Norm2 {
     static constexpr int NS = 1;
     const void* x;
-    int Vh;
     __device__ void operator()(const Unit& w, double* acc) const
     {
         cx<double> v[4];
-        ld4<P, double>(x, Vh, w.par, w.g, w.i, v);
+        ld4<P, double>(x, w, v);
 #pragma unroll
         for (int k = 0; k < 4; ++k) acc[0] += v[k].re * v[k].re + v[k].im * v[k].im;
     }
@@ -227,20 +341,19 @@ struct Axpby {
     const void* x;
     void* y;
     double a, b;
-    int Vh;
     __device__ void operator()(const Unit& w, double*) const
     {
         using R = typename Traits<(PX == F64 && PY == F64) ? F64 : F32>::real;
         cx<R> vx[4], vy[4];
-        ld4<PX, R>(x, Vh, w.par, w.g, w.i, vx);
-        if (b != 0.0) ld4<PY, R>(y, Vh, w.par, w.g, w.i, vy);
+        ld4<PX, R>(x, w, vx);
+        if (b != 0.0) ld4<PY, R>(y, w, vy);
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             cx<R> t = scale(vx[k], (R)a);
             if (b != 0.0) t = t + scale(vy[k], (R)b);
             vy[k] = t;
         }
-        st4<PY, R>(y, Vh, w.par, w.g, w.i, vy);
+        st4<PY, R>(y, w, vy);
     }
 };
 
@@ -251,17 +364,16 @@ struct ScaleNorm {
     const void* x;
     void* y;
     double s;
-    int Vh;
     __device__ void operator()(const Unit& w, double* acc) const
     {
         cx<double> vx[4];
-        ld4<PX, double>(x, Vh, w.par, w.g, w.i, vx);
+        ld4<PX, double>(x, w, vx);
         cx<double> vy[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) vy[k] = scale(vx[k], s);
-        st4<PY, double>(y, Vh, w.par, w.g, w.i, vy);
+        st4<PY, double>(y, w, vy);
         cx<double> back[4];
-        ld4<PY, double>(y, Vh, w.par, w.g, w.i, back);
+        ld4<PY, double>(y, w, back);
 #pragma unroll
         for (int k = 0; k < 4; ++k) acc[0] += back[k].re * back[k].re + back[k].im * back[k].im;
     }
@@ -276,7 +388,6 @@ struct CgStep {
     void* r;
     const void* w;
     const double* sc;
-    int Vh;
     __device__ void operator()(const Unit& u, double* acc) const
     {
         using R = typename Traits<P>::real;
@@ -285,25 +396,25 @@ struct CgStep {
         // runs into a non-finite value still holds its last finite iterate
         const bool move = a != (R)0 && isfinite(a);
         cx<R> vx[4], vp[4], vr[4], vw[4];
-        ld4<P, R>(p, Vh, u.par, u.g, u.i, vp);
-        ld4<P, R>(r, Vh, u.par, u.g, u.i, vr);
-        ld4<P, R>(w, Vh, u.par, u.g, u.i, vw);
+        ld4<P, R>(p, u, vp);
+        ld4<P, R>(r, u, vr);
+        ld4<P, R>(w, u, vw);
         if (move) {
-            ld4<PX, R>(x, Vh, u.par, u.g, u.i, vx);
+            ld4<PX, R>(x, u, vx);
 #pragma unroll
             for (int k = 0; k < 4; ++k) vx[k] = vx[k] + scale(vp[k], a);
-            st4<PX, R>(x, Vh, u.par, u.g, u.i, vx);
+            st4<PX, R>(x, u, vx);
         }
 #pragma unroll
         for (int k = 0; k < 4; ++k) vr[k] = vr[k] - scale(vw[k], a);
-        st4<P, R>(r, Vh, u.par, u.g, u.i, vr);
+        st4<P, R>(r, u, vr);
         // reduce what is stored (rounded to P), in FP64; FP64 stores the values as they are
         cx<double> back[4];
         if constexpr (P == F64) {
 #pragma unroll
             for (int k = 0; k < 4; ++k) back[k] = {(double)vr[k].re, (double)vr[k].im};
         } else {
-            ld4<P, double>(r, Vh, u.par, u.g, u.i, back);
+            ld4<P, double>(r, u, back);
         }
 #pragma unroll
         for (int k = 0; k < 4; ++k) acc[0] += back[k].re * back[k].re + back[k].im * back[k].im;
@@ -317,17 +428,16 @@ struct CgDirection {
     const void* r;
     void* p;
     const double* sc;
-    int Vh;
     __device__ void operator()(const Unit& u, double*) const
     {
         using R = typename Traits<P>::real;
         const R b = (R)sc[S_BETA];
         cx<R> vr[4], vp[4];
-        ld4<P, R>(r, Vh, u.par, u.g, u.i, vr);
-        ld4<P, R>(p, Vh, u.par, u.g, u.i, vp);
+        ld4<P, R>(r, u, vr);
+        ld4<P, R>(p, u, vp);
 #pragma unroll
         for (int k = 0; k < 4; ++k) vp[k] = vr[k] + scale(vp[k], b);
-        st4<P, R>(p, Vh, u.par, u.g, u.i, vp);
+        st4<P, R>(p, u, vp);
     }
 };
 
@@ -337,18 +447,17 @@ struct Residual {
     const void* eta;
     const void* t;
     void* r;
-    int Vh;
     __device__ void operator()(const Unit& u, double* acc) const
     {
         cx<double> ve[4], vt[4];
-        ld4<F64, double>(eta, Vh, u.par, u.g, u.i, ve);
-        ld4<F64, double>(t, Vh, u.par, u.g, u.i, vt);
+        ld4<F64, double>(eta, u, ve);
+        ld4<F64, double>(t, u, vt);
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             ve[k] = ve[k] - vt[k];
             acc[0] += ve[k].re * ve[k].re + ve[k].im * ve[k].im;
         }
-        st4<F64, double>(r, Vh, u.par, u.g, u.i, ve);
+        st4<F64, double>(r, u, ve);
     }
 };
 
@@ -359,19 +468,18 @@ struct Accumulate {
     void* xhi;
     void* xlo;
     double s;
-    int Vh;
     __device__ void operator()(const Unit& u, double*) const
     {
         cx<double> vh[4], vl[4];
-        ld4<F64, double>(xhi, Vh, u.par, u.g, u.i, vh);
-        ld4<PL, double>(xlo, Vh, u.par, u.g, u.i, vl);
+        ld4<F64, double>(xhi, u, vh);
+        ld4<PL, double>(xlo, u, vl);
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             vh[k] = vh[k] + scale(vl[k], s);
             vl[k] = {0.0, 0.0};
         }
-        st4<F64, double>(xhi, Vh, u.par, u.g, u.i, vh);
-        st4<PL, double>(xlo, Vh, u.par, u.g, u.i, vl);
+        st4<F64, double>(xhi, u, vh);
+        st4<PL, double>(xlo, u, vl);
     }
 };
 
@@ -380,11 +488,10 @@ template <int P>
 struct Zero {
     static constexpr int NS = 0;
     void* x;
-    int Vh;
     __device__ void operator()(const Unit& u, double*) const
     {
         cx<double> v[4] = {{0, 0}, {0, 0}, {0, 0}, {0, 0}};
-        st4<P, double>(x, Vh, u.par, u.g, u.i, v);
+        st4<P, double>(x, u, v);
     }
 };
 

@@ -1,16 +1,5 @@
-// blas.hip -- second reduction pass and its scalar programs.
+// blas.hip -- the BLAS-1 entry points.
 #include "blas.h"
-
-namespace qdw {
-
-// One workgroup sums the per-workgroup partials and runs the scalar program `op`.
-__global__ __launch_bounds__(256) void finalize_kernel(const double* partials, int nblk, int ns,
-                                                       double* out, int op, int k)
-{
-    finalize_body(partials, nblk, ns, out, op, k);
-}
-
-}  // namespace qdw
 
 // ---------------------------------------------------------------- C ABI
 
@@ -21,12 +10,11 @@ struct Dot {
     static constexpr int NS = 2;
     const void* x;
     const void* y;
-    int Vh;
     __device__ void operator()(const qdw::Unit& u, double* acc) const
     {
         qdw::cx<double> a[4], b[4];
-        qdw::ld4<P, double>(x, Vh, u.par, u.g, u.i, a);
-        qdw::ld4<P, double>(y, Vh, u.par, u.g, u.i, b);
+        qdw::ld4<P, double>(x, u, a);
+        qdw::ld4<P, double>(y, u, b);
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const qdw::cx<double> z = qdw::cmul_conj(a[k], b[k]);
@@ -58,7 +46,7 @@ extern "C" int qdw_axpby(qdw_op* op, double a, const void* x, double b, void* y,
     QDW_CHECK(op && x && y, QDW_EINVAL, "qdw_axpby: null argument");
     hipStream_t st = (hipStream_t)stream;
     return by_prec<AxpbySame>(prec, [&](auto& f) {
-        f.x = x; f.y = y; f.a = a; f.b = b; f.Vh = op->g.Vh;
+        f.x = x; f.y = y; f.a = a; f.b = b;
         return qdw::run_map(op, f, st);
     });
 }
@@ -68,7 +56,7 @@ extern "C" int qdw_norm2(qdw_op* op, const void* x, qdw_prec prec, double* out, 
     QDW_CHECK(op && x && out, QDW_EINVAL, "qdw_norm2: null argument");
     hipStream_t st = (hipStream_t)stream;
     int rc = by_prec<qdw::Norm2>(prec, [&](auto& f) {
-        f.x = x; f.Vh = op->g.Vh;
+        f.x = x;
         return qdw::run_map(op, f, st, op->scalars + qdw::S_TMP);
     });
     if (rc) return rc;
@@ -81,7 +69,7 @@ extern "C" int qdw_cdot(qdw_op* op, const void* x, const void* y, qdw_prec prec,
     QDW_CHECK(op && x && y && out, QDW_EINVAL, "qdw_cdot: null argument");
     hipStream_t st = (hipStream_t)stream;
     int rc = by_prec<Dot>(prec, [&](auto& f) {
-        f.x = x; f.y = y; f.Vh = op->g.Vh;
+        f.x = x; f.y = y;
         return qdw::run_map(op, f, st, op->scalars + qdw::S_TMP);
     });
     if (rc) return rc;
@@ -93,12 +81,11 @@ namespace {
 template <int PX>
 int convert_to(qdw_op* op, const void* x, void* y, qdw_prec py, double s, hipStream_t st)
 {
-    const int Vh = op->g.Vh;
     switch (py) {
-    case QDW_F64: return qdw::run_map(op, qdw::Axpby<PX, qdw::F64>{x, y, s, 0.0, Vh}, st);
-    case QDW_F32: return qdw::run_map(op, qdw::Axpby<PX, qdw::F32>{x, y, s, 0.0, Vh}, st);
-    case QDW_F16S: return qdw::run_map(op, qdw::Axpby<PX, qdw::F16S>{x, y, s, 0.0, Vh}, st);
-    case QDW_BF16S: return qdw::run_map(op, qdw::Axpby<PX, qdw::BF16S>{x, y, s, 0.0, Vh}, st);
+    case QDW_F64: return qdw::run_map(op, qdw::Axpby<PX, qdw::F64>{x, y, s, 0.0}, st);
+    case QDW_F32: return qdw::run_map(op, qdw::Axpby<PX, qdw::F32>{x, y, s, 0.0}, st);
+    case QDW_F16S: return qdw::run_map(op, qdw::Axpby<PX, qdw::F16S>{x, y, s, 0.0}, st);
+    case QDW_BF16S: return qdw::run_map(op, qdw::Axpby<PX, qdw::BF16S>{x, y, s, 0.0}, st);
     default: QDW_CHECK(false, QDW_EINVAL, "qdw_convert: bad precision");
     }
 }

@@ -37,12 +37,11 @@ struct ResetResidual {
     const void* rhi;
     void* r;
     double s_old, s_new;
-    int Vh;
     __device__ void operator()(const Unit& u, double* acc) const
     {
         cx<double> vh[4], vo[4];
-        ld4<F64, double>(rhi, Vh, u.par, u.g, u.i, vh);
-        ld4<PL, double>(r, Vh, u.par, u.g, u.i, vo);
+        ld4<F64, double>(rhi, u, vh);
+        ld4<PL, double>(r, u, vo);
         const double inv = 1.0 / s_old;
         cx<double> vn[4];
 #pragma unroll
@@ -51,8 +50,8 @@ struct ResetResidual {
             acc[1] += d.re * d.re + d.im * d.im;
             vn[k] = scale(vh[k], s_new);
         }
-        st4<PL, double>(r, Vh, u.par, u.g, u.i, vn);
-        ld4<PL, double>(r, Vh, u.par, u.g, u.i, vn);
+        st4<PL, double>(r, u, vn);
+        ld4<PL, double>(r, u, vn);
 #pragma unroll
         for (int k = 0; k < 4; ++k) acc[0] += vn[k].re * vn[k].re + vn[k].im * vn[k].im;
     }
@@ -63,7 +62,6 @@ int cgne_impl(qdw_op* op, const void* eta, void* psi, const qdw_cgne_params& prm
               qdw_info* info, hipStream_t st)
 {
     const Geom& g = op->g;
-    const int Vh = g.Vh;
     const size_t f64b = spinor_bytes(g, F64), flb = spinor_bytes(g, PL);
     void* rhi = work;
     void* t1 = work + f64b;
@@ -90,17 +88,16 @@ int cgne_impl(qdw_op* op, const void* eta, void* psi, const qdw_cgne_params& prm
 
     // the even-odd reduced system lives on the even half of every field
     const bool schur = prm.schur != 0;
-    const long nu = schur ? 3L * Vh : 0;
     auto apply = [&](const void* in, void* out, int prec, bool dag) {
         return schur ? schur_launch(op, in, out, prec, dag, st) : dw_launch(op, in, out, prec, dag, st);
     };
     CgState S;
     int rc;
 #define TRY(x) do { if ((rc = (x)) != QDW_OK) return rc; } while (0)
-    TRY(run_map(op, Zero<F64>{psi, Vh}, st));
-    if (PL != F64) TRY(run_map(op, Zero<PX>{xlo, Vh}, st, nullptr, FIN_STORE, 0, nu));
+    TRY(run_map(op, Zero<F64>{psi}, st));
+    if (PL != F64) TRY(run_map(op, Zero<PX>{xlo}, st, nullptr, FIN_STORE, 0, schur));
     double eta2;
-    TRY(run_map(op, Norm2<F64>{eta, Vh}, st, op->scalars + S_TMP, FIN_STORE, 0, nu));
+    TRY(run_map(op, Norm2<F64>{eta}, st, op->scalars + S_TMP, FIN_STORE, 0, schur));
     TRY(read_scalars(op, S_TMP, 1, &eta2, st));
     info->status = 0;
     info->nreset = 0;
@@ -112,8 +109,8 @@ int cgne_impl(qdw_op* op, const void* eta, void* psi, const qdw_cgne_params& prm
     }
     const double neta = std::sqrt(eta2);
     double s = PL == F64 ? 1.0 : sqrt24v / neta;
-    TRY(run_map(op, ScaleNorm<F64, PL>{eta, r, s, Vh}, st, op->scalars + S_RR, FIN_STORE, 0, nu));
-    TRY(run_map(op, Axpby<PL, PL>{r, p, 1.0, 0.0, Vh}, st, nullptr, FIN_STORE, 0, nu));
+    TRY(run_map(op, ScaleNorm<F64, PL>{eta, r, s}, st, op->scalars + S_RR, FIN_STORE, 0, schur));
+    TRY(run_map(op, Axpby<PL, PL>{r, p, 1.0, 0.0}, st, nullptr, FIN_STORE, 0, schur));
     double rr_reset;
     TRY(read_scalars(op, S_RR, 1, &rr_reset, st));
     double best = rr_reset, prev_true = 1.0;
@@ -130,9 +127,9 @@ int cgne_impl(qdw_op* op, const void* eta, void* psi, const qdw_cgne_params& prm
         if ((e = apply(p, q, PL, false))) return e;
         if ((e = apply(q, w, PL, true))) return e;
         S.ndw_lo += 2;
-        if ((e = run_map(op, Norm2<PL>{q, Vh}, st, op->scalars, FIN_CG_ALPHA, 0, nu))) return e;
-        if ((e = run_map(op, CgStep<PX, PL>{xlo, p, r, w, sc, Vh}, st, op->scalars, FIN_CG_BETA, 0, nu))) return e;
-        if ((e = run_map(op, CgDirection<PL>{r, p, sc, Vh}, st, nullptr, FIN_STORE, 0, nu))) return e;
+        if ((e = run_map(op, Norm2<PL>{q}, st, op->scalars, FIN_CG_ALPHA, 0, schur))) return e;
+        if ((e = run_map(op, CgStep<PX, PL>{xlo, p, r, w, sc}, st, op->scalars, FIN_CG_BETA, 0, schur))) return e;
+        if ((e = run_map(op, CgDirection<PL>{r, p, sc}, st, nullptr, FIN_STORE, 0, schur))) return e;
         ++S.steps;
         const int k = S.steps & 1;
         QDW_HIP(hipMemcpyAsync(slot + k, sc + S_RR, sizeof(double), hipMemcpyDeviceToHost, st));
@@ -146,17 +143,17 @@ int cgne_impl(qdw_op* op, const void* eta, void* psi, const qdw_cgne_params& prm
         int e;
         bool add = PL != F64;
         if (add && checked) {
-            if ((e = run_map(op, Norm2<PX>{xlo, Vh}, st, op->scalars + S_TMP, FIN_STORE, 0, nu))) return e;
+            if ((e = run_map(op, Norm2<PX>{xlo}, st, op->scalars + S_TMP, FIN_STORE, 0, schur))) return e;
             double x2;
             if ((e = read_scalars(op, S_TMP, 1, &x2, st))) return e;
             add = std::isfinite(x2);
         }
         if (add)
-            if ((e = run_map(op, Accumulate<PX>{psi, xlo, 1.0 / s, Vh}, st, nullptr, FIN_STORE, 0, nu))) return e;
+            if ((e = run_map(op, Accumulate<PX>{psi, xlo, 1.0 / s}, st, nullptr, FIN_STORE, 0, schur))) return e;
         if ((e = apply(psi, t1, F64, false))) return e;
         if ((e = apply(t1, t2, F64, true))) return e;
         S.ndw_hi += 2;
-        if ((e = run_map(op, Residual{eta, t2, rhi, Vh}, st, op->scalars + S_TMP, FIN_STORE, 0, nu))) return e;
+        if ((e = run_map(op, Residual{eta, t2, rhi}, st, op->scalars + S_TMP, FIN_STORE, 0, schur))) return e;
         double rt2;
         if ((e = read_scalars(op, S_TMP, 1, &rt2, st))) return e;
         *rel = std::sqrt(rt2) / neta;
@@ -168,7 +165,7 @@ int cgne_impl(qdw_op* op, const void* eta, void* psi, const qdw_cgne_params& prm
         int e;
         const double snew = PL == F64 ? 1.0 : sqrt24v / (rel * neta);
         // r = snew r_hi, with |r|^2 into S_RR and the drift |r_hi - r_old/s|^2 next to it
-        if ((e = run_map(op, ResetResidual<PL>{rhi, r, s, snew, Vh}, st, op->scalars + S_RR, FIN_STORE, 0, nu))) return e;
+        if ((e = run_map(op, ResetResidual<PL>{rhi, r, s, snew}, st, op->scalars + S_RR, FIN_STORE, 0, schur))) return e;
         double d2[2];
         if ((e = read_scalars(op, S_RR, 2, d2, st))) return e;
         // keep the direction only while the recursive residual had not drifted far from
@@ -176,9 +173,9 @@ int cgne_impl(qdw_op* op, const void* eta, void* psi, const qdw_cgne_params& prm
         const bool keep = prm.keep_p && std::sqrt(d2[1]) <= 0.3 * rel * neta;
         S.kept += keep;
         if (keep) {
-            if ((e = run_map(op, Axpby<PL, PL>{p, p, snew / s, 0.0, Vh}, st, nullptr, FIN_STORE, 0, nu))) return e;
+            if ((e = run_map(op, Axpby<PL, PL>{p, p, snew / s, 0.0}, st, nullptr, FIN_STORE, 0, schur))) return e;
         } else {
-            if ((e = run_map(op, Axpby<PL, PL>{r, p, 1.0, 0.0, Vh}, st, nullptr, FIN_STORE, 0, nu))) return e;
+            if ((e = run_map(op, Axpby<PL, PL>{r, p, 1.0, 0.0}, st, nullptr, FIN_STORE, 0, schur))) return e;
         }
         s = snew;
         rr_reset = d2[0];
@@ -292,7 +289,6 @@ int cascade_impl(qdw_op* op, const void* eta, void* psi, const qdw_cgne_params& 
                  qdw_info* info, hipStream_t st)
 {
     const Geom& g = op->g;
-    const int Vh = g.Vh;
     const size_t f = spinor_bytes(g, F64);
     void* rres = work;
     void* dlt = work + f;
@@ -300,7 +296,6 @@ int cascade_impl(qdw_op* op, const void* eta, void* psi, const qdw_cgne_params& 
     void* t2 = work + 3 * f;
     char* sub = work + 4 * f;
     const bool schur = prm.schur != 0;
-    const long nu = schur ? 3L * Vh : 0;
     auto apply = [&](const void* in, void* out, int prec, bool dag) {
         return schur ? schur_launch(op, in, out, prec, dag, st) : dw_launch(op, in, out, prec, dag, st);
     };
@@ -311,10 +306,10 @@ int cascade_impl(qdw_op* op, const void* eta, void* psi, const qdw_cgne_params& 
     info->n_dw_hi = info->n_dw_lo = 0;
     info->n_steps = 0;
     info->rel_res_true = 0.0;
-    TRY(run_map(op, Zero<F64>{psi, Vh}, st));
-    TRY(run_map(op, Axpby<F64, F64>{eta, rres, 1.0, 0.0, Vh}, st, nullptr, FIN_STORE, 0, nu));
+    TRY(run_map(op, Zero<F64>{psi}, st));
+    TRY(run_map(op, Axpby<F64, F64>{eta, rres, 1.0, 0.0}, st, nullptr, FIN_STORE, 0, schur));
     double eta2;
-    TRY(run_map(op, Norm2<F64>{eta, Vh}, st, op->scalars + S_TMP, FIN_STORE, 0, nu));
+    TRY(run_map(op, Norm2<F64>{eta}, st, op->scalars + S_TMP, FIN_STORE, 0, schur));
     TRY(read_scalars(op, S_TMP, 1, &eta2, st));
     if (!(eta2 > 0.0)) {
         info->status = std::isfinite(eta2) ? 0 : -3;
@@ -349,12 +344,12 @@ int cascade_impl(qdw_op* op, const void* eta, void* psi, const qdw_cgne_params& 
             break;
         }
         // psi += delta ; residual of the whole system in FP64
-        TRY(run_map(op, Axpby<F64, F64>{dlt, psi, 1.0, 1.0, Vh}, st, nullptr, FIN_STORE, 0, nu));
+        TRY(run_map(op, Axpby<F64, F64>{dlt, psi, 1.0, 1.0}, st, nullptr, FIN_STORE, 0, schur));
         TRY(apply(psi, t1, F64, false));
         TRY(apply(t1, t2, F64, true));
         info->n_dw_hi += 2;
         double r2;
-        TRY(run_map(op, Residual{eta, t2, rres, Vh}, st, op->scalars + S_TMP, FIN_STORE, 0, nu));
+        TRY(run_map(op, Residual{eta, t2, rres}, st, op->scalars + S_TMP, FIN_STORE, 0, schur));
         TRY(read_scalars(op, S_TMP, 1, &r2, st));
         rel = std::sqrt(r2) / neta;
         ++info->nreset;  // the phase switch is a reset step too

@@ -31,15 +31,14 @@ struct MultiDot {
     static constexpr int NS = 2 * K;
     const void* chi[kMaxKv];
     const void* v;
-    int Vh;
     __device__ void operator()(const Unit& u, double* acc) const
     {
         cx<double> vv[4];
-        ld4<F64, double>(v, Vh, u.par, u.g, u.i, vv);
+        ld4<F64, double>(v, u, vv);
 #pragma unroll
         for (int l = 0; l < K; ++l) {
             cx<double> c[4];
-            ld4<F64, double>(chi[l], Vh, u.par, u.g, u.i, c);
+            ld4<F64, double>(chi[l], u, c);
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const cx<double> z = cmul_conj(c[j], vv[j]);
@@ -58,21 +57,20 @@ struct GsUpdate {
     void* v;
     const void* rho;
     const double* a;  // a_lk at a[2l], a[2l+1]
-    int Vh;
     __device__ void operator()(const Unit& u, double* acc) const
     {
         cx<double> vv[4], rr[4];
-        ld4<F64, double>(v, Vh, u.par, u.g, u.i, vv);
+        ld4<F64, double>(v, u, vv);
 #pragma unroll
         for (int l = 0; l < K; ++l) {
             const cx<double> al = {a[2 * l], a[2 * l + 1]};
             cx<double> c[4];
-            ld4<F64, double>(chi[l], Vh, u.par, u.g, u.i, c);
+            ld4<F64, double>(chi[l], u, c);
 #pragma unroll
             for (int j = 0; j < 4; ++j) vv[j] = vv[j] - al * c[j];
         }
-        if (K > 0) st4<F64, double>(v, Vh, u.par, u.g, u.i, vv);
-        ld4<F64, double>(rho, Vh, u.par, u.g, u.i, rr);
+        if (K > 0) st4<F64, double>(v, u, vv);
+        ld4<F64, double>(rho, u, rr);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             acc[0] += vv[j].re * vv[j].re + vv[j].im * vv[j].im;
@@ -89,22 +87,21 @@ struct GcrUpdate {
     void* v;
     void* rho;
     const double* coef;  // 1/b, Re c/b, Im c/b
-    int Vh;
     __device__ void operator()(const Unit& u, double* acc) const
     {
         const double ib = coef[0];
         const cx<double> cb = {coef[1], coef[2]};
         cx<double> vv[4], rr[4];
-        ld4<F64, double>(v, Vh, u.par, u.g, u.i, vv);
-        ld4<F64, double>(rho, Vh, u.par, u.g, u.i, rr);
+        ld4<F64, double>(v, u, vv);
+        ld4<F64, double>(rho, u, rr);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             rr[j] = rr[j] - cb * vv[j];
             vv[j] = scale(vv[j], ib);
             acc[0] += rr[j].re * rr[j].re + rr[j].im * rr[j].im;
         }
-        st4<F64, double>(v, Vh, u.par, u.g, u.i, vv);
-        st4<F64, double>(rho, Vh, u.par, u.g, u.i, rr);
+        st4<F64, double>(v, u, vv);
+        st4<F64, double>(rho, u, rr);
     }
 };
 
@@ -115,33 +112,32 @@ struct MultiAxpy {
     void* psi;
     const void* phi[kMaxKv];
     double al[2 * kMaxKv];
-    int Vh;
     __device__ void operator()(const Unit& u, double*) const
     {
         cx<double> p[4];
-        ld4<F64, double>(psi, Vh, u.par, u.g, u.i, p);
+        ld4<F64, double>(psi, u, p);
 #pragma unroll
         for (int l = 0; l < K; ++l) {
             const cx<double> a = {al[2 * l], al[2 * l + 1]};
             cx<double> f[4];
-            ld4<F64, double>(phi[l], Vh, u.par, u.g, u.i, f);
+            ld4<F64, double>(phi[l], u, f);
 #pragma unroll
             for (int j = 0; j < 4; ++j) p[j] = p[j] + a * f[j];
         }
-        st4<F64, double>(psi, Vh, u.par, u.g, u.i, p);
+        st4<F64, double>(psi, u, p);
     }
 };
 
 template <template <int> class F, class Fill>
 int dispatch_k(int k, const qdw_op* op, hipStream_t st, Fill fill, double* out = nullptr,
-               int fin = FIN_STORE, int kk = 0)
+               int fin = FIN_STORE, int kk = 0, bool back = false)
 {
     switch (k) {
 #define QDW_K(n)                                                                       \
     case n: {                                                                          \
         F<n> f;                                                                        \
         fill(f);                                                                       \
-        return run_map(op, f, st, out, fin, kk);                                       \
+        return run_map(op, f, st, out, fin, kk, false, back);                                       \
     }
         QDW_K(0) QDW_K(1) QDW_K(2) QDW_K(3) QDW_K(4) QDW_K(5) QDW_K(6) QDW_K(7) QDW_K(8)
         QDW_K(9) QDW_K(10) QDW_K(11) QDW_K(12) QDW_K(13) QDW_K(14) QDW_K(15) QDW_K(16)
@@ -192,7 +188,6 @@ int gcr_impl(qdw_op* op, const void* eta, void* psi, const qdw_sap_gcr_params& p
              qdw_info* info, hipStream_t st)
 {
     const Geom& g = op->g;
-    const int Vh = g.Vh;
     GcrLayout L;
     layout(op, p, work, &L);
     BlockGeom B{};
@@ -207,11 +202,11 @@ int gcr_impl(qdw_op* op, const void* eta, void* psi, const qdw_sap_gcr_params& p
     info->n_dw_hi = info->n_dw_lo = 0;
     info->n_steps = 0;
     info->rel_res_true = 0.0;
-    TRY(run_map(op, Zero<F64>{psi, Vh}, st));
-    TRY(run_map(op, Axpby<F64, F64>{eta, L.rho, 1.0, 0.0, Vh}, st));
+    TRY(run_map(op, Zero<F64>{psi}, st));
+    TRY(run_map(op, Axpby<F64, F64>{eta, L.rho, 1.0, 0.0}, st));
     if (adaptive) TRY(sap_ctrl_reset_total(sap_ctrl(op, p.sdtype, L.pre), st));
     double eta2;
-    TRY(run_map(op, Norm2<F64>{eta, Vh}, st, op->scalars + S_TMP));
+    TRY(run_map(op, Norm2<F64>{eta}, st, op->scalars + S_TMP));
     TRY(read_scalars(op, S_TMP, 1, &eta2, st));
     if (!(eta2 > 0.0)) {
         info->status = std::isfinite(eta2) ? 0 : -3;
@@ -242,7 +237,7 @@ int gcr_impl(qdw_op* op, const void* eta, void* psi, const qdw_sap_gcr_params& p
                 TRY(sap_adaptive_run(op, L.rho, L.phi[k], rn, p.ncy, p.nmr, p.sap_alpha,
                                      p.res * neta / B.nblk, B, p.sdtype, L.pre, nullptr, st));
             } else {
-                TRY(run_map(op, Axpby<F64, F64>{L.rho, L.phi[k], 1.0, 0.0, Vh}, st));
+                TRY(run_map(op, Axpby<F64, F64>{L.rho, L.phi[k], 1.0, 0.0}, st));
             }
             // chi_k = D phi_k, orthogonalised against chi_0..k-1
             TRY(dw_launch(op, L.phi[k], L.chi[k], F64, false, st));
@@ -252,16 +247,14 @@ int gcr_impl(qdw_op* op, const void* eta, void* psi, const qdw_sap_gcr_params& p
                 TRY(dispatch_k<MultiDot>(k, op, st, [&](auto& f) {
                     for (int l = 0; l < k; ++l) f.chi[l] = L.chi[l];
                     f.v = L.chi[k];
-                    f.Vh = Vh;
                 }, ak));
             TRY(dispatch_k<GsUpdate>(k, op, st, [&](auto& f) {
                 for (int l = 0; l < k; ++l) f.chi[l] = L.chi[l];
                 f.v = L.chi[k];
                 f.rho = L.rho;
                 f.a = ak;
-                f.Vh = Vh;
-            }, L.gsc, FIN_GCR_NORM, k));
-            TRY(run_map(op, GcrUpdate{L.chi[k], L.rho, L.gsc + G_COEF, Vh}, st, L.gsc + G_NORM));
+            }, L.gsc, FIN_GCR_NORM, k, true));
+            TRY(run_map(op, GcrUpdate{L.chi[k], L.rho, L.gsc + G_COEF}, st, L.gsc + G_NORM));
             double r2;
             TRY(read_device(op, L.gsc + G_NORM, 1, &r2, st));
             if (!std::isfinite(r2)) {
@@ -304,11 +297,10 @@ int gcr_impl(qdw_op* op, const void* eta, void* psi, const qdw_sap_gcr_params& p
                     f.al[2 * l] = al[l].real();
                     f.al[2 * l + 1] = al[l].imag();
                 }
-                f.Vh = Vh;
             }));
             TRY(dw_launch(op, psi, L.tmp, F64, false, st));
             ++info->n_dw_hi;
-            TRY(run_map(op, Residual{eta, L.tmp, L.rho, Vh}, st, op->scalars + S_TMP));
+            TRY(run_map(op, Residual{eta, L.tmp, L.rho}, st, op->scalars + S_TMP));
             double r2;
             TRY(read_scalars(op, S_TMP, 1, &r2, st));
             ++info->nreset;

@@ -1105,17 +1105,16 @@ struct LossDiff {
     const void* out;
     const void* e;
     void* d;
-    int Vh;
     __device__ void operator()(const Unit& u, double* acc) const
     {
         cx<float> o[4], t[4];
-        ld4<F32, float>(out, Vh, u.par, u.g, u.i, o);
-        ld4<F32, float>(e, Vh, u.par, u.g, u.i, t);
+        ld4<F32, float>(out, u, o);
+        ld4<F32, float>(e, u, t);
         for (int k = 0; k < 4; ++k) {
             o[k] = o[k] - t[k];
             acc[0] += (double)o[k].re * o[k].re + (double)o[k].im * o[k].im;
         }
-        st4<F32, float>(d, Vh, u.par, u.g, u.i, o);
+        st4<F32, float>(d, u, o);
     }
 };
 
@@ -1339,13 +1338,13 @@ int nn_precondition(qdw_op* op, const void* weights, const void* rho, void* phi,
     nn_layout(op, false, work, &W, false);
     const Geom& g = op->g;
     int rc;
-    if (!(rho_norm > 0.0)) return run_map(op, Zero<F64>{phi, g.Vh}, st);
+    if (!(rho_norm > 0.0)) return run_map(op, Zero<F64>{phi}, st);
     const double s = std::sqrt(24.0 * g.V) / rho_norm;
-    if ((rc = run_map(op, ScaleNorm<F64, F32>{rho, W.act[0][0], s, g.Vh}, st,
+    if ((rc = run_map(op, ScaleNorm<F64, F32>{rho, W.act[0][0], s}, st,
                       op->scalars + S_TMP + 2)))
         return rc;
     if ((rc = forward<false>(op, (const float*)weights, W, st, false))) return rc;
-    return run_map(op, Axpby<F32, F64>{W.act[kLayers][0], phi, 1.0 / s, 0.0, g.Vh}, st);
+    return run_map(op, Axpby<F32, F64>{W.act[kLayers][0], phi, 1.0 / s, 0.0}, st);
 }
 
 }  // namespace qdw
@@ -1372,10 +1371,10 @@ extern "C" int nn_forward(qdw_op* op, const float* weights, const void* in, void
     nn_layout(op, false, align_work(work), &W);
     const Geom& g = op->g;
     int rc;
-    if ((rc = run_map(op, Axpby<F64, F32>{in, W.act[0][0], 1.0, 0.0, g.Vh}, st))) return rc;
+    if ((rc = run_map(op, Axpby<F64, F32>{in, W.act[0][0], 1.0, 0.0}, st))) return rc;
     rc = f32_mixing ? forward<true>(op, weights, W, st) : forward<false>(op, weights, W, st, false);
     if (rc) return rc;
-    return run_map(op, Axpby<F32, F64>{W.act[kLayers][0], out, 1.0, 0.0, g.Vh}, st);
+    return run_map(op, Axpby<F32, F64>{W.act[kLayers][0], out, 1.0, 0.0}, st);
 }
 
 extern "C" int nn_backward(qdw_op* op, const float* weights, const void* in, const void* gout,
@@ -1392,15 +1391,15 @@ extern "C" int nn_backward(qdw_op* op, const float* weights, const void* in, con
     const Geom& g = op->g;
     int rc;
     if ((rc = zero_dev(dW, sizeof(float) * 2 * total_weights(), st))) return rc;
-    if ((rc = run_map(op, Axpby<F64, F32>{in, W.act[0][0], 1.0, 0.0, g.Vh}, st))) return rc;
+    if ((rc = run_map(op, Axpby<F64, F32>{in, W.act[0][0], 1.0, 0.0}, st))) return rc;
     rc = f32_mixing ? forward<true>(op, weights, W, st) : forward<false>(op, weights, W, st);
     if (rc) return rc;
-    if ((rc = run_map(op, Axpby<F64, F32>{gout, W.grad[0][0], 1.0, 0.0, g.Vh}, st))) return rc;
+    if ((rc = run_map(op, Axpby<F64, F32>{gout, W.grad[0][0], 1.0, 0.0}, st))) return rc;
     float* gi = nullptr;
     rc = f32_mixing ? backward<true>(op, weights, dW, W, 1.f, st, &gi)
                     : backward<false>(op, weights, dW, W, 1.f, st, &gi);
     if (rc) return rc;
-    return run_map(op, Axpby<F32, F64>{gi, gin, 1.0, 0.0, g.Vh}, st);
+    return run_map(op, Axpby<F32, F64>{gi, gin, 1.0, 0.0}, st);
 }
 
 namespace {
@@ -1409,16 +1408,16 @@ namespace {
 template <int P>
 int pair_to_f32(qdw_op* op, const void* x, float* y, double s, hipStream_t st)
 {
-    return run_map(op, Axpby<P, F32>{x, y, s, 0.0, op->g.Vh}, st);
+    return run_map(op, Axpby<P, F32>{x, y, s, 0.0}, st);
 }
 
 int pair_norm2(qdw_op* op, const void* x, int prec, double* out, hipStream_t st)
 {
     int rc;
     switch (prec) {
-    case F64: rc = run_map(op, Norm2<F64>{x, op->g.Vh}, st, op->scalars + S_TMP); break;
-    case F32: rc = run_map(op, Norm2<F32>{x, op->g.Vh}, st, op->scalars + S_TMP); break;
-    default: rc = run_map(op, Norm2<BF16S>{x, op->g.Vh}, st, op->scalars + S_TMP); break;
+    case F64: rc = run_map(op, Norm2<F64>{x}, st, op->scalars + S_TMP); break;
+    case F32: rc = run_map(op, Norm2<F32>{x}, st, op->scalars + S_TMP); break;
+    default: rc = run_map(op, Norm2<BF16S>{x}, st, op->scalars + S_TMP); break;
     }
     if (rc) return rc;
     return read_scalars(op, S_TMP, 1, out, st);
@@ -1467,11 +1466,11 @@ extern "C" int nn_train_step(qdw_op* op, float* weights, float* adam, int step, 
         if ((rc = pair_convert(op, rho[k], pair_prec, W.act[0][0], s, st))) return rc;
         if ((rc = pair_convert(op, err[k], pair_prec, W.efield, s, st))) return rc;
         double e2;
-        if ((rc = run_map(op, Norm2<F32>{W.efield, g.Vh}, st, op->scalars + S_TMP))) return rc;
+        if ((rc = run_map(op, Norm2<F32>{W.efield}, st, op->scalars + S_TMP))) return rc;
         if ((rc = read_scalars(op, S_TMP, 1, &e2, st))) return rc;
         if ((rc = forward<false>(op, weights, W, st))) return rc;
         double d2;
-        if ((rc = run_map(op, LossDiff{W.act[kLayers][0], W.efield, W.grad[0][0], g.Vh}, st,
+        if ((rc = run_map(op, LossDiff{W.act[kLayers][0], W.efield, W.grad[0][0]}, st,
                           op->scalars + S_TMP)))
             return rc;
         if ((rc = read_scalars(op, S_TMP, 1, &d2, st))) return rc;
@@ -1482,10 +1481,10 @@ extern "C" int nn_train_step(qdw_op* op, float* weights, float* adam, int step, 
             float* t = W.grad[1][0];
             float* De = W.grad[1][1];
             if ((rc = dw_launch(op, W.grad[0][0], t, F32, false, st))) return rc;
-            if ((rc = run_map(op, Norm2<F32>{t, g.Vh}, st, op->scalars + S_TMP))) return rc;
+            if ((rc = run_map(op, Norm2<F32>{t}, st, op->scalars + S_TMP))) return rc;
             if ((rc = read_scalars(op, S_TMP, 1, &d2, st))) return rc;
             if ((rc = dw_launch(op, W.efield, De, F32, false, st))) return rc;
-            if ((rc = run_map(op, Norm2<F32>{De, g.Vh}, st, op->scalars + S_TMP))) return rc;
+            if ((rc = run_map(op, Norm2<F32>{De}, st, op->scalars + S_TMP))) return rc;
             if ((rc = read_scalars(op, S_TMP, 1, &denom, st))) return rc;
             if ((rc = dw_launch(op, t, W.grad[0][0], F32, true, st))) return rc;
         }

@@ -93,8 +93,13 @@ __device__ inline long shifted(const Geom& g, const int x[4], int mu, int dmu, i
 
 // ------------------------------------------------------------------ unitarity check
 
-// *p = 0 (a kernel, not a memset node, so the set-up can be captured)
-__global__ void zero_u64_kernel(unsigned long long* p) { *p = 0ull; }
+// *p = 0 and the arrival counters of the reductions (a kernel, not a memset node, so the
+// set-up can be captured)
+__global__ void zero_scratch_kernel(unsigned long long* p, unsigned* tickets)
+{
+    if (threadIdx.x == 0) *p = 0ull;
+    for (int k = threadIdx.x; k < kTicketWords; k += blockDim.x) tickets[k] = 0u;
+}
 
 __global__ void unitarity_kernel(const double* su3, long nlinks, unsigned long long* worst)
 {
@@ -480,7 +485,7 @@ __global__ void pack_kernel<F64>(Geom g, const double* can, void* eo)
 // aligned): compressed links and their determinants, clover blocks and their inverses in
 // every precision, then the reduction scratch.
 struct OpLayout {
-    size_t links[4], det[4], clover[4], cloverinv[4], clover54[4], partials, scalars, worst,
+    size_t links[4], det[4], clover[4], cloverinv[4], clover54[4], partials, tickets, scalars, worst,
         total;
 };
 
@@ -508,6 +513,7 @@ OpLayout op_layout(int Vh)
     const size_t c54[4] = {27 * 16, 14 * 16, 7 * 16, 7 * 16};  // compact clover, bytes per site
     for (int p = 0; p < 4; ++p) L.clover54[p] = take(ns * c54[p]);
     L.partials = take(sizeof(double) * kMaxPartials * kMaxScalars);
+    L.tickets = take(sizeof(unsigned) * kTicketWords);
     L.scalars = take(sizeof(double) * kMaxScalars);
     L.worst = take(sizeof(unsigned long long));
     L.total = off + 256;  // room to align the caller's pointer
@@ -608,6 +614,7 @@ extern "C" int qdw_create(const qdw_lattice* lat, const double* su3, const doubl
         op->clover54[p] = base + lay.clover54[p];
     }
     op->partials = (double*)(base + lay.partials);
+    op->tickets = (unsigned*)(base + lay.tickets);
     op->scalars = (double*)(base + lay.scalars);
     op->host_scalars = (double*)host_mem;
 
@@ -626,7 +633,7 @@ extern "C" int qdw_create(const qdw_lattice* lat, const double* su3, const doubl
     // 1. unitarity of the SU(3) parts (the worst deviation as the bits of a non-negative
     //    double, so an integer maximum orders them)
     unsigned long long* worst = (unsigned long long*)(base + lay.worst);
-    zero_u64_kernel<<<1, 1, 0, st>>>(worst);
+    zero_scratch_kernel<<<1, 256, 0, st>>>(worst, op->tickets);
     CREATE_HIP(hipGetLastError());
     const long nlinks = V * 4;
     unitarity_kernel<<<(unsigned)((nlinks + 255) / 256), 256, 0, st>>>(su3, nlinks, worst);

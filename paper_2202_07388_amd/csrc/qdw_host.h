@@ -25,8 +25,10 @@ struct qdw_op {
     // per walk chunk, software-pipelined hop loop, walk order, marching form); other site
     // kernels use g
     struct { int ts, nt, pipe, walk, march; } dw_shape[4];
-    // reduction scratch: per-workgroup partial sums and the final scalars
+    // reduction scratch: per-workgroup partial sums, the arrival counters of the workgroups
+    // (zero between launches) and the final scalars
     double* partials;      // device, kMaxPartials * kMaxScalars doubles
+    unsigned* tickets;     // device, kTicketWords words
     double* scalars;       // device, kMaxScalars doubles
     double* host_scalars;  // pinned host, kHostScalars doubles
 };
@@ -34,6 +36,10 @@ struct qdw_op {
 namespace qdw {
 
 constexpr int kMaxPartials = 2048;  // workgroups of a reduction launch
+// arrivals are counted in two levels, kTickets counters (one per 128 bytes) and a top one,
+// so that thousands of workgroups do not meet on one address
+constexpr int kTickets = 32;
+constexpr int kTicketWords = (kTickets + 1) * 32;
 constexpr int kMaxScalars = 64;     // doubles produced by one fused reduction
 constexpr int kHostScalars = 1024;  // doubles the host can read back in one copy
 constexpr int kMaxRhs = 64;         // right-hand sides of one multi-right-hand-side launch

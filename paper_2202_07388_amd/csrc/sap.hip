@@ -838,13 +838,13 @@ int sap_impl(qdw_op* op, const void* rho, void* phi, double rho_norm, int ncy, i
     int rc;
     if (ncy == 0 || !(rho_norm > 0.0)) {
         // no preconditioning (the (0, 0) setting), or nothing to precondition
-        return run_map(op, Axpby<F64, F64>{rho, phi, ncy == 0 ? 1.0 : 0.0, 0.0, g.Vh}, st);
+        return run_map(op, Axpby<F64, F64>{rho, phi, ncy == 0 ? 1.0 : 0.0, 0.0}, st);
     }
     const double s = std::sqrt(24.0 * g.V) / rho_norm;
-    if ((rc = run_map(op, ScaleNorm<F64, SP>{rho, rs, s, g.Vh}, st, op->scalars + S_SAP))) return rc;
-    if ((rc = run_map(op, Zero<SP>{psis, g.Vh}, st))) return rc;
+    if ((rc = run_map(op, ScaleNorm<F64, SP>{rho, rs, s}, st, op->scalars + S_SAP))) return rc;
+    if ((rc = run_map(op, Zero<SP>{psis}, st))) return rc;
     if ((rc = sap_cycles(op, B, SP, ncy, nmr, rs, psis, delta, RhsStride{}, 1, st, eo))) return rc;
-    return run_map(op, Axpby<SP, F64>{psis, phi, 1.0 / s, 0.0, g.Vh}, st);
+    return run_map(op, Axpby<SP, F64>{psis, phi, 1.0 / s, 0.0}, st);
 }
 
 // adaptive cycles: ctrl = {go, cycles done, cycles done over all applications}
@@ -879,10 +879,10 @@ int adaptive_impl(qdw_op* op, const void* rho, void* phi, double rho_norm, int n
     int* ctrl = (int*)(work + 3 * fb);
     int rc;
     if (ncy_max == 0 || !(rho_norm > 0.0))
-        return run_map(op, Axpby<F64, F64>{rho, phi, ncy_max == 0 ? 1.0 : 0.0, 0.0, g.Vh}, st);
+        return run_map(op, Axpby<F64, F64>{rho, phi, ncy_max == 0 ? 1.0 : 0.0, 0.0}, st);
     const double s = std::sqrt(24.0 * g.V) / rho_norm;
-    if ((rc = run_map(op, ScaleNorm<F64, SP>{rho, rs, s, g.Vh}, st, op->scalars + S_SAP))) return rc;
-    if ((rc = run_map(op, Zero<SP>{psis, g.Vh}, st))) return rc;
+    if ((rc = run_map(op, ScaleNorm<F64, SP>{rho, rs, s}, st, op->scalars + S_SAP))) return rc;
+    if ((rc = run_map(op, Zero<SP>{psis}, st))) return rc;
     sap_ctrl_init_kernel<<<1, 1, 0, st>>>(ctrl, 0);
     QDW_LAUNCH_CHECK();
     RhsStride gate;
@@ -903,11 +903,11 @@ int adaptive_impl(qdw_op* op, const void* rho, void* phi, double rho_norm, int n
                                                               op->det[SP], gate);
             QDW_LAUNCH_CHECK();
         }
-        if ((rc = run_map(op, Norm2<SP>{rs, g.Vh}, st, op->scalars + S_SAP_NEW))) return rc;
+        if ((rc = run_map(op, Norm2<SP>{rs}, st, op->scalars + S_SAP_NEW))) return rc;
         sap_ctrl_cycle_kernel<<<1, 1, 0, st>>>(ctrl, op->scalars);
         QDW_LAUNCH_CHECK();
     }
-    return run_map(op, Axpby<SP, F64>{psis, phi, 1.0 / s, 0.0, g.Vh}, st);
+    return run_map(op, Axpby<SP, F64>{psis, phi, 1.0 / s, 0.0}, st);
 }
 
 }  // namespace
@@ -988,7 +988,7 @@ int sap_apply_impl(const char* fn, qdw_op* op, const void* rho, void* phi, int n
     int rc = make_block_geom(op->g, bs, &B);
     if (rc) return rc;
     hipStream_t st = (hipStream_t)stream;
-    if ((rc = run_map(op, Norm2<F64>{rho, op->g.Vh}, st, op->scalars + S_TMP))) return rc;
+    if ((rc = run_map(op, Norm2<F64>{rho}, st, op->scalars + S_TMP))) return rc;
     double n2;
     if ((rc = read_scalars(op, S_TMP, 1, &n2, st))) return rc;
     char* wk = (char*)(((uintptr_t)work + 255) & ~(uintptr_t)255);
@@ -1030,7 +1030,7 @@ extern "C" int sap_adaptive_apply(qdw_op* op, const void* rho, void* phi, int nc
     int rc = make_block_geom(op->g, bs, &B);
     if (rc) return rc;
     hipStream_t st = (hipStream_t)stream;
-    if ((rc = run_map(op, Norm2<F64>{rho, op->g.Vh}, st, op->scalars + S_TMP))) return rc;
+    if ((rc = run_map(op, Norm2<F64>{rho}, st, op->scalars + S_TMP))) return rc;
     double n2;
     if ((rc = read_scalars(op, S_TMP, 1, &n2, st))) return rc;
     char* wk = (char*)(((uintptr_t)work + 255) & ~(uintptr_t)255);
