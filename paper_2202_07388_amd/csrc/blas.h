@@ -379,62 +379,31 @@ struct ScaleNorm {
     }
 };
 
-// CG step: x += alpha p ; r -= alpha w ; |r|^2   (alpha read from device scalars)
+// The iterate and the direction of a CG step in one pass: x += alpha p ; p = r + beta p
+// (alpha, beta read from device scalars; the residual has its update from cg_apply_dag)
 template <int PX, int P>
-struct CgStep {
-    static constexpr int NS = 1;
-    void* x;
-    const void* p;
-    void* r;
-    const void* w;
-    const double* sc;
-    __device__ void operator()(const Unit& u, double* acc) const
-    {
-        using R = typename Traits<P>::real;
-        const R a = (R)sc[S_ALPHA];
-        // a zero or non-finite step length leaves the iterate as it was, so that a solve that
-        // runs into a non-finite value still holds its last finite iterate
-        const bool move = a != (R)0 && isfinite(a);
-        cx<R> vx[4], vp[4], vr[4], vw[4];
-        ld4<P, R>(p, u, vp);
-        ld4<P, R>(r, u, vr);
-        ld4<P, R>(w, u, vw);
-        if (move) {
-            ld4<PX, R>(x, u, vx);
-#pragma unroll
-            for (int k = 0; k < 4; ++k) vx[k] = vx[k] + scale(vp[k], a);
-            st4<PX, R>(x, u, vx);
-        }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) vr[k] = vr[k] - scale(vw[k], a);
-        st4<P, R>(r, u, vr);
-        // reduce what is stored (rounded to P), in FP64; FP64 stores the values as they are
-        cx<double> back[4];
-        if constexpr (P == F64) {
-#pragma unroll
-            for (int k = 0; k < 4; ++k) back[k] = {(double)vr[k].re, (double)vr[k].im};
-        } else {
-            ld4<P, double>(r, u, back);
-        }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) acc[0] += back[k].re * back[k].re + back[k].im * back[k].im;
-    }
-};
-
-// p = r + beta p   (beta read from device scalars)
-template <int P>
 struct CgDirection {
     static constexpr int NS = 0;
+    void* x;
     const void* r;
     void* p;
     const double* sc;
     __device__ void operator()(const Unit& u, double*) const
     {
         using R = typename Traits<P>::real;
-        const R b = (R)sc[S_BETA];
-        cx<R> vr[4], vp[4];
-        ld4<P, R>(r, u, vr);
+        const R a = (R)sc[S_ALPHA], b = (R)sc[S_BETA];
+        // a zero or non-finite step length leaves the iterate as it was, so that a solve that
+        // runs into a non-finite value still holds its last finite iterate
+        const bool move = a != (R)0 && isfinite(a);
+        cx<R> vx[4], vp[4], vr[4];
         ld4<P, R>(p, u, vp);
+        ld4<P, R>(r, u, vr);
+        if (move) {
+            ld4<PX, R>(x, u, vx);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) vx[k] = vx[k] + scale(vp[k], a);
+            st4<PX, R>(x, u, vx);
+        }
 #pragma unroll
         for (int k = 0; k < 4; ++k) vp[k] = vr[k] + scale(vp[k], b);
         st4<P, R>(p, u, vp);
@@ -500,6 +469,11 @@ struct Zero {
 int dw_launch(qdw_op* op, const void* in, void* out, int prec, bool dag, hipStream_t st);
 // the even-odd reduced operator on the even half of in (odd half of out: scratch)
 int schur_launch(qdw_op* op, const void* in, void* out, int prec, bool dag, hipStream_t st);
+// the two operator applications of a CG step with the step's sums and residual in them:
+//   q = D p, |q|^2 -> alpha ;  r -= alpha D^+ q, |r|^2 -> beta
+// (schur: the even-odd reduced operator; t is then the scratch its odd half needs)
+int cg_apply(qdw_op* op, const void* p, void* q, int prec, bool schur, hipStream_t st);
+int cg_apply_dag(qdw_op* op, const void* q, void* r, void* t, int prec, bool schur, hipStream_t st);
 
 // read `n` device doubles at `src` (synchronises the stream)
 inline int read_device(const qdw_op* op, const double* src, int n, double* out, hipStream_t st)

@@ -124,12 +124,10 @@ int cgne_impl(qdw_op* op, const void* eta, void* psi, const qdw_cgne_params& prm
 
     auto iterate = [&]() -> int {
         int e;
-        if ((e = apply(p, q, PL, false))) return e;
-        if ((e = apply(q, w, PL, true))) return e;
+        if ((e = cg_apply(op, p, q, PL, schur, st))) return e;
+        if ((e = cg_apply_dag(op, q, r, w, PL, schur, st))) return e;
         S.ndw_lo += 2;
-        if ((e = run_map(op, Norm2<PL>{q}, st, op->scalars, FIN_CG_ALPHA, 0, schur))) return e;
-        if ((e = run_map(op, CgStep<PX, PL>{xlo, p, r, w, sc}, st, op->scalars, FIN_CG_BETA, 0, schur))) return e;
-        if ((e = run_map(op, CgDirection<PL>{r, p, sc}, st, nullptr, FIN_STORE, 0, schur))) return e;
+        if ((e = run_map(op, CgDirection<PX, PL>{xlo, r, p, sc}, st, nullptr, FIN_STORE, 0, schur))) return e;
         ++S.steps;
         const int k = S.steps & 1;
         QDW_HIP(hipMemcpyAsync(slot + k, sc + S_RR, sizeof(double), hipMemcpyDeviceToHost, st));

@@ -31,7 +31,7 @@
 #include <type_traits>
 #include <vector>
 
-#include "qdw_host.h"
+#include "blas.h"
 #include "dirac_core.h"
 
 using namespace qdw;
@@ -46,6 +46,41 @@ struct RhsTable {
 }  // namespace qdw
 
 namespace {
+
+// What a kernel does with an output spinor beside storing it. EPI_NORM also sums |out|^2 (as
+// stored). EPI_STEP is the second half of a CG step: w = out stays in registers, r -= alpha w
+// is stored instead, and |r|^2 (as stored) is summed; alpha comes from the device scalars.
+// Either saves passes over whole fields: a separate norm reads q again, and a separate
+// residual update writes and reads w.
+enum { EPI_NONE = 0, EPI_NORM, EPI_STEP };
+struct Epi {
+    Sums sums;
+    void* r;
+    const double* sc;
+};
+
+template <int P, int EPI>
+__device__ __forceinline__ void store_out(void* out, const Epi& e, int Vh, int par, int i,
+                                          cx<typename Traits<P>::real> acc[12], double& sum)
+{
+    using R = typename Traits<P>::real;
+    if constexpr (EPI == EPI_STEP) {
+        const R a = (R)e.sc[S_ALPHA];
+        cx<R> r[12];
+        load_spinor<P>(e.r, Vh, par, i, r);
+#pragma unroll
+        for (int c = 0; c < 12; ++c) acc[c] = r[c] - scale(acc[c], a);
+        out = e.r;
+    }
+    store_spinor<P>(out, Vh, par, i, acc);
+    if constexpr (EPI != EPI_NONE) {
+#pragma unroll
+        for (int c = 0; c < 12; ++c) {
+            const double re = to_real<P>(to_store<P>(acc[c].re)), im = to_real<P>(to_store<P>(acc[c].im));
+            sum = __builtin_fma(re, re, __builtin_fma(im, im, sum));
+        }
+    }
+}
 
 template <int P>
 struct HopIn {
@@ -125,10 +160,10 @@ __device__ __forceinline__ void compute_k(int k, const Geom& g, const int x[4], 
 // One lane per site. With half-precision storage and no software pipelining the kernel
 // fits four waves per SIMD without spilling (123 VGPRs instead of 156 at three), which
 // hides more of the gather latency.
-template <int P, bool DAG, bool PIPE>
+template <int P, bool DAG, bool PIPE, int EPI>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(P >= F16S && !PIPE ? 4 : 1)))
 void dw_kernel(Geom g, RhsTable tab, int nrhs, const void* __restrict__ links,
-               const void* __restrict__ dets, const void* __restrict__ clover)
+               const void* __restrict__ dets, const void* __restrict__ clover, Epi epi)
 {
     using R = typename Traits<P>::real;
     const int logical = xcd_tile(blockIdx.x, gridDim.x);
@@ -138,40 +173,43 @@ void dw_kernel(Geom g, RhsTable tab, int nrhs, const void* __restrict__ links,
     const void* __restrict__ in = tab.in[rhs];
     void* __restrict__ out = tab.out[rhs];
     int par, i;
-    if (!walk_site(g, tile, threadIdx.x, par, i)) return;
-    int x[4], lex;
-    eo_coords(g, par, i, x, lex);
-    cx<R> hop[12];
+    double sum = 0.0;
+    if (walk_site(g, tile, threadIdx.x, par, i)) {
+        int x[4], lex;
+        eo_coords(g, par, i, x, lex);
+        cx<R> hop[12];
 #pragma unroll
-    for (int c = 0; c < 12; ++c) hop[c] = {(R)0, (R)0};
-    if constexpr (PIPE) {
-        HopIn<P> A, B;
-        load_k<P>(0, g, in, links, dets, par, i, x, lex, A);
+        for (int c = 0; c < 12; ++c) hop[c] = {(R)0, (R)0};
+        if constexpr (PIPE) {
+            HopIn<P> A, B;
+            load_k<P>(0, g, in, links, dets, par, i, x, lex, A);
 #pragma unroll 1
-        for (int k = 0; k < 8; k += 2) {
-            int ii = i, ll = lex, xx[4] = {x[0], x[1], x[2], x[3]};
-            asm volatile("" : "+v"(ii), "+v"(ll), "+v"(xx[0]), "+v"(xx[1]), "+v"(xx[2]), "+v"(xx[3]));
-            load_k<P>(k + 1, g, in, links, dets, par, ii, xx, ll, B);
-            compute_k<P, DAG>(k, g, xx, A, hop);
-            if (k + 2 < 8) load_k<P>(k + 2, g, in, links, dets, par, ii, xx, ll, A);
-            compute_k<P, DAG>(k + 1, g, xx, B, hop);
-        }
-    } else {
-        HopIn<P> A;
+            for (int k = 0; k < 8; k += 2) {
+                int ii = i, ll = lex, xx[4] = {x[0], x[1], x[2], x[3]};
+                asm volatile("" : "+v"(ii), "+v"(ll), "+v"(xx[0]), "+v"(xx[1]), "+v"(xx[2]), "+v"(xx[3]));
+                load_k<P>(k + 1, g, in, links, dets, par, ii, xx, ll, B);
+                compute_k<P, DAG>(k, g, xx, A, hop);
+                if (k + 2 < 8) load_k<P>(k + 2, g, in, links, dets, par, ii, xx, ll, A);
+                compute_k<P, DAG>(k + 1, g, xx, B, hop);
+            }
+        } else {
+            HopIn<P> A;
 #pragma unroll 1
-        for (int k = 0; k < 8; ++k) {
-            int ii = i, ll = lex, xx[4] = {x[0], x[1], x[2], x[3]};
-            asm volatile("" : "+v"(ii), "+v"(ll), "+v"(xx[0]), "+v"(xx[1]), "+v"(xx[2]), "+v"(xx[3]));
-            load_k<P>(k, g, in, links, dets, par, ii, xx, ll, A);
-            compute_k<P, DAG>(k, g, xx, A, hop);
+            for (int k = 0; k < 8; ++k) {
+                int ii = i, ll = lex, xx[4] = {x[0], x[1], x[2], x[3]};
+                asm volatile("" : "+v"(ii), "+v"(ll), "+v"(xx[0]), "+v"(xx[1]), "+v"(xx[2]), "+v"(xx[3]));
+                load_k<P>(k, g, in, links, dets, par, ii, xx, ll, A);
+                compute_k<P, DAG>(k, g, xx, A, hop);
+            }
         }
+        cx<R> s[12], acc[12];
+        load_spinor<P>(in, g.Vh, par, i, s);
+        clover54_apply<P>(clover, g.Vh, par, i, (R)g.cdiag, s, acc);
+#pragma unroll
+        for (int c = 0; c < 12; ++c) acc[c] = acc[c] - scale(hop[c], (R)0.5);
+        store_out<P, EPI>(out, epi, g.Vh, par, i, acc, sum);
     }
-    cx<R> s[12], acc[12];
-    load_spinor<P>(in, g.Vh, par, i, s);
-    clover54_apply<P>(clover, g.Vh, par, i, (R)g.cdiag, s, acc);
-#pragma unroll
-    for (int c = 0; c < 12; ++c) acc[c] = acc[c] - scale(hop[c], (R)0.5);
-    store_spinor<P>(out, g.Vh, par, i, acc);
+    if constexpr (EPI != EPI_NONE) grid_sums<1>(&sum, epi.sums, blockIdx.x, gridDim.x);
 }
 
 // Marching form: a workgroup owns one spatial tile (both parities) and walks the nt time
@@ -225,11 +263,11 @@ __device__ __forceinline__ void march_site_hops(const Geom& g, const void* in, c
     }
 }
 
-template <int P, bool DAG, bool PIPE>
+template <int P, bool DAG, bool PIPE, int EPI>
 __global__ __launch_bounds__(256) void dw_march_kernel(Geom g, RhsTable tab, int nrhs,
                                                        const void* __restrict__ links,
                                                        const void* __restrict__ dets,
-                                                       const void* __restrict__ clover)
+                                                       const void* __restrict__ clover, Epi epi)
 {
     using R = typename Traits<P>::real;
     constexpr int SGF = DAG ? +1 : -1;  // projector of the +t hop: 1 + SGF gamma_0
@@ -297,6 +335,7 @@ __global__ __launch_bounds__(256) void dw_march_kernel(Geom g, RhsTable tab, int
     // loaded it for the partner (a reload one step later would come from HBM again), and
     // so does the accumulator of the current slice, begun in the step before
     cx<R> own[12], acc[12];
+    double sum = 0.0;
     if (valid) {
         const int tp = t0 == 0 ? g.L[0] - 1 : t0 - 1;
         cx<R> u[6], d;
@@ -343,7 +382,7 @@ __global__ __launch_bounds__(256) void dw_march_kernel(Geom g, RhsTable tab, int
                 for (int q = 0; q < 6; ++q) w[q] = scale(w[q], (R)-0.5);
                 expand_add<R, 0, SGB>(w, acc);
             }
-            store_spinor<P>(out, g.Vh, par, i, acc);
+            store_out<P, EPI>(out, epi, g.Vh, par, i, acc, sum);
             // (3) the next slice's clover term and spatial hops, on the spinors loaded in
             //     this step
             if (step + 1 < g.nt) {
@@ -353,6 +392,7 @@ __global__ __launch_bounds__(256) void dw_march_kernel(Geom g, RhsTable tab, int
             }
         }
     }
+    if constexpr (EPI != EPI_NONE) grid_sums<1>(&sum, epi.sums, blockIdx.x, gridDim.x);
 }
 
 // Even-odd reduced operator D^ = A_ee - D_eo A_oo^-1 D_oe on the even half of a field, in
@@ -361,12 +401,12 @@ __global__ __launch_bounds__(256) void dw_march_kernel(Geom g, RhsTable tab, int
 //   stage 2, even sites: out = A_ee psi_e - D_eo t = A_ee psi_e + 1/2 sum of the hops of t
 // t lives in the odd half of the output field. D^+ = gamma_5 D^ gamma_5 flips the
 // projector signs as for D (A and A^-1 commute with gamma_5).
-template <int P, bool DAG, int STAGE, bool PIPE>
+template <int P, bool DAG, int STAGE, bool PIPE, int EPI>
 __global__ __launch_bounds__(256) void schur_kernel(Geom g, int ntile1, const void* hsrc,
                                                     const void* dsrc, void* out,
                                                     const void* __restrict__ links,
                                                     const void* __restrict__ dets,
-                                                    const void* __restrict__ diag)
+                                                    const void* __restrict__ diag, Epi epi)
 {
     using R = typename Traits<P>::real;
     constexpr int par = STAGE == 1 ? 1 : 0;
@@ -379,63 +419,66 @@ __global__ __launch_bounds__(256) void schur_kernel(Geom g, int ntile1, const vo
     const int sidx = r / g.nt;
     const int t = c * g.nt + (r - sidx * g.nt);
     const int k = sidx * 256 + (int)threadIdx.x;
-    if (k >= g.S) return;
-    const int i = t * g.S + k;
-    int x[4], lex;
-    eo_coords(g, par, i, x, lex);
-    cx<R> hop[12];
+    double sum = 0.0;
+    if (k < g.S) {
+        const int i = t * g.S + k;
+        int x[4], lex;
+        eo_coords(g, par, i, x, lex);
+        cx<R> hop[12];
 #pragma unroll
-    for (int q = 0; q < 12; ++q) hop[q] = {(R)0, (R)0};
-    if constexpr (PIPE) {
-        HopIn<P> A, B;
-        load_k<P>(0, g, hsrc, links, dets, par, i, x, lex, A);
+        for (int q = 0; q < 12; ++q) hop[q] = {(R)0, (R)0};
+        if constexpr (PIPE) {
+            HopIn<P> A, B;
+            load_k<P>(0, g, hsrc, links, dets, par, i, x, lex, A);
 #pragma unroll 1
-        for (int kk = 0; kk < 8; kk += 2) {
-            int ii = i, ll = lex, xx[4] = {x[0], x[1], x[2], x[3]};
-            asm volatile("" : "+v"(ii), "+v"(ll), "+v"(xx[0]), "+v"(xx[1]), "+v"(xx[2]), "+v"(xx[3]));
-            load_k<P>(kk + 1, g, hsrc, links, dets, par, ii, xx, ll, B);
-            compute_k<P, DAG>(kk, g, xx, A, hop);
-            if (kk + 2 < 8) load_k<P>(kk + 2, g, hsrc, links, dets, par, ii, xx, ll, A);
-            compute_k<P, DAG>(kk + 1, g, xx, B, hop);
-        }
-    } else {
-        HopIn<P> A;
+            for (int kk = 0; kk < 8; kk += 2) {
+                int ii = i, ll = lex, xx[4] = {x[0], x[1], x[2], x[3]};
+                asm volatile("" : "+v"(ii), "+v"(ll), "+v"(xx[0]), "+v"(xx[1]), "+v"(xx[2]), "+v"(xx[3]));
+                load_k<P>(kk + 1, g, hsrc, links, dets, par, ii, xx, ll, B);
+                compute_k<P, DAG>(kk, g, xx, A, hop);
+                if (kk + 2 < 8) load_k<P>(kk + 2, g, hsrc, links, dets, par, ii, xx, ll, A);
+                compute_k<P, DAG>(kk + 1, g, xx, B, hop);
+            }
+        } else {
+            HopIn<P> A;
 #pragma unroll 1
-        for (int kk = 0; kk < 8; ++kk) {
-            int ii = i, ll = lex, xx[4] = {x[0], x[1], x[2], x[3]};
-            asm volatile("" : "+v"(ii), "+v"(ll), "+v"(xx[0]), "+v"(xx[1]), "+v"(xx[2]), "+v"(xx[3]));
-            load_k<P>(kk, g, hsrc, links, dets, par, ii, xx, ll, A);
-            compute_k<P, DAG>(kk, g, xx, A, hop);
+            for (int kk = 0; kk < 8; ++kk) {
+                int ii = i, ll = lex, xx[4] = {x[0], x[1], x[2], x[3]};
+                asm volatile("" : "+v"(ii), "+v"(ll), "+v"(xx[0]), "+v"(xx[1]), "+v"(xx[2]), "+v"(xx[3]));
+                load_k<P>(kk, g, hsrc, links, dets, par, ii, xx, ll, A);
+                compute_k<P, DAG>(kk, g, xx, A, hop);
+            }
         }
-    }
-    cx<R> acc[12];
-    if constexpr (STAGE == 1) {
+        cx<R> acc[12];
+        if constexpr (STAGE == 1) {
 #pragma unroll
-        for (int q = 0; q < 12; ++q) hop[q] = scale(hop[q], (R)-0.5);
-        clover_apply<P>(diag, g.Vh, par, i, hop, acc);
-    } else {
-        cx<R> sp[12];
-        load_spinor<P>(dsrc, g.Vh, par, i, sp);
-        clover_apply<P>(diag, g.Vh, par, i, sp, acc);
+            for (int q = 0; q < 12; ++q) hop[q] = scale(hop[q], (R)-0.5);
+            clover_apply<P>(diag, g.Vh, par, i, hop, acc);
+        } else {
+            cx<R> sp[12];
+            load_spinor<P>(dsrc, g.Vh, par, i, sp);
+            clover_apply<P>(diag, g.Vh, par, i, sp, acc);
 #pragma unroll
-        for (int q = 0; q < 12; ++q) acc[q] = acc[q] + scale(hop[q], (R)0.5);
+            for (int q = 0; q < 12; ++q) acc[q] = acc[q] + scale(hop[q], (R)0.5);
+        }
+        store_out<P, EPI>(out, epi, g.Vh, par, i, acc, sum);
     }
-    store_spinor<P>(out, g.Vh, par, i, acc);
+    if constexpr (EPI != EPI_NONE) grid_sums<1>(&sum, epi.sums, blockIdx.x, gridDim.x);
 }
 
-template <int P, bool DAG>
-int schur_launch_t(qdw_op* op, const void* in, void* out, hipStream_t st)
+template <int P, bool DAG, int EPI>
+int schur_launch_t(qdw_op* op, const void* in, void* out, const Epi& epi, hipStream_t st)
 {
     const Geom& g = op->g;
     const int ntile1 = (g.S + 255) / 256;
     const int nb = g.L[0] * ntile1;
     // the hop loop is software-pipelined where the registers allow it (FP64, FP32), as for D
     constexpr bool PIPE = P == F64 || P == F32;
-    schur_kernel<P, DAG, 1, PIPE><<<nb, 256, 0, st>>>(g, ntile1, in, nullptr, out, op->links[P],
-                                                      op->det[P], op->cloverinv[P]);
+    schur_kernel<P, DAG, 1, PIPE, EPI_NONE><<<nb, 256, 0, st>>>(
+        g, ntile1, in, nullptr, out, op->links[P], op->det[P], op->cloverinv[P], Epi{});
     QDW_LAUNCH_CHECK();
-    schur_kernel<P, DAG, 2, PIPE><<<nb, 256, 0, st>>>(g, ntile1, out, in, out, op->links[P],
-                                                      op->det[P], op->clover[P]);
+    schur_kernel<P, DAG, 2, PIPE, EPI><<<nb, 256, 0, st>>>(
+        g, ntile1, out, in, out, op->links[P], op->det[P], op->clover[P], epi);
     QDW_LAUNCH_CHECK();
     return QDW_OK;
 }
@@ -448,8 +491,8 @@ inline Geom shaped(const qdw_op* op, int P)
     return g;
 }
 
-template <int P, bool DAG>
-int launch(qdw_op* op, const RhsTable& tab, int nrhs, hipStream_t st)
+template <int P, bool DAG, int EPI>
+int launch(qdw_op* op, const RhsTable& tab, int nrhs, const Epi& epi, hipStream_t st)
 {
     const Geom g = shaped(op, P);
     if (op->dw_shape[P].march) {
@@ -458,34 +501,44 @@ int launch(qdw_op* op, const RhsTable& tab, int nrhs, hipStream_t st)
         const size_t lds = (size_t)2 * 2 * 12 * (2 * g.ts) * sizeof(R);
         static_assert(sizeof(R) == 8 || sizeof(R) == 4, "real type");
         if (op->dw_shape[P].pipe)
-            dw_march_kernel<P, DAG, true><<<nblk, 2 * g.ts, lds, st>>>(g, tab, nrhs, op->links[P],
-                                                                       op->det[P], op->clover54[P]);
+            dw_march_kernel<P, DAG, true, EPI><<<nblk, 2 * g.ts, lds, st>>>(
+                g, tab, nrhs, op->links[P], op->det[P], op->clover54[P], epi);
         else
-            dw_march_kernel<P, DAG, false><<<nblk, 2 * g.ts, lds, st>>>(g, tab, nrhs, op->links[P],
-                                                                        op->det[P], op->clover54[P]);
+            dw_march_kernel<P, DAG, false, EPI><<<nblk, 2 * g.ts, lds, st>>>(
+                g, tab, nrhs, op->links[P], op->det[P], op->clover54[P], epi);
         QDW_LAUNCH_CHECK();
         return QDW_OK;
     }
     const int nblk = walk_blocks(g) * nrhs;
     if (op->dw_shape[P].pipe)
-        dw_kernel<P, DAG, true><<<nblk, 2 * g.ts, 0, st>>>(g, tab, nrhs, op->links[P], op->det[P],
-                                                           op->clover54[P]);
+        dw_kernel<P, DAG, true, EPI><<<nblk, 2 * g.ts, 0, st>>>(g, tab, nrhs, op->links[P], op->det[P],
+                                                                op->clover54[P], epi);
     else
-        dw_kernel<P, DAG, false><<<nblk, 2 * g.ts, 0, st>>>(g, tab, nrhs, op->links[P], op->det[P],
-                                                            op->clover54[P]);
+        dw_kernel<P, DAG, false, EPI><<<nblk, 2 * g.ts, 0, st>>>(g, tab, nrhs, op->links[P],
+                                                                 op->det[P], op->clover54[P], epi);
     QDW_LAUNCH_CHECK();
     return QDW_OK;
 }
 
-int dispatch(qdw_op* op, const RhsTable& tab, int nrhs, int prec, bool dag, hipStream_t st)
+// f(precision as a compile-time constant)
+template <class F>
+int by_precision(int prec, F f)
 {
     switch (prec) {
-    case QDW_F64: return dag ? launch<F64, true>(op, tab, nrhs, st) : launch<F64, false>(op, tab, nrhs, st);
-    case QDW_F32: return dag ? launch<F32, true>(op, tab, nrhs, st) : launch<F32, false>(op, tab, nrhs, st);
-    case QDW_F16S: return dag ? launch<F16S, true>(op, tab, nrhs, st) : launch<F16S, false>(op, tab, nrhs, st);
-    case QDW_BF16S: return dag ? launch<BF16S, true>(op, tab, nrhs, st) : launch<BF16S, false>(op, tab, nrhs, st);
+    case QDW_F64: return f(std::integral_constant<int, F64>{});
+    case QDW_F32: return f(std::integral_constant<int, F32>{});
+    case QDW_F16S: return f(std::integral_constant<int, F16S>{});
+    case QDW_BF16S: return f(std::integral_constant<int, BF16S>{});
     default: QDW_CHECK(false, QDW_EINVAL, "dw_apply: bad precision");
     }
+}
+
+int dispatch(qdw_op* op, const RhsTable& tab, int nrhs, int prec, bool dag, hipStream_t st)
+{
+    return by_precision(prec, [&](auto P) {
+        return dag ? launch<P.value, true, EPI_NONE>(op, tab, nrhs, Epi{}, st)
+                   : launch<P.value, false, EPI_NONE>(op, tab, nrhs, Epi{}, st);
+    });
 }
 
 // ------------------------------------------------------------------ uncompressed control
@@ -614,13 +667,34 @@ int dw_launch(qdw_op* op, const void* in, void* out, int prec, bool dag, hipStre
 
 int schur_launch(qdw_op* op, const void* in, void* out, int prec, bool dag, hipStream_t st)
 {
-    switch (prec) {
-    case F64: return dag ? schur_launch_t<F64, true>(op, in, out, st) : schur_launch_t<F64, false>(op, in, out, st);
-    case F32: return dag ? schur_launch_t<F32, true>(op, in, out, st) : schur_launch_t<F32, false>(op, in, out, st);
-    case F16S: return dag ? schur_launch_t<F16S, true>(op, in, out, st) : schur_launch_t<F16S, false>(op, in, out, st);
-    case BF16S: return dag ? schur_launch_t<BF16S, true>(op, in, out, st) : schur_launch_t<BF16S, false>(op, in, out, st);
-    default: QDW_CHECK(false, QDW_EINVAL, "schur: bad precision");
-    }
+    return by_precision(prec, [&](auto P) {
+        return dag ? schur_launch_t<P.value, true, EPI_NONE>(op, in, out, Epi{}, st)
+                   : schur_launch_t<P.value, false, EPI_NONE>(op, in, out, Epi{}, st);
+    });
+}
+
+int cg_apply(qdw_op* op, const void* p, void* q, int prec, bool schur, hipStream_t st)
+{
+    const Epi e = {{op->partials, op->tickets, op->scalars, FIN_CG_ALPHA, 0}, nullptr, nullptr};
+    RhsTable tab{};
+    tab.in[0] = p;
+    tab.out[0] = q;
+    return by_precision(prec, [&](auto P) {
+        return schur ? schur_launch_t<P.value, false, EPI_NORM>(op, p, q, e, st)
+                     : launch<P.value, false, EPI_NORM>(op, tab, 1, e, st);
+    });
+}
+
+int cg_apply_dag(qdw_op* op, const void* q, void* r, void* t, int prec, bool schur, hipStream_t st)
+{
+    const Epi e = {{op->partials, op->tickets, op->scalars, FIN_CG_BETA, 0}, r, op->scalars};
+    RhsTable tab{};
+    tab.in[0] = q;
+    tab.out[0] = r;
+    return by_precision(prec, [&](auto P) {
+        return schur ? schur_launch_t<P.value, true, EPI_STEP>(op, q, t, e, st)
+                     : launch<P.value, true, EPI_STEP>(op, tab, 1, e, st);
+    });
 }
 
 int dw_launch_multi(qdw_op* op, const void* const* in, void* const* out, int nrhs, int prec,

@@ -2,6 +2,7 @@
 // pack/unpack, and the error plumbing of the C ABI.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <string>
@@ -489,7 +490,8 @@ struct OpLayout {
         total;
 };
 
-OpLayout op_layout(int Vh)
+// max_blocks: workgroups of the largest site-kernel launch (each may leave one partial sum)
+OpLayout op_layout(int Vh, size_t max_blocks)
 {
     OpLayout L{};
     size_t off = 0;
@@ -512,12 +514,19 @@ OpLayout op_layout(int Vh)
     for (int p = 0; p < 4; ++p) L.cloverinv[p] = take(ns * 72 * creal[p]);
     const size_t c54[4] = {27 * 16, 14 * 16, 7 * 16, 7 * 16};  // compact clover, bytes per site
     for (int p = 0; p < 4; ++p) L.clover54[p] = take(ns * c54[p]);
-    L.partials = take(sizeof(double) * kMaxPartials * kMaxScalars);
+    L.partials = take(sizeof(double) * std::max((size_t)kMaxPartials * kMaxScalars, max_blocks));
     L.tickets = take(sizeof(unsigned) * kTicketWords);
     L.scalars = take(sizeof(double) * kMaxScalars);
     L.worst = take(sizeof(unsigned long long));
     L.total = off + 256;  // room to align the caller's pointer
     return L;
+}
+
+// 64-site tiles of a time slice, or of its x1 slabs, times the time slices
+size_t max_site_blocks(const int L[4])
+{
+    const size_t slab = (size_t)L[2] * L[3] / 2, S = slab * L[1];
+    return (size_t)L[0] * std::max((S + 63) / 64, (size_t)L[1] * ((slab + 63) / 64));
 }
 
 // lattice checks shared by the size query and qdw_create
@@ -540,7 +549,8 @@ extern "C" size_t qdw_op_device_bytes(const qdw_lattice* lat)
 {
     if (check_lattice(lat)) return 0;
     const long V = (long)lat->T * lat->L1 * lat->L2 * lat->L3;
-    return op_layout((int)(V / 2)).total;
+    const int L[4] = {lat->T, lat->L1, lat->L2, lat->L3};
+    return op_layout((int)(V / 2), max_site_blocks(L)).total;
 }
 
 extern "C" size_t qdw_op_host_bytes(void) { return sizeof(double) * kHostScalars; }
@@ -555,7 +565,7 @@ extern "C" int qdw_create(const qdw_lattice* lat, const double* su3, const doubl
     if (const int rc = check_lattice(lat)) return rc;
     const int L[4] = {lat->T, lat->L1, lat->L2, lat->L3};
     const long V = (long)L[0] * L[1] * L[2] * L[3];
-    const OpLayout lay = op_layout((int)(V / 2));
+    const OpLayout lay = op_layout((int)(V / 2), max_site_blocks(L));
     QDW_CHECK(dev_bytes >= lay.total, QDW_EWORKSPACE,
               "qdw_create: device block smaller than qdw_op_device_bytes()");
     QDW_CHECK(host_bytes >= qdw_op_host_bytes(), QDW_EWORKSPACE,

@@ -27,7 +27,7 @@ struct qdw_op {
     struct { int ts, nt, pipe, walk, march; } dw_shape[4];
     // reduction scratch: per-workgroup partial sums, the arrival counters of the workgroups
     // (zero between launches) and the final scalars
-    double* partials;      // device, kMaxPartials * kMaxScalars doubles
+    double* partials;      // device, kMaxPartials * kMaxScalars doubles, or one per site workgroup
     unsigned* tickets;     // device, kTicketWords words
     double* scalars;       // device, kMaxScalars doubles
     double* host_scalars;  // pinned host, kHostScalars doubles
