@@ -89,7 +89,7 @@ inline Runs runs_of(const Geom& g, bool even_half, bool back)
 // scalar programs run by the finalising workgroup after the sums are formed
 enum FinOp {
     FIN_STORE = 0,   // out[j] = sum_j
-    FIN_CG_ALPHA,    // out = CG scalars: pap = sum_0; alpha = rr / pap
+    FIN_CG_ALPHA,    // out = CG scalars: pap = sum_0; alpha = rr / pap (also at S_RING + k)
     FIN_CG_BETA,     // out = CG scalars: rrnew = sum_0; beta = rrnew / rr; rr = rrnew
     FIN_GCR_NORM,    // out = GCR scalars, step k: b_k = sqrt(sum_0), c_k = (sum_1 + i sum_2)/b_k,
                      //   coefficients 1/b_k and c_k/b_k for the update pass
@@ -102,7 +102,13 @@ enum { G_A = 0, G_B = 2 * kMaxKv * kMaxKv, G_C = G_B + kMaxKv, G_COEF = G_C + 2 
        G_NORM = G_COEF + 4, G_SIZE = G_NORM + 4 };
 
 // scalar slots of the CG solver
-enum { S_RR = 0, S_PAP = 1, S_ALPHA = 2, S_RRNEW = 3, S_BETA = 4, S_TMP = 8 };
+enum { S_RR = 0, S_PAP = 1, S_ALPHA = 2, S_RRNEW = 3, S_BETA = 4, S_TMP = 8, S_RING = 40 };
+
+// Directions of a CG that the iterate has not moved along yet, with their step lengths at
+// S_RING. The iterate (FP32 or FP64) is the widest field of a step: moving it along four
+// directions at a time reads and writes it a quarter as often for one more read of each
+// direction (FP16 storage: 228 instead of 336 B per site and step on average).
+constexpr int kRing = 4;
 
 // the scalar program `op` on the grid's sums (one lane)
 __device__ inline void scalar_program(const double* sums, int ns, double* out, int op, int k)
@@ -113,7 +119,7 @@ __device__ inline void scalar_program(const double* sums, int ns, double* out, i
         break;
     case FIN_CG_ALPHA:  // a vanishing direction leaves the iterate unchanged
         out[S_PAP] = sums[0];
-        out[S_ALPHA] = sums[0] != 0.0 ? out[S_RR] / sums[0] : 0.0;
+        out[S_ALPHA] = out[S_RING + k] = sums[0] != 0.0 ? out[S_RR] / sums[0] : 0.0;
         break;
     case FIN_CG_BETA:
         out[S_RRNEW] = sums[0];
@@ -379,34 +385,63 @@ struct ScaleNorm {
     }
 };
 
-// The iterate and the direction of a CG step in one pass: x += alpha p ; p = r + beta p
-// (alpha, beta read from device scalars; the residual has its update from cg_apply_dag)
-template <int PX, int P>
+// p_next = r + beta p   (beta read from device scalars)
+template <int P>
 struct CgDirection {
     static constexpr int NS = 0;
-    void* x;
     const void* r;
-    void* p;
+    const void* p;
+    void* next;
     const double* sc;
     __device__ void operator()(const Unit& u, double*) const
     {
         using R = typename Traits<P>::real;
-        const R a = (R)sc[S_ALPHA], b = (R)sc[S_BETA];
-        // a zero or non-finite step length leaves the iterate as it was, so that a solve that
-        // runs into a non-finite value still holds its last finite iterate
-        const bool move = a != (R)0 && isfinite(a);
-        cx<R> vx[4], vp[4], vr[4];
-        ld4<P, R>(p, u, vp);
+        const R b = (R)sc[S_BETA];
+        cx<R> vr[4], vp[4];
         ld4<P, R>(r, u, vr);
-        if (move) {
-            ld4<PX, R>(x, u, vx);
-#pragma unroll
-            for (int k = 0; k < 4; ++k) vx[k] = vx[k] + scale(vp[k], a);
-            st4<PX, R>(x, u, vx);
-        }
+        ld4<P, R>(p, u, vp);
 #pragma unroll
         for (int k = 0; k < 4; ++k) vp[k] = vr[k] + scale(vp[k], b);
-        st4<P, R>(p, u, vp);
+        st4<P, R>(next, u, vp);
+    }
+};
+
+// x += sum of alpha_l p_l over the first n directions of the ring, one after the other; with
+// TURN (a full ring) also p_0 = r + beta p_{n-1}, the next direction
+template <int PX, int P, bool TURN>
+struct CgMove {
+    static constexpr int NS = 0;
+    void* x;
+    void* p[kRing];
+    const void* r;
+    const double* sc;
+    int n;
+    __device__ void operator()(const Unit& u, double*) const
+    {
+        using R = typename Traits<P>::real;
+        cx<R> vx[4], vp[kRing][4], vr[4];
+        ld4<PX, R>(x, u, vx);
+#pragma unroll
+        for (int l = 0; l < kRing; ++l)
+            if (TURN || l < n) ld4<P, R>(p[l], u, vp[l]);
+        if (TURN) ld4<P, R>(r, u, vr);
+#pragma unroll
+        for (int l = 0; l < kRing; ++l) {
+            const R a = (R)sc[S_RING + l];
+            // a zero or non-finite step length leaves the iterate as it was, so that a solve
+            // that runs into a non-finite value still holds its last finite iterate
+            if ((TURN || l < n) && a != (R)0 && isfinite(a)) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) vx[k] = vx[k] + scale(vp[l][k], a);
+            }
+        }
+        st4<PX, R>(x, u, vx);
+        if (TURN) {
+            const R b = (R)sc[S_BETA];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) vr[k] = vr[k] + scale(vp[kRing - 1][k], b);
+            st4<P, R>(p[0], u, vr);
+        }
     }
 };
 
@@ -471,8 +506,9 @@ int dw_launch(qdw_op* op, const void* in, void* out, int prec, bool dag, hipStre
 int schur_launch(qdw_op* op, const void* in, void* out, int prec, bool dag, hipStream_t st);
 // the two operator applications of a CG step with the step's sums and residual in them:
 //   q = D p, |q|^2 -> alpha ;  r -= alpha D^+ q, |r|^2 -> beta
-// (schur: the even-odd reduced operator; t is then the scratch its odd half needs)
-int cg_apply(qdw_op* op, const void* p, void* q, int prec, bool schur, hipStream_t st);
+// (schur: the even-odd reduced operator; t is then the scratch its odd half needs; alpha is
+// also kept at place `ring` of S_RING)
+int cg_apply(qdw_op* op, const void* p, void* q, int prec, bool schur, int ring, hipStream_t st);
 int cg_apply_dag(qdw_op* op, const void* q, void* r, void* t, int prec, bool schur, hipStream_t st);
 
 // read `n` device doubles at `src` (synchronises the stream)

@@ -5,6 +5,7 @@
 // FP32, or psi itself when PL = FP64):
 //     alpha = |r|^2 / |q|^2 ; x_lo += alpha p ; r -= alpha w ; beta = |r_new|^2/|r|^2 ;
 //     p = r + beta p
+// (x_lo moves along the last few directions at once, see kRing)
 // with every reduction in FP64 and the scalars alpha, beta kept in device memory (no
 // host round trip inside an iteration). The host reads |r|^2 one iteration late, so the
 // GPU never idles waiting for it.
@@ -77,6 +78,10 @@ int cgne_impl(qdw_op* op, const void* eta, void* psi, const qdw_cgne_params& prm
     void* q = wp + 2 * flb;
     void* w = wp + 3 * flb;
     double* sc = op->scalars;
+    // the ring of directions: place 0 is p; the others lie over rhi, t1 and t2, which only a
+    // reset uses, after the ring has been emptied
+    void* ring[kRing] = {p, work, work + flb, work + 2 * flb};
+    int cur = 0;
     const double sqrt24v = std::sqrt(24.0 * g.V);
     const double eps_inner = PL == F64 ? std::ldexp(1.0, -52) : PL == F32 ? std::ldexp(1.0, -23)
                              : PL == F16S ? std::ldexp(1.0, -10) : std::ldexp(1.0, -7);
@@ -124,10 +129,18 @@ int cgne_impl(qdw_op* op, const void* eta, void* psi, const qdw_cgne_params& prm
 
     auto iterate = [&]() -> int {
         int e;
-        if ((e = cg_apply(op, p, q, PL, schur, st))) return e;
+        if ((e = cg_apply(op, ring[cur], q, PL, schur, cur, st))) return e;
         if ((e = cg_apply_dag(op, q, r, w, PL, schur, st))) return e;
         S.ndw_lo += 2;
-        if ((e = run_map(op, CgDirection<PX, PL>{xlo, r, p, sc}, st, nullptr, FIN_STORE, 0, schur))) return e;
+        if (cur == kRing - 1) {
+            if ((e = run_map(op, CgMove<PX, PL, true>{xlo, {ring[0], ring[1], ring[2], ring[3]}, r, sc, kRing},
+                             st, nullptr, FIN_STORE, 0, schur)))
+                return e;
+            cur = 0;
+        } else {
+            if ((e = run_map(op, CgDirection<PL>{r, ring[cur], ring[cur + 1], sc}, st, nullptr, FIN_STORE, 0, schur))) return e;
+            ++cur;
+        }
         ++S.steps;
         const int k = S.steps & 1;
         QDW_HIP(hipMemcpyAsync(slot + k, sc + S_RR, sizeof(double), hipMemcpyDeviceToHost, st));
@@ -135,10 +148,23 @@ int cgne_impl(qdw_op* op, const void* eta, void* psi, const qdw_cgne_params& prm
         return QDW_OK;
     };
 
+    // move the iterate along the directions still in the ring and bring the current one home
+    auto empty_ring = [&]() -> int {
+        int e;
+        if (cur == 0) return QDW_OK;
+        if ((e = run_map(op, CgMove<PX, PL, false>{xlo, {ring[0], ring[1], ring[2], ring[3]}, r, sc, cur},
+                         st, nullptr, FIN_STORE, 0, schur)))
+            return e;
+        if ((e = run_map(op, Axpby<PL, PL>{ring[cur], p, 1.0, 0.0}, st, nullptr, FIN_STORE, 0, schur))) return e;
+        cur = 0;
+        return QDW_OK;
+    };
+
     // psi += x_lo / s ; r_hi = eta - D^+ D psi ; returns |r_hi| / |eta| in *rel. With
     // checked, x_lo is added only when it is finite (after a non-finite step).
     auto true_residual = [&](double* rel, bool checked = false) -> int {
         int e;
+        if ((e = empty_ring())) return e;
         bool add = PL != F64;
         if (add && checked) {
             if ((e = run_map(op, Norm2<PX>{xlo}, st, op->scalars + S_TMP, FIN_STORE, 0, schur))) return e;

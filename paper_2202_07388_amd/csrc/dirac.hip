@@ -673,9 +673,9 @@ int schur_launch(qdw_op* op, const void* in, void* out, int prec, bool dag, hipS
     });
 }
 
-int cg_apply(qdw_op* op, const void* p, void* q, int prec, bool schur, hipStream_t st)
+int cg_apply(qdw_op* op, const void* p, void* q, int prec, bool schur, int ring, hipStream_t st)
 {
-    const Epi e = {{op->partials, op->tickets, op->scalars, FIN_CG_ALPHA, 0}, nullptr, nullptr};
+    const Epi e = {{op->partials, op->tickets, op->scalars, FIN_CG_ALPHA, ring}, nullptr, nullptr};
     RhsTable tab{};
     tab.in[0] = p;
     tab.out[0] = q;
