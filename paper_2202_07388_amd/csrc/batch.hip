@@ -74,7 +74,7 @@ __global__ __launch_bounds__(256) void bmap_kernel(Runs runs, F f, double* parti
     }
     if constexpr (F::NS > 0)
         grid_sums<F::NS>(acc, {partials + r * kPartStride, tickets + (long)r * kTicketWords,
-                               sc + (long)r * B_SIZE + off, fin, k},
+                               sc + (long)r * B_SIZE + off, fin, k, nullptr},
                          blockIdx.x, gridDim.x);
 }
 
@@ -201,7 +201,7 @@ struct BMultiDot {
     }
 };
 
-// chi_k -= sum_l a_lk chi_l ; |chi_k|^2 ; chi_k^+ rho
+// chi_k -= sum_l (a_lk / b_l) chi_l ; |chi_k|^2 ; chi_k^+ rho
 template <int K>
 struct BGsUpdate {
     static constexpr int NS = 3;
@@ -210,13 +210,15 @@ struct BGsUpdate {
     int nr;
     __device__ void operator()(const Unit& u, double* acc, int r) const
     {
-        const double* a = sc + (long)r * B_SIZE + G_A + 2 * kMaxKv * K;
+        const double* sr = sc + (long)r * B_SIZE;
+        const double* a = sr + G_A + 2 * kMaxKv * K;
         void* v = chi.at(K * nr + r);
         cx<double> vv[4], rr[4];
         ld4<F64, double>(v, u, vv);
 #pragma unroll
         for (int l = 0; l < K; ++l) {
-            const cx<double> al = {a[2 * l], a[2 * l + 1]};
+            const double ib = sr[G_IB + l];
+            const cx<double> al = {a[2 * l] * ib, a[2 * l + 1] * ib};
             cx<double> c[4];
             ld4<F64, double>(chi.at(l * nr + r), u, c);
 #pragma unroll
@@ -234,7 +236,7 @@ struct BGsUpdate {
     }
 };
 
-// chi_k = chi_k / b_k ; rho -= (c_k / b_k) chi_k ; |rho|^2
+// rho -= (c_k / b_k) chi_k ; |rho|^2
 struct BGcrUpdate {
     static constexpr int NS = 1;
     Fld chi, rho;
@@ -243,19 +245,16 @@ struct BGcrUpdate {
     __device__ void operator()(const Unit& u, double* acc, int r) const
     {
         const double* coef = sc + (long)r * B_SIZE + G_COEF;
-        const double ib = coef[0];
-        const cx<double> cb = {coef[1], coef[2]};
-        void* v = chi.at(k * nr + r);
+        const cx<double> cb = {coef[0], coef[1]};
+        const void* v = chi.at(k * nr + r);
         cx<double> vv[4], rr[4];
         ld4<F64, double>(v, u, vv);
         ld4<F64, double>(rho.at(r), u, rr);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             rr[j] = rr[j] - cb * vv[j];
-            vv[j] = scale(vv[j], ib);
             acc[0] += rr[j].re * rr[j].re + rr[j].im * rr[j].im;
         }
-        st4<F64, double>(v, u, vv);
         st4<F64, double>(rho.at(r), u, rr);
     }
 };
@@ -465,7 +464,7 @@ int cycle(const Group& G, const qdw_sap_gcr_params& p, hipStream_t st)
                 f.chi = {G.chi, G.fb};
                 f.nr = nr;
                 f.k = k;
-                return brun(G, f, F_INCYCLE, st, G_A + 2 * kMaxKv * k);
+                return brun(G, f, F_INCYCLE, st, 0, FIN_GCR_DOT, k);
             })))
             return rc;
         if ((rc = by_k<BGsUpdate>(k, [&](auto& f) {

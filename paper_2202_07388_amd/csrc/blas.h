@@ -91,15 +91,19 @@ enum FinOp {
     FIN_STORE = 0,   // out[j] = sum_j
     FIN_CG_ALPHA,    // out = CG scalars: pap = sum_0; alpha = rr / pap (also at S_RING + k)
     FIN_CG_BETA,     // out = CG scalars: rrnew = sum_0; beta = rrnew / rr; rr = rrnew
-    FIN_GCR_NORM,    // out = GCR scalars, step k: b_k = sqrt(sum_0), c_k = (sum_1 + i sum_2)/b_k,
-                     //   coefficients 1/b_k and c_k/b_k for the update pass
+    FIN_GCR_DOT,     // out = GCR scalars, step k: a_lk = sum_l / b_l for l < k
+    FIN_GCR_NORM,    // out = GCR scalars, step k: b_k = sqrt(sum_0), 1/b_k,
+                     //   c_k = (sum_1 + i sum_2)/b_k and the update's coefficient c_k/b_k
 };
 
-// GCR scalar block (doubles): a[k][l] complex at 2*(16*k + l), b_k at G_B + k,
-// c_k complex at G_C + 2k, update coefficients at G_COEF (1/b, Re c/b, Im c/b)
+// The basis vectors chi_k of a GCR cycle are stored as they come out of the Gram-Schmidt
+// pass, with norm b_k; the coefficients refer to chi_k / b_k. (Normalising them in memory
+// took one more pass over a field per step.)
+// GCR scalar block (doubles): a[k][l] complex at 2*(16*k + l), b_k at G_B + k, c_k complex
+// at G_C + 2k, 1/b_k at G_IB + k, the update coefficient c_k/b_k at G_COEF
 constexpr int kMaxKv = 16;
-enum { G_A = 0, G_B = 2 * kMaxKv * kMaxKv, G_C = G_B + kMaxKv, G_COEF = G_C + 2 * kMaxKv,
-       G_NORM = G_COEF + 4, G_SIZE = G_NORM + 4 };
+enum { G_A = 0, G_B = 2 * kMaxKv * kMaxKv, G_C = G_B + kMaxKv, G_IB = G_C + 2 * kMaxKv,
+       G_COEF = G_IB + kMaxKv, G_NORM = G_COEF + 2, G_SIZE = G_NORM + 2 };
 
 // scalar slots of the CG solver
 enum { S_RR = 0, S_PAP = 1, S_ALPHA = 2, S_RRNEW = 3, S_BETA = 4, S_TMP = 8, S_RING = 40 };
@@ -126,15 +130,18 @@ __device__ inline void scalar_program(const double* sums, int ns, double* out, i
         out[S_BETA] = out[S_RR] != 0.0 ? sums[0] / out[S_RR] : 0.0;
         out[S_RR] = sums[0];
         break;
+    case FIN_GCR_DOT:
+        for (int j = 0; j < ns; ++j) out[G_A + 2 * kMaxKv * k + j] = sums[j] * out[G_IB + j / 2];
+        break;
     case FIN_GCR_NORM: {
         const double b = sqrt(sums[0]);
         const double ib = b > 0.0 ? 1.0 / b : 0.0;
         out[G_B + k] = b;
         out[G_C + 2 * k] = sums[1] * ib;
         out[G_C + 2 * k + 1] = sums[2] * ib;
-        out[G_COEF] = ib;
-        out[G_COEF + 1] = sums[1] * ib * ib;
-        out[G_COEF + 2] = sums[2] * ib * ib;
+        out[G_IB + k] = ib;
+        out[G_COEF] = sums[1] * ib * ib;
+        out[G_COEF + 1] = sums[2] * ib * ib;
         break;
     }
     default:
@@ -156,6 +163,7 @@ struct Sums {
     unsigned* ticket;   // kTicketWords, zero between launches
     double* out;        // scalar program's block
     int fin, k;
+    double* host;       // pinned host memory for the sums themselves, or nullptr
 };
 
 __device__ __forceinline__ double agent_load(const double* p)
@@ -284,7 +292,11 @@ __device__ __forceinline__ void grid_sums(const double* acc, const Sums& s, unsi
         }
     }
     __syncthreads();
-    if (threadIdx.x == 0) scalar_program(sums, NS, s.out, s.fin, s.k);
+    if (threadIdx.x != 0) return;
+    scalar_program(sums, NS, s.out, s.fin, s.k);
+    if (s.host)
+        for (int j = 0; j < NS; ++j)
+            __hip_atomic_store(s.host + j, sums[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // map over the runs of a field, a wavefront per run; F::NS doubles are summed over the grid
@@ -316,10 +328,11 @@ inline int map_blocks(unsigned nw)
 // program fin on its sums
 template <class F>
 int run_map(const qdw_op* op, const F& f, hipStream_t st, double* out = nullptr,
-            int fin = FIN_STORE, int k = 0, bool even_half = false, bool back = false)
+            int fin = FIN_STORE, int k = 0, bool even_half = false, bool back = false,
+            double* host = nullptr)
 {
     const Runs r = runs_of(op->g, even_half, back);
-    const Sums s = {op->partials, op->tickets, out ? out : op->scalars, fin, k};
+    const Sums s = {op->partials, op->tickets, out ? out : op->scalars, fin, k, host};
     map_kernel<F><<<map_blocks<F::NS>(r.nw), 256, 0, st>>>(r, f, s);
     QDW_LAUNCH_CHECK();
     return QDW_OK;
@@ -507,25 +520,33 @@ int schur_launch(qdw_op* op, const void* in, void* out, int prec, bool dag, hipS
 // the two operator applications of a CG step with the step's sums and residual in them:
 //   q = D p, |q|^2 -> alpha ;  r -= alpha D^+ q, |r|^2 -> beta
 // (schur: the even-odd reduced operator; t is then the scratch its odd half needs; alpha is
-// also kept at place `ring` of S_RING)
+// also kept at place `ring` of S_RING; host: where the host is to find |r|^2, or nullptr)
 int cg_apply(qdw_op* op, const void* p, void* q, int prec, bool schur, int ring, hipStream_t st);
-int cg_apply_dag(qdw_op* op, const void* q, void* r, void* t, int prec, bool schur, hipStream_t st);
+int cg_apply_dag(qdw_op* op, const void* q, void* r, void* t, int prec, bool schur, double* host,
+                 hipStream_t st);
+
+// run F and wait for its sums (also stored at `out`, by default the scratch scalars): the
+// last workgroup writes them to the host block, so no copy follows the kernel (4 us and a
+// launch gap each)
+template <class F>
+int run_sum(const qdw_op* op, const F& f, hipStream_t st, double* sums, bool even_half = false,
+            double* out = nullptr)
+{
+    if (!out) out = op->scalars + S_TMP;
+    const int rc = run_map(op, f, st, out, FIN_STORE, 0, even_half, false, op->host_dev);
+    if (rc) return rc;
+    if (!op->host_dev)
+        QDW_HIP(hipMemcpyAsync(op->host_scalars, out, sizeof(double) * F::NS, hipMemcpyDeviceToHost, st));
+    QDW_HIP(hipStreamSynchronize(st));
+    for (int j = 0; j < F::NS; ++j) sums[j] = ((volatile double*)op->host_scalars)[j];
+    return QDW_OK;
+}
 
 // read `n` device doubles at `src` (synchronises the stream)
 inline int read_device(const qdw_op* op, const double* src, int n, double* out, hipStream_t st)
 {
     QDW_CHECK(n >= 1 && n <= kHostScalars, QDW_EINVAL, "internal: read-back too large");
     QDW_HIP(hipMemcpyAsync(op->host_scalars, src, sizeof(double) * n, hipMemcpyDeviceToHost, st));
-    QDW_HIP(hipStreamSynchronize(st));
-    for (int k = 0; k < n; ++k) out[k] = op->host_scalars[k];
-    return QDW_OK;
-}
-
-// read `n` device scalars starting at `slot` (synchronises the stream)
-inline int read_scalars(const qdw_op* op, int slot, int n, double* out, hipStream_t st)
-{
-    QDW_HIP(hipMemcpyAsync(op->host_scalars, op->scalars + slot, sizeof(double) * n,
-                           hipMemcpyDeviceToHost, st));
     QDW_HIP(hipStreamSynchronize(st));
     for (int k = 0; k < n; ++k) out[k] = op->host_scalars[k];
     return QDW_OK;

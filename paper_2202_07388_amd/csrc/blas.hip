@@ -55,12 +55,10 @@ extern "C" int qdw_norm2(qdw_op* op, const void* x, qdw_prec prec, double* out, 
 {
     QDW_CHECK(op && x && out, QDW_EINVAL, "qdw_norm2: null argument");
     hipStream_t st = (hipStream_t)stream;
-    int rc = by_prec<qdw::Norm2>(prec, [&](auto& f) {
+    return by_prec<qdw::Norm2>(prec, [&](auto& f) {
         f.x = x;
-        return qdw::run_map(op, f, st, op->scalars + qdw::S_TMP);
+        return qdw::run_sum(op, f, st, out);
     });
-    if (rc) return rc;
-    return qdw::read_scalars(op, qdw::S_TMP, 1, out, st);
 }
 
 extern "C" int qdw_cdot(qdw_op* op, const void* x, const void* y, qdw_prec prec, double* out,
@@ -68,12 +66,10 @@ extern "C" int qdw_cdot(qdw_op* op, const void* x, const void* y, qdw_prec prec,
 {
     QDW_CHECK(op && x && y && out, QDW_EINVAL, "qdw_cdot: null argument");
     hipStream_t st = (hipStream_t)stream;
-    int rc = by_prec<Dot>(prec, [&](auto& f) {
+    return by_prec<Dot>(prec, [&](auto& f) {
         f.x = x; f.y = y;
-        return qdw::run_map(op, f, st, op->scalars + qdw::S_TMP);
+        return qdw::run_sum(op, f, st, out);
     });
-    if (rc) return rc;
-    return qdw::read_scalars(op, qdw::S_TMP, 2, out, st);
 }
 
 namespace {

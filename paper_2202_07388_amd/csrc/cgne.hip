@@ -102,8 +102,7 @@ int cgne_impl(qdw_op* op, const void* eta, void* psi, const qdw_cgne_params& prm
     TRY(run_map(op, Zero<F64>{psi}, st));
     if (PL != F64) TRY(run_map(op, Zero<PX>{xlo}, st, nullptr, FIN_STORE, 0, schur));
     double eta2;
-    TRY(run_map(op, Norm2<F64>{eta}, st, op->scalars + S_TMP, FIN_STORE, 0, schur));
-    TRY(read_scalars(op, S_TMP, 1, &eta2, st));
+    TRY(run_sum(op, Norm2<F64>{eta}, st, &eta2, schur));
     info->status = 0;
     info->nreset = 0;
     info->n_dw_hi = info->n_dw_lo = 0;
@@ -114,10 +113,9 @@ int cgne_impl(qdw_op* op, const void* eta, void* psi, const qdw_cgne_params& prm
     }
     const double neta = std::sqrt(eta2);
     double s = PL == F64 ? 1.0 : sqrt24v / neta;
-    TRY(run_map(op, ScaleNorm<F64, PL>{eta, r, s}, st, op->scalars + S_RR, FIN_STORE, 0, schur));
-    TRY(run_map(op, Axpby<PL, PL>{r, p, 1.0, 0.0}, st, nullptr, FIN_STORE, 0, schur));
     double rr_reset;
-    TRY(read_scalars(op, S_RR, 1, &rr_reset, st));
+    TRY(run_sum(op, ScaleNorm<F64, PL>{eta, r, s}, st, &rr_reset, schur, op->scalars + S_RR));
+    TRY(run_map(op, Axpby<PL, PL>{r, p, 1.0, 0.0}, st, nullptr, FIN_STORE, 0, schur));
     double best = rr_reset, prev_true = 1.0;
     int since = 0, bad_resets = 0;
     const int stall_window = 100;
@@ -130,7 +128,11 @@ int cgne_impl(qdw_op* op, const void* eta, void* psi, const qdw_cgne_params& prm
     auto iterate = [&]() -> int {
         int e;
         if ((e = cg_apply(op, ring[cur], q, PL, schur, cur, st))) return e;
-        if ((e = cg_apply_dag(op, q, r, w, PL, schur, st))) return e;
+        const int k = (S.steps + 1) & 1;
+        if ((e = cg_apply_dag(op, q, r, w, PL, schur, op->host_dev ? op->host_dev + 32 + k : nullptr, st)))
+            return e;
+        if (!op->host_dev)
+            QDW_HIP(hipMemcpyAsync(slot + k, sc + S_RR, sizeof(double), hipMemcpyDeviceToHost, st));
         S.ndw_lo += 2;
         if (cur == kRing - 1) {
             if ((e = run_map(op, CgMove<PX, PL, true>{xlo, {ring[0], ring[1], ring[2], ring[3]}, r, sc, kRing},
@@ -142,8 +144,6 @@ int cgne_impl(qdw_op* op, const void* eta, void* psi, const qdw_cgne_params& prm
             ++cur;
         }
         ++S.steps;
-        const int k = S.steps & 1;
-        QDW_HIP(hipMemcpyAsync(slot + k, sc + S_RR, sizeof(double), hipMemcpyDeviceToHost, st));
         QDW_HIP(hipEventRecord(ev[k], st));
         return QDW_OK;
     };
@@ -167,9 +167,8 @@ int cgne_impl(qdw_op* op, const void* eta, void* psi, const qdw_cgne_params& prm
         if ((e = empty_ring())) return e;
         bool add = PL != F64;
         if (add && checked) {
-            if ((e = run_map(op, Norm2<PX>{xlo}, st, op->scalars + S_TMP, FIN_STORE, 0, schur))) return e;
             double x2;
-            if ((e = read_scalars(op, S_TMP, 1, &x2, st))) return e;
+            if ((e = run_sum(op, Norm2<PX>{xlo}, st, &x2, schur))) return e;
             add = std::isfinite(x2);
         }
         if (add)
@@ -177,9 +176,8 @@ int cgne_impl(qdw_op* op, const void* eta, void* psi, const qdw_cgne_params& prm
         if ((e = apply(psi, t1, F64, false))) return e;
         if ((e = apply(t1, t2, F64, true))) return e;
         S.ndw_hi += 2;
-        if ((e = run_map(op, Residual{eta, t2, rhi}, st, op->scalars + S_TMP, FIN_STORE, 0, schur))) return e;
         double rt2;
-        if ((e = read_scalars(op, S_TMP, 1, &rt2, st))) return e;
+        if ((e = run_sum(op, Residual{eta, t2, rhi}, st, &rt2, schur))) return e;
         *rel = std::sqrt(rt2) / neta;
         return QDW_OK;
     };
@@ -189,9 +187,8 @@ int cgne_impl(qdw_op* op, const void* eta, void* psi, const qdw_cgne_params& prm
         int e;
         const double snew = PL == F64 ? 1.0 : sqrt24v / (rel * neta);
         // r = snew r_hi, with |r|^2 into S_RR and the drift |r_hi - r_old/s|^2 next to it
-        if ((e = run_map(op, ResetResidual<PL>{rhi, r, s, snew}, st, op->scalars + S_RR, FIN_STORE, 0, schur))) return e;
         double d2[2];
-        if ((e = read_scalars(op, S_RR, 2, d2, st))) return e;
+        if ((e = run_sum(op, ResetResidual<PL>{rhi, r, s, snew}, st, d2, schur, op->scalars + S_RR))) return e;
         // keep the direction only while the recursive residual had not drifted far from
         // the true one; otherwise restart from the true residual
         const bool keep = prm.keep_p && std::sqrt(d2[1]) <= 0.3 * rel * neta;
@@ -219,7 +216,7 @@ int cgne_impl(qdw_op* op, const void* eta, void* psi, const qdw_cgne_params& prm
         // value of the iteration before the one just enqueued (or the last one)
         const int k = more ? ((S.steps - 1) & 1) : (S.steps & 1);
         QDW_HIP(hipEventSynchronize(ev[k]));
-        const double v = slot[k];
+        const double v = ((volatile double*)slot)[k];
         if (!std::isfinite(v)) {
             QDW_HIP(hipStreamSynchronize(st));
             TRY(true_residual(&rel_true, true));
@@ -333,8 +330,7 @@ int cascade_impl(qdw_op* op, const void* eta, void* psi, const qdw_cgne_params& 
     TRY(run_map(op, Zero<F64>{psi}, st));
     TRY(run_map(op, Axpby<F64, F64>{eta, rres, 1.0, 0.0}, st, nullptr, FIN_STORE, 0, schur));
     double eta2;
-    TRY(run_map(op, Norm2<F64>{eta}, st, op->scalars + S_TMP, FIN_STORE, 0, schur));
-    TRY(read_scalars(op, S_TMP, 1, &eta2, st));
+    TRY(run_sum(op, Norm2<F64>{eta}, st, &eta2, schur));
     if (!(eta2 > 0.0)) {
         info->status = std::isfinite(eta2) ? 0 : -3;
         return QDW_OK;
@@ -373,8 +369,7 @@ int cascade_impl(qdw_op* op, const void* eta, void* psi, const qdw_cgne_params& 
         TRY(apply(t1, t2, F64, true));
         info->n_dw_hi += 2;
         double r2;
-        TRY(run_map(op, Residual{eta, t2, rres}, st, op->scalars + S_TMP, FIN_STORE, 0, schur));
-        TRY(read_scalars(op, S_TMP, 1, &r2, st));
+        TRY(run_sum(op, Residual{eta, t2, rres}, st, &r2, schur));
         rel = std::sqrt(r2) / neta;
         ++info->nreset;  // the phase switch is a reset step too
         if (!std::isfinite(rel)) {

@@ -675,7 +675,7 @@ int schur_launch(qdw_op* op, const void* in, void* out, int prec, bool dag, hipS
 
 int cg_apply(qdw_op* op, const void* p, void* q, int prec, bool schur, int ring, hipStream_t st)
 {
-    const Epi e = {{op->partials, op->tickets, op->scalars, FIN_CG_ALPHA, ring}, nullptr, nullptr};
+    const Epi e = {{op->partials, op->tickets, op->scalars, FIN_CG_ALPHA, ring, nullptr}, nullptr, nullptr};
     RhsTable tab{};
     tab.in[0] = p;
     tab.out[0] = q;
@@ -685,9 +685,10 @@ int cg_apply(qdw_op* op, const void* p, void* q, int prec, bool schur, int ring,
     });
 }
 
-int cg_apply_dag(qdw_op* op, const void* q, void* r, void* t, int prec, bool schur, hipStream_t st)
+int cg_apply_dag(qdw_op* op, const void* q, void* r, void* t, int prec, bool schur, double* host,
+                 hipStream_t st)
 {
-    const Epi e = {{op->partials, op->tickets, op->scalars, FIN_CG_BETA, 0}, r, op->scalars};
+    const Epi e = {{op->partials, op->tickets, op->scalars, FIN_CG_BETA, 0, host}, r, op->scalars};
     RhsTable tab{};
     tab.in[0] = q;
     tab.out[0] = r;

@@ -5,8 +5,8 @@
 //
 // Step k of a cycle: phi_k = M(rho); chi_k = D phi_k; Gram-Schmidt against chi_0..k-1
 // with all coefficients from one fused multi-dot pass (classical GS), then one pass
-// that subtracts them and forms |chi_k|^2 and chi_k^+ rho, then one pass that normalises
-// chi_k and updates rho (with |rho|^2). Coefficients never leave the device within a
+// that subtracts them and forms |chi_k|^2 and chi_k^+ rho, then one pass that updates rho
+// (with |rho|^2). Coefficients never leave the device within a
 // cycle; the host reads |rho| per step (convergence) and the triangular factor R and c
 // once per cycle, solves R alpha = c and updates psi += sum alpha_l phi_l. The restart
 // step recomputes rho = eta - D psi in FP64.
@@ -49,21 +49,23 @@ struct MultiDot {
     }
 };
 
-// v -= sum_l a_lk chi_l ; |v|^2 ; v^+ rho
+// v -= sum_l (a_lk / b_l) chi_l ; |v|^2 ; v^+ rho
 template <int K>
 struct GsUpdate {
     static constexpr int NS = 3;
     const void* chi[kMaxKv];
     void* v;
     const void* rho;
-    const double* a;  // a_lk at a[2l], a[2l+1]
+    const double* sc;  // the cycle's GCR scalars
     __device__ void operator()(const Unit& u, double* acc) const
     {
+        const double* a = sc + G_A + 2 * kMaxKv * K;
         cx<double> vv[4], rr[4];
         ld4<F64, double>(v, u, vv);
 #pragma unroll
         for (int l = 0; l < K; ++l) {
-            const cx<double> al = {a[2 * l], a[2 * l + 1]};
+            const double ib = sc[G_IB + l];
+            const cx<double> al = {a[2 * l] * ib, a[2 * l + 1] * ib};
             cx<double> c[4];
             ld4<F64, double>(chi[l], u, c);
 #pragma unroll
@@ -81,27 +83,25 @@ struct GsUpdate {
     }
 };
 
-// chi_k = v / b_k ; rho -= (c_k / b_k) v ; |rho|^2
+// next = rho - (c_k / b_k) chi_k ; |next|^2   (next may be rho)
 struct GcrUpdate {
     static constexpr int NS = 1;
-    void* v;
-    void* rho;
-    const double* coef;  // 1/b, Re c/b, Im c/b
+    const void* v;
+    const void* rho;
+    void* next;
+    const double* coef;  // Re c/b, Im c/b
     __device__ void operator()(const Unit& u, double* acc) const
     {
-        const double ib = coef[0];
-        const cx<double> cb = {coef[1], coef[2]};
+        const cx<double> cb = {coef[0], coef[1]};
         cx<double> vv[4], rr[4];
         ld4<F64, double>(v, u, vv);
         ld4<F64, double>(rho, u, rr);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             rr[j] = rr[j] - cb * vv[j];
-            vv[j] = scale(vv[j], ib);
             acc[0] += rr[j].re * rr[j].re + rr[j].im * rr[j].im;
         }
-        st4<F64, double>(v, u, vv);
-        st4<F64, double>(rho, u, rr);
+        st4<F64, double>(next, u, rr);
     }
 };
 
@@ -203,11 +203,14 @@ int gcr_impl(qdw_op* op, const void* eta, void* psi, const qdw_sap_gcr_params& p
     info->n_steps = 0;
     info->rel_res_true = 0.0;
     TRY(run_map(op, Zero<F64>{psi}, st));
-    TRY(run_map(op, Axpby<F64, F64>{eta, L.rho, 1.0, 0.0}, st));
+    // the residual before step k of a cycle; without a preconditioner it is phi_k itself, so
+    // every update writes the residual to the next place of phi and nothing is copied
+    const bool plain = p.precond == QDW_PRECOND_NONE;
+    auto rho = [&](int k) { return plain && k < p.nkv ? L.phi[k] : L.rho; };
+    TRY(run_map(op, Axpby<F64, F64>{eta, rho(0), 1.0, 0.0}, st));
     if (adaptive) TRY(sap_ctrl_reset_total(sap_ctrl(op, p.sdtype, L.pre), st));
     double eta2;
-    TRY(run_map(op, Norm2<F64>{eta}, st, op->scalars + S_TMP));
-    TRY(read_scalars(op, S_TMP, 1, &eta2, st));
+    TRY(run_sum(op, Norm2<F64>{eta}, st, &eta2));
     if (!(eta2 > 0.0)) {
         info->status = std::isfinite(eta2) ? 0 : -3;
         return QDW_OK;
@@ -236,27 +239,24 @@ int gcr_impl(qdw_op* op, const void* eta, void* psi, const qdw_sap_gcr_params& p
                 // block tolerance: the solve's absolute target shared among the blocks
                 TRY(sap_adaptive_run(op, L.rho, L.phi[k], rn, p.ncy, p.nmr, p.sap_alpha,
                                      p.res * neta / B.nblk, B, p.sdtype, L.pre, nullptr, st));
-            } else {
-                TRY(run_map(op, Axpby<F64, F64>{L.rho, L.phi[k], 1.0, 0.0}, st));
             }
             // chi_k = D phi_k, orthogonalised against chi_0..k-1
             TRY(dw_launch(op, L.phi[k], L.chi[k], F64, false, st));
             ++info->n_dw_hi;
-            double* ak = L.gsc + G_A + 2 * kMaxKv * k;
             if (k > 0)
                 TRY(dispatch_k<MultiDot>(k, op, st, [&](auto& f) {
                     for (int l = 0; l < k; ++l) f.chi[l] = L.chi[l];
                     f.v = L.chi[k];
-                }, ak));
+                }, L.gsc, FIN_GCR_DOT, k));
             TRY(dispatch_k<GsUpdate>(k, op, st, [&](auto& f) {
                 for (int l = 0; l < k; ++l) f.chi[l] = L.chi[l];
                 f.v = L.chi[k];
-                f.rho = L.rho;
-                f.a = ak;
+                f.rho = rho(k);
+                f.sc = L.gsc;
             }, L.gsc, FIN_GCR_NORM, k, true));
-            TRY(run_map(op, GcrUpdate{L.chi[k], L.rho, L.gsc + G_COEF}, st, L.gsc + G_NORM));
             double r2;
-            TRY(read_device(op, L.gsc + G_NORM, 1, &r2, st));
+            TRY(run_sum(op, GcrUpdate{L.chi[k], rho(k), rho(k + 1), L.gsc + G_COEF}, st, &r2, false,
+                        L.gsc + G_NORM));
             if (!std::isfinite(r2)) {
                 // a non-finite preconditioner output (or step): the column is dropped, and the
                 // restart below builds psi from the finite columns 0..k-1 and recomputes rho
@@ -300,9 +300,8 @@ int gcr_impl(qdw_op* op, const void* eta, void* psi, const qdw_sap_gcr_params& p
             }));
             TRY(dw_launch(op, psi, L.tmp, F64, false, st));
             ++info->n_dw_hi;
-            TRY(run_map(op, Residual{eta, L.tmp, L.rho}, st, op->scalars + S_TMP));
             double r2;
-            TRY(read_scalars(op, S_TMP, 1, &r2, st));
+            TRY(run_sum(op, Residual{eta, L.tmp, rho(0)}, st, &r2));
             ++info->nreset;
             rn = std::sqrt(r2);
         }

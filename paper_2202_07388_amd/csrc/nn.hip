@@ -1413,14 +1413,11 @@ int pair_to_f32(qdw_op* op, const void* x, float* y, double s, hipStream_t st)
 
 int pair_norm2(qdw_op* op, const void* x, int prec, double* out, hipStream_t st)
 {
-    int rc;
     switch (prec) {
-    case F64: rc = run_map(op, Norm2<F64>{x}, st, op->scalars + S_TMP); break;
-    case F32: rc = run_map(op, Norm2<F32>{x}, st, op->scalars + S_TMP); break;
-    default: rc = run_map(op, Norm2<BF16S>{x}, st, op->scalars + S_TMP); break;
+    case F64: return run_sum(op, Norm2<F64>{x}, st, out);
+    case F32: return run_sum(op, Norm2<F32>{x}, st, out);
+    default: return run_sum(op, Norm2<BF16S>{x}, st, out);
     }
-    if (rc) return rc;
-    return read_scalars(op, S_TMP, 1, out, st);
 }
 
 int pair_convert(qdw_op* op, const void* x, int prec, float* y, double s, hipStream_t st)
@@ -1466,14 +1463,10 @@ extern "C" int nn_train_step(qdw_op* op, float* weights, float* adam, int step, 
         if ((rc = pair_convert(op, rho[k], pair_prec, W.act[0][0], s, st))) return rc;
         if ((rc = pair_convert(op, err[k], pair_prec, W.efield, s, st))) return rc;
         double e2;
-        if ((rc = run_map(op, Norm2<F32>{W.efield}, st, op->scalars + S_TMP))) return rc;
-        if ((rc = read_scalars(op, S_TMP, 1, &e2, st))) return rc;
+        if ((rc = run_sum(op, Norm2<F32>{W.efield}, st, &e2))) return rc;
         if ((rc = forward<false>(op, weights, W, st))) return rc;
         double d2;
-        if ((rc = run_map(op, LossDiff{W.act[kLayers][0], W.efield, W.grad[0][0]}, st,
-                          op->scalars + S_TMP)))
-            return rc;
-        if ((rc = read_scalars(op, S_TMP, 1, &d2, st))) return rc;
+        if ((rc = run_sum(op, LossDiff{W.act[kLayers][0], W.efield, W.grad[0][0]}, st, &d2))) return rc;
         double denom = e2;
         if (loss_kind == 1) {
             // D-norm: d = N(rho) - e  ->  t = D d, |t|^2, gradient direction D^+ t; the
@@ -1481,11 +1474,9 @@ extern "C" int nn_train_step(qdw_op* op, float* weights, float* adam, int step, 
             float* t = W.grad[1][0];
             float* De = W.grad[1][1];
             if ((rc = dw_launch(op, W.grad[0][0], t, F32, false, st))) return rc;
-            if ((rc = run_map(op, Norm2<F32>{t}, st, op->scalars + S_TMP))) return rc;
-            if ((rc = read_scalars(op, S_TMP, 1, &d2, st))) return rc;
+            if ((rc = run_sum(op, Norm2<F32>{t}, st, &d2))) return rc;
             if ((rc = dw_launch(op, W.efield, De, F32, false, st))) return rc;
-            if ((rc = run_map(op, Norm2<F32>{De}, st, op->scalars + S_TMP))) return rc;
-            if ((rc = read_scalars(op, S_TMP, 1, &denom, st))) return rc;
+            if ((rc = run_sum(op, Norm2<F32>{De}, st, &denom))) return rc;
             if ((rc = dw_launch(op, t, W.grad[0][0], F32, true, st))) return rc;
         }
         total += d2 / denom;

@@ -627,6 +627,12 @@ extern "C" int qdw_create(const qdw_lattice* lat, const double* su3, const doubl
     op->tickets = (unsigned*)(base + lay.tickets);
     op->scalars = (double*)(base + lay.scalars);
     op->host_scalars = (double*)host_mem;
+    // reductions write what the host waits for straight into its block; a block that the
+    // device cannot address is read by copies instead
+    if (hipHostGetDevicePointer((void**)&op->host_dev, host_mem, 0) != hipSuccess) {
+        (void)hipGetLastError();
+        op->host_dev = nullptr;
+    }
 
     auto fail = [&](int code, const std::string& msg) {
         set_error(msg);

@@ -31,6 +31,7 @@ struct qdw_op {
     unsigned* tickets;     // device, kTicketWords words
     double* scalars;       // device, kMaxScalars doubles
     double* host_scalars;  // pinned host, kHostScalars doubles
+    double* host_dev;      // the same block as kernels address it (nullptr: not mapped)
 };
 
 namespace qdw {

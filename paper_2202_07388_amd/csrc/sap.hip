@@ -988,9 +988,8 @@ int sap_apply_impl(const char* fn, qdw_op* op, const void* rho, void* phi, int n
     int rc = make_block_geom(op->g, bs, &B);
     if (rc) return rc;
     hipStream_t st = (hipStream_t)stream;
-    if ((rc = run_map(op, Norm2<F64>{rho}, st, op->scalars + S_TMP))) return rc;
     double n2;
-    if ((rc = read_scalars(op, S_TMP, 1, &n2, st))) return rc;
+    if ((rc = run_sum(op, Norm2<F64>{rho}, st, &n2))) return rc;
     char* wk = (char*)(((uintptr_t)work + 255) & ~(uintptr_t)255);
     return sap_run(op, rho, phi, std::sqrt(n2), ncy, nmr, B, sdtype, wk, st, eo);
 }
@@ -1030,9 +1029,8 @@ extern "C" int sap_adaptive_apply(qdw_op* op, const void* rho, void* phi, int nc
     int rc = make_block_geom(op->g, bs, &B);
     if (rc) return rc;
     hipStream_t st = (hipStream_t)stream;
-    if ((rc = run_map(op, Norm2<F64>{rho}, st, op->scalars + S_TMP))) return rc;
     double n2;
-    if ((rc = read_scalars(op, S_TMP, 1, &n2, st))) return rc;
+    if ((rc = run_sum(op, Norm2<F64>{rho}, st, &n2))) return rc;
     char* wk = (char*)(((uintptr_t)work + 255) & ~(uintptr_t)255);
     int* ctrl = sap_ctrl(op, sdtype, wk);
     if ((rc = sap_ctrl_reset_total(ctrl, st))) return rc;
