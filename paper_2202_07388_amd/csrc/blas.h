@@ -376,7 +376,24 @@ struct Axpby {
     }
 };
 
-// y = s x (down-conversion with scaling) and |y|^2 of the stored values
+// y = s x (down-conversion with scaling, one rounding)
+template <int PX, int PY>
+struct ScaleTo {
+    static constexpr int NS = 0;
+    const void* x;
+    void* y;
+    double s;
+    __device__ void operator()(const Unit& w, double*) const
+    {
+        cx<double> v[4];
+        ld4<PX, double>(x, w, v);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = scale(v[k], s);
+        st4<PY, double>(y, w, v);
+    }
+};
+
+// y = s x as above and |y|^2 of the stored values
 template <int PX, int PY>
 struct ScaleNorm {
     static constexpr int NS = 1;

@@ -19,8 +19,9 @@
 
 namespace qdw {
 
-int nn_precondition(qdw_op* op, const void* nn, const void* rho, void* phi, double rho_norm,
-                    char* work, hipStream_t st);
+int nn_prepare(qdw_op* op, const void* weights, char* work, hipStream_t st);
+int nn_precondition(qdw_op* op, const void* rho, void* phi, double rho_norm, char* work,
+                    hipStream_t st);
 size_t nn_precond_workspace(const qdw_op* op);
 
 namespace {
@@ -220,6 +221,7 @@ int gcr_impl(qdw_op* op, const void* eta, void* psi, const qdw_sap_gcr_params& p
     double rn = neta;
     int steps = 0, status = 0;
     bool nn_ok = p.precond == QDW_PRECOND_NN || p.precond == QDW_PRECOND_NN_SAP;
+    if (nn_ok) TRY(nn_prepare(op, p.nn_weights, L.pre, st));
     std::vector<double> hs(G_SIZE);
     while (true) {
         int k = 0;
@@ -229,7 +231,7 @@ int gcr_impl(qdw_op* op, const void* eta, void* psi, const qdw_sap_gcr_params& p
             const double rn_before = rn;
             bool use_nn = nn_ok;
             if (use_nn) {
-                TRY(nn_precondition(op, p.nn_weights, L.rho, L.phi[k], rn, L.pre, st));
+                TRY(nn_precondition(op, L.rho, L.phi[k], rn, L.pre, st));
             } else if (p.precond == QDW_PRECOND_SAP || p.precond == QDW_PRECOND_NN_SAP ||
                        sap_eo) {
                 TRY(sap_run(op, L.rho, L.phi[k], rn, p.ncy, p.nmr, B, p.sdtype, L.pre, st,

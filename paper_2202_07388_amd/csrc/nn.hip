@@ -38,6 +38,14 @@ typedef short s4 __attribute__((ext_vector_type(4)));
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
+// channel fields of a layer boundary, at a fixed distance in the workspace (passed by value:
+// no pointer table to copy to the device, and its loads are known to be global ones)
+struct Chan {
+    char* base = nullptr;
+    long stride = 0;
+    __host__ __device__ __forceinline__ void* at(int c) const { return base + c * stride; }
+};
+
 inline int layer_K(int l) { return (kPaths * kCh[l] * 8 + 15) & ~15; }
 inline int layer_N(int l) { return std::max(16, kCh[l + 1] * 8); }
 inline int layer_w_offset(int l)  // in complex numbers
@@ -110,7 +118,7 @@ __device__ __forceinline__ long f32_addr(int Vh, int par, int i, int s, int c)
 // no stale values from earlier use of the workspace.
 template <bool F32M, int PIN>
 __global__ __launch_bounds__(256) void nn_transport_kernel(Geom g, int Cin, int Kpad, long Mp,
-                                                           const void* const* in, void* A,
+                                                           Chan in, void* A,
                                                            const void* links, const void* dets)
 {
     const long tid = (long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -131,7 +139,7 @@ __global__ __launch_bounds__(256) void nn_transport_kernel(Geom g, int Cin, int 
     }
     int x[4], lex;
     eo_coords(g, par, i, x, lex);
-    const void* v = in[b];
+    const void* v = in.at(b);
     for (int p = 0; p < kPaths; ++p) {
         cx<float> s[12], w[12];
         if (p == 0) {
@@ -175,7 +183,7 @@ __global__ __launch_bounds__(256) void nn_transport_kernel(Geom g, int Cin, int 
 
 // g_b(x) = sum_p T_p^+ dA[p][b](x): T_{+mu}^+ = T_{-mu}, T_{-mu}^+ = T_{+mu}
 __global__ __launch_bounds__(256) void nn_transport_adj_kernel(Geom g, int Cin, long Mp,
-                                                               const float* dA, float* const* gout,
+                                                               const float* dA, Chan gout,
                                                                const void* links, const void* dets)
 {
     const long tid = (long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -226,7 +234,7 @@ __global__ __launch_bounds__(256) void nn_transport_adj_kernel(Geom g, int Cin, 
             }
         }
     }
-    store_spinor<F32>(gout[b], g.Vh, par, i, acc);
+    store_spinor<F32>(gout.at(b), g.Vh, par, i, acc);
 }
 
 // ------------------------------------------------------------------ weights as matrices
@@ -246,16 +254,46 @@ __device__ __forceinline__ float embed(const float* W, int Cin, int Cout, int k,
     return ri == 0 ? im : re;
 }
 
+// The same for every layer and form in one launch (blockIdx.y: 0..2 the layers; in bf16 also
+// 3, the 8-channel layer as the fused kernel's LDS image -- for each path p the block of Bt
+// (rows n < 64, columns k = 64 p + 0..63) as [k / 8][n][k % 8], so that a lane's eight
+// consecutive k of one column n are one 16-byte read -- and 4, the last layer's path mixing
+// Bm[n][k], n = (p*4 + s)*2 + re/im (72, padded to 80), k = (b*4 + t)*2 + re/im).
+struct Embedded {
+    void* Bt[kLayers];
+    void* Bk[kLayers];
+    uint16_t* Bl;
+    uint16_t* Bm;
+};
+
 template <bool F32M>
-__global__ void nn_embed_kernel(const float* W, int Cin, int Cout, int Kpad, int Npad, void* Bt,
-                                void* Bk)
+__global__ void nn_embed_kernel(const float* W, Embedded E)
 {
-    const int tid = blockIdx.x * blockDim.x + threadIdx.x;
-    if (tid >= Kpad * Npad) return;
-    const int n = tid / Kpad, k = tid - n * Kpad;
-    const float v = (k < kPaths * Cin * 8) ? embed(W, Cin, Cout, k, n) : 0.f;
-    put_el<F32M>(Bt, (long)n * Kpad + k, v);
-    put_el<F32M>(Bk, (long)k * Npad + n, v);
+    const int tid = blockIdx.x * blockDim.x + threadIdx.x, job = blockIdx.y;
+    const int off[kLayers] = {0, kPaths * kCh[0] * kCh[1] * 16, kPaths * (kCh[0] * kCh[1] + kCh[1] * kCh[2]) * 16};
+    if (job < kLayers) {
+        const int Cin = kCh[job], Cout = kCh[job + 1];
+        const int Kpad = (kPaths * Cin * 8 + 15) & ~15, Npad = Cout * 8 < 16 ? 16 : Cout * 8;
+        if (tid >= Kpad * Npad) return;
+        const int n = tid / Kpad, k = tid - n * Kpad;
+        const float v = (k < kPaths * Cin * 8) ? embed(W + 2 * off[job], Cin, Cout, k, n) : 0.f;
+        put_el<F32M>(E.Bt[job], (long)n * Kpad + k, v);
+        put_el<F32M>(E.Bk[job], (long)k * Npad + n, v);
+    } else if (job == 3) {
+        if (tid >= kPaths * 64 * 64) return;
+        const int e = tid & 7, n = (tid >> 3) & 63, kq = (tid >> 9) & 7, p = tid >> 12;
+        E.Bl[tid] = bf16_bits(embed(W + 2 * off[1], 8, 8, p * 64 + kq * 8 + e, n));
+    } else {
+        if (tid >= 80 * 64) return;
+        const int n = tid / 64, k = tid - n * 64;
+        float v = 0.f;
+        if (n < 72) {
+            const int p = n >> 3, sro = n & 7;            // (s, re/im) of the output
+            const int b = k >> 3, tri = k & 7;            // (t, re/im) of the input
+            v = embed(W + 2 * off[2], 8, 1, (p * 8 + b) * 8 + tri, sro);
+        }
+        E.Bm[tid] = bf16_bits(v);
+    }
 }
 
 // dW (complex, dL/dRe W + i dL/dIm W) += the real-embedding gradient dB[k][n]
@@ -302,7 +340,7 @@ __device__ __forceinline__ void mfma_step(const void* A, long arow, const void* 
 template <bool F32M>
 __global__ __launch_bounds__(256) void nn_gemm_out_kernel(Geom g, int Kpad, int Npad, int Cout,
                                                           long Mp, const void* A, const void* Bt,
-                                                          float* const* out)
+                                                          Chan out)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const long m0 = (long)blockIdx.x * 64 + wave * 16;
@@ -326,7 +364,7 @@ __global__ __launch_bounds__(256) void nn_gemm_out_kernel(Geom g, int Kpad, int 
             if (q >= 2L * Vp || a >= Cout) continue;
             const int par = (int)(q / Vp), i = (int)(q - (long)par * Vp);
             if (i >= g.Vh) continue;
-            out[a][f32_addr(g.Vh, par, i, s, c) + ri] = acc[j][r];
+            ((float*)out.at(a))[f32_addr(g.Vh, par, i, s, c) + ri] = acc[j][r];
         }
 }
 
@@ -408,7 +446,7 @@ __global__ void nn_reduce_db_kernel(const float* part, int nsplit, int KN, float
 // G rows from a channel gradient (FP32 fields), times `scale`
 template <bool F32M>
 __global__ __launch_bounds__(256) void nn_pack_g_kernel(Geom g, int Cout, int Npad,
-                                                        const float* const* gf, float scale, void* G)
+                                                        Chan gf, float scale, void* G)
 {
     const long tid = (long)blockIdx.x * blockDim.x + threadIdx.x;
     const int Vp = padded(g.Vh);
@@ -419,7 +457,7 @@ __global__ __launch_bounds__(256) void nn_pack_g_kernel(Geom g, int Cout, int Np
         for (int n = 0; n < Npad; ++n) {
             const int a = n >> 3, s = (n >> 1) & 3, ri = n & 1;
             float v = 0.f;
-            if (a < Cout && i < g.Vh) v = scale * gf[a][f32_addr(g.Vh, par, i, s, c) + ri];
+            if (a < Cout && i < g.Vh) v = scale * ((const float*)gf.at(a))[f32_addr(g.Vh, par, i, s, c) + ri];
             put_el<F32M>(G, (tid * 3 + c) * Npad + n, v);
         }
 }
@@ -549,18 +587,6 @@ __device__ __forceinline__ void nn_apply_m(bool fwd, const cx<float> m[9], const
 constexpr int kWBlock = 64 * 64 * 2;
 typedef __attribute__((address_space(1))) const u32x4 g_cu4;
 
-// the 8-channel layer's weights in the fused kernel's LDS image: for each path p the block
-// of Bt (rows n < 64, columns k = 64 p + 0..63) as [k / 4][n][k % 4], so that one lane's
-// four consecutive k of one column n are 8 contiguous bytes and the 16 lanes of a
-// matrix-core operand row read 128 contiguous bytes
-__global__ void nn_embed_lds_kernel(const uint16_t* Bt, int Kpad, uint16_t* Bl)
-{
-    const int tid = blockIdx.x * blockDim.x + threadIdx.x;
-    if (tid >= kPaths * 64 * 64) return;
-    const int e = tid & 7, n = (tid >> 3) & 63, kq = (tid >> 9) & 7, p = tid >> 12;
-    Bl[tid] = Bt[(long)n * Kpad + p * 64 + kq * 8 + e];
-}
-
 // LDS row stride (in bf16 halves) of a tile with KB columns: at least KB + 8, rows 16-byte
 // aligned, and a lane's three rows (the lane-to-lane step of the 16-byte row writes) 4 banks
 // apart modulo the 64 banks, so the 64 lanes of a write hit every bank equally
@@ -636,9 +662,8 @@ __device__ __forceinline__ void nn_rows_raw(const u32x4 raw[3], bf16x8 T[3])
 // (the compiler's own choice, 132, allows three); the eight-channel layers keep theirs.
 template <int CIN, int COUT, int PIN, int POUT, bool MIXOUT = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CIN == 1 ? 4 : 1)))
-void nn_layer_fused_kernel(Geom g, int Kpad, const void* const* in, const void* Bt,
-                           const void* Bl, void* const* out, const void* links,
-                           const void* dets, const uint16_t* Bm = nullptr)
+void nn_layer_fused_kernel(Geom g, int Kpad, Chan in, const void* Bt, const void* Bl, Chan out,
+                           const void* links, const void* dets, const uint16_t* Bm = nullptr)
 {
     constexpr int PB = CIN == 1 ? kPaths : 1;          // paths per batch
     constexpr int KB = (PB * CIN * 8 + 15) & ~15;      // columns per batch (80 or 64)
@@ -732,12 +757,12 @@ void nn_layer_fused_kernel(Geom g, int Kpad, const void* const* in, const void* 
             cx<float> u[6], d;
             float sg;
         };
-        // the lane's two channel fields, read from the pointer table once and accessed as
-        // global memory: loads through generic pointers would be flat loads, which may
-        // complete out of order with the LDS accesses, so that every wait in the path loop
-        // would become a wait for all loads in flight, the prefetched ones included
-        const g_cu4* const c0 = (const g_cu4*)in[cg];
-        const g_cu4* const c1 = (const g_cu4*)in[cg + 4];
+        // the lane's two channel fields, accessed as global memory: loads through generic
+        // pointers would be flat loads, which may complete out of order with the LDS
+        // accesses, so that every wait in the path loop would become a wait for all loads in
+        // flight, the prefetched ones included
+        const g_cu4* const c0 = (const g_cu4*)in.at(cg);
+        const g_cu4* const c1 = (const g_cu4*)in.at(cg + 4);
         // the spinors of path p: the lane's own site for p = 0, else the neighbour
         auto fetch_sp = [&](int p, SpStage& S) {
             int j = i, pp = par;
@@ -863,13 +888,13 @@ void nn_layer_fused_kernel(Geom g, int Kpad, const void* const* in, const void* 
                 continue;
             }
             if (p == 0) {
-                load_spinor<PIN>(in[0], g.Vh, par, i, w);
+                load_spinor<PIN>(in.base, g.Vh, par, i, w);
             } else {
                 int j;
                 float sg;
                 cx<float> u[6], d, sp[12];
                 nn_path_setup(g, par, i, x, lex, p, links, dets, j, sg, u, d);
-                load_spinor<PIN>(in[0], g.Vh, 1 - par, j, sp);
+                load_spinor<PIN>(in.base, g.Vh, 1 - par, j, sp);
                 cx<float> m[9];
                 nn_link_matrix(u, d, sg, m);
                 nn_apply_m(((p - 1) & 1) == 0, m, sp, w);
@@ -926,7 +951,7 @@ void nn_layer_fused_kernel(Geom g, int Kpad, const void* const* in, const void* 
             const int p = u / 192, rem = u - p * 192, ch = rem >> 6, site = rem & 63;
             if (mi0 + site >= g.Vh) continue;
             const uint4 raw = *(const uint4*)&ob[(p * 3 + ch) * OROW + site * 8];
-            ((uint4*)out[p])[chunk_at(g.Vh, 3, mpar, ch, mi0 + site)] = raw;
+            ((uint4*)out.at(p))[chunk_at(g.Vh, 3, mpar, ch, mi0 + site)] = raw;
         }
         return;
     }
@@ -953,7 +978,7 @@ void nn_layer_fused_kernel(Geom g, int Kpad, const void* const* in, const void* 
         const int a = u / 192, rem = u - a * 192, ch = rem >> 6, site = rem & 63;
         if (oi0 + site >= g.Vh) continue;
         const uint4 raw = *(const uint4*)&ob[(a * 3 + ch) * OROW + site * 8];
-        ((uint4*)out[a])[chunk_at(g.Vh, 3, opar, ch, oi0 + site)] = raw;
+        ((uint4*)out.at(a))[chunk_at(g.Vh, 3, opar, ch, oi0 + site)] = raw;
     }
 }
 
@@ -967,23 +992,8 @@ void nn_layer_fused_kernel(Geom g, int Kpad, const void* const* in, const void* 
 // channels x 4 spins x re/im, N = 9 paths x 4 spins x re/im), storing them in bf16; pass 2
 // is a plain stencil over them. Each site then gathers 9 spinors instead of 72.
 
-// Bm[n][k]: n = (p*4 + s)*2 + re/im (72, padded to 80), k = (b*4 + t)*2 + re/im (64)
-__global__ void nn_embed_mix_kernel(const float* W, uint16_t* Bm)
-{
-    const int tid = blockIdx.x * blockDim.x + threadIdx.x;
-    if (tid >= 80 * 64) return;
-    const int n = tid / 64, k = tid - n * 64;
-    float v = 0.f;
-    if (n < 72) {
-        const int p = n >> 3, sro = n & 7;            // (s, re/im) of the output
-        const int b = k >> 3, tri = k & 7;            // (t, re/im) of the input
-        v = embed(W, 8, 1, (p * 8 + b) * 8 + tri, sro);
-    }
-    Bm[tid] = float_to_bf16(v);
-}
-
-__global__ __launch_bounds__(256) void nn_mix_paths_kernel(Geom g, const void* const* in,
-                                                           const uint16_t* Bm, void* const* mix)
+__global__ __launch_bounds__(256) void nn_mix_paths_kernel(Geom g, Chan in, const uint16_t* Bm,
+                                                           Chan mix)
 {
     constexpr int KB = 64, LS = tile_stride(KB), NT = 5;
     // output staging in bf16: one row per (path, 16-byte chunk) of 64 sites x 8 halves,
@@ -1001,8 +1011,8 @@ __global__ __launch_bounds__(256) void nn_mix_paths_kernel(Geom g, const void* c
     // rows of the tile: the site's eight input channels (channels wave and wave + 4)
     if (i < g.Vh) {
         cx<float> w0[12], w1[12];
-        load_spinor<BF16S>(in[wave], g.Vh, par, i, w0);
-        load_spinor<BF16S>(in[wave + 4], g.Vh, par, i, w1);
+        load_spinor<BF16S>(in.at(wave), g.Vh, par, i, w0);
+        load_spinor<BF16S>(in.at(wave + 4), g.Vh, par, i, w1);
         nn_put_rows<LS>(tile, lane, wave * 8, w0);
         nn_put_rows<LS>(tile, lane, (wave + 4) * 8, w1);
     } else {
@@ -1045,14 +1055,15 @@ __global__ __launch_bounds__(256) void nn_mix_paths_kernel(Geom g, const void* c
         const int p = u / 192, rem = u - p * 192, ch = rem >> 6, site = rem & 63;
         if (i0 + site >= g.Vh) continue;
         const uint4 raw = *(const uint4*)&ob[(p * 3 + ch) * ROW + site * 8];
-        ((uint4*)mix[p])[chunk_at(g.Vh, 3, par, ch, i0 + site)] = raw;
+        ((uint4*)mix.at(p))[chunk_at(g.Vh, 3, par, ch, i0 + site)] = raw;
     }
 }
 
-// out(x) = m_0(x) + sum_{p = 1..8} (T_p m_p)(x)   (FP32 output)
-__global__ __launch_bounds__(256) void nn_transport_sum_kernel(Geom g, const void* const* mix,
-                                                               float* out, const void* links,
-                                                               const void* dets)
+// out(x) = a (m_0(x) + sum_{p = 1..8} (T_p m_p)(x)), formed in FP32 and stored as FP32 or, for
+// a caller's FP64 field, as the FP64 of that (no second pass to convert it)
+template <int POUT>
+__global__ __launch_bounds__(256) void nn_transport_sum_kernel(Geom g, Chan mix, void* out, float a,
+                                                               const void* links, const void* dets)
 {
     // 256-site blocks of the two parities alternate, XCD-contiguously (as nn_block_q0)
     const int w = xcd_tile(blockIdx.x, gridDim.x);
@@ -1062,7 +1073,7 @@ __global__ __launch_bounds__(256) void nn_transport_sum_kernel(Geom g, const voi
     int x[4], lex;
     eo_coords(g, par, i, x, lex);
     cx<float> acc[12];
-    load_spinor<BF16S>(mix[0], g.Vh, par, i, acc);
+    load_spinor<BF16S>(mix.base, g.Vh, par, i, acc);
 #pragma unroll 1
     for (int p = 1; p < kPaths; ++p) {
         int j;
@@ -1072,14 +1083,20 @@ __global__ __launch_bounds__(256) void nn_transport_sum_kernel(Geom g, const voi
         u32x4 raw[3];
         const long b0 = chunk_at(g.Vh, 3, 1 - par, 0, j);
 #pragma unroll
-        for (int k = 0; k < 3; ++k) raw[k] = ((const u32x4*)mix[p])[b0 + (long)k * kSB];
+        for (int k = 0; k < 3; ++k) raw[k] = ((const u32x4*)mix.at(p))[b0 + (long)k * kSB];
         cx<float> m[9];
         LinkBF lb;
         nn_link_matrix(u, d, sg, m);
         nn_link_bf16(((p - 1) & 1) == 0, m, lb);
         nn_transport_dot2<true>(lb, raw, acc);
     }
-    store_spinor<F32>(out, g.Vh, par, i, acc);
+    cx<typename Traits<POUT>::real> o[12];
+#pragma unroll
+    for (int k = 0; k < 12; ++k) {
+        const cx<float> v = scale(acc[k], a);
+        o[k] = {v.re, v.im};
+    }
+    store_spinor<POUT>(out, g.Vh, par, i, o);
 }
 
 __global__ void fill_kernel(uint32_t* p, long n)
@@ -1121,23 +1138,17 @@ struct LossDiff {
 // ------------------------------------------------------------------ host side
 
 struct NnWork {
-    float* act[kLayers + 1][8];  // channel fields per layer boundary (FP32 space; the hidden
+    Chan act[kLayers + 1];       // channel fields per layer boundary (FP32 space; the hidden
                                  // ones hold bf16 fields in the bf16 forward pass)
-    float* grad[2][8];           // gradient channel fields (ping-pong)
+    Chan grad[2];                // gradient channel fields (ping-pong)
     float* efield;               // target (FP32)
     void* A;                     // transported rows, [Mpad][Kmax]
     float* dA;                   // [Mpad][Kmax] (training only)
     void* G;                     // [Mpad][Nmax]
-    void* Bt;                    // [Nmax][Kmax]
-    void* Bk;                    // [Kmax][Nmax]
+    Embedded E;                  // per layer Bt [Nmax][Kmax] and Bk [Kmax][Nmax]; Bl, Bm
     float* part;                 // [nsplit][Kmax][Nmax]
     float* dB;                   // [Kmax][Nmax]
-    void* mix[kPaths];           // bf16 fields m_p of the last layer's path mixing
-    uint16_t* Bm;                // [80][64] bf16: the last layer's mixing matrix
-    uint16_t* Bl;                // [9][16][64][4] bf16: the 8-channel layer's weights as
-                                 // the fused kernel's LDS image
-    float** ptrs;                // device pointer tables (8 pointers per slot)
-    char* end;
+    Chan mix;                    // bf16 fields m_p of the last layer's path mixing
 };
 
 constexpr int kSplit = 64;
@@ -1154,28 +1165,35 @@ size_t nn_layout(const qdw_op* op, bool training, char* base, NnWork* W, bool ne
         off += (n + 255) & ~(size_t)255;
         return at;
     };
-    for (int l = 0; l <= kLayers; ++l)
-        for (int c = 0; c < 8; ++c) W->act[l][c] = c < kCh[l] ? (float*)take(fb) : nullptr;
-    for (int h = 0; h < 2; ++h)
-        for (int c = 0; c < 8; ++c) W->grad[h][c] = training ? (float*)take(fb) : nullptr;
+    auto channels = [&](int n, size_t bytes) {
+        const size_t each = (bytes + 255) & ~(size_t)255;
+        return Chan{take(each * n), (long)each};
+    };
+    for (int l = 0; l <= kLayers; ++l) W->act[l] = channels(kCh[l], fb);
+    for (int h = 0; h < 2; ++h) W->grad[h] = training ? channels(8, fb) : Chan{};
     W->efield = training ? (float*)take(fb) : nullptr;
     W->A = need_A || training ? take((size_t)Mp * kMaxK * 4) : nullptr;
-    for (int p = 0; p < kPaths; ++p) W->mix[p] = take(spinor_bytes(g, BF16S));
-    W->Bm = (uint16_t*)take(80 * 64 * 2);
-    W->Bl = (uint16_t*)take((size_t)kPaths * kWBlock);
+    W->mix = channels(kPaths, spinor_bytes(g, BF16S));
+    W->E.Bm = (uint16_t*)take(80 * 64 * 2);
+    W->E.Bl = (uint16_t*)take((size_t)kPaths * kWBlock);
     W->dA = training ? (float*)take((size_t)Mp * kMaxK * 4) : nullptr;
     W->G = training ? take((size_t)Mp * kMaxN * 4) : nullptr;
-    W->Bt = take((size_t)kMaxN * kMaxK * 4);
-    W->Bk = take((size_t)kMaxN * kMaxK * 4);
+    for (int l = 0; l < kLayers; ++l) {
+        W->E.Bt[l] = take((size_t)kMaxN * kMaxK * 4);
+        W->E.Bk[l] = take((size_t)kMaxN * kMaxK * 4);
+    }
     W->part = training ? (float*)take((size_t)kSplit * kMaxN * kMaxK * 4) : nullptr;
     W->dB = training ? (float*)take((size_t)kMaxN * kMaxK * 4) : nullptr;
-    W->ptrs = (float**)take(64 * sizeof(float*));
     return off + 256;
 }
 
-int set_ptrs(float** dev, float* const* host, int n, int slot, hipStream_t st)
+// the weights in every form the passes read; once per set of weights
+template <bool F32M>
+int embed_weights(const float* weights, const NnWork& W, hipStream_t st)
 {
-    QDW_HIP(hipMemcpyAsync(dev + 8 * slot, host, sizeof(float*) * n, hipMemcpyHostToDevice, st));
+    nn_embed_kernel<F32M><<<dim3((kMaxK * kMaxN + 255) / 256, F32M ? kLayers : kLayers + 2), 256, 0, st>>>(
+        weights, W.E);
+    QDW_LAUNCH_CHECK();
     return QDW_OK;
 }
 
@@ -1187,114 +1205,83 @@ int zero_dev(void* p, size_t bytes, hipStream_t st)
     return QDW_OK;
 }
 
-// forward through all layers, input already in act[0][0]; keeps every layer's input
-// (keep_hidden, needed by the gradients), or, in bf16 inference passes without it, fuses
-// the last layer's path mixing into the 8 -> 8 layer so that the second hidden layer's
-// channels never go to memory
+// forward through all layers, input already in act[0] and the weights embedded; keeps every
+// layer's input (keep_hidden, needed by the gradients), or, in bf16 inference passes without
+// it, fuses the last layer's path mixing into the 8 -> 8 layer so that the second hidden
+// layer's channels never go to memory. The output times `a` goes to `out64` (FP64) if given,
+// else to act[kLayers] (FP32, a = 1).
 template <bool F32M>
-int forward(qdw_op* op, const float* weights, NnWork& W, hipStream_t st, bool keep_hidden = true)
+int forward(qdw_op* op, NnWork& W, hipStream_t st, bool keep_hidden = true, void* out64 = nullptr,
+            float a = 1.f)
 {
     const Geom& g = op->g;
-    const long Mp = rows_padded(g);
     const long nq = 2L * padded(g.Vh);
-    int rc;
-    for (int l = 0; l < kLayers; ++l) {
-        const int Cin = kCh[l], Cout = kCh[l + 1], Kp = layer_K(l), Np = layer_N(l);
-        if ((rc = set_ptrs(W.ptrs, W.act[l], Cin, 0, st))) return rc;
-        if ((rc = set_ptrs(W.ptrs, W.act[l + 1], Cout, 1, st))) return rc;
-        nn_embed_kernel<F32M><<<(Kp * Np + 255) / 256, 256, 0, st>>>(
-            weights + 2 * layer_w_offset(l), Cin, Cout, Kp, Np, W.Bt, W.Bk);
-        QDW_LAUNCH_CHECK();
-        if constexpr (!F32M) {
-            // hidden activations (between the layers) are stored in bf16, the network's
-            // input and output in FP32
-            const unsigned nb = (unsigned)(nq / 64);
-            const void* L = op->links[F32];
-            const void* D = op->det[F32];
-            const void* const* pin = (const void* const*)W.ptrs;
-            void* const* pout = (void* const*)(W.ptrs + 8);
-            if (Cin == 1) {
-                nn_layer_fused_kernel<1, 8, F32, BF16S><<<nb, 256, 0, st>>>(g, Kp, pin, W.Bt, nullptr,
-                                                                             pout, L, D);
-                QDW_LAUNCH_CHECK();
-            } else if (Cout == 8) {
-                nn_embed_lds_kernel<<<(kPaths * 64 * 64 + 255) / 256, 256, 0, st>>>(
-                    (const uint16_t*)W.Bt, Kp, W.Bl);
-                QDW_LAUNCH_CHECK();
-                if (keep_hidden) {
-                    nn_layer_fused_kernel<8, 8, BF16S, BF16S><<<nb, 256, 0, st>>>(
-                        g, Kp, pin, W.Bt, W.Bl, pout, L, D);
-                } else {
-                    // the last layer's mixing matrix first: its product runs in this launch
-                    if ((rc = set_ptrs(W.ptrs, (float* const*)W.mix, kPaths, 3, st))) return rc;
-                    nn_embed_mix_kernel<<<(80 * 64 + 255) / 256, 256, 0, st>>>(
-                        weights + 2 * layer_w_offset(l + 1), W.Bm);
-                    QDW_LAUNCH_CHECK();
-                    nn_layer_fused_kernel<8, 8, BF16S, BF16S, true><<<nb, 256, 0, st>>>(
-                        g, Kp, pin, W.Bt, W.Bl, (void* const*)(W.ptrs + 24), L, D, W.Bm);
-                }
-                QDW_LAUNCH_CHECK();
-            } else {
-                // one output channel: mix the paths first (already done by the 8 -> 8
-                // layer's launch when the hidden channels are not kept), then transport 9
-                // fields
-                if (keep_hidden) {
-                    if ((rc = set_ptrs(W.ptrs, (float* const*)W.mix, kPaths, 3, st))) return rc;
-                    nn_embed_mix_kernel<<<(80 * 64 + 255) / 256, 256, 0, st>>>(
-                        weights + 2 * layer_w_offset(l), W.Bm);
-                    QDW_LAUNCH_CHECK();
-                    nn_mix_paths_kernel<<<nb, 256, 0, st>>>(g, pin, W.Bm,
-                                                            (void* const*)(W.ptrs + 24));
-                    QDW_LAUNCH_CHECK();
-                }
-                nn_transport_sum_kernel<<<2 * ((g.Vh + 255) / 256), 256, 0, st>>>(
-                    g, (const void* const*)(W.ptrs + 24), W.act[l + 1][0], L, D);
-                QDW_LAUNCH_CHECK();
-            }
-        } else {
-            nn_transport_kernel<F32M, F32><<<(unsigned)((nq * Cin + 255) / 256), 256, 0, st>>>(
-                g, Cin, Kp, Mp, (const void* const*)W.ptrs, W.A, op->links[F32], op->det[F32]);
+    const void* L = op->links[F32];
+    const void* D = op->det[F32];
+    if constexpr (F32M) {
+        const long Mp = rows_padded(g);
+        for (int l = 0; l < kLayers; ++l) {
+            const int Cin = kCh[l], Cout = kCh[l + 1], Kp = layer_K(l), Np = layer_N(l);
+            nn_transport_kernel<true, F32><<<(unsigned)((nq * Cin + 255) / 256), 256, 0, st>>>(
+                g, Cin, Kp, Mp, W.act[l], W.A, L, D);
             QDW_LAUNCH_CHECK();
-            nn_gemm_out_kernel<F32M><<<(unsigned)(Mp / 64), 256, 0, st>>>(g, Kp, Np, Cout, Mp, W.A,
-                                                                          W.Bt, W.ptrs + 8);
+            nn_gemm_out_kernel<true><<<(unsigned)(Mp / 64), 256, 0, st>>>(g, Kp, Np, Cout, Mp, W.A,
+                                                                         W.E.Bt[l], W.act[l + 1]);
             QDW_LAUNCH_CHECK();
         }
+        return out64 ? run_map(op, Axpby<F32, F64>{W.act[kLayers].base, out64, a, 0.0}, st) : QDW_OK;
     }
+    // hidden activations (between the layers) are stored in bf16, the network's input and
+    // output in FP32
+    const unsigned nb = (unsigned)(nq / 64);
+    nn_layer_fused_kernel<1, 8, F32, BF16S><<<nb, 256, 0, st>>>(g, layer_K(0), W.act[0], W.E.Bt[0],
+                                                                 nullptr, W.act[1], L, D);
+    QDW_LAUNCH_CHECK();
+    if (keep_hidden) {
+        nn_layer_fused_kernel<8, 8, BF16S, BF16S><<<nb, 256, 0, st>>>(g, layer_K(1), W.act[1], W.E.Bt[1],
+                                                                       W.E.Bl, W.act[2], L, D);
+        QDW_LAUNCH_CHECK();
+        // one output channel: mix the paths first, then transport 9 fields
+        nn_mix_paths_kernel<<<nb, 256, 0, st>>>(g, W.act[2], W.E.Bm, W.mix);
+    } else {
+        nn_layer_fused_kernel<8, 8, BF16S, BF16S, true><<<nb, 256, 0, st>>>(
+            g, layer_K(1), W.act[1], W.E.Bt[1], W.E.Bl, W.mix, L, D, W.E.Bm);
+    }
+    QDW_LAUNCH_CHECK();
+    const unsigned ns = 2 * ((g.Vh + 255) / 256);
+    if (out64)
+        nn_transport_sum_kernel<F64><<<ns, 256, 0, st>>>(g, W.mix, out64, a, L, D);
+    else
+        nn_transport_sum_kernel<F32><<<ns, 256, 0, st>>>(g, W.mix, W.act[kLayers].base, a, L, D);
+    QDW_LAUNCH_CHECK();
     return QDW_OK;
 }
 
 // backward from the real gradient of the network output (grad[0][0], times gscale);
 // accumulates dL/dRe W + i dL/dIm W into dW and leaves the input gradient in grad[x][0]
 template <bool F32M>
-int backward(qdw_op* op, const float* weights, float* dW, NnWork& W, float gscale, hipStream_t st,
-             float** gin_out)
+int backward(qdw_op* op, float* dW, NnWork& W, float gscale, hipStream_t st, float** gin_out)
 {
     const Geom& g = op->g;
     const long Mp = rows_padded(g);
     const long nq = 2L * padded(g.Vh);
     const long M = rows_of(g);
-    int rc;
     int cur = 0;  // grad[cur] holds the gradient of layer l's output
     for (int l = kLayers - 1; l >= 0; --l) {
         const int Cin = kCh[l], Cout = kCh[l + 1], Kp = layer_K(l), Np = layer_N(l);
         // recompute this layer's transported input rows (hidden activations are bf16 in
         // the bf16 forward pass)
-        if ((rc = set_ptrs(W.ptrs, W.act[l], Cin, 0, st))) return rc;
         const unsigned ntb = (unsigned)((nq * Cin + 255) / 256);
         if (F32M || l == 0)
             nn_transport_kernel<F32M, F32><<<ntb, 256, 0, st>>>(
-                g, Cin, Kp, Mp, (const void* const*)W.ptrs, W.A, op->links[F32], op->det[F32]);
+                g, Cin, Kp, Mp, W.act[l], W.A, op->links[F32], op->det[F32]);
         else
             nn_transport_kernel<F32M, BF16S><<<ntb, 256, 0, st>>>(
-                g, Cin, Kp, Mp, (const void* const*)W.ptrs, W.A, op->links[F32], op->det[F32]);
-        QDW_LAUNCH_CHECK();
-        nn_embed_kernel<F32M><<<(Kp * Np + 255) / 256, 256, 0, st>>>(
-            weights + 2 * layer_w_offset(l), Cin, Cout, Kp, Np, W.Bt, W.Bk);
+                g, Cin, Kp, Mp, W.act[l], W.A, op->links[F32], op->det[F32]);
         QDW_LAUNCH_CHECK();
         // G rows from the output gradient
-        if ((rc = set_ptrs(W.ptrs, W.grad[cur], Cout, 1, st))) return rc;
         nn_pack_g_kernel<F32M><<<(unsigned)((nq + 255) / 256), 256, 0, st>>>(
-            g, Cout, Np, W.ptrs + 8, l == kLayers - 1 ? gscale : 1.f, W.G);
+            g, Cout, Np, W.grad[cur], l == kLayers - 1 ? gscale : 1.f, W.G);
         QDW_LAUNCH_CHECK();
         // weight gradient dB = A^T G
         const long rows_per = ((M + kSplit - 1) / kSplit + 15) & ~15L;
@@ -1308,15 +1295,14 @@ int backward(qdw_op* op, const float* weights, float* dW, NnWork& W, float gscal
                                                        dW + 2 * layer_w_offset(l));
         QDW_LAUNCH_CHECK();
         // input gradient dA = G B^T, then the adjoint transport
-        nn_gemm_da_kernel<F32M><<<(unsigned)(Mp / 64), 256, 0, st>>>(Kp, Np, Mp, W.G, W.Bk, W.dA);
+        nn_gemm_da_kernel<F32M><<<(unsigned)(Mp / 64), 256, 0, st>>>(Kp, Np, Mp, W.G, W.E.Bk[l], W.dA);
         QDW_LAUNCH_CHECK();
-        if ((rc = set_ptrs(W.ptrs, W.grad[1 - cur], Cin, 2, st))) return rc;
         nn_transport_adj_kernel<<<(unsigned)((nq * Cin + 255) / 256), 256, 0, st>>>(
-            g, Cin, Mp, W.dA, W.ptrs + 16, op->links[F32], op->det[F32]);
+            g, Cin, Mp, W.dA, W.grad[1 - cur], op->links[F32], op->det[F32]);
         QDW_LAUNCH_CHECK();
         cur = 1 - cur;
     }
-    if (gin_out) *gin_out = W.grad[cur][0];
+    if (gin_out) *gin_out = (float*)W.grad[cur].base;
     return QDW_OK;
 }
 
@@ -1330,9 +1316,18 @@ size_t nn_precond_workspace(const qdw_op* op)
     return nn_layout(op, false, nullptr, &W, false);  // bf16 forward only: no A
 }
 
-// phi = N(rho): rho, phi FP64 eo-SoA fields; |rho| given (sets the FP32 scale)
-int nn_precondition(qdw_op* op, const void* weights, const void* rho, void* phi, double rho_norm,
-                    char* work, hipStream_t st)
+// the weights of a solve, embedded into the preconditioner's workspace once
+int nn_prepare(qdw_op* op, const void* weights, char* work, hipStream_t st)
+{
+    NnWork W;
+    nn_layout(op, false, work, &W, false);
+    return embed_weights<false>((const float*)weights, W, st);
+}
+
+// phi = N(rho): rho, phi FP64 eo-SoA fields; |rho| given (sets the FP32 scale); after
+// nn_prepare on the same workspace
+int nn_precondition(qdw_op* op, const void* rho, void* phi, double rho_norm, char* work,
+                    hipStream_t st)
 {
     NnWork W;
     nn_layout(op, false, work, &W, false);
@@ -1340,11 +1335,8 @@ int nn_precondition(qdw_op* op, const void* weights, const void* rho, void* phi,
     int rc;
     if (!(rho_norm > 0.0)) return run_map(op, Zero<F64>{phi}, st);
     const double s = std::sqrt(24.0 * g.V) / rho_norm;
-    if ((rc = run_map(op, ScaleNorm<F64, F32>{rho, W.act[0][0], s}, st,
-                      op->scalars + S_TMP + 2)))
-        return rc;
-    if ((rc = forward<false>(op, (const float*)weights, W, st, false))) return rc;
-    return run_map(op, Axpby<F32, F64>{W.act[kLayers][0], phi, 1.0 / s, 0.0}, st);
+    if ((rc = run_map(op, ScaleTo<F64, F32>{rho, W.act[0].base, s}, st))) return rc;
+    return forward<false>(op, W, st, false, phi, (float)(1.0 / s));
 }
 
 }  // namespace qdw
@@ -1371,10 +1363,10 @@ extern "C" int nn_forward(qdw_op* op, const float* weights, const void* in, void
     nn_layout(op, false, align_work(work), &W);
     const Geom& g = op->g;
     int rc;
-    if ((rc = run_map(op, Axpby<F64, F32>{in, W.act[0][0], 1.0, 0.0}, st))) return rc;
-    rc = f32_mixing ? forward<true>(op, weights, W, st) : forward<false>(op, weights, W, st, false);
-    if (rc) return rc;
-    return run_map(op, Axpby<F32, F64>{W.act[kLayers][0], out, 1.0, 0.0}, st);
+    if ((rc = run_map(op, Axpby<F64, F32>{in, W.act[0].base, 1.0, 0.0}, st))) return rc;
+    if ((rc = f32_mixing ? embed_weights<true>(weights, W, st) : embed_weights<false>(weights, W, st)))
+        return rc;
+    return f32_mixing ? forward<true>(op, W, st, true, out) : forward<false>(op, W, st, false, out);
 }
 
 extern "C" int nn_backward(qdw_op* op, const float* weights, const void* in, const void* gout,
@@ -1391,13 +1383,14 @@ extern "C" int nn_backward(qdw_op* op, const float* weights, const void* in, con
     const Geom& g = op->g;
     int rc;
     if ((rc = zero_dev(dW, sizeof(float) * 2 * total_weights(), st))) return rc;
-    if ((rc = run_map(op, Axpby<F64, F32>{in, W.act[0][0], 1.0, 0.0}, st))) return rc;
-    rc = f32_mixing ? forward<true>(op, weights, W, st) : forward<false>(op, weights, W, st);
-    if (rc) return rc;
-    if ((rc = run_map(op, Axpby<F64, F32>{gout, W.grad[0][0], 1.0, 0.0}, st))) return rc;
+    if ((rc = run_map(op, Axpby<F64, F32>{in, W.act[0].base, 1.0, 0.0}, st))) return rc;
+    if ((rc = f32_mixing ? embed_weights<true>(weights, W, st) : embed_weights<false>(weights, W, st)))
+        return rc;
+    if ((rc = f32_mixing ? forward<true>(op, W, st) : forward<false>(op, W, st))) return rc;
+    if ((rc = run_map(op, Axpby<F64, F32>{gout, W.grad[0].base, 1.0, 0.0}, st))) return rc;
     float* gi = nullptr;
-    rc = f32_mixing ? backward<true>(op, weights, dW, W, 1.f, st, &gi)
-                    : backward<false>(op, weights, dW, W, 1.f, st, &gi);
+    rc = f32_mixing ? backward<true>(op, dW, W, 1.f, st, &gi)
+                    : backward<false>(op, dW, W, 1.f, st, &gi);
     if (rc) return rc;
     return run_map(op, Axpby<F32, F64>{gi, gin, 1.0, 0.0}, st);
 }
@@ -1406,7 +1399,7 @@ namespace {
 
 // x (pair storage precision P) -> FP32 field times s; |x|^2 of the input when want_norm
 template <int P>
-int pair_to_f32(qdw_op* op, const void* x, float* y, double s, hipStream_t st)
+int pair_to_f32(qdw_op* op, const void* x, void* y, double s, hipStream_t st)
 {
     return run_map(op, Axpby<P, F32>{x, y, s, 0.0}, st);
 }
@@ -1420,7 +1413,7 @@ int pair_norm2(qdw_op* op, const void* x, int prec, double* out, hipStream_t st)
     }
 }
 
-int pair_convert(qdw_op* op, const void* x, int prec, float* y, double s, hipStream_t st)
+int pair_convert(qdw_op* op, const void* x, int prec, void* y, double s, hipStream_t st)
 {
     switch (prec) {
     case F64: return pair_to_f32<F64>(op, x, y, s, st);
@@ -1453,6 +1446,7 @@ extern "C" int nn_train_step(qdw_op* op, float* weights, float* adam, int step, 
     const Geom& g = op->g;
     int rc;
     if ((rc = zero_dev(dW, sizeof(float) * nw2, st))) return rc;
+    if ((rc = embed_weights<false>(weights, W, st))) return rc;
     double total = 0.0;
     for (int k = 0; k < nbatch; ++k) {
         // scale the pair so that the residual has unit component size (the map is linear)
@@ -1460,29 +1454,29 @@ extern "C" int nn_train_step(qdw_op* op, float* weights, float* adam, int step, 
         if ((rc = pair_norm2(op, rho[k], pair_prec, &r2, st))) return rc;
         QDW_CHECK(r2 > 0.0, QDW_EINVAL, "nn_train_step: a residual is zero");
         const double s = std::sqrt(24.0 * g.V / r2);
-        if ((rc = pair_convert(op, rho[k], pair_prec, W.act[0][0], s, st))) return rc;
+        if ((rc = pair_convert(op, rho[k], pair_prec, W.act[0].base, s, st))) return rc;
         if ((rc = pair_convert(op, err[k], pair_prec, W.efield, s, st))) return rc;
         double e2;
         if ((rc = run_sum(op, Norm2<F32>{W.efield}, st, &e2))) return rc;
-        if ((rc = forward<false>(op, weights, W, st))) return rc;
+        if ((rc = forward<false>(op, W, st))) return rc;
         double d2;
-        if ((rc = run_sum(op, LossDiff{W.act[kLayers][0], W.efield, W.grad[0][0]}, st, &d2))) return rc;
+        if ((rc = run_sum(op, LossDiff{W.act[kLayers].base, W.efield, W.grad[0].base}, st, &d2))) return rc;
         double denom = e2;
         if (loss_kind == 1) {
             // D-norm: d = N(rho) - e  ->  t = D d, |t|^2, gradient direction D^+ t; the
             // normalisation |D e|^2 is |rho|^2 of the stored pair
-            float* t = W.grad[1][0];
-            float* De = W.grad[1][1];
-            if ((rc = dw_launch(op, W.grad[0][0], t, F32, false, st))) return rc;
+            void* t = W.grad[1].at(0);
+            void* De = W.grad[1].at(1);
+            if ((rc = dw_launch(op, W.grad[0].base, t, F32, false, st))) return rc;
             if ((rc = run_sum(op, Norm2<F32>{t}, st, &d2))) return rc;
             if ((rc = dw_launch(op, W.efield, De, F32, false, st))) return rc;
             if ((rc = run_sum(op, Norm2<F32>{De}, st, &denom))) return rc;
-            if ((rc = dw_launch(op, t, W.grad[0][0], F32, true, st))) return rc;
+            if ((rc = dw_launch(op, t, W.grad[0].base, F32, true, st))) return rc;
         }
         total += d2 / denom;
         // dL/d(out re, im) = 2 (out - e) / |e|^2, or 2 D^+ D (out - e) / |D e|^2, batch mean
         const float gs = (float)(2.0 / (denom * nbatch));
-        if ((rc = backward<false>(op, weights, dW, W, gs, st, nullptr))) return rc;
+        if ((rc = backward<false>(op, dW, W, gs, st, nullptr))) return rc;
     }
     *loss = total / nbatch;
     const float b1 = 0.9f, b2 = 0.999f;
