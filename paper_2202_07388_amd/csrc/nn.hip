@@ -8,18 +8,15 @@
 // (s the fermion boundary sign) and W_p[a][b] a complex 4x4 matrix acting on spin only,
 // so the network commutes with gauge transformations.
 //
-// GPU mapping of a layer: (1) a transport kernel writes, for every site x and colour c,
-// one row of the matrix A[(x, c)][(p, b, t, re/im)] (t a spin index), stored in panels of
-// eight columns (one (p, b) group per panel, so each lane writes contiguous runs and
-// consecutive lanes write consecutive runs); (2) the channel
-// mixing is the real GEMM out[(x, c)][(a, s, re/im)] = A B with B the real embedding of the
-// complex weights, run on the matrix cores: bf16 operands and FP32 accumulation
-// (v_mfma_f32_16x16x16_bf16), or FP32 operands (v_mfma_f32_16x16x4_f32) for gradient
-// checks. Backward: dA = G B^T (matrix cores), then the adjoint transport gathers dA back
-// to the input channels; dB = A^T G (matrix cores, split over rows, fixed-order reduction)
-// gives the weight gradient. Adam updates FP32 master weights.
+// GPU mapping of a layer: transports feed the channel mixing, the real product
+// out[(x, c)][(a, s, re/im)] = A B with rows (site x, colour c), columns
+// A[(x, c)][(p, b, t, re/im)] = (T_p in_b)(x) and B the real embedding of the complex
+// weights, on the matrix cores: bf16 operands and FP32 accumulation. Backward: dA = G B^T and
+// the adjoint transports give the input gradient, dB = A^T G the weight gradient (fixed-order
+// sums). All of it runs in fused kernels that keep A and dA out of memory; the FP32-operand
+// passes for gradient checks form them there. Adam updates FP32 master weights.
 #include <cmath>
-#include <vector>
+#include <type_traits>
 
 #include "blas.h"
 #include "dirac_core.h"
@@ -78,21 +75,11 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi)
 }
 
 // 8 consecutive values of one panel row
-template <bool F32M>
-__device__ __forceinline__ void put8(void* A, long at, const float v[8])
+__device__ __forceinline__ void put8(float* A, long at, const float v[8])
 {
-    if constexpr (F32M) {
-        float4* d = (float4*)((float*)A + at);
-        d[0] = make_float4(v[0], v[1], v[2], v[3]);
-        d[1] = make_float4(v[4], v[5], v[6], v[7]);
-    } else {
-        uint4 r;
-        r.x = pack_bf16x2(v[0], v[1]);
-        r.y = pack_bf16x2(v[2], v[3]);
-        r.z = pack_bf16x2(v[4], v[5]);
-        r.w = pack_bf16x2(v[6], v[7]);
-        *(uint4*)((uint16_t*)A + at) = r;
-    }
+    float4* d = (float4*)(A + at);
+    d[0] = make_float4(v[0], v[1], v[2], v[3]);
+    d[1] = make_float4(v[4], v[5], v[6], v[7]);
 }
 
 __device__ __forceinline__ uint16_t bf16_bits(float f) { return float_to_bf16(f); }
@@ -111,14 +98,16 @@ __device__ __forceinline__ long f32_addr(int Vh, int par, int i, int s, int c)
     return chunk_at(Vh, 6, par, k12 >> 1, i) * 4 + (k12 & 1) * 2;
 }
 
-// ------------------------------------------------------------------ transport
+// ------------------------------------------------------------------ FP32-operand passes
+//
+// Gradient checks run with FP32 operands, through matrices in memory: A (transported rows),
+// G (output gradients) and dA = G B^T. The bf16 passes never form them (fused layers below).
 //
 // A[(q, c)][((p*Cin + b)*4 + t)*2 + re/im] = (T_p in_b)(q)[t][c], q = par*Vp + i. Rows of
 // padded sites and the padding columns K..Kpad-1 are written as zeros, so the matrix holds
 // no stale values from earlier use of the workspace.
-template <bool F32M, int PIN>
 __global__ __launch_bounds__(256) void nn_transport_kernel(Geom g, int Cin, int Kpad, long Mp,
-                                                           Chan in, void* A,
+                                                           Chan in, float* A,
                                                            const void* links, const void* dets)
 {
     const long tid = (long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -131,10 +120,10 @@ __global__ __launch_bounds__(256) void nn_transport_kernel(Geom g, int Cin, int 
     const float zero[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     if (b == Cin - 1)
         for (int kg = kPaths * Cin; kg < Kpad / 8; ++kg)
-            for (int c = 0; c < 3; ++c) put8<F32M>(A, pidx(Mp, q * 3 + c, kg * 8), zero);
+            for (int c = 0; c < 3; ++c) put8(A, pidx(Mp, q * 3 + c, kg * 8), zero);
     if (i >= g.Vh) {
         for (int p = 0; p < kPaths; ++p)
-            for (int c = 0; c < 3; ++c) put8<F32M>(A, pidx(Mp, q * 3 + c, (p * Cin + b) * 8), zero);
+            for (int c = 0; c < 3; ++c) put8(A, pidx(Mp, q * 3 + c, (p * Cin + b) * 8), zero);
         return;
     }
     int x[4], lex;
@@ -143,13 +132,13 @@ __global__ __launch_bounds__(256) void nn_transport_kernel(Geom g, int Cin, int 
     for (int p = 0; p < kPaths; ++p) {
         cx<float> s[12], w[12];
         if (p == 0) {
-            load_spinor<PIN>(v, g.Vh, par, i, s);
+            load_spinor<F32>(v, g.Vh, par, i, s);
             for (int k = 0; k < 12; ++k) w[k] = s[k];
         } else {
             const int mu = (p - 1) >> 1;
             const bool fwd = ((p - 1) & 1) == 0;
             const int j = (fwd ? lex_fwd(g, x, lex, mu) : lex_bwd(g, x, lex, mu)) >> 1;
-            load_spinor<PIN>(v, g.Vh, 1 - par, j, s);
+            load_spinor<F32>(v, g.Vh, 1 - par, j, s);
             cx<float> u[6], d;
             float sg = 1.f;
             if (fwd) {
@@ -176,7 +165,7 @@ __global__ __launch_bounds__(256) void nn_transport_kernel(Geom g, int Cin, int 
                 v[2 * t] = w[t * 3 + c].re;
                 v[2 * t + 1] = w[t * 3 + c].im;
             }
-            put8<F32M>(A, pidx(Mp, q * 3 + c, k0), v);
+            put8(A, pidx(Mp, q * 3 + c, k0), v);
         }
     }
 }
@@ -296,63 +285,32 @@ __global__ void nn_embed_kernel(const float* W, Embedded E)
     }
 }
 
-// dW (complex, dL/dRe W + i dL/dIm W) += the real-embedding gradient dB[k][n]
-__global__ void nn_dw_kernel(const float* dB, int Cin, int Cout, int Npad, float* dW)
-{
-    const int tid = blockIdx.x * blockDim.x + threadIdx.x;
-    const int nw = kPaths * Cout * Cin * 16;
-    if (tid >= nw) return;
-    const int t = tid & 3, s = (tid >> 2) & 3, rest = tid >> 4;
-    const int b = rest % Cin, a = (rest / Cin) % Cout, p = rest / (Cin * Cout);
-    const int kr = (((p * Cin + b) * 4 + t) * 2), nr = ((a * 4 + s) * 2);
-    const float d_rr = dB[(long)kr * Npad + nr], d_ii = dB[(long)(kr + 1) * Npad + nr + 1];
-    const float d_ir = dB[(long)(kr + 1) * Npad + nr], d_ri = dB[(long)kr * Npad + nr + 1];
-    dW[2 * tid] += d_rr + d_ii;
-    dW[2 * tid + 1] += d_ri - d_ir;
-}
-
 // ------------------------------------------------------------------ GEMMs on matrix cores
 
-// acc[j] += A[m0 : m0+16][k0 : k0+KS] * B[k0 : k0+KS][16 j : 16 j + 16] for one wave;
-// A row-major (element (m, k) at arow + k for this lane's row) or, with Mp > 0, in panels
-template <bool F32M>
-__device__ __forceinline__ void mfma_step(const void* A, long arow, const void* Bt, long brow0,
+// acc[j] += A[m0 : m0+16][k0 : k0+4] * B[k0 : k0+4][16 j : 16 j + 16] for one wave; A
+// row-major (element (m, k) at arow + k for this lane's row) or, with Mp > 0, in panels
+__device__ __forceinline__ void mfma_step(const float* A, long arow, const float* Bt, long brow0,
                                           long bstride, int kofs, int nt, f4 acc[4], long Mp = 0,
                                           long row = 0)
 {
-    const long ai = Mp > 0 ? pidx(Mp, row, kofs) : arow + kofs;
-    if constexpr (!F32M) {
-        const s4 a = *(const s4*)((const uint16_t*)A + ai);
-        for (int j = 0; j < nt; ++j) {
-            const s4 b = *(const s4*)((const uint16_t*)Bt + brow0 + j * 16 * bstride + kofs);
-            acc[j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc[j], 0, 0, 0);
-        }
-    } else {
-        const float a = ((const float*)A)[ai];
-        for (int j = 0; j < nt; ++j) {
-            const float b = ((const float*)Bt)[brow0 + j * 16 * bstride + kofs];
-            acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, acc[j], 0, 0, 0);
-        }
-    }
+    const float a = A[Mp > 0 ? pidx(Mp, row, kofs) : arow + kofs];
+    for (int j = 0; j < nt; ++j)
+        acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, Bt[brow0 + j * 16 * bstride + kofs], acc[j], 0, 0, 0);
 }
 
 // out channels (FP32 fields) = A Bt^T; a workgroup computes 64 rows, a wave 16 rows x Npad
-template <bool F32M>
-__global__ __launch_bounds__(256) void nn_gemm_out_kernel(Geom g, int Kpad, int Npad, int Cout,
-                                                          long Mp, const void* A, const void* Bt,
-                                                          Chan out)
+__global__ __launch_bounds__(256) void nn_gemm_out_kernel(Geom g, int Kpad, int Npad, int Cout, long Mp,
+                                                          const float* A, const float* Bt, Chan out)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const long m0 = (long)blockIdx.x * 64 + wave * 16;
     const int nt = Npad / 16;
     f4 acc[4];
     for (int j = 0; j < 4; ++j) acc[j] = f4{0.f, 0.f, 0.f, 0.f};
-    const int KS = F32M ? 4 : 16;
     const long row = m0 + (lane & 15);
     const long brow0 = (long)(lane & 15) * Kpad;
-    const int kl = F32M ? (lane >> 4) : 4 * (lane >> 4);
-    for (int k0 = 0; k0 < Kpad; k0 += KS)
-        mfma_step<F32M>(A, 0, Bt, brow0, Kpad, k0 + kl, nt, acc, Mp, row);
+    for (int k0 = 0; k0 < Kpad; k0 += 4)
+        mfma_step(A, 0, Bt, brow0, Kpad, k0 + (lane >> 4), nt, acc, Mp, row);
     const int Vp = padded(g.Vh);
     for (int j = 0; j < nt; ++j)
         for (int r = 0; r < 4; ++r) {
@@ -369,22 +327,19 @@ __global__ __launch_bounds__(256) void nn_gemm_out_kernel(Geom g, int Kpad, int 
 }
 
 // dA[m][k] = sum_n G[m][n] Bk[k][n]  (G = gradient of the layer output, FP32 rows)
-template <bool F32M>
-__global__ __launch_bounds__(256) void nn_gemm_da_kernel(int Kpad, int Npad, long Mp, const void* G,
-                                                         const void* Bk, float* dA)
+__global__ __launch_bounds__(256) void nn_gemm_da_kernel(int Kpad, int Npad, long Mp, const float* G,
+                                                         const float* Bk, float* dA)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const long m0 = (long)blockIdx.x * 64 + wave * 16;
-    const int KS = F32M ? 4 : 16;
     const long arow = (m0 + (lane & 15)) * Npad;
-    const int kl = F32M ? (lane >> 4) : 4 * (lane >> 4);
     for (int kt = 0; kt < Kpad / 16; kt += 4) {
         const int nt = std::min(4, Kpad / 16 - kt);
         f4 acc[4];
         for (int j = 0; j < 4; ++j) acc[j] = f4{0.f, 0.f, 0.f, 0.f};
         const long brow0 = (long)(kt * 16 + (lane & 15)) * Npad;
-        for (int n0 = 0; n0 < Npad; n0 += KS)
-            mfma_step<F32M>(G, arow, Bk, brow0, Npad, n0 + kl, nt, acc);
+        for (int n0 = 0; n0 < Npad; n0 += 4)
+            mfma_step(G, arow, Bk, brow0, Npad, n0 + (lane >> 4), nt, acc);
         for (int j = 0; j < nt; ++j)
             for (int r = 0; r < 4; ++r)
                 dA[pidx(Mp, m0 + 4 * (lane >> 4) + r, (kt + j) * 16 + (lane & 15))] = acc[j][r];
@@ -392,10 +347,8 @@ __global__ __launch_bounds__(256) void nn_gemm_da_kernel(int Kpad, int Npad, lon
 }
 
 // partial dB[k][n] over a slice of rows: D[k][n] += sum_m A[m][k] G[m][n]
-template <bool F32M>
-__global__ __launch_bounds__(256) void nn_gemm_db_kernel(long M, int Kpad, int Npad, int rows_per,
-                                                         long Mp, const void* A, const void* G,
-                                                         float* part)
+__global__ __launch_bounds__(256) void nn_gemm_db_kernel(long M, int Kpad, int Npad, int rows_per, long Mp,
+                                                         const float* A, const float* G, float* part)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int kt = blockIdx.x;     // 16 columns k of A
@@ -407,26 +360,9 @@ __global__ __launch_bounds__(256) void nn_gemm_db_kernel(long M, int Kpad, int N
     f4 acc = f4{0.f, 0.f, 0.f, 0.f};
     const int kcol = kt * 16 + (lane & 15);
     const int ncol = wave * 16 + (lane & 15);
-    if constexpr (!F32M) {
-        const uint16_t* Au = (const uint16_t*)A;
-        const uint16_t* Gu = (const uint16_t*)G;
-        for (long m = mbeg; m < mend; m += 16) {
-            s4 a, b;
-            for (int j = 0; j < 4; ++j) {
-                const long mm = m + 4 * (lane >> 4) + j;
-                a[j] = (short)Au[pidx(Mp, mm, kcol)];
-                b[j] = (short)Gu[mm * Npad + ncol];
-            }
-            acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc, 0, 0, 0);
-        }
-    } else {
-        const float* Af = (const float*)A;
-        const float* Gf = (const float*)G;
-        for (long m = mbeg; m < mend; m += 4) {
-            const long mm = m + (lane >> 4);
-            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(Af[pidx(Mp, mm, kcol)], Gf[mm * Npad + ncol],
-                                                        acc, 0, 0, 0);
-        }
+    for (long m = mbeg; m < mend; m += 4) {
+        const long mm = m + (lane >> 4);
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(A[pidx(Mp, mm, kcol)], G[mm * Npad + ncol], acc, 0, 0, 0);
     }
     for (int r = 0; r < 4; ++r) {
         const int k = kt * 16 + 4 * (lane >> 4) + r;
@@ -434,19 +370,9 @@ __global__ __launch_bounds__(256) void nn_gemm_db_kernel(long M, int Kpad, int N
     }
 }
 
-__global__ void nn_reduce_db_kernel(const float* part, int nsplit, int KN, float* dB)
-{
-    const int tid = blockIdx.x * blockDim.x + threadIdx.x;
-    if (tid >= KN) return;
-    float s = 0.f;
-    for (int p = 0; p < nsplit; ++p) s += part[(long)p * KN + tid];
-    dB[tid] = s;
-}
-
 // G rows from a channel gradient (FP32 fields), times `scale`
-template <bool F32M>
-__global__ __launch_bounds__(256) void nn_pack_g_kernel(Geom g, int Cout, int Npad,
-                                                        Chan gf, float scale, void* G)
+__global__ __launch_bounds__(256) void nn_pack_g_kernel(Geom g, int Cout, int Npad, Chan gf, float scale,
+                                                        float* G)
 {
     const long tid = (long)blockIdx.x * blockDim.x + threadIdx.x;
     const int Vp = padded(g.Vh);
@@ -458,7 +384,7 @@ __global__ __launch_bounds__(256) void nn_pack_g_kernel(Geom g, int Cout, int Np
             const int a = n >> 3, s = (n >> 1) & 3, ri = n & 1;
             float v = 0.f;
             if (a < Cout && i < g.Vh) v = scale * ((const float*)gf.at(a))[f32_addr(g.Vh, par, i, s, c) + ri];
-            put_el<F32M>(G, (tid * 3 + c) * Npad + n, v);
+            G[(tid * 3 + c) * Npad + n] = v;
         }
 }
 
@@ -1099,6 +1025,391 @@ __global__ __launch_bounds__(256) void nn_transport_sum_kernel(Geom g, Chan mix,
     store_spinor<POUT>(out, g.Vh, par, i, o);
 }
 
+// ------------------------------------------------------------------ fused backward layer
+//
+// The bf16 backward pass of a layer out_a = sum_p sum_b W_p[a][b] T_p in_b, without the
+// matrices of transported rows and of their gradients in memory (A and dA, 1152 and 2304
+// times 3 bytes per site for eight channels, each written and read once). G, the gradient of
+// the layer's outputs, is a set of bf16 fields: the operand precision of the products.
+//
+// Input gradient: dA_p[b](y) = sum_a W_p[a][b]^+ G_a(y) is used at one site only, the one
+// that T_p takes to y, so the workgroup that forms dx(x) = sum_p T_p^+ dA_p at 64 sites
+// gathers G at the eight neighbours and the sites themselves, multiplies on the matrix
+// cores and transports the FP32 products from the registers that hold them. The products
+// are formed transposed (weights first), the 16 sites of a wave in the columns and the
+// colours in the three row tiles, so a lane ends up with two spins and all colours of one
+// channel: what one link multiplies. It supplies the same two spins of channels
+// 2 step + lane / 32 of G, 24 contiguous bytes of a stored spinor.
+
+// the half spinor (two spins) of G that a lane supplies in one product step, as stored
+struct HalfRaw {
+    u32x4 a;
+    uint2 b;
+};
+
+template <int CIN, int COUT, int POUT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(COUT == 8 && CIN == 8 ? 1 : 2)))
+void nn_dx_kernel(Geom g, Chan G, const uint16_t* Bk, Chan out, const void* links, const void* dets)
+{
+    constexpr int NP = COUT * 8 < 16 ? 16 : COUT * 8;  // columns n of G (zero from COUT * 8)
+    constexpr int KS = NP / 16;                        // product steps
+    constexpr int NJ = CIN == 8 ? 4 : 1;               // 16-column tiles of a path's inputs
+    constexpr int JH = CIN == 8 ? 2 : 1;               // tiles multiplied at a time (registers)
+    constexpr int LS = NP + 8;                         // LDS row of weights (halves)
+    constexpr int WQ = NJ * 16 * NP * 2 / 16;          // 16-byte pieces of a path's weights
+    __shared__ __attribute__((aligned(16))) uint16_t wb[2][NJ * 16 * LS];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, tid = threadIdx.x;
+    const int qd = lane >> 4, hf = qd & 1;
+    const int Vp = padded(g.Vh);
+    const long q0 = nn_block_q0(Vp), qs = q0 + wave * 16 + (lane & 15);
+    const int par = (int)(qs / Vp), i = (int)(qs - (long)par * Vp);
+    const bool real = i < g.Vh;
+    int x[4] = {0, 0, 0, 0}, lex = 0;
+    if (real) eo_coords(g, par, i, x, lex);
+
+    // The weights of path p: rows k of Bk from p * CIN * 8, in pieces of 16 bytes, loaded one
+    // path ahead and stored after the path before is done (as the forward layer does)
+    constexpr int WL = (WQ + 255) / 256;
+    auto load_w = [&](int p, u32x4 r[WL]) {
+        const g_cu4* src = (const g_cu4*)(Bk + (long)p * CIN * 8 * NP);
+#pragma unroll
+        for (int k = 0; k < WL; ++k)
+            if (WQ % 256 == 0 || tid + 256 * k < WQ) r[k] = src[tid + 256 * k];
+    };
+    auto store_w = [&](int buf, const u32x4 r[WL]) {
+#pragma unroll
+        for (int k = 0; k < WL; ++k) {
+            const int at = tid + 256 * k, row = at / (NP / 8), col = at % (NP / 8);
+            if (WQ % 256 == 0 || at < WQ) *(u32x4*)&wb[buf][row * LS + col * 8] = r[k];
+        }
+    };
+    // Paths 1 + 2 mu come from the site below (BELOW), paths 2 + 2 mu from the one above; the
+    // loop over mu keeps its indices opaque, as the D kernels do, so that the addresses of all
+    // nine paths are not formed at once and held. Padded lanes load the neighbours of site 0,
+    // in bounds and not used.
+    auto neighbour = [&](bool below, int mu, const int xx[4], int ll) {
+        const int xm = mu == 0 ? xx[0] : mu == 1 ? xx[1] : mu == 2 ? xx[2] : xx[3];
+        const int wrap = (g.L[mu] - 1) * g.stride[mu];
+        return (below ? (xm == 0 ? ll + wrap : ll - g.stride[mu])
+                      : (xm == g.L[mu] - 1 ? ll - wrap : ll + g.stride[mu])) >> 1;
+    };
+    auto load_g = [&](int pp, int j, HalfRaw r[KS]) {
+        const long b0 = chunk_at(g.Vh, 3, pp, 0, j);
+#pragma unroll
+        for (int k = 0; k < KS; ++k) {
+            if (COUT == 1 && qd >= 2) {
+                r[k].a = u32x4{0u, 0u, 0u, 0u};
+                r[k].b = uint2{0u, 0u};
+                continue;
+            }
+            const char* f = (const char*)G.at(2 * k + (qd >> 1));
+            r[k].a = ((const g_cu4*)f)[b0 + (hf ? 2 * kSB : 0)];
+            const __attribute__((address_space(1))) uint32_t* h =
+                (const __attribute__((address_space(1))) uint32_t*)f + (b0 + kSB) * 4 + 2 * hf;
+            r[k].b = uint2{h[0], h[1]};
+        }
+    };
+    struct Lk {
+        cx<float> u[6], d;
+        float sg;
+    };
+    // G and the link of the path from below / above in direction mu
+    auto fetch = [&](bool below, int mu, HalfRaw r[KS], Lk& L) {
+        int ii = i, ll = lex, xx[4] = {x[0], x[1], x[2], x[3]};
+        asm volatile("" : "+v"(ii), "+v"(ll), "+v"(xx[0]), "+v"(xx[1]), "+v"(xx[2]), "+v"(xx[3]));
+        const int j = neighbour(below, mu, xx, ll);
+        load_link<F32>(links, dets, g.Vh, below ? 1 - par : par, below ? j : ii, mu, L.u, L.d);
+        L.sg = mu == 0 && xx[0] == (below ? 0 : g.L[0] - 1) ? (float)g.bc_t : 1.f;
+        load_g(1 - par, j, r);
+    };
+    cx<float> dx[NJ][6];
+    // tiles j0 .. j0 + JH of the products of one path, dA in acc, from weight buffer `buf`
+    auto products = [&](int buf, const HalfRaw gc[KS], int j0, f4 acc[3][JH]) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+#pragma unroll
+            for (int j = 0; j < JH; ++j) acc[c][j] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < KS; ++k) {
+            // words (spin, colour) of the half spinor: the lower half starts with the 16-byte
+            // piece, the upper half with the 8-byte one
+            const uint32_t A[4] = {gc[k].a.x, gc[k].a.y, gc[k].a.z, gc[k].a.w};
+            const uint32_t v[6] = {hf ? gc[k].b.x : A[0], hf ? gc[k].b.y : A[1], hf ? A[0] : A[2],
+                                   hf ? A[1] : A[3], hf ? A[2] : gc[k].b.x, hf ? A[3] : gc[k].b.y};
+            s4 w[JH];
+#pragma unroll
+            for (int j = 0; j < JH; ++j)
+                w[j] = *(const s4*)&wb[buf][((j0 + j) * 16 + (lane & 15)) * LS + k * 16 + 4 * qd];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const uint32_t t[2] = {v[c], v[3 + c]};
+                s4 b;
+                __builtin_memcpy(&b, t, 8);
+#pragma unroll
+                for (int j = 0; j < JH; ++j)
+                    acc[c][j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(w[j], b, acc[c][j], 0, 0, 0);
+            }
+        }
+    };
+    auto half = [&](const f4 acc[3][JH], int j, cx<float> h[6]) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            h[c] = {acc[c][j][0], acc[c][j][1]};
+            h[3 + c] = {acc[c][j][2], acc[c][j][3]};
+        }
+    };
+    // dx += T_p^+ dA_p
+    auto path = [&](auto below_c, int buf, const HalfRaw gc[KS], const Lk& L) {
+        constexpr bool BELOW = decltype(below_c)::value;
+#pragma unroll
+        for (int j0 = 0; j0 < NJ; j0 += JH) {
+            f4 acc[3][JH];
+            products(buf, gc, j0, acc);
+#pragma unroll
+            for (int j = 0; j < JH; ++j) {
+                cx<float> h[6], o[6];
+                half(acc, j, h);
+#pragma unroll
+                for (int k = 0; k < 6; ++k) h[k] = scale(h[k], L.sg);
+                su3_mul<float, BELOW>(L.u, L.d, h, o);
+#pragma unroll
+                for (int k = 0; k < 6; ++k) dx[j0 + j][k] = dx[j0 + j][k] + o[k];
+            }
+            __builtin_amdgcn_sched_barrier(0);  // one half's registers at a time
+        }
+    };
+    HalfRaw ga[KS], gb[KS];
+    Lk la, lb;
+    u32x4 w[WL];
+    load_w(0, w);
+    load_g(par, i, gb);
+    store_w(0, w);
+    __syncthreads();
+    {
+        load_w(1, w);
+        fetch(true, 0, ga, la);
+#pragma unroll
+        for (int j0 = 0; j0 < NJ; j0 += JH) {
+            f4 acc[3][JH];
+            products(0, gb, j0, acc);
+#pragma unroll
+            for (int j = 0; j < JH; ++j) half(acc, j, dx[j0 + j]);
+        }
+        store_w(1, w);
+        __syncthreads();
+    }
+#pragma unroll 1
+    for (int mu = 0; mu < 4; ++mu) {
+        load_w(2 + 2 * mu, w);
+        fetch(false, mu, gb, lb);
+        path(std::true_type{}, 1, ga, la);
+        store_w(0, w);
+        __syncthreads();
+        if (mu < 3) {
+            load_w(3 + 2 * mu, w);
+            fetch(true, mu + 1, ga, la);
+        }
+        path(std::false_type{}, 0, gb, lb);
+        if (mu < 3) {
+            store_w(1, w);
+            __syncthreads();
+        }
+    }
+    if (!real) return;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+        if (CIN == 1 && qd >= 2) continue;  // columns of the next path
+        void* f = out.at(CIN == 1 ? 0 : 2 * j + (qd >> 1));
+        if constexpr (POUT == F32) {
+            const long b0 = chunk_at(g.Vh, 6, par, 0, i);
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+                ((float4*)f)[b0 + (long)(3 * hf + k) * kSB] =
+                    make_float4(dx[j][2 * k].re, dx[j][2 * k].im, dx[j][2 * k + 1].re, dx[j][2 * k + 1].im);
+        } else {
+            const long b0 = chunk_at(g.Vh, 3, par, 0, i);
+            uint32_t v[6];
+#pragma unroll
+            for (int k = 0; k < 6; ++k) v[k] = pack_bf16x2(dx[j][k].re, dx[j][k].im);
+            uint32_t* mid = (uint32_t*)f + (b0 + kSB) * 4;
+            if (hf) {
+                *(uint2*)(mid + 2) = uint2{v[0], v[1]};
+                ((uint4*)f)[b0 + 2 * kSB] = uint4{v[2], v[3], v[4], v[5]};
+            } else {
+                ((uint4*)f)[b0] = uint4{v[0], v[1], v[2], v[3]};
+                *(uint2*)mid = uint2{v[4], v[5]};
+            }
+        }
+    }
+}
+
+// Weight gradient: partial dB[k][n] = sum_m A[m][k] G[m][n] over the rows m = (site, colour)
+// of a share of the 64-site blocks. A workgroup owns one path of the eight channels (or the
+// whole one-channel layer), transports a block's inputs as the forward pass of these
+// gradients does (FP32, rounded to bf16 once), leaves A and G transposed in LDS, row index
+// fastest and colour-major, and multiplies on the matrix cores with FP32 accumulators in
+// registers for its whole share. A never goes to memory; G is read once per path, mostly
+// from L2 (the nine paths of a share run side by side).
+template <int CIN, int COUT, int PIN>
+__global__ __launch_bounds__(256)
+void nn_dw_partial_kernel(Geom g, Chan in, Chan G, const void* links, const void* dets, int nsplit,
+                          float* part)
+{
+    constexpr int KB = CIN == 8 ? 64 : 80;             // columns k of this workgroup
+    constexpr int KPAD = (kPaths * CIN * 8 + 15) & ~15;
+    constexpr int NP = COUT * 8 < 16 ? 16 : COUT * 8;
+    constexpr int LS = 192 + 8;                        // LDS row (halves): 4 banks apart
+    constexpr int NI = CIN == 8 ? 2 : 3;               // transports of a lane per block
+    constexpr int NG = COUT == 8 ? 2 : 1;              // output channels a lane loads
+    constexpr int KT = KB / 16;
+    constexpr int MT = COUT == 8 ? KT : 1;             // accumulator tiles of a wave
+    static_assert(COUT == 8 || CIN == 8, "the one-output layer has eight inputs");
+    __shared__ __attribute__((aligned(16))) uint16_t At[KB * LS], Gt[NP * LS];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int wg = xcd_tile(blockIdx.x, gridDim.x);  // the paths of a share on one XCD
+    const int path0 = CIN == 8 ? wg % kPaths : 0;
+    const int split = CIN == 8 ? wg / kPaths : wg;
+    const int Vp = padded(g.Vh), nblk = 2 * Vp / 64;
+    // rows of LDS that no block writes: the padding columns
+    for (int k = threadIdx.x; k < (KB - (CIN == 8 ? 64 : 72)) * LS; k += 256) At[72 * LS + k] = 0;
+    for (int k = threadIdx.x; k < (NP - COUT * 8) * LS; k += 256) Gt[COUT * 8 * LS + k] = 0;
+    f4 acc[MT];
+#pragma unroll
+    for (int t = 0; t < MT; ++t) acc[t] = f4{0.f, 0.f, 0.f, 0.f};
+
+    // one word (re, im) of row (site = lane, colour c), columns k and k + 1
+    auto put = [&](uint16_t* T, int k, int c, uint32_t v) {
+        T[k * LS + c * 64 + lane] = (uint16_t)(v & 0xFFFFu);
+        T[(k + 1) * LS + c * 64 + lane] = (uint16_t)(v >> 16);
+    };
+    for (int blk = split; blk < nblk; blk += nsplit) {
+        // the two parities of one index range follow each other
+        const int par = blk & 1, i = (blk >> 1) * 64 + lane;
+        const bool real = i < g.Vh;
+        int x[4] = {0, 0, 0, 0}, lex = 0;
+        if (real) eo_coords(g, par, i, x, lex);
+        u32x4 gr[NG][3];
+#pragma unroll
+        for (int n = 0; n < NG; ++n) {
+            const long b0 = chunk_at(g.Vh, 3, par, 0, i);
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+                gr[n][k] = COUT == 8 || wave == 0 ? ((const g_cu4*)G.at(COUT == 8 ? wave + 4 * n : 0))[b0 + (long)k * kSB]
+                                                  : u32x4{0u, 0u, 0u, 0u};
+        }
+        auto transport = [&](int p, int b, int k0) {
+            cx<float> s[12], w[12];
+            if (!real) {
+#pragma unroll
+                for (int k = 0; k < 12; ++k) w[k] = {0.f, 0.f};
+            } else if (p == 0) {
+                load_spinor<PIN>(in.at(b), g.Vh, par, i, w);
+            } else {
+                const int mu = (p - 1) >> 1;
+                const bool fwd = ((p - 1) & 1) == 0;
+                const int j = (fwd ? lex_fwd(g, x, lex, mu) : lex_bwd(g, x, lex, mu)) >> 1;
+                load_spinor<PIN>(in.at(b), g.Vh, 1 - par, j, s);
+                cx<float> u[6], d, h[6], o[6];
+                float sg = 1.f;
+                if (fwd) {
+                    load_link<F32>(links, dets, g.Vh, par, i, mu, u, d);
+                    if (mu == 0 && x[0] == g.L[0] - 1) sg = (float)g.bc_t;
+                } else {
+                    load_link<F32>(links, dets, g.Vh, 1 - par, j, mu, u, d);
+                    if (mu == 0 && x[0] == 0) sg = (float)g.bc_t;
+                }
+#pragma unroll
+                for (int half = 0; half < 2; ++half) {
+#pragma unroll
+                    for (int k = 0; k < 6; ++k) h[k] = scale(s[6 * half + k], sg);
+                    if (fwd) su3_mul<float, false>(u, d, h, o);
+                    else su3_mul<float, true>(u, d, h, o);
+#pragma unroll
+                    for (int k = 0; k < 6; ++k) w[6 * half + k] = o[k];
+                }
+            }
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int c = 0; c < 3; ++c)
+                    put(At, k0 + 2 * t, c, pack_bf16x2(w[3 * t + c].re, w[3 * t + c].im));
+        };
+        __syncthreads();  // the products of the block before have read LDS
+#pragma unroll
+        for (int n = 0; n < NI; ++n) {
+            const int b = wave + 4 * n;
+            if (CIN == 8) transport(path0, b, b * 8);
+            else if (b < kPaths) transport(b, 0, b * 8);
+        }
+#pragma unroll
+        for (int n = 0; n < NG; ++n) {
+            if (COUT == 1 && wave != 0) continue;
+            const int a = COUT == 8 ? wave + 4 * n : 0;
+            const uint32_t v[12] = {gr[n][0].x, gr[n][0].y, gr[n][0].z, gr[n][0].w, gr[n][1].x, gr[n][1].y,
+                                    gr[n][1].z, gr[n][1].w, gr[n][2].x, gr[n][2].y, gr[n][2].z, gr[n][2].w};
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+#pragma unroll
+                for (int c = 0; c < 3; ++c) put(Gt, (a * 4 + s) * 2, c, real ? v[3 * s + c] : 0u);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int m = 0; m < 192; m += 32) {
+            const int mo = m + 8 * (lane >> 4);
+            if constexpr (COUT == 8) {
+                const bf16x8 gb = *(const bf16x8*)&Gt[(wave * 16 + (lane & 15)) * LS + mo];
+#pragma unroll
+                for (int t = 0; t < KT; ++t) {
+                    const bf16x8 a = *(const bf16x8*)&At[(t * 16 + (lane & 15)) * LS + mo];
+                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, gb, acc[t], 0, 0, 0);
+                }
+            } else {
+                const bf16x8 gb = *(const bf16x8*)&Gt[(lane & 15) * LS + mo];
+                const bf16x8 a = *(const bf16x8*)&At[(wave * 16 + (lane & 15)) * LS + mo];
+                acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, gb, acc[0], 0, 0, 0);
+            }
+        }
+    }
+#pragma unroll
+    for (int t = 0; t < MT; ++t)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int k = path0 * 64 + (COUT == 8 ? t : wave) * 16 + 4 * (lane >> 4) + e;
+            const int n = (COUT == 8 ? wave * 16 : 0) + (lane & 15);
+            part[((long)split * KPAD + k) * NP + n] = acc[t][e];
+        }
+}
+
+// dW (complex, dL/dRe W + i dL/dIm W) += the partial real-embedding gradients summed over the
+// shares: 64 weights a workgroup, a quarter of the shares per wavefront
+__global__ __launch_bounds__(256) void nn_dw_reduce_kernel(const float* part, int nsplit, int Cin, int Cout,
+                                                           int Kpad, int Npad, float* dW)
+{
+    __shared__ float red[4][2][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int w = blockIdx.x * 64 + lane, nw = kPaths * Cout * Cin * 16;
+    float re = 0.f, im = 0.f;
+    if (w < nw) {
+        const int t = w & 3, s = (w >> 2) & 3, rest = w >> 4;
+        const int b = rest % Cin, a = (rest / Cin) % Cout, p = rest / (Cin * Cout);
+        const long at = (long)(((p * Cin + b) * 4 + t) * 2) * Npad + (a * 4 + s) * 2;
+#pragma unroll 4
+        for (int q = wave; q < nsplit; q += 4) {
+            const float* P = part + (long)q * Kpad * Npad + at;
+            const float2 lo = *(const float2*)P, hi = *(const float2*)(P + Npad);
+            re += lo.x + hi.y;
+            im += lo.y - hi.x;
+        }
+    }
+    red[wave][0][lane] = re;
+    red[wave][1][lane] = im;
+    __syncthreads();
+    if (wave == 0 && w < nw) {
+        dW[2 * w] += (red[0][0][lane] + red[1][0][lane]) + (red[2][0][lane] + red[3][0][lane]);
+        dW[2 * w + 1] += (red[0][1][lane] + red[1][1][lane]) + (red[2][1][lane] + red[3][1][lane]);
+    }
+}
+
 __global__ void fill_kernel(uint32_t* p, long n)
 {
     for (long k = (long)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += (long)gridDim.x * blockDim.x)
@@ -1147,11 +1458,19 @@ struct NnWork {
     void* G;                     // [Mpad][Nmax]
     Embedded E;                  // per layer Bt [Nmax][Kmax] and Bk [Kmax][Nmax]; Bl, Bm
     float* part;                 // [nsplit][Kmax][Nmax]
-    float* dB;                   // [Kmax][Nmax]
     Chan mix;                    // bf16 fields m_p of the last layer's path mixing
 };
 
-constexpr int kSplit = 64;
+constexpr int kSplit = 64;  // row slices of the FP32-operand weight gradient
+// Shares of the blocks in the fused weight gradients, so that one round of workgroups fills
+// the machine: nine paths of the 8 -> 8 layer three workgroups per CU (what their LDS
+// allows), of the 8 -> 1 layer four (their registers), the one-channel layer one per CU.
+// One buffer of partial gradients, sized for the first, serves all of them and the slices.
+constexpr int kShares = 85;
+template <int CIN, int COUT>
+constexpr int shares_of() { return CIN == 1 ? 256 : COUT == 1 ? 113 : kShares; }
+static_assert(kShares >= kSplit && 113 * 16 <= kShares * kMaxN && 256 * 80 * 64 <= kShares * kMaxN * kMaxK,
+              "the partial gradients fit");
 
 // need_A: the materialised transport matrix A (FP32-operand forward passes, training)
 size_t nn_layout(const qdw_op* op, bool training, char* base, NnWork* W, bool need_A = true)
@@ -1182,8 +1501,7 @@ size_t nn_layout(const qdw_op* op, bool training, char* base, NnWork* W, bool ne
         W->E.Bt[l] = take((size_t)kMaxN * kMaxK * 4);
         W->E.Bk[l] = take((size_t)kMaxN * kMaxK * 4);
     }
-    W->part = training ? (float*)take((size_t)kSplit * kMaxN * kMaxK * 4) : nullptr;
-    W->dB = training ? (float*)take((size_t)kMaxN * kMaxK * 4) : nullptr;
+    W->part = training ? (float*)take((size_t)kShares * kMaxN * kMaxK * 4) : nullptr;
     return off + 256;
 }
 
@@ -1222,11 +1540,11 @@ int forward(qdw_op* op, NnWork& W, hipStream_t st, bool keep_hidden = true, void
         const long Mp = rows_padded(g);
         for (int l = 0; l < kLayers; ++l) {
             const int Cin = kCh[l], Cout = kCh[l + 1], Kp = layer_K(l), Np = layer_N(l);
-            nn_transport_kernel<true, F32><<<(unsigned)((nq * Cin + 255) / 256), 256, 0, st>>>(
-                g, Cin, Kp, Mp, W.act[l], W.A, L, D);
+            nn_transport_kernel<<<(unsigned)((nq * Cin + 255) / 256), 256, 0, st>>>(
+                g, Cin, Kp, Mp, W.act[l], (float*)W.A, L, D);
             QDW_LAUNCH_CHECK();
-            nn_gemm_out_kernel<true><<<(unsigned)(Mp / 64), 256, 0, st>>>(g, Kp, Np, Cout, Mp, W.A,
-                                                                         W.E.Bt[l], W.act[l + 1]);
+            nn_gemm_out_kernel<<<(unsigned)(Mp / 64), 256, 0, st>>>(
+                g, Kp, Np, Cout, Mp, (const float*)W.A, (const float*)W.E.Bt[l], W.act[l + 1]);
             QDW_LAUNCH_CHECK();
         }
         return out64 ? run_map(op, Axpby<F32, F64>{W.act[kLayers].base, out64, a, 0.0}, st) : QDW_OK;
@@ -1257,10 +1575,42 @@ int forward(qdw_op* op, NnWork& W, hipStream_t st, bool keep_hidden = true, void
     return QDW_OK;
 }
 
-// backward from the real gradient of the network output (grad[0][0], times gscale);
-// accumulates dL/dRe W + i dL/dIm W into dW and leaves the input gradient in grad[x][0]
-template <bool F32M>
-int backward(qdw_op* op, float* dW, NnWork& W, float gscale, hipStream_t st, float** gin_out)
+// dx of one layer from G (bf16 fields), and its weight gradient
+template <int CIN, int COUT, int PIN, int POUT>
+int backward_layer(qdw_op* op, int l, Chan in, Chan G, Chan dx, float* dW, const NnWork& W, hipStream_t st)
+{
+    const Geom& g = op->g;
+    const int nblk = 2 * padded(g.Vh) / 64, shares = std::min(shares_of<CIN, COUT>(), nblk);
+    nn_dw_partial_kernel<CIN, COUT, PIN><<<shares * (CIN == 8 ? kPaths : 1), 256, 0, st>>>(
+        g, in, G, op->links[F32], op->det[F32], shares, W.part);
+    QDW_LAUNCH_CHECK();
+    const int nw = kPaths * COUT * CIN * 16;
+    nn_dw_reduce_kernel<<<(nw + 63) / 64, 256, 0, st>>>(W.part, shares, CIN, COUT, layer_K(l), layer_N(l),
+                                                       dW + 2 * layer_w_offset(l));
+    QDW_LAUNCH_CHECK();
+    if (dx.base) {
+        nn_dx_kernel<CIN, COUT, POUT><<<nblk, 256, 0, st>>>(g, G, (const uint16_t*)W.E.Bk[l], dx,
+                                                            op->links[F32], op->det[F32]);
+        QDW_LAUNCH_CHECK();
+    }
+    return QDW_OK;
+}
+
+// backward from the real gradient of the network output (grad[0], channel 0, times gscale);
+// accumulates dL/dRe W + i dL/dIm W into dW and, if asked for, leaves the input gradient in
+// *gin_out. The gradients between the layers are bf16 fields, the operands of the products.
+int backward_bf16(qdw_op* op, float* dW, NnWork& W, float gscale, hipStream_t st, float** gin_out)
+{
+    int rc;
+    if ((rc = run_map(op, Axpby<F32, BF16S>{W.grad[0].base, W.grad[1].base, gscale, 0.0}, st))) return rc;
+    if ((rc = backward_layer<8, 1, BF16S, BF16S>(op, 2, W.act[2], W.grad[1], W.grad[0], dW, W, st))) return rc;
+    if ((rc = backward_layer<8, 8, BF16S, BF16S>(op, 1, W.act[1], W.grad[0], W.grad[1], dW, W, st))) return rc;
+    if (gin_out) *gin_out = (float*)W.grad[0].base;
+    return backward_layer<1, 8, F32, F32>(op, 0, W.act[0], W.grad[1], gin_out ? W.grad[0] : Chan{}, dW, W, st);
+}
+
+// the same with FP32 operands, through the matrices in memory (gradient checks)
+int backward_f32(qdw_op* op, float* dW, NnWork& W, float gscale, hipStream_t st, float** gin_out)
 {
     const Geom& g = op->g;
     const long Mp = rows_padded(g);
@@ -1269,33 +1619,26 @@ int backward(qdw_op* op, float* dW, NnWork& W, float gscale, hipStream_t st, flo
     int cur = 0;  // grad[cur] holds the gradient of layer l's output
     for (int l = kLayers - 1; l >= 0; --l) {
         const int Cin = kCh[l], Cout = kCh[l + 1], Kp = layer_K(l), Np = layer_N(l);
-        // recompute this layer's transported input rows (hidden activations are bf16 in
-        // the bf16 forward pass)
-        const unsigned ntb = (unsigned)((nq * Cin + 255) / 256);
-        if (F32M || l == 0)
-            nn_transport_kernel<F32M, F32><<<ntb, 256, 0, st>>>(
-                g, Cin, Kp, Mp, W.act[l], W.A, op->links[F32], op->det[F32]);
-        else
-            nn_transport_kernel<F32M, BF16S><<<ntb, 256, 0, st>>>(
-                g, Cin, Kp, Mp, W.act[l], W.A, op->links[F32], op->det[F32]);
+        // recompute this layer's transported input rows
+        nn_transport_kernel<<<(unsigned)((nq * Cin + 255) / 256), 256, 0, st>>>(
+            g, Cin, Kp, Mp, W.act[l], (float*)W.A, op->links[F32], op->det[F32]);
         QDW_LAUNCH_CHECK();
         // G rows from the output gradient
-        nn_pack_g_kernel<F32M><<<(unsigned)((nq + 255) / 256), 256, 0, st>>>(
-            g, Cout, Np, W.grad[cur], l == kLayers - 1 ? gscale : 1.f, W.G);
+        nn_pack_g_kernel<<<(unsigned)((nq + 255) / 256), 256, 0, st>>>(
+            g, Cout, Np, W.grad[cur], l == kLayers - 1 ? gscale : 1.f, (float*)W.G);
         QDW_LAUNCH_CHECK();
         // weight gradient dB = A^T G
         const long rows_per = ((M + kSplit - 1) / kSplit + 15) & ~15L;
-        nn_gemm_db_kernel<F32M><<<dim3(Kp / 16, kSplit), 256, 0, st>>>(M, Kp, Np, (int)rows_per,
-                                                                      Mp, W.A, W.G, W.part);
-        QDW_LAUNCH_CHECK();
-        nn_reduce_db_kernel<<<(Kp * Np + 255) / 256, 256, 0, st>>>(W.part, kSplit, Kp * Np, W.dB);
+        nn_gemm_db_kernel<<<dim3(Kp / 16, kSplit), 256, 0, st>>>(
+            M, Kp, Np, (int)rows_per, Mp, (const float*)W.A, (const float*)W.G, W.part);
         QDW_LAUNCH_CHECK();
         const int nw = kPaths * Cout * Cin * 16;
-        nn_dw_kernel<<<(nw + 255) / 256, 256, 0, st>>>(W.dB, Cin, Cout, Np,
-                                                       dW + 2 * layer_w_offset(l));
+        nn_dw_reduce_kernel<<<(nw + 63) / 64, 256, 0, st>>>(W.part, kSplit, Cin, Cout, Kp, Np,
+                                                           dW + 2 * layer_w_offset(l));
         QDW_LAUNCH_CHECK();
         // input gradient dA = G B^T, then the adjoint transport
-        nn_gemm_da_kernel<F32M><<<(unsigned)(Mp / 64), 256, 0, st>>>(Kp, Np, Mp, W.G, W.E.Bk[l], W.dA);
+        nn_gemm_da_kernel<<<(unsigned)(Mp / 64), 256, 0, st>>>(Kp, Np, Mp, (const float*)W.G,
+                                                               (const float*)W.E.Bk[l], W.dA);
         QDW_LAUNCH_CHECK();
         nn_transport_adj_kernel<<<(unsigned)((nq * Cin + 255) / 256), 256, 0, st>>>(
             g, Cin, Mp, W.dA, W.grad[1 - cur], op->links[F32], op->det[F32]);
@@ -1361,7 +1704,6 @@ extern "C" int nn_forward(qdw_op* op, const float* weights, const void* in, void
     hipStream_t st = (hipStream_t)stream;
     NnWork W;
     nn_layout(op, false, align_work(work), &W);
-    const Geom& g = op->g;
     int rc;
     if ((rc = run_map(op, Axpby<F64, F32>{in, W.act[0].base, 1.0, 0.0}, st))) return rc;
     if ((rc = f32_mixing ? embed_weights<true>(weights, W, st) : embed_weights<false>(weights, W, st)))
@@ -1380,7 +1722,6 @@ extern "C" int nn_backward(qdw_op* op, const float* weights, const void* in, con
     hipStream_t st = (hipStream_t)stream;
     NnWork W;
     nn_layout(op, true, align_work(work), &W);
-    const Geom& g = op->g;
     int rc;
     if ((rc = zero_dev(dW, sizeof(float) * 2 * total_weights(), st))) return rc;
     if ((rc = run_map(op, Axpby<F64, F32>{in, W.act[0].base, 1.0, 0.0}, st))) return rc;
@@ -1389,8 +1730,8 @@ extern "C" int nn_backward(qdw_op* op, const float* weights, const void* in, con
     if ((rc = f32_mixing ? forward<true>(op, W, st) : forward<false>(op, W, st))) return rc;
     if ((rc = run_map(op, Axpby<F64, F32>{gout, W.grad[0].base, 1.0, 0.0}, st))) return rc;
     float* gi = nullptr;
-    rc = f32_mixing ? backward<true>(op, dW, W, 1.f, st, &gi)
-                    : backward<false>(op, dW, W, 1.f, st, &gi);
+    rc = f32_mixing ? backward_f32(op, dW, W, 1.f, st, &gi)
+                    : backward_bf16(op, dW, W, 1.f, st, &gi);
     if (rc) return rc;
     return run_map(op, Axpby<F32, F64>{gi, gin, 1.0, 0.0}, st);
 }
@@ -1476,7 +1817,7 @@ extern "C" int nn_train_step(qdw_op* op, float* weights, float* adam, int step, 
         total += d2 / denom;
         // dL/d(out re, im) = 2 (out - e) / |e|^2, or 2 D^+ D (out - e) / |D e|^2, batch mean
         const float gs = (float)(2.0 / (denom * nbatch));
-        if ((rc = backward<false>(op, dW, W, gs, st, nullptr))) return rc;
+        if ((rc = backward_bf16(op, dW, W, gs, st, nullptr))) return rc;
     }
     *loss = total / nbatch;
     const float b1 = 0.9f, b2 = 0.999f;
