@@ -248,12 +248,12 @@ __device__ __forceinline__ double sum_strided(const double* p, unsigned first, u
     return v;
 }
 
-// Sums acc[NS] of every lane of the grid (whole workgroups of at most 256 lanes, all of
+// Sums acc[NS] of every lane of the grid (whole workgroups of at most 512 lanes, all of
 // whose lanes call this; workgroup blk of nblk) into s.out through s.fin.
 template <int NS>
 __device__ __forceinline__ void grid_sums(const double* acc, const Sums& s, unsigned blk, unsigned nblk)
 {
-    __shared__ double red[4][NS];
+    __shared__ double red[NS == 1 ? 8 : 4][NS];  // only single sums run in 512-lane workgroups
     __shared__ double sums[NS];
     __shared__ int last;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwv = blockDim.x >> 6;
@@ -531,7 +531,8 @@ struct Zero {
 
 // ---------------------------------------------------------------- host helpers
 
-int dw_launch(qdw_op* op, const void* in, void* out, int prec, bool dag, hipStream_t st);
+// split = false keeps the form of the operator's shape on small lattices too
+int dw_launch(qdw_op* op, const void* in, void* out, int prec, bool dag, hipStream_t st, bool split = true);
 // the even-odd reduced operator on the even half of in (odd half of out: scratch)
 int schur_launch(qdw_op* op, const void* in, void* out, int prec, bool dag, hipStream_t st);
 // the two operator applications of a CG step with the step's sums and residual in them:

@@ -37,12 +37,25 @@
 using namespace qdw;
 
 namespace qdw {
+// (the last argument of a kernel, its first field beside the gate: a launch on one field
+// reads a few neighbouring words of it)
 struct RhsTable {
-    const void* in[kMaxRhs];
-    void* out[kMaxRhs];
     const int* gate;  // optional: right-hand side r is skipped when gate[r * gstride] == 0
     int gstride;
+    int nrhs;
+    struct {
+        const void* in;
+        void* out;
+    } f[kMaxRhs];
 };
+
+inline RhsTable one_field(const void* in, void* out)
+{
+    RhsTable tab{};
+    tab.nrhs = 1;
+    tab.f[0] = {in, out};
+    return tab;
+}
 }  // namespace qdw
 
 namespace {
@@ -101,15 +114,15 @@ __device__ __forceinline__ void hop_load(const Geom& g, const void* in, const vo
     else load_link<P>(links, dets, g.Vh, 1 - par, j, MU, b.u, b.d);      // U_mu(x - mu)
 }
 
-// acc += U (1 -+ gamma) psi(x + mu)  or  U^+ (1 +- gamma) psi(x - mu), times the boundary
-// sign; with HALF the term is scaled by -1/2 (the hopping term's factor) before it is added
+// w = U (1 -+ gamma) psi(x + mu) or U^+ (1 +- gamma) psi(x - mu), times the boundary sign (and
+// -1/2 with HALF), as a half spinor
 template <int P, int MU, bool FWD, bool DAG, bool HALF = false>
-__device__ __forceinline__ void hop_compute(const Geom& g, const int x[4], const HopIn<P>& b,
-                                            cx<typename Traits<P>::real> acc[12])
+__device__ __forceinline__ void hop_half(const Geom& g, const int x[4], const HopIn<P>& b,
+                                         cx<typename Traits<P>::real> w[6])
 {
     using R = typename Traits<P>::real;
     constexpr int SG = (FWD != DAG) ? -1 : +1;  // projector 1 + SG gamma_mu
-    cx<R> h[6], w[6];
+    cx<R> h[6];
     project<R, MU, SG>(b.s, h);
     const bool flip = MU == 0 && g.bc_t < 0 && x[0] == (FWD ? g.L[0] - 1 : 0);
     if (HALF) {
@@ -121,6 +134,18 @@ __device__ __forceinline__ void hop_compute(const Geom& g, const int x[4], const
         for (int c = 0; c < 6; ++c) h[c] = -h[c];
     }
     su3_mul<R, !FWD>(b.u, b.d, h, w);
+}
+
+// acc += U (1 -+ gamma) psi(x + mu)  or  U^+ (1 +- gamma) psi(x - mu), times the boundary
+// sign; with HALF the term is scaled by -1/2 (the hopping term's factor) before it is added
+template <int P, int MU, bool FWD, bool DAG, bool HALF = false>
+__device__ __forceinline__ void hop_compute(const Geom& g, const int x[4], const HopIn<P>& b,
+                                            cx<typename Traits<P>::real> acc[12])
+{
+    using R = typename Traits<P>::real;
+    constexpr int SG = (FWD != DAG) ? -1 : +1;  // projector 1 + SG gamma_mu
+    cx<R> w[6];
+    hop_half<P, MU, FWD, DAG, HALF>(g, x, b, w);
     expand_add<R, MU, SG>(w, acc);
 }
 
@@ -162,16 +187,16 @@ __device__ __forceinline__ void compute_k(int k, const Geom& g, const int x[4], 
 // hides more of the gather latency.
 template <int P, bool DAG, bool PIPE, int EPI>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(P >= F16S && !PIPE ? 4 : 1)))
-void dw_kernel(Geom g, RhsTable tab, int nrhs, const void* __restrict__ links,
-               const void* __restrict__ dets, const void* __restrict__ clover, Epi epi)
+void dw_kernel(Geom g, const void* __restrict__ links, const void* __restrict__ dets,
+               const void* __restrict__ clover, Epi epi, RhsTable tab)
 {
     using R = typename Traits<P>::real;
     const int logical = xcd_tile(blockIdx.x, gridDim.x);
-    const int tile = logical / nrhs;
-    const int rhs = logical - tile * nrhs;
+    const int tile = logical / tab.nrhs;
+    const int rhs = logical - tile * tab.nrhs;
     if (tab.gate && !tab.gate[(long)rhs * tab.gstride]) return;
-    const void* __restrict__ in = tab.in[rhs];
-    void* __restrict__ out = tab.out[rhs];
+    const void* __restrict__ in = tab.f[rhs].in;
+    void* __restrict__ out = tab.f[rhs].out;
     int par, i;
     double sum = 0.0;
     if (walk_site(g, tile, threadIdx.x, par, i)) {
@@ -264,10 +289,10 @@ __device__ __forceinline__ void march_site_hops(const Geom& g, const void* in, c
 }
 
 template <int P, bool DAG, bool PIPE, int EPI>
-__global__ __launch_bounds__(256) void dw_march_kernel(Geom g, RhsTable tab, int nrhs,
-                                                       const void* __restrict__ links,
+__global__ __launch_bounds__(256) void dw_march_kernel(Geom g, const void* __restrict__ links,
                                                        const void* __restrict__ dets,
-                                                       const void* __restrict__ clover, Epi epi)
+                                                       const void* __restrict__ clover, Epi epi,
+                                                       RhsTable tab)
 {
     using R = typename Traits<P>::real;
     constexpr int SGF = DAG ? +1 : -1;  // projector of the +t hop: 1 + SGF gamma_0
@@ -277,11 +302,11 @@ __global__ __launch_bounds__(256) void dw_march_kernel(Geom g, RhsTable tab, int
     R* hp = (R*)smem;           // [2 slots][12 reals][nl]: projected +t neighbours
     R* pw = hp + 2 * 12 * nl;   // [2 slots][12 reals][nl]: transported -t neighbours
     const int logical = xcd_tile(blockIdx.x, gridDim.x);
-    const int wg = logical / nrhs;
-    const int rhs = logical - wg * nrhs;
+    const int wg = logical / tab.nrhs;
+    const int rhs = logical - wg * tab.nrhs;
     if (tab.gate && !tab.gate[(long)rhs * tab.gstride]) return;  // the whole workgroup
-    const void* __restrict__ in = tab.in[rhs];
-    void* __restrict__ out = tab.out[rhs];
+    const void* __restrict__ in = tab.f[rhs].in;
+    void* __restrict__ out = tab.f[rhs].out;
     const int c = wg / g.ntile, s = wg - c * g.ntile;
     const int t0 = c * g.nt;
     const int tid = threadIdx.x;
@@ -466,10 +491,244 @@ __global__ __launch_bounds__(256) void schur_kernel(Geom g, int ntile1, const vo
     if constexpr (EPI != EPI_NONE) grid_sums<1>(&sum, epi.sums, blockIdx.x, gridDim.x);
 }
 
+// Small lattices: with one lane per site a lattice of some ten thousand sites leaves most of
+// the machine without work, and the launch lasts as long as one lane's chain of eight hops
+// (FP64 at 4^4: 9.7 us, whatever the shape). Here a workgroup of eight wavefronts owns 64
+// consecutive sites of one parity, one hop direction per wavefront: the hops run side by side
+// and meet in LDS as half spinors, and then four wavefronts form one spin of the outputs
+// each, adding the diagonal term, whose loads they issue first. Any 64-site block is a
+// workgroup, so lattices of any shape split evenly.
+//   KIND 0: out = A psi - 1/2 hops(psi), both parities (D)
+//   KIND 1: out = A^-1 (-1/2 hops(psi)) on the odd sites, KIND 2: out = A psi + 1/2 hops(t)
+//           on the even sites (the stages of the reduced operator)
+template <int P, int KIND, int SPIN, bool DAG>
+struct SplitRow {
+    using T = Traits<P>;
+    using R = typename T::real;
+    static constexpr int BLK = SPIN / 2, UP = SPIN % 2;  // chirality block, row group in it
+    R a[KIND == 0 ? Cl54Chunks<P>::n * T::PER_CHUNK : 36];
+    cx<R> s[6];  // the block's half of psi
+
+    // (entries that the row does not use are not loaded)
+    __device__ __forceinline__ void load(const Geom& g, const void* psi, const void* diag, int par, int i)
+    {
+        if constexpr (KIND == 0) {
+            const long base = chunk_at(g.Vh, Cl54Chunks<P>::n, par, 0, i);
+#pragma unroll
+            for (int k = 0; k < Cl54Chunks<P>::n; ++k) {
+                const Chunk<P> c = load_chunk<P>(diag, base + (long)k * kSB);
+#pragma unroll
+                for (int j = 0; j < T::PER_CHUNK; ++j) a[k * T::PER_CHUNK + j] = to_real<P>(c.v[j]);
+            }
+        } else {
+            const long base = chunk_at(g.Vh, T::CLOVER_CHUNKS, par, 0, i);
+#pragma unroll
+            for (int k = 0; k < T::CLOVER_CHUNKS; ++k) {
+                if ((k + 1) * T::PER_CHUNK <= 36 * BLK || k * T::PER_CHUNK >= 36 * BLK + 36) continue;
+                const Chunk<P> c = load_chunk<P>(diag, base + (long)k * kSB);
+#pragma unroll
+                for (int j = 0; j < T::PER_CHUNK; ++j) {
+                    const int q = k * T::PER_CHUNK + j - 36 * BLK;
+                    if (q >= 0 && q < 36) a[q] = to_real<P>(c.v[j]);
+                }
+            }
+        }
+        if constexpr (KIND != 1) {
+            cx<R> all[12];
+            load_spinor<P>(psi, g.Vh, par, i, all);
+#pragma unroll
+            for (int k = 0; k < 6; ++k) s[k] = all[6 * BLK + k];
+        }
+    }
+
+    // this spin's part of hop (MU, SG) from its half spinor in LDS: w0 or w1 times a phase
+    template <int MU, int SG, int SP>
+    __device__ __forceinline__ static void add_hop(const R (*w)[64], int lane, cx<R> o[3])
+    {
+        constexpr bool second = SP < 2 ? SP == 1 : (MU == 0 || MU == 3) ? SP == 3 : SP == 2;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const int q = 2 * (3 * second + c);
+            const cx<R> v = {w[q][lane], w[q + 1][lane]};
+            if (SP < 2) o[c] = o[c] + v;
+            else if (MU == 0) o[c] = SG > 0 ? o[c] - v : o[c] + v;
+            else if (MU == 1) o[c] = SG > 0 ? o[c] + times_i(v) : o[c] - times_i(v);
+            else if (MU == 2) o[c] = (SG > 0) == (SP == 2) ? o[c] + v : o[c] - v;
+            else o[c] = (SG > 0) == (SP == 2) ? o[c] + times_i(v) : o[c] - times_i(v);
+        }
+    }
+    template <int SP>
+    __device__ __forceinline__ static void hop_sum(const R (*hw)[12][64], int lane, cx<R> o[3])
+    {
+        constexpr int F = DAG ? 1 : -1, Bk = -F;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) o[c] = {(R)0, (R)0};
+        add_hop<0, F, SP>(hw[0], lane, o);
+        add_hop<0, Bk, SP>(hw[1], lane, o);
+        add_hop<1, F, SP>(hw[2], lane, o);
+        add_hop<1, Bk, SP>(hw[3], lane, o);
+        add_hop<2, F, SP>(hw[4], lane, o);
+        add_hop<2, Bk, SP>(hw[5], lane, o);
+        add_hop<3, F, SP>(hw[6], lane, o);
+        add_hop<3, Bk, SP>(hw[7], lane, o);
+    }
+
+    // the three output components of this spin
+    __device__ __forceinline__ void row(const Geom& g, const R (*hw)[12][64], int lane, cx<R> o[3]) const
+    {
+        cx<R> v[6];
+        if constexpr (KIND == 1) {
+            cx<R> h[6];
+            hop_sum<2 * BLK>(hw, lane, h);
+            hop_sum<2 * BLK + 1>(hw, lane, h + 3);
+#pragma unroll
+            for (int k = 0; k < 6; ++k) h[k] = scale(h[k], (R)-0.5);
+            herm6_apply<R>(a, h, v);
+#pragma unroll
+            for (int c = 0; c < 3; ++c) o[c] = v[3 * UP + c];
+        } else {
+            cx<R> h[3];
+            hop_sum<SPIN>(hw, lane, h);
+            if constexpr (KIND == 0)
+                cl54_block<R>((R)g.cdiag, a + 3 * BLK, a + (BLK ? 30 : 6), a + (BLK ? 36 : 12), s, v);
+            else
+                herm6_apply<R>(a, s, v);
+#pragma unroll
+            for (int c = 0; c < 3; ++c)
+                o[c] = KIND == 0 ? v[3 * UP + c] - scale(h[c], (R)0.5) : v[3 * UP + c] + scale(h[c], (R)0.5);
+        }
+    }
+};
+
+// place of component k (of 12) of a stored spinor, in storage scalars
+template <int P>
+__device__ __forceinline__ long component_at(int Vh, int par, int i, int k)
+{
+    using T = Traits<P>;
+    constexpr int CPC = T::PER_CHUNK / 2;
+    return chunk_at(Vh, T::SPIN_CHUNKS, par, k / CPC, i) * T::PER_CHUNK + 2 * (k % CPC);
+}
+
+template <int P, int KIND, bool DAG, int EPI>
+__global__ __launch_bounds__(512)
+void dw_split_kernel(Geom g, const void* psi, const void* __restrict__ links,
+                     const void* __restrict__ dets, const void* __restrict__ diag, Epi epi, RhsTable tab)
+{
+    using T = Traits<P>;
+    using R = typename T::real;
+    using S = typename T::store;
+    __shared__ R hw[8][12][64];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int logical = xcd_tile(blockIdx.x, gridDim.x);
+    const int tile = logical / tab.nrhs, rhs = logical - tile * tab.nrhs;
+    if (tab.gate && !tab.gate[(long)rhs * tab.gstride]) return;  // the whole workgroup
+    const void* in = tab.f[rhs].in;
+    void* out = tab.f[rhs].out;
+    if (KIND == 0) psi = in;
+    // blocks of the two parities of one index range follow each other
+    const int par = KIND == 0 ? tile & 1 : KIND == 1 ? 1 : 0;
+    const int i = (KIND == 0 ? tile >> 1 : tile) * 64 + lane;
+    const bool live = i < g.Vh;
+    int x[4] = {0, 0, 0, 0}, lex = 0;
+    double sum = 0.0;
+    if (live) eo_coords_fast(g, par, i, x, lex);
+
+    auto hop = [&](auto mu_c, auto fwd_c) {
+        constexpr int MU = decltype(mu_c)::value;
+        constexpr bool FWD = decltype(fwd_c)::value;
+        HopIn<P> b;
+        cx<R> w[6];
+        hop_load<P, MU, FWD>(g, in, links, dets, par, i, x, lex, b);
+        hop_half<P, MU, FWD, DAG>(g, x, b, w);
+#pragma unroll
+        for (int q = 0; q < 6; ++q) {
+            hw[wave][2 * q][lane] = w[q].re;
+            hw[wave][2 * q + 1][lane] = w[q].im;
+        }
+    };
+    auto store = [&](int spin, cx<R> o[3]) {
+        const R a = EPI == EPI_STEP ? (R)epi.sc[S_ALPHA] : (R)0;
+        S* f = (S*)(EPI == EPI_STEP ? epi.r : out);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            S* at = f + component_at<P>(g.Vh, par, i, 3 * spin + c);
+            S v[2];
+            if constexpr (EPI == EPI_STEP) {
+                __builtin_memcpy(v, at, 2 * sizeof(S));
+                o[c] = cx<R>{to_real<P>(v[0]), to_real<P>(v[1])} - scale(o[c], a);
+            }
+            v[0] = to_store<P>(o[c].re);
+            v[1] = to_store<P>(o[c].im);
+            __builtin_memcpy(__builtin_assume_aligned(at, 2 * sizeof(S)), v, 2 * sizeof(S));
+            if constexpr (EPI != EPI_NONE) {
+                const double re = to_real<P>(v[0]), im = to_real<P>(v[1]);
+                sum = __builtin_fma(re, re, __builtin_fma(im, im, sum));
+            }
+        }
+    };
+    auto run = [&](auto spin_c, auto mu_c, auto fwd_c) {
+        constexpr int SPIN = decltype(spin_c)::value;
+        if constexpr (SPIN < 4) {
+            SplitRow<P, KIND, SPIN, DAG> row;
+            if (live) {
+                row.load(g, psi, diag, par, i);
+                hop(mu_c, fwd_c);
+            }
+            __syncthreads();
+            if (live) {
+                cx<R> o[3];
+                row.row(g, hw, lane, o);
+                store(SPIN, o);
+            }
+        } else {
+            if (live) hop(mu_c, fwd_c);
+            __syncthreads();
+        }
+    };
+    using std::integral_constant;
+    using Fw = std::true_type;
+    using Bw = std::false_type;
+    switch (wave) {
+    case 0: run(integral_constant<int, 0>{}, integral_constant<int, 0>{}, Fw{}); break;
+    case 1: run(integral_constant<int, 1>{}, integral_constant<int, 0>{}, Bw{}); break;
+    case 2: run(integral_constant<int, 2>{}, integral_constant<int, 1>{}, Fw{}); break;
+    case 3: run(integral_constant<int, 3>{}, integral_constant<int, 1>{}, Bw{}); break;
+    case 4: run(integral_constant<int, 4>{}, integral_constant<int, 2>{}, Fw{}); break;
+    case 5: run(integral_constant<int, 4>{}, integral_constant<int, 2>{}, Bw{}); break;
+    case 6: run(integral_constant<int, 4>{}, integral_constant<int, 3>{}, Fw{}); break;
+    default: run(integral_constant<int, 4>{}, integral_constant<int, 3>{}, Bw{}); break;
+    }
+    if constexpr (EPI != EPI_NONE) grid_sums<1>(&sum, epi.sums, blockIdx.x, gridDim.x);
+}
+
+// Where the split form is used: up to the lattice size (times the fields of a launch) at which
+// the other forms have enough sites in flight to overtake it. Kernel times on either side, us,
+// split against the default shape: FP64 D 11.2 / 14.2 at 16 x 12^3, 22.8 / 19.7 at 16^4; FP32
+// 12.3 / 13.4 at 16^4, 19.0 / 16.9 at 20x14x18x22; FP16 10.1 / 12.0 and 15.1 / 13.5 at the
+// same; both stages of the reduced operator: FP64 27.5 / 33.5 at 16^4, 47.9 / 41.4 at
+// 20x14x18x22, FP32 15.6 / 23.6 and 25.9 / 26.6, FP16 13.0 / 21.2 and 18.6 / 20.1; at 4^4 5.1 /
+// 10.6 (FP64 D), 4.2 / 8.4 (FP32), 3.9 / 9.0 (FP16).
+inline bool split_form(int P, bool schur, long sites)
+{
+    constexpr long kD[4] = {40000, 80000, 90000, 90000}, kSchur[4] = {85000, 120000, 200000, 200000};
+    return sites <= (schur ? kSchur[P] : kD[P]);
+}
+
 template <int P, bool DAG, int EPI>
 int schur_launch_t(qdw_op* op, const void* in, void* out, const Epi& epi, hipStream_t st)
 {
     const Geom& g = op->g;
+    if (split_form(P, true, g.V)) {
+        const int nblk = padded(g.Vh) / kSB;
+        dw_split_kernel<P, 1, DAG, EPI_NONE><<<nblk, 512, 0, st>>>(
+            g, nullptr, op->links[P], op->det[P], op->cloverinv[P], Epi{}, one_field(in, out));
+        QDW_LAUNCH_CHECK();
+        dw_split_kernel<P, 2, DAG, EPI><<<nblk, 512, 0, st>>>(
+            g, in, op->links[P], op->det[P], op->clover[P], epi, one_field(out, out));
+        QDW_LAUNCH_CHECK();
+        return QDW_OK;
+    }
     const int ntile1 = (g.S + 255) / 256;
     const int nb = g.L[0] * ntile1;
     // the hop loop is software-pipelined where the registers allow it (FP64, FP32), as for D
@@ -483,18 +742,29 @@ int schur_launch_t(qdw_op* op, const void* in, void* out, const Epi& epi, hipStr
     return QDW_OK;
 }
 
-// the operator's geometry with the D kernel's own shape for precision P
-inline Geom shaped(const qdw_op* op, int P)
+// the operator's geometry with the D kernel's own shape for precision P (the default
+// marching shape: with the walk chunk for this many fields)
+inline Geom shaped(const qdw_op* op, int P, int nrhs)
 {
     Geom g = op->g;
-    set_walk(g, op->dw_shape[P].ts, op->dw_shape[P].nt, op->dw_shape[P].walk);
+    const auto& s = op->dw_shape[P];
+    const int nt = op->dw_auto[P] && s.march && nrhs > 1 ? march_chunk(g, P, nrhs) : s.nt;
+    set_walk(g, s.ts, nt, s.walk);
     return g;
 }
 
 template <int P, bool DAG, int EPI>
-int launch(qdw_op* op, const RhsTable& tab, int nrhs, const Epi& epi, hipStream_t st)
+int launch(qdw_op* op, const RhsTable& tab, const Epi& epi, hipStream_t st, bool split = true)
 {
-    const Geom g = shaped(op, P);
+    const int nrhs = tab.nrhs;
+    const Geom g = shaped(op, P, nrhs);
+    if (split && op->dw_auto[P] && split_form(P, false, (long)g.V * nrhs)) {
+        const int nblk = 2 * (padded(g.Vh) / kSB) * nrhs;
+        dw_split_kernel<P, 0, DAG, EPI><<<nblk, 512, 0, st>>>(g, nullptr, op->links[P], op->det[P],
+                                                             op->clover54[P], epi, tab);
+        QDW_LAUNCH_CHECK();
+        return QDW_OK;
+    }
     if (op->dw_shape[P].march) {
         using R = typename Traits<P>::real;
         const int nblk = (g.L[0] / g.nt) * g.ntile * nrhs;
@@ -502,20 +772,20 @@ int launch(qdw_op* op, const RhsTable& tab, int nrhs, const Epi& epi, hipStream_
         static_assert(sizeof(R) == 8 || sizeof(R) == 4, "real type");
         if (op->dw_shape[P].pipe)
             dw_march_kernel<P, DAG, true, EPI><<<nblk, 2 * g.ts, lds, st>>>(
-                g, tab, nrhs, op->links[P], op->det[P], op->clover54[P], epi);
+                g, op->links[P], op->det[P], op->clover54[P], epi, tab);
         else
             dw_march_kernel<P, DAG, false, EPI><<<nblk, 2 * g.ts, lds, st>>>(
-                g, tab, nrhs, op->links[P], op->det[P], op->clover54[P], epi);
+                g, op->links[P], op->det[P], op->clover54[P], epi, tab);
         QDW_LAUNCH_CHECK();
         return QDW_OK;
     }
     const int nblk = walk_blocks(g) * nrhs;
     if (op->dw_shape[P].pipe)
-        dw_kernel<P, DAG, true, EPI><<<nblk, 2 * g.ts, 0, st>>>(g, tab, nrhs, op->links[P], op->det[P],
-                                                                op->clover54[P], epi);
+        dw_kernel<P, DAG, true, EPI><<<nblk, 2 * g.ts, 0, st>>>(g, op->links[P], op->det[P], op->clover54[P],
+                                                                epi, tab);
     else
-        dw_kernel<P, DAG, false, EPI><<<nblk, 2 * g.ts, 0, st>>>(g, tab, nrhs, op->links[P],
-                                                                 op->det[P], op->clover54[P], epi);
+        dw_kernel<P, DAG, false, EPI><<<nblk, 2 * g.ts, 0, st>>>(g, op->links[P], op->det[P], op->clover54[P],
+                                                                 epi, tab);
     QDW_LAUNCH_CHECK();
     return QDW_OK;
 }
@@ -533,11 +803,11 @@ int by_precision(int prec, F f)
     }
 }
 
-int dispatch(qdw_op* op, const RhsTable& tab, int nrhs, int prec, bool dag, hipStream_t st)
+int dispatch(qdw_op* op, const RhsTable& tab, int prec, bool dag, hipStream_t st, bool split = true)
 {
     return by_precision(prec, [&](auto P) {
-        return dag ? launch<P.value, true, EPI_NONE>(op, tab, nrhs, Epi{}, st)
-                   : launch<P.value, false, EPI_NONE>(op, tab, nrhs, Epi{}, st);
+        return dag ? launch<P.value, true, EPI_NONE>(op, tab, Epi{}, st, split)
+                   : launch<P.value, false, EPI_NONE>(op, tab, Epi{}, st, split);
     });
 }
 
@@ -647,22 +917,18 @@ int apply_checked(qdw_op* op, const void* in, void* out, qdw_prec prec, bool dag
 {
     QDW_CHECK(op && in && out, QDW_EINVAL, "dw_apply: null argument");
     QDW_CHECK(in != out, QDW_EINVAL, "dw_apply: in and out must be distinct fields");
-    RhsTable tab{};
-    tab.in[0] = in;
-    tab.out[0] = out;
-    return dispatch(op, tab, 1, prec, dag, (hipStream_t)stream);
+    const RhsTable tab = one_field(in, out);
+    return dispatch(op, tab, prec, dag, (hipStream_t)stream);
 }
 
 }  // namespace
 
 namespace qdw {
 // internal entries used by the solvers (same kernels, no argument re-validation)
-int dw_launch(qdw_op* op, const void* in, void* out, int prec, bool dag, hipStream_t st)
+int dw_launch(qdw_op* op, const void* in, void* out, int prec, bool dag, hipStream_t st, bool split)
 {
-    RhsTable tab{};
-    tab.in[0] = in;
-    tab.out[0] = out;
-    return dispatch(op, tab, 1, prec, dag, st);
+    const RhsTable tab = one_field(in, out);
+    return dispatch(op, tab, prec, dag, st, split);
 }
 
 int schur_launch(qdw_op* op, const void* in, void* out, int prec, bool dag, hipStream_t st)
@@ -676,12 +942,10 @@ int schur_launch(qdw_op* op, const void* in, void* out, int prec, bool dag, hipS
 int cg_apply(qdw_op* op, const void* p, void* q, int prec, bool schur, int ring, hipStream_t st)
 {
     const Epi e = {{op->partials, op->tickets, op->scalars, FIN_CG_ALPHA, ring, nullptr}, nullptr, nullptr};
-    RhsTable tab{};
-    tab.in[0] = p;
-    tab.out[0] = q;
+    const RhsTable tab = one_field(p, q);
     return by_precision(prec, [&](auto P) {
         return schur ? schur_launch_t<P.value, false, EPI_NORM>(op, p, q, e, st)
-                     : launch<P.value, false, EPI_NORM>(op, tab, 1, e, st);
+                     : launch<P.value, false, EPI_NORM>(op, tab, e, st);
     });
 }
 
@@ -689,12 +953,10 @@ int cg_apply_dag(qdw_op* op, const void* q, void* r, void* t, int prec, bool sch
                  hipStream_t st)
 {
     const Epi e = {{op->partials, op->tickets, op->scalars, FIN_CG_BETA, 0, host}, r, op->scalars};
-    RhsTable tab{};
-    tab.in[0] = q;
-    tab.out[0] = r;
+    const RhsTable tab = one_field(q, r);
     return by_precision(prec, [&](auto P) {
         return schur ? schur_launch_t<P.value, true, EPI_STEP>(op, q, t, e, st)
-                     : launch<P.value, true, EPI_STEP>(op, tab, 1, e, st);
+                     : launch<P.value, true, EPI_STEP>(op, tab, e, st);
     });
 }
 
@@ -704,11 +966,9 @@ int dw_launch_multi(qdw_op* op, const void* const* in, void* const* out, int nrh
     RhsTable tab{};
     tab.gate = gate;
     tab.gstride = gstride;
-    for (int r = 0; r < nrhs; ++r) {
-        tab.in[r] = in[r];
-        tab.out[r] = out[r];
-    }
-    return dispatch(op, tab, nrhs, prec, dag, st);
+    tab.nrhs = nrhs;
+    for (int r = 0; r < nrhs; ++r) tab.f[r] = {in[r], out[r]};
+    return dispatch(op, tab, prec, dag, st);
 }
 }  // namespace qdw
 
@@ -847,6 +1107,7 @@ extern "C" int qdw_set_dw_shape(qdw_op* op, qdw_prec prec, int ts, int nt, int p
     const int rc = check_shape(op, prec, ts, nt, pipe, walk, march);
     if (rc) return rc;
     op->dw_shape[prec] = {ts, nt, pipe, walk, march};
+    op->dw_auto[prec] = false;
     return QDW_OK;
 }
 
@@ -882,12 +1143,12 @@ extern "C" int qdw_autotune(qdw_op* op, qdw_prec prec, int nrhs, void* work, siz
     const size_t fb = spinor_bytes(g, prec);
     char* buf = (char*)(((uintptr_t)work + 255) & ~(uintptr_t)255);
     RhsTable tab{};
-    for (int r = 0; r < nrhs; ++r) {
-        tab.in[r] = buf + (size_t)r * fb;
-        tab.out[r] = buf + (size_t)(nrhs + r) * fb;
-    }
+    tab.nrhs = nrhs;
+    for (int r = 0; r < nrhs; ++r) tab.f[r] = {buf + (size_t)r * fb, buf + (size_t)(nrhs + r) * fb};
     hipEvent_t e0 = nullptr, e1 = nullptr;
     const auto keep = op->dw_shape[prec];
+    const bool keep_auto = op->dw_auto[prec], split = split_form(prec, false, (long)g.V * nrhs);
+    float split_ms = 0.f;
     struct Cand { int ts, nt, pipe, walk, march; float ms; };
     std::vector<Cand> cands;
     for (int march = 0; march < 2; ++march)
@@ -905,20 +1166,30 @@ extern "C" int qdw_autotune(qdw_op* op, qdw_prec prec, int nrhs, void* work, siz
         if (r0) return r0;
         QDW_HIP(hipEventCreate(&e0));
         QDW_HIP(hipEventCreate(&e1));
-        for (Cand& c : cands) {
-            op->dw_shape[prec] = {c.ts, c.nt, c.pipe, c.walk, c.march};
+        auto time_form = [&](float* out_ms) -> int {
             int r;
             for (int w = 0; w < 2; ++w)
-                if ((r = dispatch(op, tab, nrhs, prec, false, st))) return r;
+                if ((r = dispatch(op, tab, prec, false, st))) return r;
             const int reps = 8;
             QDW_HIP(hipEventRecord(e0, st));
             for (int w = 0; w < reps; ++w)
-                if ((r = dispatch(op, tab, nrhs, prec, false, st))) return r;
+                if ((r = dispatch(op, tab, prec, false, st))) return r;
             QDW_HIP(hipEventRecord(e1, st));
             QDW_HIP(hipEventSynchronize(e1));
             float ms = 0.f;
             QDW_HIP(hipEventElapsedTime(&ms, e0, e1));
-            c.ms = ms / reps;
+            *out_ms = ms / reps;
+            return QDW_OK;
+        };
+        int r;
+        if (split) {
+            op->dw_auto[prec] = true;
+            if ((r = time_form(&split_ms))) return r;
+        }
+        op->dw_auto[prec] = false;
+        for (Cand& c : cands) {
+            op->dw_shape[prec] = {c.ts, c.nt, c.pipe, c.walk, c.march};
+            if ((r = time_form(&c.ms))) return r;
         }
         return QDW_OK;
     };
@@ -928,12 +1199,15 @@ extern "C" int qdw_autotune(qdw_op* op, qdw_prec prec, int nrhs, void* work, siz
     (void)hipStreamSynchronize(st);
     if (rc) {
         op->dw_shape[prec] = keep;
+        op->dw_auto[prec] = keep_auto;
         return rc;
     }
     const Cand* best = &cands[0];
     for (const Cand& c : cands)
         if (c.ms < best->ms) best = &c;
     op->dw_shape[prec] = {best->ts, best->nt, best->pipe, best->walk, best->march};
+    // a small lattice keeps the split form where no shape beats it
+    op->dw_auto[prec] = split && split_ms < best->ms;
     if (report && report_len) {
         std::string s;
         char line[200];
@@ -942,6 +1216,10 @@ extern "C" int qdw_autotune(qdw_op* op, qdw_prec prec, int nrhs, void* work, siz
                       g.L[0], g.L[1], g.L[2], g.L[3], (int)prec, nrhs, best->ts, best->nt,
                       best->pipe, best->walk, best->march, best->ms);
         s += line;
+        if (split) {
+            std::snprintf(line, sizeof line, " split form %.4f;", split_ms);
+            s += line;
+        }
         for (const Cand& c : cands) {
             std::snprintf(line, sizeof line, " [%d,%d,%d,%d,%d]=%.4f", c.ts, c.nt, c.pipe, c.walk,
                           c.march, c.ms);

@@ -575,7 +575,10 @@ extern "C" int qdw_create(const qdw_lattice* lat, const double* su3, const doubl
     qdw_op* op = new qdw_op();
     std::memset(op, 0, sizeof(*op));
     Geom& g = op->g;
-    for (int mu = 0; mu < 4; ++mu) g.L[mu] = L[mu];
+    for (int mu = 0; mu < 4; ++mu) {
+        g.L[mu] = L[mu];
+        g.div[mu] = fast_div(L[mu]);
+    }
     g.stride[3] = 1;
     g.stride[2] = L[3];
     g.stride[1] = L[3] * L[2];
@@ -593,22 +596,15 @@ extern "C" int qdw_create(const qdw_lattice* lat, const double* su3, const doubl
     }
     {
         // default D-kernel shapes (qdw_autotune or qdw_set_dw_shape may change them).
-        // FP64 and FP32: the marching form on 64-site tiles, with the longest walk chunk
-        // (at most 32 slices, dividing T) that still gives 512 workgroups, two per CU, so
-        // that they march side by side in one round
-        const int ntile = (g.S + 63) / 64;
-        int nt = 1;
-        for (int d = 32; d >= 1; d /= 2)
-            if (L[0] % d == 0 && (long)(L[0] / d) * ntile >= 512) {
-                nt = d;
-                break;
-            }
-        op->dw_shape[F64] = {64, nt, 0, 0, 1};
-        op->dw_shape[F32] = {64, nt, 1, 0, 1};
+        // FP64 and FP32: the marching form on 64-site tiles, with the walk chunk that
+        // march_chunk expects to be fastest
+        op->dw_shape[F64] = {64, march_chunk(g, F64, 1), 0, 0, 1};
+        op->dw_shape[F32] = {64, march_chunk(g, F32, 1), 1, 0, 1};
         // half-precision storage: the plain form (one lane per site, four waves per SIMD)
         // on 128-site tiles in chunks of two slices (T is even)
         op->dw_shape[F16S] = {128, 2, 0, 0, 0};
         op->dw_shape[BF16S] = {128, 2, 0, 0, 0};
+        for (int p = 0; p < 4; ++p) op->dw_auto[p] = true;
     }
     op->m0 = m0;
     op->csw = csw;

@@ -30,6 +30,23 @@ namespace qdw {
 
 enum Prec { F64 = 0, F32 = 1, F16S = 2, BF16S = 3 };
 
+// n / d for 0 <= n < 2^31 and a lattice extent d >= 2 by one high multiplication: with
+// l = ceil(log2 d) and m = ceil(2^(31 + l) / d) < 2^32, the product n m / 2^(31 + l) exceeds
+// n / d by less than n / 2^31 / d, too little to reach the next integer
+struct FastDiv {
+    unsigned m;
+    int sh;
+};
+
+inline FastDiv fast_div(int d)
+{
+    int l = 1;
+    while ((1L << l) < d) ++l;
+    return {(unsigned)(((1ull << (31 + l)) + d - 1) / d), l - 1};
+}
+
+__device__ __forceinline__ int div_by(int n, FastDiv f) { return (int)(__umulhi((unsigned)n, f.m) >> f.sh); }
+
 struct Geom {
     int L[4];      // T, L1, L2, L3 (direction 0 is time)
     int stride[4]; // lexicographic strides
@@ -43,6 +60,7 @@ struct Geom {
     int walk;      // workgroup order within a chunk (walk_site)
     int slab;      // even-odd sites per parity of one x1 slab of a time slice (L2*L3/2)
     int tps;       // ts-site tiles per slab (walk 1)
+    FastDiv div[4];  // by L[1..3]
 };
 
 // set the walk of the site kernels (ts, nt, walk as in walk_site)
@@ -246,6 +264,20 @@ __device__ __forceinline__ void eo_coords(const Geom& g, int par, int i, int x[4
     int r2 = r / g.L[2];
     x[2] = r - r2 * g.L[2];
     int r3 = r2 / g.L[1];
+    x[1] = r2 - r3 * g.L[1];
+    x[0] = r3;
+    if (((x[0] + x[1] + x[2] + x[3]) & 1) != par) { x[3] += 1; l += 1; }
+    lex = l;
+}
+
+// the same with multiplications for the divisions: a third of the instructions, for kernels
+// in which several lanes work on one site (one lane per site gains nothing from it)
+__device__ __forceinline__ void eo_coords_fast(const Geom& g, int par, int i, int x[4], int& lex)
+{
+    int l = 2 * i;
+    const int r = div_by(l, g.div[3]), r2 = div_by(r, g.div[2]), r3 = div_by(r2, g.div[1]);
+    x[3] = l - r * g.L[3];
+    x[2] = r - r2 * g.L[2];
     x[1] = r2 - r3 * g.L[1];
     x[0] = r3;
     if (((x[0] + x[1] + x[2] + x[3]) & 1) != par) { x[3] += 1; l += 1; }
