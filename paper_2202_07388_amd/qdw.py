@@ -170,17 +170,27 @@ def _torch():
     return torch
 
 
-def _stream():
-    torch = _torch()
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+_raw_stream = _current_device = None
 
 
-def _ptr(t) -> ctypes.c_void_p:
+def _stream() -> int:
+    """The handle of torch's current stream on the current device. (Small lattices are bound
+    by the calls themselves: a Stream object and a device check per call cost more than the
+    launch, so the device is looked for once and the handle is asked for directly.)"""
+    global _raw_stream, _current_device
+    if _raw_stream is None:
+        torch = _torch()
+        torch.cuda.current_stream()  # initialises the runtime
+        _raw_stream, _current_device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
+    return _raw_stream(_current_device())
+
+
+def _ptr(t) -> int:
     if not t.is_cuda:
         raise QdwError("expected a device tensor")
     if not t.is_contiguous():
         raise QdwError("expected a contiguous tensor")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 class Op:
@@ -405,7 +415,7 @@ def solve_from(op: Op, eta, x0, psi, solver: str = "gcr", res: float = 1e-10, **
 
 
 def _ptr_array(ts):
-    return (ctypes.c_void_p * len(ts))(*[_ptr(t).value for t in ts])
+    return (ctypes.c_void_p * len(ts))(*[_ptr(t) for t in ts])
 
 
 def dw_apply_multi(op: Op, xs, outs, prec: str = "f64"):
