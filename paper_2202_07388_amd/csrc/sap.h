@@ -13,7 +13,13 @@ struct BlockGeom {
     int bvol;        // sites per block = workgroup size (64..256, whole wavefronts)
     int lstride[4];  // strides of the local site index (x3 fastest)
     int nblk;        // number of blocks
+    // links inside a block, direction by direction: the link of site l in direction mu (its
+    // local coordinate below bs[mu] - 1) is number loff[mu] + sum_nu l[nu] lcs[mu][nu]
+    int loff[4], lcs[4][4];
 };
+
+// most links inside a block of 256 sites: sum_mu (1 - 1/bs[mu]) is largest for equal extents
+constexpr int kBlockLinks = 768;
 
 enum { S_SAP = 12, S_SAP_NEW = 13 };  // scalar slots of the preconditioner
 

@@ -5,16 +5,16 @@
 // dropped), with the residual brought up to date between the two colours.
 //
 // GPU mapping: one workgroup per block, one lane per site (block volume 64..256 sites).
-// A block's residual lives in LDS for all nmr steps; every lane keeps its own clover
-// blocks and its four forward links in registers. The backward hop into a site is
-// computed by the lane that owns the link (the site below it) and handed over through
-// LDS as a transported half spinor, so each link is read from HBM once per sweep.
+// A block's residual and its links live in LDS for all nmr steps; every lane gathers its
+// hops from there and keeps its part of the diagonal term in registers (the reduced block
+// solve hands the backward hops over through LDS instead).
 // Storage precision SP (FP32, FP16 or BF16) for every field in HBM; FP32 arithmetic;
 // block reductions accumulate per lane in FP32 and combine across lanes in FP64.
 //
 // After a colour's block solves, the block residuals r_b are exactly the new residual
 // on that colour; the other colour's residual loses the hops from the block corrections
-// that cross into it (D_partial chi, Fig. 3 right), applied by a second kernel.
+// that cross into it (D_partial chi, Fig. 3 right), which its blocks apply as they load it
+// (or, in the adaptive form, a kernel of its own, since the cycle's |r| is needed).
 #include <map>
 #include <mutex>
 
@@ -45,6 +45,17 @@ int make_block_geom(const Geom& g, const int bs[4], BlockGeom* B)
     B->lstride[1] = bs[3] * bs[2];
     B->lstride[0] = bs[3] * bs[2] * bs[1];
     B->nblk = B->nb[0] * B->nb[1] * B->nb[2] * B->nb[3];
+    int off = 0;
+    for (int mu = 0; mu < 4; ++mu) {
+        int stride = 1;
+        for (int nu = 3; nu >= 0; --nu) {
+            B->lcs[mu][nu] = stride;
+            stride *= nu == mu ? bs[nu] - 1 : bs[nu];
+        }
+        B->loff[mu] = off;
+        off += stride;
+    }
+    QDW_CHECK(off <= kBlockLinks, QDW_EBLOCK, "SAP: internal: too many links in a block");
     return QDW_OK;
 }
 
@@ -52,38 +63,26 @@ namespace {
 
 constexpr int kBMax = 256;
 
-template <int SP, int MU>
-__device__ __forceinline__ void push_backward(float (*hb)[12][kBMax], const BlockGeom& B,
-                                              const int l[4], int t, const cx<float> r[12],
-                                              const cx<float> u[6], cx<float> d)
+// The low / high 16-bit value of a word as FP32. For binary16 the conversion is written out:
+// left to itself the compiler folds it into v_fma_mix_f32 at every use, which issues at little
+// more than half the rate of v_fma_f32 (4.5 against 2.7 cycles a wavefront) and every value
+// here is used several times.
+template <int SP>
+__device__ __forceinline__ float low16(uint32_t w)
 {
-    if (l[MU] < B.bs[MU] - 1) {
-        cx<float> h[6], w[6];
-        project<float, MU, +1>(r, h);
-        su3_mul<float, true>(u, d, h, w);
-        const int dst = t + B.lstride[MU];
-#pragma unroll
-        for (int c = 0; c < 6; ++c) {
-            hb[MU][2 * c][dst] = w[c].re;
-            hb[MU][2 * c + 1][dst] = w[c].im;
-        }
-    }
+    float f;
+    if constexpr (SP == F16S) asm("v_cvt_f32_f16 %0, %1" : "=v"(f) : "v"(w));
+    else f = bf16_to_float((uint16_t)(w & 0xFFFFu));
+    return f;
 }
-
-template <int SP, int MU>
-__device__ __forceinline__ void hop_forward(float (*rl)[kBMax], const BlockGeom& B, const int l[4],
-                                            int t, const cx<float> u[6], cx<float> d,
-                                            cx<float> v[12])
+template <int SP>
+__device__ __forceinline__ float high16(uint32_t w)
 {
-    if (l[MU] < B.bs[MU] - 1) {
-        const int src = t + B.lstride[MU];
-        cx<float> s[12], h[6], w[6];
-#pragma unroll
-        for (int c = 0; c < 12; ++c) s[c] = {rl[2 * c][src], rl[2 * c + 1][src]};
-        project<float, MU, -1>(s, h);
-        su3_mul<float, false>(u, d, h, w);
-        expand_add<float, MU, -1>(w, v);
-    }
+    float f;
+    if constexpr (SP == F16S)
+        asm("v_cvt_f32_f16_sdwa %0, %1 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_1" : "=v"(f) : "v"(w));
+    else f = bf16_to_float((uint16_t)(w >> 16));
+    return f;
 }
 
 template <int MU, int N = kBMax>
@@ -137,14 +136,7 @@ struct SiteOps<SP, true> {
     uint32_t lk[4][7];  // per link: rows 0, 1 (12 values) and det U (2 values)
     __device__ __forceinline__ static float widen(uint32_t w, int hi)
     {
-        const uint16_t b = hi ? (uint16_t)(w >> 16) : (uint16_t)(w & 0xFFFFu);
-        if constexpr (SP == F16S) {
-            _Float16 h;
-            __builtin_memcpy(&h, &b, 2);
-            return (float)h;
-        } else {
-            return bf16_to_float(b);
-        }
+        return hi ? high16<SP>(w) : low16<SP>(w);
     }
     __device__ __forceinline__ void load(const Geom& g, const void* clover, const void* links,
                                          const void* dets, int par, int i)
@@ -196,58 +188,6 @@ struct SiteOps<SP, true> {
         }
     }
 };
-
-// w = M h (DAGGER: M^+ h) with the full 3x3 matrix M, for both spin components of h
-template <bool DAGGER>
-__device__ __forceinline__ void mat_mul(const cx<float> m[9], const cx<float> h[6], cx<float> w[6])
-{
-#pragma unroll
-    for (int a = 0; a < 2; ++a) {
-        const cx<float> h0 = h[3 * a], h1 = h[3 * a + 1], h2 = h[3 * a + 2];
-#pragma unroll
-        for (int r = 0; r < 3; ++r) {
-            if (!DAGGER)
-                w[3 * a + r] = cmadd(cmadd(m[3 * r] * h0, m[3 * r + 1], h1), m[3 * r + 2], h2);
-            else
-                w[3 * a + r] = cmadd_conj(cmadd_conj(cmul_conj(m[r], h0), m[3 + r], h1), m[6 + r], h2);
-        }
-    }
-}
-
-// direction MU of a block-D application for this lane: the hand-over of U^+ (1 + gamma) r
-// to the +MU neighbour (read by it after the barrier) and the forward hop from it, with the
-// link widened and its third row rebuilt once for both
-template <int SP, int MU>
-__device__ __forceinline__ void push_and_forward(float (*hb)[12][kBMax], float (*rl)[kBMax],
-                                                 const BlockGeom& B, const int l[4], int t,
-                                                 const cx<float> r[12], const SiteOps<SP>& so,
-                                                 cx<float> v[12])
-{
-    if (l[MU] < B.bs[MU] - 1) {
-        cx<float> u[6], d, m[9];
-        so.template link<MU>(u, d);
-        m[6] = d * conj_(cmadd(u[1] * u[5], -u[2], u[4]));
-        m[7] = d * conj_(cmadd(u[2] * u[3], -u[0], u[5]));
-        m[8] = d * conj_(cmadd(u[0] * u[4], -u[1], u[3]));
-#pragma unroll
-        for (int c = 0; c < 6; ++c) m[c] = u[c];
-        const int nb = t + B.lstride[MU];
-        cx<float> h[6], w[6];
-        project<float, MU, +1>(r, h);
-        mat_mul<true>(m, h, w);
-#pragma unroll
-        for (int c = 0; c < 6; ++c) {
-            hb[MU][2 * c][nb] = w[c].re;
-            hb[MU][2 * c + 1][nb] = w[c].im;
-        }
-        cx<float> sn[12];
-#pragma unroll
-        for (int c = 0; c < 12; ++c) sn[c] = {rl[2 * c][nb], rl[2 * c + 1][nb]};
-        project<float, MU, -1>(sn, h);
-        mat_mul<false>(m, h, w);
-        expand_add<float, MU, -1>(w, v);
-    }
-}
 
 // The same hand-over and forward hop with the neighbour's lane given explicitly (-1: the
 // neighbour is outside the block), for blocks whose lanes are not numbered by site
@@ -332,37 +272,265 @@ __device__ __forceinline__ void cross_hops(const Geom& g, const BlockGeom& B, co
 // between the two colours (Fig. 3 right) done by the receiving blocks, in FP32 on the loaded
 // values, instead of a separate pass over the lattice (sap_boundary_kernel) that rounds r
 // to storage once more.
+// A site has at most one such hop per direction (unless the block is one site wide there),
+// so the four neighbours and links are loaded together, as stored, before any is used.
+template <int SP>
+struct CrossHop {
+    u32x4 s[Traits<SP>::SPIN_CHUNKS], l[Traits<SP>::LINK_CHUNKS];
+    float2 d;
+
+    template <int MU>
+    __device__ __forceinline__ void load(const Geom& g, const BlockGeom& B, const void* delta, const void* links,
+                                         const void* dets, int par, int i, const int x[4], int lex,
+                                         const int lc[4])
+    {
+        const bool up = lc[MU] == B.bs[MU] - 1;
+        if (!up && lc[MU] != 0) return;
+        const int j = (up ? lex_fwd(g, x, lex, MU) : lex_bwd(g, x, lex, MU)) >> 1;
+        const long sb = chunk_at(g.Vh, Traits<SP>::SPIN_CHUNKS, 1 - par, 0, j);
+#pragma unroll
+        for (int k = 0; k < Traits<SP>::SPIN_CHUNKS; ++k) s[k] = ((const u32x4*)delta)[sb + (long)k * kSB];
+        const int row = (up ? par : 1 - par) * 4 + MU, li = up ? i : j;
+#pragma unroll
+        for (int k = 0; k < Traits<SP>::LINK_CHUNKS; ++k)
+            l[k] = ((const u32x4*)links)[chunk_at(g.Vh, Traits<SP>::LINK_CHUNKS, row, k, li)];
+        if (SP == F32) d = ((const float2*)dets)[(long)row * g.Vh + li];
+    }
+    template <int MU>
+    __device__ __forceinline__ void add(const Geom& g, const BlockGeom& B, const int x[4], const int lc[4],
+                                        cx<float> acc[12]) const
+    {
+        const bool up = lc[MU] == B.bs[MU] - 1;
+        if (!up && lc[MU] != 0) return;
+        float v[24], w[Traits<SP>::LINK_CHUNKS * Traits<SP>::PER_CHUNK];
+        widen(s, v);
+        widen(l, w);
+        cx<float> sp[12], u[6], h[6], o[6];
+#pragma unroll
+        for (int c = 0; c < 12; ++c) sp[c] = {v[2 * c], v[2 * c + 1]};
+#pragma unroll
+        for (int c = 0; c < 6; ++c) u[c] = {w[2 * c], w[2 * c + 1]};
+        cx<float> det;
+        if constexpr (SP == F32) det = {d.x, d.y};
+        else det = {w[12], w[13]};
+        const float sg = MU == 0 && g.bc_t < 0 && x[0] == (up ? g.L[0] - 1 : 0) ? -1.f : 1.f;
+        if (up) {
+            project<float, MU, -1>(sp, h);
+#pragma unroll
+            for (int c = 0; c < 6; ++c) h[c] = scale(h[c], sg);
+            su3_mul<float, false>(u, det, h, o);
+            expand_add<float, MU, -1>(o, acc);
+        } else {
+            project<float, MU, +1>(sp, h);
+#pragma unroll
+            for (int c = 0; c < 6; ++c) h[c] = scale(h[c], sg);
+            su3_mul<float, true>(u, det, h, o);
+            expand_add<float, MU, +1>(o, acc);
+        }
+    }
+    template <int N>
+    __device__ __forceinline__ static void widen(const u32x4 (&raw)[N], float* v)
+    {
+        using T = Traits<SP>;
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            Chunk<SP> c;
+            __builtin_memcpy(&c, &raw[k], 16);
+#pragma unroll
+            for (int j = 0; j < T::PER_CHUNK; ++j) v[k * T::PER_CHUNK + j] = to_real<SP>(c.v[j]);
+        }
+    }
+};
+
+// (lc: the site's coordinates within its block)
 template <int SP>
 __device__ __forceinline__ void apply_cross_hops(const Geom& g, const BlockGeom& B, const void* delta,
                                                  const void* links, const void* dets, int par,
-                                                 int i, const int x[4], int lex, cx<float> r[12])
+                                                 int i, const int x[4], int lex, const int lc[4],
+                                                 cx<float> r[12])
 {
     if (!delta) return;
     cx<float> acc[12];
 #pragma unroll
     for (int c = 0; c < 12; ++c) acc[c] = {0.f, 0.f};
-    bool any = false;
-    cross_hops<SP, 0>(g, B, delta, links, dets, par, i, x, lex, acc, any);
-    cross_hops<SP, 1>(g, B, delta, links, dets, par, i, x, lex, acc, any);
-    cross_hops<SP, 2>(g, B, delta, links, dets, par, i, x, lex, acc, any);
-    cross_hops<SP, 3>(g, B, delta, links, dets, par, i, x, lex, acc, any);
+    if (B.bs[0] > 1 && B.bs[1] > 1 && B.bs[2] > 1 && B.bs[3] > 1) {
+        CrossHop<SP> h0, h1, h2, h3;
+        h0.template load<0>(g, B, delta, links, dets, par, i, x, lex, lc);
+        h1.template load<1>(g, B, delta, links, dets, par, i, x, lex, lc);
+        h2.template load<2>(g, B, delta, links, dets, par, i, x, lex, lc);
+        h3.template load<3>(g, B, delta, links, dets, par, i, x, lex, lc);
+        h0.template add<0>(g, B, x, lc, acc);
+        h1.template add<1>(g, B, x, lc, acc);
+        h2.template add<2>(g, B, x, lc, acc);
+        h3.template add<3>(g, B, x, lc, acc);
+    } else {
+        bool any = false;
+        cross_hops<SP, 0>(g, B, delta, links, dets, par, i, x, lex, acc, any);
+        cross_hops<SP, 1>(g, B, delta, links, dets, par, i, x, lex, acc, any);
+        cross_hops<SP, 2>(g, B, delta, links, dets, par, i, x, lex, acc, any);
+        cross_hops<SP, 3>(g, B, delta, links, dets, par, i, x, lex, acc, any);
+    }
 #pragma unroll
     for (int c = 0; c < 12; ++c) r[c] = r[c] + scale(acc[c], 0.5f);  // hops carry -1/2
 }
 
-// 16-bit storage: registers for two waves per SIMD (two 256-site blocks per CU)
+// A block's links in LDS, as stored (16-byte chunks; FP32 keeps det U beside them).
 template <int SP>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SP == F32 ? 1 : 2)))
-void sap_mr_kernel(Geom g, BlockGeom B, int colour, int nmr,
-                                                     void* __restrict__ rs, void* __restrict__ psis,
-                                                     void* __restrict__ delta,
-                                                     const void* __restrict__ links,
-                                                     const void* __restrict__ dets,
-                                                     const void* __restrict__ clover,
-                                                     RhsStride bat, SapAdapt ad)
+struct BlockLinks {
+    static constexpr int NC = Traits<SP>::LINK_CHUNKS;
+    u32x4 c[NC][kBlockLinks];
+    float2 d[SP == F32 ? kBlockLinks : 1];
+
+    // this lane's forward links, those whose other end is inside the block
+    __device__ __forceinline__ void fill(const Geom& g, const BlockGeom& B, const int l[4], const int ln[4],
+                                         const void* links, const void* dets, int par, int i)
+    {
+#pragma unroll
+        for (int mu = 0; mu < 4; ++mu) {
+            if (l[mu] == B.bs[mu] - 1) continue;
+            const int row = par * 4 + mu;
+#pragma unroll
+            for (int k = 0; k < NC; ++k) c[k][ln[mu]] = ((const u32x4*)links)[chunk_at(g.Vh, NC, row, k, i)];
+            if (SP == F32) d[ln[mu]] = ((const float2*)dets)[(long)row * g.Vh + i];
+        }
+    }
+    __device__ __forceinline__ void get(int n, cx<float> u[6], cx<float>& det) const
+    {
+        uint32_t w[4 * NC];
+#pragma unroll
+        for (int k = 0; k < NC; ++k) {
+            const u32x4 raw = c[k][n];
+            w[4 * k] = raw.x;
+            w[4 * k + 1] = raw.y;
+            w[4 * k + 2] = raw.z;
+            w[4 * k + 3] = raw.w;
+        }
+        if constexpr (SP == F32) {
+            __builtin_memcpy(u, w, 48);
+            det = {d[n].x, d[n].y};
+        } else {
+#pragma unroll
+            for (int k = 0; k < 6; ++k) u[k] = {low16<SP>(w[k]), high16<SP>(w[k])};
+            det = {low16<SP>(w[6]), high16<SP>(w[6])};
+        }
+    }
+};
+
+// numbers of this site's links (BlockGeom), one per direction
+__device__ __forceinline__ void link_numbers(const BlockGeom& B, const int l[4], int ln[4])
 {
-    __shared__ float rl[24][kBMax];
-    __shared__ float hb[4][12][kBMax];
+#pragma unroll
+    for (int mu = 0; mu < 4; ++mu)
+        ln[mu] = B.loff[mu] + l[0] * B.lcs[mu][0] + l[1] * B.lcs[mu][1] + l[2] * B.lcs[mu][2] + l[3] * B.lcs[mu][3];
+}
+
+// a spinor of a block in LDS, in float4 pieces [6][N] (one 16-byte access per piece)
+template <int N>
+__device__ __forceinline__ void lds_put(float4 (*r)[N], int t, const cx<float> v[12])
+{
+#pragma unroll
+    for (int k = 0; k < 6; ++k) r[k][t] = make_float4(v[2 * k].re, v[2 * k].im, v[2 * k + 1].re, v[2 * k + 1].im);
+}
+template <int N>
+__device__ __forceinline__ void lds_get(const float4 (*r)[N], int t, cx<float> v[12])
+{
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+        const float4 q = r[k][t];
+        v[2 * k] = {q.x, q.y};
+        v[2 * k + 1] = {q.z, q.w};
+    }
+}
+
+// v += both hops of direction MU into site l of the block from the spinors in r; `up` and
+// `down` are the places of the neighbours there, ln the number of the site's forward link
+template <int SP, int MU, int N>
+__device__ __forceinline__ void block_hops(const float4 (*r)[N], const BlockLinks<SP>& lk, const BlockGeom& B,
+                                           const int l[4], int ln, int up, int down, cx<float> v[12])
+{
+    if (l[MU] < B.bs[MU] - 1) {
+        cx<float> s[12], h[6], w[6], u[6], d;
+        lk.get(ln, u, d);
+        lds_get<N>(r, up, s);
+        project<float, MU, -1>(s, h);
+        su3_mul<float, false>(u, d, h, w);
+        expand_add<float, MU, -1>(w, v);
+    }
+    __builtin_amdgcn_sched_barrier(0);  // one hop's registers at a time
+    if (l[MU] > 0) {
+        cx<float> s[12], h[6], w[6], u[6], d;
+        lk.get(ln - B.lcs[MU][MU], u, d);
+        lds_get<N>(r, down, s);
+        project<float, MU, +1>(s, h);
+        su3_mul<float, true>(u, d, h, w);
+        expand_add<float, MU, +1>(w, v);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// A lane's diagonal term in the compact form (54 reals) as stored, widened where it is used;
+// opaque() keeps the optimiser from holding the widened values across steps.
+template <int SP>
+struct SiteDiag54 {
+    static constexpr int NC = Cl54Chunks<SP>::n;
+    uint32_t w[4 * NC];
+    __device__ __forceinline__ void load(const Geom& g, const void* cl, int par, int i)
+    {
+        const long base = chunk_at(g.Vh, NC, par, 0, i);
+#pragma unroll
+        for (int k = 0; k < NC; ++k) {
+            const Chunk<SP> c = load_chunk<SP>(cl, base + (long)k * kSB);
+            __builtin_memcpy(w + 4 * k, &c, 16);
+        }
+    }
+    __device__ __forceinline__ void opaque()
+    {
+        if (SP != F32)
+#pragma unroll
+            for (int k = 0; k < 27; ++k) asm volatile("" : "+v"(w[k]));
+    }
+    __device__ __forceinline__ float at(int k) const
+    {
+        if constexpr (SP == F32) {
+            float f;
+            __builtin_memcpy(&f, &w[k], 4);
+            return f;
+        } else {
+            return k & 1 ? high16<SP>(w[k >> 1]) : low16<SP>(w[k >> 1]);
+        }
+    }
+    __device__ __forceinline__ void apply(float c, const cx<float> v[12], cx<float> o[12]) const
+    {
+#pragma unroll
+        for (int blk = 0; blk < 2; ++blk) {
+            float hd[3], a[24];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) hd[k] = at(3 * blk + k);
+#pragma unroll
+            for (int k = 0; k < 24; ++k) a[k] = at((blk ? 30 : 6) + k);
+            cl54_block<float>(c, hd, a, a + 6, v + 6 * blk, o + 6 * blk);
+        }
+    }
+};
+
+// Block solve by nmr MR steps. What bounds it is latency: a wave issues a vector instruction
+// every 5 to 9 cycles at best, LDS and the two barriers of a step included, so the number of
+// waves beside it decides. Every lane gathers its hops: the neighbours' residuals and the
+// block's links (each read from HBM once) are in LDS, so a step needs two barriers (residuals
+// written; sums written) and a lane keeps only its residual, the correction and the compact
+// diagonal term in registers. That lets three 256-site blocks share a CU with 16-bit storage
+// (two with FP32). The form before it handed the backward hops over through LDS (48 KB more),
+// kept links and the full clover blocks in registers and took four barriers a step, at two
+// blocks per CU (one with FP32). One application at 24^3 x 48 (5 cycles, 4 steps, 4^4 blocks),
+// before and after: FP16 1729 -> 1480 us, BF16 1668 -> 1443, FP32 3426 -> 2400.
+template <int SP>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SP == F32 ? 2 : 3)))
+void sap_mr_kernel(Geom g, BlockGeom B, int colour, int nmr, void* __restrict__ rs, void* __restrict__ psis,
+                   void* __restrict__ delta, const void* __restrict__ links, const void* __restrict__ dets,
+                   const void* __restrict__ clover54, RhsStride bat, SapAdapt ad, const void* odelta)
+{
+    __shared__ float4 rl[6][kBMax];
+    __shared__ BlockLinks<SP> lk;
     __shared__ double red[4][3];
     __shared__ double red2[2][4];
     // right-hand side `rhs` of a batch (fields at a fixed byte stride), block `blk` of the
@@ -372,7 +540,8 @@ void sap_mr_kernel(Geom g, BlockGeom B, int colour, int nmr,
     rs = (char*)rs + rhs * bat.fstride;
     psis = (char*)psis + rhs * bat.fstride;
     delta = (char*)delta + rhs * bat.fstride;
-    const int t = threadIdx.x;
+    if (odelta) odelta = (const char*)odelta + rhs * bat.fstride;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const int nw = B.bvol >> 6;
     // the blockIdx-th block of this colour (blocks per x3 row is even, so colours alternate)
     int b[4];
@@ -398,17 +567,18 @@ void sap_mr_kernel(Geom g, BlockGeom B, int colour, int nmr,
     const int lex = ((x[0] * g.L[1] + x[1]) * g.L[2] + x[2]) * g.L[3] + x[3];
     const int par = (x[0] + x[1] + x[2] + x[3]) & 1;
     const int i = lex >> 1;
+    int ln[4];
+    link_numbers(B, l, ln);
 
     cx<float> r[12], chi[12];
     load_spinor<SP>(rs, g.Vh, par, i, r);
-    SiteOps<SP> so;
-    so.load(g, clover, links, dets, par, i);
+    lk.fill(g, B, l, ln, links, dets, par, i);
+    apply_cross_hops<SP>(g, B, odelta, links, dets, par, i, x, lex, l, r);
+    SiteDiag54<SP> dg;
+    dg.load(g, clover54, par, i);
+    lds_put(rl, t, r);
 #pragma unroll
-    for (int c = 0; c < 12; ++c) {
-        chi[c] = {0.f, 0.f};
-        rl[2 * c][t] = r[c].re;
-        rl[2 * c + 1][t] = r[c].im;
-    }
+    for (int c = 0; c < 12; ++c) chi[c] = {0.f, 0.f};
     // adaptive exits (Sec. 3.2): the block residual norm before the first step and after
     // every step decides, uniformly in the workgroup, whether the MR loop goes on
     double prev = 0.0;
@@ -421,26 +591,22 @@ void sap_mr_kernel(Geom g, BlockGeom B, int colour, int nmr,
         prev = sqrt(block_sum((double)l2, red2[0], t, nw));
         go = !(prev < (double)ad.tol);
     }
+    __syncthreads();  // rl holds the block residual, lk the links
     for (int k = 0; k < nmr && go; ++k) {
-        __syncthreads();  // rl holds the current block residual
-        cx<float> v[12], vh[12];
+        // v = D_b r = -1/2 (-2 A r + hops inside the block), one accumulator; r is not held
+        // through the hops
+        cx<float> v[12];
+        dg.opaque();
+        dg.apply((float)g.cdiag, r, v);
 #pragma unroll
-        for (int c = 0; c < 12; ++c) vh[c] = {0.f, 0.f};
-        so.opaque();
-        push_and_forward<SP, 0>(hb, rl, B, l, t, r, so, vh);
-        push_and_forward<SP, 1>(hb, rl, B, l, t, r, so, vh);
-        push_and_forward<SP, 2>(hb, rl, B, l, t, r, so, vh);
-        push_and_forward<SP, 3>(hb, rl, B, l, t, r, so, vh);
-        __syncthreads();  // every pushed half spinor is in hb
-        hop_backward<0>(hb, l, t, vh);
-        hop_backward<1>(hb, l, t, vh);
-        hop_backward<2>(hb, l, t, vh);
-        hop_backward<3>(hb, l, t, vh);
-        // v = D_b r = A r - 1/2 (hops inside the block)
-        so.opaque();
-        so.diag(r, v);
+        for (int c = 0; c < 12; ++c) v[c] = scale(v[c], -2.f);
+        block_hops<SP, 0>(rl, lk, B, l, ln[0], t + B.lstride[0], t - B.lstride[0], v);
+        block_hops<SP, 1>(rl, lk, B, l, ln[1], t + B.lstride[1], t - B.lstride[1], v);
+        block_hops<SP, 2>(rl, lk, B, l, ln[2], t + B.lstride[2], t - B.lstride[2], v);
+        block_hops<SP, 3>(rl, lk, B, l, ln[3], t + B.lstride[3], t - B.lstride[3], v);
 #pragma unroll
-        for (int c = 0; c < 12; ++c) v[c] = v[c] - scale(vh[c], 0.5f);
+        for (int c = 0; c < 12; ++c) v[c] = scale(v[c], -0.5f);
+        lds_get(rl, t, r);
         // omega = (v, r) / (v, v) over the block
         float nre = 0.f, nim = 0.f, den = 0.f;
 #pragma unroll
@@ -450,19 +616,9 @@ void sap_mr_kernel(Geom g, BlockGeom B, int colour, int nmr,
             nim = z.im;
             den = fmar(v[c].re, v[c].re, fmar(v[c].im, v[c].im, den));
         }
-        double a0 = nre, a1 = nim, a2 = den;
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            a0 += __shfl_xor(a0, o, 64);
-            a1 += __shfl_xor(a1, o, 64);
-            a2 += __shfl_xor(a2, o, 64);
-        }
-        if ((t & 63) == 0) {
-            red[t >> 6][0] = a0;
-            red[t >> 6][1] = a1;
-            red[t >> 6][2] = a2;
-        }
-        __syncthreads();
+        const double part[3] = {nre, nim, den};
+        wave_sums<3>(part, lane, red[wave]);
+        __syncthreads();  // the sums are there, and every lane has read rl
         double s0 = 0.0, s1 = 0.0, s2 = 0.0;
         for (int w = 0; w < nw; ++w) {
             s0 += red[w][0];
@@ -476,21 +632,15 @@ void sap_mr_kernel(Geom g, BlockGeom B, int colour, int nmr,
             chi[c] = chi[c] + om * r[c];
             r[c] = r[c] - om * v[c];
         }
+        lds_put(rl, t, r);
         if (ad.on) {
             float l2 = 0.f;
 #pragma unroll
             for (int c = 0; c < 12; ++c) l2 += r[c].re * r[c].re + r[c].im * r[c].im;
-            double v2 = l2;
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) v2 += __shfl_xor(v2, o, 64);
-            if ((t & 63) == 0) red2[(k + 1) & 1][t >> 6] = v2;
+            const double v2 = wave_sum((double)l2);
+            if (lane == 0) red2[(k + 1) & 1][wave] = v2;
         }
-        __syncthreads();  // all lanes have read red and rl of this step
-#pragma unroll
-        for (int c = 0; c < 12; ++c) {
-            rl[2 * c][t] = r[c].re;
-            rl[2 * c + 1][t] = r[c].im;
-        }
+        __syncthreads();  // rl holds the new residual; red has been read
         ++nsteps;
         if (ad.on) {
             double c2 = 0.0;
@@ -605,7 +755,7 @@ void sap_mr_eo_kernel(Geom g, BlockGeom B, int colour, int nmr,
 
     cx<float> r[12];
     load_spinor<SP>(rs, g.Vh, par, i, r);
-    apply_cross_hops<SP>(g, B, odelta, links, dets, par, i, x, lex, r);
+    apply_cross_hops<SP>(g, B, odelta, links, dets, par, i, x, lex, l, r);
     SiteOps<SP> so;  // A on even sites, A^-1 on odd sites
     so.load(g, ev ? clover : cloverinv, links, dets, par, i);
 
@@ -792,35 +942,26 @@ int cycles_impl(qdw_op* op, const BlockGeom& B, int ncy, int nmr, void* rs, void
     const Geom& g = op->g;
     RhsStride bat = bat_in;
     bat.nrhs = nrhs;
-    const dim3 gmr(B.nblk / 2 * nrhs), gbd(walk_blocks(g) * nrhs);
+    const dim3 gmr(B.nblk / 2 * nrhs);
     for (int cy = 0; cy < ncy; ++cy)
         for (int c = 0; c < 2; ++c) {
-            if (eo) {
-                // the reduced block solve takes the hops of the other colour's last
-                // corrections into its residual as it loads it (cheaper there than a pass
-                // of its own: 191 against 168 + 33 us per colour at 24^3 x 48, FP16); after
-                // the last colour of the last cycle the residual is not used (only psi is),
-                // so that last update is not made
-                const void* od = cy == 0 && c == 0 ? nullptr : delta;
-                if (B.bs[3] % 2 == 0)
-                    sap_mr_eo_kernel<SP, true><<<gmr, B.bvol, 0, st>>>(
-                        g, B, c, nmr, rs, psis, delta, op->links[SP], op->det[SP], op->clover[SP],
-                        op->cloverinv[SP], bat, od);
-                else
-                    sap_mr_eo_kernel<SP, false><<<gmr, B.bvol, 0, st>>>(
-                        g, B, c, nmr, rs, psis, delta, op->links[SP], op->det[SP], op->clover[SP],
-                        op->cloverinv[SP], bat, od);
-                QDW_LAUNCH_CHECK();
-                continue;
-            }
-            // the plain block solve, at two waves per SIMD, hides the latency of those
-            // loads worse than a pass of their own (169 against 132 + 33 us)
-            sap_mr_kernel<SP><<<gmr, B.bvol, 0, st>>>(g, B, c, nmr, rs, psis, delta,
-                                                      op->links[SP], op->det[SP],
-                                                      op->clover[SP], bat, SapAdapt{});
-            QDW_LAUNCH_CHECK();
-            sap_boundary_kernel<SP><<<gbd, 2 * g.ts, 0, st>>>(g, B, c, rs, delta, op->links[SP],
-                                                              op->det[SP], bat);
+            // a block solve takes the hops of the other colour's last corrections into its
+            // residual as it loads it (cheaper there than a pass of its own over the
+            // lattice: plain blocks, FP16, 24^3 x 48: 148 against 159 us per colour); after
+            // the last colour of the last cycle the residual is not used (only psi is), so
+            // that last update is not made
+            const void* od = cy == 0 && c == 0 ? nullptr : delta;
+            if (!eo)
+                sap_mr_kernel<SP><<<gmr, B.bvol, 0, st>>>(g, B, c, nmr, rs, psis, delta, op->links[SP],
+                                                          op->det[SP], op->clover54[SP], bat, SapAdapt{}, od);
+            else if (B.bs[3] % 2 == 0)
+                sap_mr_eo_kernel<SP, true><<<gmr, B.bvol, 0, st>>>(
+                    g, B, c, nmr, rs, psis, delta, op->links[SP], op->det[SP], op->clover[SP],
+                    op->cloverinv[SP], bat, od);
+            else
+                sap_mr_eo_kernel<SP, false><<<gmr, B.bvol, 0, st>>>(
+                    g, B, c, nmr, rs, psis, delta, op->links[SP], op->det[SP], op->clover[SP],
+                    op->cloverinv[SP], bat, od);
             QDW_LAUNCH_CHECK();
         }
     return QDW_OK;
@@ -896,8 +1037,8 @@ int adaptive_impl(qdw_op* op, const void* rho, void* phi, double rho_norm, int n
         for (int c = 0; c < 2; ++c) {
             ad.steps = steps ? steps + (long)(2 * cy + c) * (B.nblk / 2) : nullptr;
             sap_mr_kernel<SP><<<gmr, B.bvol, 0, st>>>(g, B, c, nmr_max, rs, psis, delta,
-                                                      op->links[SP], op->det[SP], op->clover[SP],
-                                                      gate, ad);
+                                                      op->links[SP], op->det[SP], op->clover54[SP],
+                                                      gate, ad, nullptr);
             QDW_LAUNCH_CHECK();
             sap_boundary_kernel<SP><<<gbd, 2 * g.ts, 0, st>>>(g, B, c, rs, delta, op->links[SP],
                                                               op->det[SP], gate);
