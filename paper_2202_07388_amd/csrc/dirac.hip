@@ -238,29 +238,99 @@ void dw_kernel(Geom g, const void* __restrict__ links, const void* __restrict__ 
 }
 
 // Marching form: a workgroup owns one spatial tile (both parities) and walks the nt time
-// slices of its chunk in order. The time hops then never go to memory twice:
-//   * +t: at step t every lane loads the spinor its own lane will need at t+1; projected
-//     with the +t projector it is exactly the +t neighbour of the partner lane (the other
-//     parity, same even-odd index: the same spatial point one slice down), so it goes to
-//     the partner through LDS;
-//   * -t: at the end of step t each lane has its own spinor and its own forward t link in
-//     hand; it forms U_0^+ (1 -+ gamma_0) psi, the -t hop of the partner's site at t+1,
-//     and hands it over through LDS.
-// The lane's own spinor of a slice is loaded once, as the +t neighbour one step earlier,
-// and kept in registers for the clover term and the hand-over (a reload a step later
-// would find it evicted from L2); the t link likewise within a step.
-// Only the spatial hops read neighbours from memory, and they are done one step early: in
-// the step that loads slice t+1 (every lane its own site, all workgroups of an XCD at about
-// the same time), the lane also forms A psi and the six spatial hops of its site at t+1,
-// while those spinors are still in L2; the time hops are added in the next step, once the
-// partner has handed them over. Gathering a slice in the step after it was loaded found
-// most of it evicted (an XCD streams more than its 4 MB L2 per step) and read it from HBM
-// a second time. One barrier per step: the LDS buffers are double-buffered by slice
-// parity (see the step comments).
+// slices of its chunk in order. The tile's spinors of the newest slice are kept in LDS (each
+// lane loads its own site's once), and serve from there
+//   * the +t hop of the slice before: the +t neighbour of a site is the partner lane's spinor
+//     (the other parity, same even-odd index: the same spatial point one slice on);
+//   * the spatial hops that stay inside the tile (most of x3 and x2); only the others read a
+//     neighbour from memory;
+//   * the -t hop of the slice after: each lane forms U_0^+ (1 -+ gamma_0) psi of its own site
+//     with the forward t link that it has in hand and gives it to the partner through LDS.
+// A psi and the six spatial hops of a site are done one step early, in the step that loads
+// its slice (every lane its own site, all workgroups of an XCD at about the same time), while
+// the neighbours outside the tile are still in L2; the time hops are added in the next step.
+// Gathering a slice in the step after it was loaded found most of it evicted (an XCD streams
+// more than its 4 MB L2 per step) and read it from HBM a second time. Two barriers a step.
+// (In LDS a lane's values lie 64 lanes apart, so that one address and constant offsets reach
+// them all; with the lane count as the stride every value's address was held in a register.)
+template <class R>
+struct Tile {
+    // (typed as LDS: as generic pointers their loads and the global ones beside them are folded
+    // into one load of either)
+    template <class T> using Lds = __attribute__((address_space(3))) T;
+    Lds<u32x4>* p;     // [lane / 64][24 reals as 16-byte pieces][lane % 64]
+    Lds<R>* half;      // [lane / 64][12 reals][lane % 64]: transported -t neighbours
+    int base, n;  // spatial index of the tile's first site; sites of each parity
+    static constexpr int NP = 24 * sizeof(R) / 16;
+
+    __device__ __forceinline__ void put(int who, const cx<R> v[12]) const
+    {
+        u32x4 w[NP];
+        Lds<u32x4>* at = p + (who >> 6) * (NP * 64) + (who & 63);
+        __builtin_memcpy(w, v, sizeof(w));
+#pragma unroll
+        for (int q = 0; q < NP; ++q) at[q * 64] = w[q];
+    }
+    __device__ __forceinline__ void get(int who, cx<R> v[12]) const
+    {
+        u32x4 w[NP];
+        const Lds<u32x4>* at = p + (who >> 6) * (NP * 64) + (who & 63);
+#pragma unroll
+        for (int q = 0; q < NP; ++q) w[q] = at[q * 64];
+        __builtin_memcpy(v, w, sizeof(w));
+    }
+    __device__ __forceinline__ void put_half(int who, const cx<R> v[6]) const
+    {
+        Lds<R>* at = half + (who >> 6) * (12 * 64) + (who & 63);
+#pragma unroll
+        for (int q = 0; q < 6; ++q) {
+            at[(2 * q) * 64] = v[q].re;
+            at[(2 * q + 1) * 64] = v[q].im;
+        }
+    }
+    __device__ __forceinline__ void get_half(int who, cx<R> v[6]) const
+    {
+        const Lds<R>* at = half + (who >> 6) * (12 * 64) + (who & 63);
+#pragma unroll
+        for (int q = 0; q < 6; ++q) v[q] = {at[(2 * q) * 64], at[(2 * q + 1) * 64]};
+    }
+};
+
+// loads of spatial hop (MU, FWD) into site x of the slice in `tile`
+template <int P, int MU, bool FWD>
+__device__ __forceinline__ void tile_hop_load(const Geom& g, const Tile<typename Traits<P>::real>& tile,
+                                              const void* in, const void* links, const void* dets, int par,
+                                              int i, const int x[4], int lex, HopIn<P>& b)
+{
+    const int j = (FWD ? lex_fwd(g, x, lex, MU) : lex_bwd(g, x, lex, MU)) >> 1;
+    const int off = j - x[0] * g.S - tile.base;
+    const bool inside = (unsigned)off < (unsigned)tile.n;
+    tile.get((1 - par) * g.ts + (inside ? off : 0), b.s);
+    if (!inside) load_spinor<P>(in, g.Vh, 1 - par, j, b.s);
+    if (FWD) load_link<P>(links, dets, g.Vh, par, i, MU, b.u, b.d);       // U_mu(x)
+    else load_link<P>(links, dets, g.Vh, 1 - par, j, MU, b.u, b.d);      // U_mu(x - mu)
+}
+
+template <int P>
+__device__ __forceinline__ void tile_load_k(int k, const Geom& g, const Tile<typename Traits<P>::real>& tile,
+                                            const void* in, const void* links, const void* dets, int par, int i,
+                                            const int x[4], int lex, HopIn<P>& b)
+{
+    switch (k) {
+    case 2: tile_hop_load<P, 1, true>(g, tile, in, links, dets, par, i, x, lex, b); break;
+    case 3: tile_hop_load<P, 1, false>(g, tile, in, links, dets, par, i, x, lex, b); break;
+    case 4: tile_hop_load<P, 2, true>(g, tile, in, links, dets, par, i, x, lex, b); break;
+    case 5: tile_hop_load<P, 2, false>(g, tile, in, links, dets, par, i, x, lex, b); break;
+    case 6: tile_hop_load<P, 3, true>(g, tile, in, links, dets, par, i, x, lex, b); break;
+    default: tile_hop_load<P, 3, false>(g, tile, in, links, dets, par, i, x, lex, b); break;
+    }
+}
+
 template <int P, bool DAG, bool PIPE>
-__device__ __forceinline__ void march_site_hops(const Geom& g, const void* in, const void* links,
-                                                const void* dets, int par, int i, const int x[4],
-                                                int lex, cx<typename Traits<P>::real> acc[12])
+__device__ __forceinline__ void march_site_hops(const Geom& g, const Tile<typename Traits<P>::real>& tile,
+                                                const void* in, const void* links, const void* dets, int par,
+                                                int i, const int x[4], int lex,
+                                                cx<typename Traits<P>::real> acc[12])
 {
     if constexpr (!PIPE) {
         // the six spatial hops (loop steps 2..7 of dw_kernel), one register buffer
@@ -269,38 +339,43 @@ __device__ __forceinline__ void march_site_hops(const Geom& g, const void* in, c
         for (int k = 2; k < 8; ++k) {
             int ii = i, ll = lex, xx[4] = {x[0], x[1], x[2], x[3]};
             asm volatile("" : "+v"(ii), "+v"(ll), "+v"(xx[0]), "+v"(xx[1]), "+v"(xx[2]), "+v"(xx[3]));
-            load_k<P>(k, g, in, links, dets, par, ii, xx, ll, A);
+            tile_load_k<P>(k, g, tile, in, links, dets, par, ii, xx, ll, A);
             compute_k<P, DAG, true>(k, g, xx, A, acc);
         }
         return;
     }
     // the six spatial hops (loop steps 2..7 of dw_kernel), two register buffers
     HopIn<P> A, B;
-    load_k<P>(2, g, in, links, dets, par, i, x, lex, A);
+    tile_load_k<P>(2, g, tile, in, links, dets, par, i, x, lex, A);
 #pragma unroll 1
     for (int k = 2; k < 8; k += 2) {
         int ii = i, ll = lex, xx[4] = {x[0], x[1], x[2], x[3]};
         asm volatile("" : "+v"(ii), "+v"(ll), "+v"(xx[0]), "+v"(xx[1]), "+v"(xx[2]), "+v"(xx[3]));
-        load_k<P>(k + 1, g, in, links, dets, par, ii, xx, ll, B);
+        tile_load_k<P>(k + 1, g, tile, in, links, dets, par, ii, xx, ll, B);
         compute_k<P, DAG, true>(k, g, xx, A, acc);
-        if (k + 2 < 8) load_k<P>(k + 2, g, in, links, dets, par, ii, xx, ll, A);
+        if (k + 2 < 8) tile_load_k<P>(k + 2, g, tile, in, links, dets, par, ii, xx, ll, A);
         compute_k<P, DAG, true>(k + 1, g, xx, B, acc);
     }
 }
 
+// bytes of LDS for ts sites per parity: a spinor and a half spinor per lane
+template <class R>
+constexpr size_t march_lds(int ts)
+{
+    return (size_t)2 * ts * 36 * sizeof(R);
+}
+inline size_t march_lds(int prec, int ts) { return prec == F64 ? march_lds<double>(ts) : march_lds<float>(ts); }
+
 template <int P, bool DAG, bool PIPE, int EPI>
-__global__ __launch_bounds__(256) void dw_march_kernel(Geom g, const void* __restrict__ links,
-                                                       const void* __restrict__ dets,
-                                                       const void* __restrict__ clover, Epi epi,
-                                                       RhsTable tab)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
+void dw_march_kernel(Geom g, const void* __restrict__ links, const void* __restrict__ dets,
+                     const void* __restrict__ clover, Epi epi, RhsTable tab)
 {
     using R = typename Traits<P>::real;
     constexpr int SGF = DAG ? +1 : -1;  // projector of the +t hop: 1 + SGF gamma_0
     constexpr int SGB = -SGF;           // of the -t hop
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int nl = blockDim.x;  // 2 ts lanes
-    R* hp = (R*)smem;           // [2 slots][12 reals][nl]: projected +t neighbours
-    R* pw = hp + 2 * 12 * nl;   // [2 slots][12 reals][nl]: transported -t neighbours
     const int logical = xcd_tile(blockIdx.x, gridDim.x);
     const int wg = logical / tab.nrhs;
     const int rhs = logical - wg * tab.nrhs;
@@ -313,109 +388,100 @@ __global__ __launch_bounds__(256) void dw_march_kernel(Geom g, const void* __res
     const int par = tid >= g.ts ? 1 : 0;
     const int lane = tid - par * g.ts;
     const int partner = tid + (par ? -g.ts : g.ts);
-    int k;
-    bool valid;
+    Tile<R> tile{(typename Tile<R>::template Lds<u32x4>*)smem,
+                 (typename Tile<R>::template Lds<R>*)(smem + 24 * sizeof(R) * nl), 0, 0};
     if (g.walk == 0) {
-        k = s * g.ts + lane;
-        valid = k < g.S;
+        tile.base = s * g.ts;
+        tile.n = min(g.ts, g.S - tile.base);
     } else {
         const int b = s / g.L[1], x1 = s - b * g.L[1];
-        k = x1 * g.slab + b * g.ts + lane;
-        valid = b * g.ts + lane < g.slab;
+        tile.base = x1 * g.slab + b * g.ts;
+        tile.n = min(g.ts, g.slab - b * g.ts);
     }
-    auto put6 = [&](R* buf, int slot, int who, const cx<R> v[6]) {
-#pragma unroll
-        for (int q = 0; q < 6; ++q) {
-            buf[(slot * 12 + 2 * q) * nl + who] = v[q].re;
-            buf[(slot * 12 + 2 * q + 1) * nl + who] = v[q].im;
-        }
-    };
-    auto get6 = [&](const R* buf, int slot, cx<R> v[6]) {
-#pragma unroll
-        for (int q = 0; q < 6; ++q)
-            v[q] = {buf[(slot * 12 + 2 * q) * nl + tid], buf[(slot * 12 + 2 * q + 1) * nl + tid]};
-    };
-    // U_0(y)^+ (1 + SGB gamma_0) psi(y) for the partner's site one slice up (sign when the
-    // hop wraps from T-1 to 0)
-    auto push = [&](int t, int slot, const cx<R> sp[12], const cx<R> u[6], cx<R> d) {
-        cx<R> h[6], w[6];
+    // (a lane past the tile's end does the last site again, without storing it: a branch around
+    // each step kept two copies of what lives across it)
+    const bool valid = lane < tile.n;
+    const int k = tile.base + min(lane, tile.n - 1);
+    // U_0(y)^+ (1 + SGB gamma_0) psi(y), y the lane's site at slice t: the -t hop of the
+    // partner's site one slice up (sign when the hop wraps from T-1 to 0)
+    auto transport = [&](int t, const cx<R> sp[12], const cx<R> u[6], cx<R> d, cx<R> w[6]) {
+        cx<R> h[6];
         project<R, 0, SGB>(sp, h);
         if (g.bc_t < 0 && t == g.L[0] - 1) {
 #pragma unroll
             for (int q = 0; q < 6; ++q) h[q] = {-h[q].re, -h[q].im};
         }
         su3_mul<R, true>(u, d, h, w);
-        put6(pw, slot, partner, w);
     };
-    // A psi plus the six spatial hops (scaled by -1/2) of this lane's site at slice tt,
-    // whose spinor `sp` the lane holds
-    auto site_part = [&](int tt, const cx<R> sp[12], cx<R> acc[12]) {
+    // A psi plus the six spatial hops (scaled by -1/2) of this lane's site at slice tt, the
+    // slice in `tile`
+    auto site_part = [&](int tt, cx<R> acc[12]) {
         const int i = tt * g.S + k;
         int x[4], lex;
         eo_coords(g, par, i, x, lex);
-        clover54_apply<P>(clover, g.Vh, par, i, (R)g.cdiag, sp, acc);
-        march_site_hops<P, DAG, PIPE>(g, in, links, dets, par, i, x, lex, acc);
+        {
+            cx<R> sp[12];
+            tile.get(tid, sp);
+            clover54_apply<P>(clover, g.Vh, par, i, (R)g.cdiag, sp, acc);
+        }
+        march_site_hops<P, DAG, PIPE>(g, tile, in, links, dets, par, i, x, lex, acc);
     };
-    // the lane's own spinor of the current slice stays in registers from the step that
-    // loaded it for the partner (a reload one step later would come from HBM again), and
-    // so does the accumulator of the current slice, begun in the step before
-    cx<R> own[12], acc[12];
+    // the accumulator of the current slice, begun in the step before
+    cx<R> acc[12];
     double sum = 0.0;
-    if (valid) {
+    {
         const int tp = t0 == 0 ? g.L[0] - 1 : t0 - 1;
-        cx<R> u[6], d;
-        load_spinor<P>(in, g.Vh, par, tp * g.S + k, own);
+        cx<R> sp[12], u[6], d, w[6];
+        load_spinor<P>(in, g.Vh, par, tp * g.S + k, sp);
         load_link<P>(links, dets, g.Vh, par, tp * g.S + k, 0, u, d);
-        push(tp, t0 & 1, own, u, d);
-        load_spinor<P>(in, g.Vh, par, t0 * g.S + k, own);
-        site_part(t0, own, acc);
+        transport(tp, sp, u, d, w);
+        tile.put_half(partner, w);
+        load_spinor<P>(in, g.Vh, par, t0 * g.S + k, sp);
+        tile.put(tid, sp);
     }
-    for (int step = 0; step < g.nt; ++step) {
+    __syncthreads();
+    site_part(t0, acc);
+    for (int step = 0;; ++step) {
         const int t = t0 + step;
         const int tn = t + 1 == g.L[0] ? 0 : t + 1;
-        // (1) the spinor this lane owns at t+1, projected for the partner's +t hop; slot
-        //     (t+1)&1 was last read two steps ago, before the previous barrier
-        cx<R> nxt[12];
-        if (valid) {
-            cx<R> h[6];
-            load_spinor<P>(in, g.Vh, par, tn * g.S + k, nxt);
-            project<R, 0, SGF>(nxt, h);
-            put6(hp, (t + 1) & 1, partner, h);
+        const int i = t * g.S + k;
+        // (1) the spinor of the lane's site at t+1; the site's forward t link, which serves
+        //     the +t hop and the partner's -t hop at t+1
+        cx<R> nxt[12], u0[6], d0, wn[6], wb[6];
+        load_spinor<P>(in, g.Vh, par, tn * g.S + k, nxt);
+        load_link<P>(links, dets, g.Vh, par, i, 0, u0, d0);
+        {
+            // (read again: kept from site_part it would take registers through the hops)
+            int me = tid;
+            asm volatile("" : "+v"(me));
+            cx<R> own[12];
+            tile.get(me, own);
+            transport(t, own, u0, d0, wn);
         }
-        __syncthreads();
-        if (valid) {
-            const int i = t * g.S + k;
-            const int x0 = t;  // the time coordinate of the site
-            // the site's forward t link serves the +t hop and the hand-over below
-            cx<R> u0[6], d0;
-            load_link<P>(links, dets, g.Vh, par, i, 0, u0, d0);
-            // (2) the partner's -t hop at t+1; slot (t+1)&1 was read one step ago, before
-            //     this step's barrier
-            if (step + 1 < g.nt) push(t, (t + 1) & 1, own, u0, d0);
-            {
-                // +t: U_0(x) times the projected neighbour from the partner
-                cx<R> h[6], w[6];
-                get6(hp, (t + 1) & 1, h);
-                const R f = (g.bc_t < 0 && x0 == g.L[0] - 1) ? (R)0.5 : (R)-0.5;
+        __syncthreads();  // slice t in the tile has been read, with its -t hops given
+        tile.put(tid, nxt);
+        tile.get_half(tid, wb);
+        __syncthreads();  // the tile holds slice t+1, and the -t hops have been read
+        tile.put_half(partner, wn);
+        {
+            // +t: U_0(x) times the projected neighbour
+            cx<R> sp[12], h[6], w[6];
+            tile.get(partner, sp);
+            project<R, 0, SGF>(sp, h);
+            const R f = (g.bc_t < 0 && t == g.L[0] - 1) ? (R)0.5 : (R)-0.5;
 #pragma unroll
-                for (int q = 0; q < 6; ++q) h[q] = scale(h[q], f);
-                su3_mul<R, false>(u0, d0, h, w);
-                expand_add<R, 0, SGF>(w, acc);
-                // -t: already transported by the partner
-                get6(pw, t & 1, w);
+            for (int q = 0; q < 6; ++q) h[q] = scale(h[q], f);
+            su3_mul<R, false>(u0, d0, h, w);
+            expand_add<R, 0, SGF>(w, acc);
+            // -t: already transported by the partner
 #pragma unroll
-                for (int q = 0; q < 6; ++q) w[q] = scale(w[q], (R)-0.5);
-                expand_add<R, 0, SGB>(w, acc);
-            }
-            store_out<P, EPI>(out, epi, g.Vh, par, i, acc, sum);
-            // (3) the next slice's clover term and spatial hops, on the spinors loaded in
-            //     this step
-            if (step + 1 < g.nt) {
-#pragma unroll
-                for (int q = 0; q < 12; ++q) own[q] = nxt[q];
-                site_part(tn, own, acc);
-            }
+            for (int q = 0; q < 6; ++q) wb[q] = scale(wb[q], (R)-0.5);
+            expand_add<R, 0, SGB>(wb, acc);
         }
+        if (valid) store_out<P, EPI>(out, epi, g.Vh, par, i, acc, sum);
+        if (step + 1 == g.nt) break;
+        // (2) the next slice's clover term and spatial hops
+        site_part(tn, acc);
     }
     if constexpr (EPI != EPI_NONE) grid_sums<1>(&sum, epi.sums, blockIdx.x, gridDim.x);
 }
@@ -711,7 +777,7 @@ void dw_split_kernel(Geom g, const void* psi, const void* __restrict__ links,
 // 10.6 (FP64 D), 4.2 / 8.4 (FP32), 3.9 / 9.0 (FP16).
 inline bool split_form(int P, bool schur, long sites)
 {
-    constexpr long kD[4] = {40000, 80000, 90000, 90000}, kSchur[4] = {85000, 120000, 200000, 200000};
+    constexpr long kD[4] = {40000, 70000, 90000, 90000}, kSchur[4] = {85000, 120000, 200000, 200000};
     return sites <= (schur ? kSchur[P] : kD[P]);
 }
 
@@ -743,13 +809,14 @@ int schur_launch_t(qdw_op* op, const void* in, void* out, const Epi& epi, hipStr
 }
 
 // the operator's geometry with the D kernel's own shape for precision P (the default
-// marching shape: with the walk chunk for this many fields)
-inline Geom shaped(const qdw_op* op, int P, int nrhs)
+// marching shape: with the walk chunk and pipelining for this many fields)
+inline Geom shaped(const qdw_op* op, int P, int nrhs, bool& pipe)
 {
     Geom g = op->g;
     const auto& s = op->dw_shape[P];
-    const int nt = op->dw_auto[P] && s.march && nrhs > 1 ? march_chunk(g, P, nrhs) : s.nt;
-    set_walk(g, s.ts, nt, s.walk);
+    const MarchShape m = op->dw_auto[P] && s.march && nrhs > 1 ? march_shape(g, P, nrhs) : MarchShape{s.nt, s.pipe};
+    pipe = m.pipe;
+    set_walk(g, s.ts, m.nt, s.walk);
     return g;
 }
 
@@ -757,7 +824,8 @@ template <int P, bool DAG, int EPI>
 int launch(qdw_op* op, const RhsTable& tab, const Epi& epi, hipStream_t st, bool split = true)
 {
     const int nrhs = tab.nrhs;
-    const Geom g = shaped(op, P, nrhs);
+    bool pipe;
+    const Geom g = shaped(op, P, nrhs, pipe);
     if (split && op->dw_auto[P] && split_form(P, false, (long)g.V * nrhs)) {
         const int nblk = 2 * (padded(g.Vh) / kSB) * nrhs;
         dw_split_kernel<P, 0, DAG, EPI><<<nblk, 512, 0, st>>>(g, nullptr, op->links[P], op->det[P],
@@ -768,9 +836,8 @@ int launch(qdw_op* op, const RhsTable& tab, const Epi& epi, hipStream_t st, bool
     if (op->dw_shape[P].march) {
         using R = typename Traits<P>::real;
         const int nblk = (g.L[0] / g.nt) * g.ntile * nrhs;
-        const size_t lds = (size_t)2 * 2 * 12 * (2 * g.ts) * sizeof(R);
-        static_assert(sizeof(R) == 8 || sizeof(R) == 4, "real type");
-        if (op->dw_shape[P].pipe)
+        const size_t lds = march_lds<R>(g.ts);
+        if (pipe)
             dw_march_kernel<P, DAG, true, EPI><<<nblk, 2 * g.ts, lds, st>>>(
                 g, op->links[P], op->det[P], op->clover54[P], epi, tab);
         else
@@ -780,7 +847,7 @@ int launch(qdw_op* op, const RhsTable& tab, const Epi& epi, hipStream_t st, bool
         return QDW_OK;
     }
     const int nblk = walk_blocks(g) * nrhs;
-    if (op->dw_shape[P].pipe)
+    if (pipe)
         dw_kernel<P, DAG, true, EPI><<<nblk, 2 * g.ts, 0, st>>>(g, op->links[P], op->det[P], op->clover54[P],
                                                                 epi, tab);
     else
@@ -1080,9 +1147,6 @@ int fill_pattern(void* buf, size_t bytes, int prec, hipStream_t st)
     QDW_LAUNCH_CHECK();
     return QDW_OK;
 }
-
-// LDS of a marching workgroup: two double-buffered hand-over arrays of 12 reals per lane
-inline size_t march_lds(int prec, int ts) { return (size_t)96 * ts * (prec == F64 ? 8 : 4); }
 
 int check_shape(const qdw_op* op, int prec, int ts, int nt, int pipe, int walk, int march)
 {

@@ -596,10 +596,12 @@ extern "C" int qdw_create(const qdw_lattice* lat, const double* su3, const doubl
     }
     {
         // default D-kernel shapes (qdw_autotune or qdw_set_dw_shape may change them).
-        // FP64 and FP32: the marching form on 64-site tiles, with the walk chunk that
-        // march_chunk expects to be fastest
-        op->dw_shape[F64] = {64, march_chunk(g, F64, 1), 0, 0, 1};
-        op->dw_shape[F32] = {64, march_chunk(g, F32, 1), 1, 0, 1};
+        // FP64 and FP32: the marching form on 64-site tiles, with the walk chunk and
+        // pipelining that march_shape expects to be fastest
+        for (int p : {F64, F32}) {
+            const MarchShape s = march_shape(g, p, 1);
+            op->dw_shape[p] = {64, s.nt, s.pipe, 0, 1};
+        }
         // half-precision storage: the plain form (one lane per site, four waves per SIMD)
         // on 128-site tiles in chunks of two slices (T is even)
         op->dw_shape[F16S] = {128, 2, 0, 0, 0};

@@ -55,35 +55,48 @@ inline size_t spinor_bytes(const Geom& g, int prec)
     return (size_t)2 * padded(g.Vh) * 24 * r;
 }
 
-// The walk chunk nt of the marching form on 64-site tiles. A workgroup walks nt slices after
-// loading one more (0.2 of a step: its neighbour in time has mostly just loaded it), and the
-// machine holds 512 workgroups (FP64, one wave per SIMD) or 1024 (FP32, two) at once, so a
-// launch takes whole rounds and a rest. A step of a rest that fills a share x of the machine
-// is shorter than that of a full round, down to the latency of one step: measured 0.68 (FP64)
-// and 0.48 (FP32) of a full step. The chunk with the smallest sum wins. Measured against the
-// longest power of two that gives 512 workgroups: FP64 24^3 x 48 183 instead of 231 us
-// (nt 6 instead of 8), 24^4 81 instead of 106 us, 32^3 x 40 328 instead of 401 us; FP32
-// 32^3 x 64 275 instead of 318 us (nt 16 instead of 32), 16^3 x 32 18.0 instead of 22.8 us. Several fields of one launch
-// are that many times the workgroups.
-inline int march_chunk(const Geom& g, int prec, int nrhs)
+// The walk chunk and pipelining of the marching form on 64-site tiles. A workgroup walks nt
+// slices after loading one more (0.2 of a step: its neighbour in time has mostly just loaded
+// it), and the machine holds `room` workgroups at once: two waves per SIMD (FP64, and FP32 with
+// the pipelined hop loop) or three (FP32 without). A launch takes whole rounds and a rest; a
+// step of a rest that fills a share x of the machine is shorter than that of a full round, down
+// to the latency of one step. FP32 rounds of three waves are 1.5 times as long and 4 % slower
+// for the same work, so that form is for launches that would leave the other's last round
+// nearly empty. The choice with the smallest sum wins. Measured against the longest power of
+// two that gives 512 workgroups: FP64 24^3 x 48 175 instead of 230 us (nt 6 instead of 8), 32^3
+// x 40 334 instead of 397 us; FP32 32^3 x 64 262 instead of 315 us (nt 16 instead of 32); FP32
+// pipelined against not: 16.6 and 16.7 us at 20x14x18x22 (880 workgroups), 23.8 and 19.2 at
+// 24x20x18x16 (1080), 260 and 275 at 32^3 x 64.
+// Several fields of one launch are that many times the workgroups, and from three on the L2
+// holds fewer slices of each: short chunks are faster whatever the rounds (FP64, 4 fields, 32^3
+// x 64: 1690 us with nt 4, 1860 with 64; 8 fields 3200 and 4000), and so are three waves (FP32,
+// 4 fields, 24^3 x 48: 259 against 267 us), unless the launch is less than a round.
+struct MarchShape {
+    int nt, pipe;
+};
+inline MarchShape march_shape(const Geom& g, int prec, int nrhs)
 {
-    const int room = prec == F64 ? 512 : 1024, ntile = (g.S + 63) / 64;
+    const int ntile = (g.S + 63) / 64, most = nrhs < 3 ? 64 : prec == F64 ? 4 : 8;
     double best = 0.0;
-    int chunk = 0;
-    for (int nt = 1; nt <= 64 && nt <= g.L[0]; ++nt) {
-        if (g.L[0] % nt) continue;
-        const long nwg = (long)(g.L[0] / nt) * ntile * nrhs;
-        const double x = (double)(nwg % room) / room;
-        const double rest = nwg % room == 0 ? 0.0
-                            : prec == F64   ? std::max(0.68, 0.45 + 0.55 * x)
-                                            : std::max(0.48, 0.1 + 0.9 * x);
-        const double steps = (nt + 0.2) * ((double)(nwg / room) + rest);
-        if (!chunk || steps < best) {
-            best = steps;
-            chunk = nt;
+    MarchShape s{0, 0};
+    for (int pipe = prec == F32 ? 1 : 0; pipe >= 0; --pipe)
+        for (int nt = 1; nt <= most && nt <= g.L[0]; ++nt) {
+            if (g.L[0] % nt) continue;
+            const bool three = prec == F32 && !pipe;
+            const long nwg = (long)(g.L[0] / nt) * ntile * nrhs, room = three ? 1536 : 1024;
+            if (pipe && nrhs > 2 && nwg > room) continue;
+            const double x = (double)(nwg % room) / room;
+            const double rest = nwg % room == 0      ? 0.0
+                                : !three             ? std::max(0.48, 0.2 + 0.8 * x)
+                                : nrhs > 2           ? std::max(0.6, 0.3 + 0.7 * x)
+                                                     : std::max(0.5, x);
+            const double steps = (nt + 0.2) * ((double)(nwg / room) + rest) * (three ? 1.56 : 1.0);
+            if (!s.nt || steps < best) {
+                best = steps;
+                s = {nt, pipe};
+            }
         }
-    }
-    return chunk;
+    return s;
 }
 
 }  // namespace qdw
