@@ -814,9 +814,9 @@ inline Geom shaped(const qdw_op* op, int P, int nrhs, bool& pipe)
 {
     Geom g = op->g;
     const auto& s = op->dw_shape[P];
-    const MarchShape m = op->dw_auto[P] && s.march && nrhs > 1 ? march_shape(g, P, nrhs) : MarchShape{s.nt, s.pipe};
+    const MarchShape m = op->dw_auto[P] && s.march && nrhs > 1 ? march_shape(g, P, nrhs) : MarchShape{s.nt, s.pipe, s.walk};
     pipe = m.pipe;
-    set_walk(g, s.ts, m.nt, s.walk);
+    set_walk(g, s.ts, m.nt, m.walk);
     return g;
 }
 

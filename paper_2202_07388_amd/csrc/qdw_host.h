@@ -67,33 +67,43 @@ inline size_t spinor_bytes(const Geom& g, int prec)
 // x 40 334 instead of 397 us; FP32 32^3 x 64 262 instead of 315 us (nt 16 instead of 32); FP32
 // pipelined against not: 16.6 and 16.7 us at 20x14x18x22 (880 workgroups), 23.8 and 19.2 at
 // 24x20x18x16 (1080), 260 and 275 at 32^3 x 64.
-// Several fields of one launch are that many times the workgroups, and from three on the L2
-// holds fewer slices of each: short chunks are faster whatever the rounds (FP64, 4 fields, 32^3
-// x 64: 1690 us with nt 4, 1860 with 64; 8 fields 3200 and 4000), and so are three waves (FP32,
-// 4 fields, 24^3 x 48: 259 against 267 us), unless the launch is less than a round.
+// Several fields of one launch are that many times the workgroups. In one round they keep in
+// step, and the links and neighbours that they share stay in L2 (4 FP64 fields at 32^3 x 64:
+// 1483 us with nt 64 and the planes of x1 side by side, 1631 with nt 64 in index order, 1690
+// with nt 4, 1860 with nt 32 in two rounds); launches of more rounds are faster with short
+// chunks (8 fields 3200 us with nt 4, 4180 with 64). FP32 takes its pipelined form in one round
+// only (4 fields at 32^3 x 64: 755 us, three waves 823) and is 10 % further behind there than
+// with one field (8 fields at 24^3 x 48: 549 us in one round, 529 with three waves and nt 8).
 struct MarchShape {
-    int nt, pipe;
+    int nt, pipe, walk;
 };
 inline MarchShape march_shape(const Geom& g, int prec, int nrhs)
 {
-    const int ntile = (g.S + 63) / 64, most = nrhs < 3 ? 64 : prec == F64 ? 4 : 8;
+    const int ntile = (g.S + 63) / 64, most = prec == F64 ? 4 : 8;
     double best = 0.0;
-    MarchShape s{0, 0};
+    MarchShape s{0, 0, 0};
     for (int pipe = prec == F32 ? 1 : 0; pipe >= 0; --pipe)
-        for (int nt = 1; nt <= most && nt <= g.L[0]; ++nt) {
+        for (int nt = 1; nt <= 64 && nt <= g.L[0]; ++nt) {
             if (g.L[0] % nt) continue;
-            const bool three = prec == F32 && !pipe;
+            const bool three = prec == F32 && !pipe, several = nrhs > 1;
             const long nwg = (long)(g.L[0] / nt) * ntile * nrhs, room = three ? 1536 : 1024;
-            if (pipe && nrhs > 2 && nwg > room) continue;
-            const double x = (double)(nwg % room) / room;
-            const double rest = nwg % room == 0      ? 0.0
-                                : !three             ? std::max(0.48, 0.2 + 0.8 * x)
-                                : nrhs > 2           ? std::max(0.6, 0.3 + 0.7 * x)
-                                                     : std::max(0.5, x);
-            const double steps = (nt + 0.2) * ((double)(nwg / room) + rest) * (three ? 1.56 : 1.0);
+            const bool one = nwg <= room;
+            if (several && !one && (pipe || nt > most)) continue;
+            const long last = one ? nwg : nwg % room;
+            const double x = (double)last / room;
+            double rounds = one ? 0.0 : (double)(nwg / room);
+            // (FP64 by the workgroups on the fullest of 256 CUs: one to four take 0.37, 0.54, 0.71
+            // and 0.92 of a full round's step, so 588 workgroups as long as 768)
+            if (last && prec == F64) rounds += (one ? 0.2 : 0.28) + 0.18 * ((last + 255) / 256);
+            else if (last)
+                rounds += !three ? std::max(0.48, 0.2 + 0.8 * x) : several ? std::max(0.6, 0.3 + 0.7 * x) : std::max(0.5, x);
+            const double slower = three ? 1.56 : several && pipe ? 1.095 : 1.0;
+            const double steps = (nt + 0.2) * rounds * slower;
             if (!s.nt || steps < best) {
                 best = steps;
-                s = {nt, pipe};
+                // (planes of x1 side by side: where they are whole tiles; chunks of fewer than
+                // 16 slices and FP32 are as fast or faster in index order)
+                s = {nt, pipe, several && one && prec == F64 && nt >= 16 && g.L[2] * g.L[3] / 2 % 64 == 0};
             }
         }
     return s;
