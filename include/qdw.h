@@ -175,10 +175,12 @@ size_t qdw_autotune_workspace_bytes(const qdw_op* op, qdw_prec prec, int nrhs);
  * may differ in the last bit. */
 int qdw_autotune(qdw_op* op, qdw_prec prec, int nrhs, void* work, size_t work_bytes,
                  char* report, size_t report_len, void* stream);
-/* Shapes at qdw_create: FP64 and FP32 march on 64-site tiles with the longest walk chunk
- * (at most 32, dividing T) that still gives at least 512 workgroups (FP64 plain, FP32
- * pipelined hop loop); FP16 / BF16 storage: the plain one-lane-per-site form on 128-site
- * tiles, nt = 2.
+/* Shapes at qdw_create: FP64 and FP32 march on 64-site tiles with the walk chunk (and, FP32,
+ * the hop-loop form) whose workgroups fill the machine in the fewest steps; FP16 / BF16
+ * storage: the plain one-lane-per-site form on 128-site tiles, nt = 2. Until a shape is set or
+ * tuned for a precision, launches of several fields choose chunk, hop loop and walk anew for
+ * that many, and small lattices take a form of their own (one hop direction per wavefront),
+ * which may differ in the last bit.
  * Set / read the D kernel's shape for precision prec by hand (ts 64 or 128, nt in 1..64
  * dividing T, pipe 0 or 1, walk 0 or 1, march 0 or 1; shape5 = {ts, nt, pipe, walk,
  * march}); QDW_EINVAL for anything else. */
