@@ -253,6 +253,9 @@ void dw_kernel(Geom g, const void* __restrict__ links, const void* __restrict__ 
 // more than its 4 MB L2 per step) and read it from HBM a second time. Two barriers a step.
 // (In LDS a lane's values lie 64 lanes apart, so that one address and constant offsets reach
 // them all; with the lane count as the stride every value's address was held in a register.)
+// Two waves per SIMD, except FP64 with the pipelined hop loop: its two register buffers need
+// 340 registers, and held to 256 it spilled 516 of them (32^3 x 64 on 512 workgroups: 1132 us
+// instead of 513, one wave per SIMD).
 template <class R>
 struct Tile {
     // (typed as LDS: as generic pointers their loads and the global ones beside them are folded
@@ -367,7 +370,7 @@ constexpr size_t march_lds(int ts)
 inline size_t march_lds(int prec, int ts) { return prec == F64 ? march_lds<double>(ts) : march_lds<float>(ts); }
 
 template <int P, bool DAG, bool PIPE, int EPI>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(P == F64 && PIPE ? 1 : 2)))
 void dw_march_kernel(Geom g, const void* __restrict__ links, const void* __restrict__ dets,
                      const void* __restrict__ clover, Epi epi, RhsTable tab)
 {
