@@ -150,7 +150,7 @@ int dw_schur_dag_apply(qdw_op* op, const void* in, void* out, qdw_prec prec, voi
  * operator). in, out: host arrays of device eo-SoA fields of precision prec; no output may
  * alias any input. Workgroups of different right-hand sides on the same tile run side by
  * side, so the links and clover blocks of a tile come from HBM about once for the batch.
- * Results equal dw_apply on each field. */
+ * Results equal dw_apply on each field bit for bit. */
 int dw_apply_multi(qdw_op* op, const void* const* in, void* const* out, int nrhs,
                    qdw_prec prec, void* stream);
 
@@ -170,17 +170,16 @@ size_t qdw_autotune_workspace_bytes(const qdw_op* op, qdw_prec prec, int nrhs);
  * NULL). Times on two scratch fields per right-hand side filled with a fixed non-zero
  * pattern, in work (device, qdw_autotune_workspace_bytes bytes, clobbered); the two timing
  * events it creates are destroyed before it returns; synchronises the stream. Results do
- * not depend on
- * ts, nt or walk; the hop-loop forms and the marching form are separately compiled and
- * may differ in the last bit. */
+ * not depend on ts, nt, pipe or walk; the marching form adds a site's terms in another order
+ * than the one-workgroup-per-slice form and may differ in the last bits. */
 int qdw_autotune(qdw_op* op, qdw_prec prec, int nrhs, void* work, size_t work_bytes,
                  char* report, size_t report_len, void* stream);
 /* Shapes at qdw_create: FP64 and FP32 march on 64-site tiles with the walk chunk (and, FP32,
  * the hop-loop form) whose workgroups fill the machine in the fewest steps; FP16 / BF16
  * storage: the plain one-lane-per-site form on 128-site tiles, nt = 2. Until a shape is set or
  * tuned for a precision, launches of several fields choose chunk, hop loop and walk anew for
- * that many, and small lattices take a form of their own (one hop direction per wavefront),
- * which may differ in the last bit.
+ * that many, and small lattices take a form of their own (one hop direction per wavefront);
+ * a field's result has the same bits in all of them.
  * Set / read the D kernel's shape for precision prec by hand (ts 64 or 128, nt in 1..64
  * dividing T, pipe 0 or 1, walk 0 or 1, march 0 or 1; shape5 = {ts, nt, pipe, walk,
  * march}); QDW_EINVAL for anything else. */

@@ -531,8 +531,7 @@ struct Zero {
 
 // ---------------------------------------------------------------- host helpers
 
-// split = false keeps the form of the operator's shape on small lattices too
-int dw_launch(qdw_op* op, const void* in, void* out, int prec, bool dag, hipStream_t st, bool split = true);
+int dw_launch(qdw_op* op, const void* in, void* out, int prec, bool dag, hipStream_t st);
 // the even-odd reduced operator on the even half of in (odd half of out: scratch)
 int schur_launch(qdw_op* op, const void* in, void* out, int prec, bool dag, hipStream_t st);
 // the two operator applications of a CG step with the step's sums and residual in them:

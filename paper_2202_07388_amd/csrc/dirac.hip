@@ -72,6 +72,16 @@ struct Epi {
     const double* sc;
 };
 
+// A value about to be stored, as a rounded FP32 number: left to itself the compiler folds the
+// conversion to binary16 into the last FMA of some components, a different choice per kernel,
+// and the two ways differ in the last bit for one value in some thousands.
+template <int P, typename R>
+__device__ __forceinline__ R settled(R v)
+{
+    if constexpr (P == F16S) asm("" : "+v"(v));
+    return v;
+}
+
 template <int P, int EPI>
 __device__ __forceinline__ void store_out(void* out, const Epi& e, int Vh, int par, int i,
                                           cx<typename Traits<P>::real> acc[12], double& sum)
@@ -85,6 +95,8 @@ __device__ __forceinline__ void store_out(void* out, const Epi& e, int Vh, int p
         for (int c = 0; c < 12; ++c) acc[c] = r[c] - scale(acc[c], a);
         out = e.r;
     }
+#pragma unroll
+    for (int c = 0; c < 12; ++c) acc[c] = {settled<P>(acc[c].re), settled<P>(acc[c].im)};
     store_spinor<P>(out, Vh, par, i, acc);
     if constexpr (EPI != EPI_NONE) {
 #pragma unroll
@@ -566,7 +578,9 @@ __global__ __launch_bounds__(256) void schur_kernel(Geom g, int ntile1, const vo
 // consecutive sites of one parity, one hop direction per wavefront: the hops run side by side
 // and meet in LDS as half spinors, and then four wavefronts form one spin of the outputs
 // each, adding the diagonal term, whose loads they issue first. Any 64-site block is a
-// workgroup, so lattices of any shape split evenly.
+// workgroup, so lattices of any shape split evenly. Every term is added in the order in which
+// the default form of larger launches adds it, so a field's D has the same bits however many
+// fields share its launch.
 //   KIND 0: out = A psi - 1/2 hops(psi), both parities (D)
 //   KIND 1: out = A^-1 (-1/2 hops(psi)) on the odd sites, KIND 2: out = A psi + 1/2 hops(t)
 //           on the even sites (the stages of the reduced operator)
@@ -610,15 +624,16 @@ struct SplitRow {
         }
     }
 
-    // this spin's part of hop (MU, SG) from its half spinor in LDS: w0 or w1 times a phase
-    template <int MU, int SG, int SP>
+    // this spin's part of hop (MU, SG) from its half spinor in LDS: w0 or w1 times a phase (and
+    // -1/2 with HALF)
+    template <int MU, int SG, int SP, bool HALF = false>
     __device__ __forceinline__ static void add_hop(const R (*w)[64], int lane, cx<R> o[3])
     {
         constexpr bool second = SP < 2 ? SP == 1 : (MU == 0 || MU == 3) ? SP == 3 : SP == 2;
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
             const int q = 2 * (3 * second + c);
-            const cx<R> v = {w[q][lane], w[q + 1][lane]};
+            const cx<R> raw = {w[q][lane], w[q + 1][lane]}, v = HALF ? scale(raw, (R)-0.5) : raw;
             if (SP < 2) o[c] = o[c] + v;
             else if (MU == 0) o[c] = SG > 0 ? o[c] - v : o[c] + v;
             else if (MU == 1) o[c] = SG > 0 ? o[c] + times_i(v) : o[c] - times_i(v);
@@ -655,7 +670,22 @@ struct SplitRow {
             herm6_apply<R>(a, h, v);
 #pragma unroll
             for (int c = 0; c < 3; ++c) o[c] = v[3 * UP + c];
+        } else if constexpr (KIND == 0 && (P == F64 || P == F32)) {
+            // the order of the marching forms: A psi, the spatial hops, the time hops
+            constexpr int F = DAG ? 1 : -1, Bk = -F;
+            cl54_block<R>((R)g.cdiag, a + 3 * BLK, a + (BLK ? 30 : 6), a + (BLK ? 36 : 12), s, v);
+#pragma unroll
+            for (int c = 0; c < 3; ++c) o[c] = v[3 * UP + c];
+            add_hop<1, F, SPIN, true>(hw[2], lane, o);
+            add_hop<1, Bk, SPIN, true>(hw[3], lane, o);
+            add_hop<2, F, SPIN, true>(hw[4], lane, o);
+            add_hop<2, Bk, SPIN, true>(hw[5], lane, o);
+            add_hop<3, F, SPIN, true>(hw[6], lane, o);
+            add_hop<3, Bk, SPIN, true>(hw[7], lane, o);
+            add_hop<0, F, SPIN, true>(hw[0], lane, o);
+            add_hop<0, Bk, SPIN, true>(hw[1], lane, o);
         } else {
+            // the order of the one-lane-per-site kernels: the eight hops, then half of their sum
             cx<R> h[3];
             hop_sum<SPIN>(hw, lane, h);
             if constexpr (KIND == 0)
@@ -727,8 +757,8 @@ void dw_split_kernel(Geom g, const void* psi, const void* __restrict__ links,
                 __builtin_memcpy(v, at, 2 * sizeof(S));
                 o[c] = cx<R>{to_real<P>(v[0]), to_real<P>(v[1])} - scale(o[c], a);
             }
-            v[0] = to_store<P>(o[c].re);
-            v[1] = to_store<P>(o[c].im);
+            v[0] = to_store<P>(settled<P>(o[c].re));
+            v[1] = to_store<P>(settled<P>(o[c].im));
             __builtin_memcpy(__builtin_assume_aligned(at, 2 * sizeof(S)), v, 2 * sizeof(S));
             if constexpr (EPI != EPI_NONE) {
                 const double re = to_real<P>(v[0]), im = to_real<P>(v[1]);
@@ -824,12 +854,12 @@ inline Geom shaped(const qdw_op* op, int P, int nrhs, bool& pipe)
 }
 
 template <int P, bool DAG, int EPI>
-int launch(qdw_op* op, const RhsTable& tab, const Epi& epi, hipStream_t st, bool split = true)
+int launch(qdw_op* op, const RhsTable& tab, const Epi& epi, hipStream_t st)
 {
     const int nrhs = tab.nrhs;
     bool pipe;
     const Geom g = shaped(op, P, nrhs, pipe);
-    if (split && op->dw_auto[P] && split_form(P, false, (long)g.V * nrhs)) {
+    if (op->dw_auto[P] && split_form(P, false, (long)g.V * nrhs)) {
         const int nblk = 2 * (padded(g.Vh) / kSB) * nrhs;
         dw_split_kernel<P, 0, DAG, EPI><<<nblk, 512, 0, st>>>(g, nullptr, op->links[P], op->det[P],
                                                              op->clover54[P], epi, tab);
@@ -873,11 +903,11 @@ int by_precision(int prec, F f)
     }
 }
 
-int dispatch(qdw_op* op, const RhsTable& tab, int prec, bool dag, hipStream_t st, bool split = true)
+int dispatch(qdw_op* op, const RhsTable& tab, int prec, bool dag, hipStream_t st)
 {
     return by_precision(prec, [&](auto P) {
-        return dag ? launch<P.value, true, EPI_NONE>(op, tab, Epi{}, st, split)
-                   : launch<P.value, false, EPI_NONE>(op, tab, Epi{}, st, split);
+        return dag ? launch<P.value, true, EPI_NONE>(op, tab, Epi{}, st)
+                   : launch<P.value, false, EPI_NONE>(op, tab, Epi{}, st);
     });
 }
 
@@ -995,10 +1025,10 @@ int apply_checked(qdw_op* op, const void* in, void* out, qdw_prec prec, bool dag
 
 namespace qdw {
 // internal entries used by the solvers (same kernels, no argument re-validation)
-int dw_launch(qdw_op* op, const void* in, void* out, int prec, bool dag, hipStream_t st, bool split)
+int dw_launch(qdw_op* op, const void* in, void* out, int prec, bool dag, hipStream_t st)
 {
     const RhsTable tab = one_field(in, out);
-    return dispatch(op, tab, prec, dag, st, split);
+    return dispatch(op, tab, prec, dag, st);
 }
 
 int schur_launch(qdw_op* op, const void* in, void* out, int prec, bool dag, hipStream_t st)

@@ -1805,15 +1805,14 @@ extern "C" int nn_train_step(qdw_op* op, float* weights, float* adam, int step, 
         double denom = e2;
         if (loss_kind == 1) {
             // D-norm: d = N(rho) - e  ->  t = D d, |t|^2, gradient direction D^+ t; the
-            // normalisation |D e|^2 is |rho|^2 of the stored pair. The gradients are rounded
-            // to bf16 next, where a last bit of D shows: one form of D for every lattice size
+            // normalisation |D e|^2 is |rho|^2 of the stored pair
             void* t = W.grad[1].at(0);
             void* De = W.grad[1].at(1);
-            if ((rc = dw_launch(op, W.grad[0].base, t, F32, false, st, false))) return rc;
+            if ((rc = dw_launch(op, W.grad[0].base, t, F32, false, st))) return rc;
             if ((rc = run_sum(op, Norm2<F32>{t}, st, &d2))) return rc;
-            if ((rc = dw_launch(op, W.efield, De, F32, false, st, false))) return rc;
+            if ((rc = dw_launch(op, W.efield, De, F32, false, st))) return rc;
             if ((rc = run_sum(op, Norm2<F32>{De}, st, &denom))) return rc;
-            if ((rc = dw_launch(op, t, W.grad[0].base, F32, true, st, false))) return rc;
+            if ((rc = dw_launch(op, t, W.grad[0].base, F32, true, st))) return rc;
         }
         total += d2 / denom;
         // dL/d(out re, im) = 2 (out - e) / |e|^2, or 2 D^+ D (out - e) / |D e|^2, batch mean

@@ -216,6 +216,16 @@ template <typename R> __device__ __forceinline__ cx<R> cmadd_conj(cx<R> c, cx<R>
 {
     return {fmar(a.re, b.re, fmar(a.im, b.im, c.re)), fmar(a.re, b.im, fmar(-a.im, b.re, c.im))};
 }
+// a b and conj(a) b with the fused operation of each part written out: which of two products
+// the compiler folds into the sum would otherwise differ from kernel to kernel
+template <typename R> __device__ __forceinline__ cx<R> cprod(cx<R> a, cx<R> b)
+{
+    return {fmar(a.re, b.re, -(a.im * b.im)), fmar(a.re, b.im, a.im * b.re)};
+}
+template <typename R> __device__ __forceinline__ cx<R> cprod_conj(cx<R> a, cx<R> b)
+{
+    return {fmar(a.re, b.re, a.im * b.im), fmar(a.re, b.im, -(a.im * b.re))};
+}
 template <typename R> __device__ __forceinline__ cx<R> times_i(cx<R> a) { return {-a.im, a.re}; }
 template <typename R> __device__ __forceinline__ cx<R> scale(cx<R> a, R s) { return {a.re * s, a.im * s}; }
 
