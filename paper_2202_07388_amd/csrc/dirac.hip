@@ -501,6 +501,177 @@ void dw_march_kernel(Geom g, const void* __restrict__ links, const void* __restr
     if constexpr (EPI != EPI_NONE) grid_sums<1>(&sum, epi.sums, blockIdx.x, gridDim.x);
 }
 
+// The marching form without the tile (hand_over says where). Nothing of the tile is kept in
+// LDS but what partners exchange: the +t neighbour as a projected half spinor, the -t neighbour
+// as a transported one, each in two slots, so that a step has one barrier; a lane's own spinor
+// stays in registers and the spatial hops read their neighbours from memory. With about one
+// wave per SIMD nothing hides a step's chain of loads, LDS accesses and barriers, and this
+// chain is the shorter one; it needs a wave's whole register file, which is free there. The
+// order of the sums is dw_march_kernel's.
+template <int P, bool DAG, bool PIPE>
+__device__ __forceinline__ void hand_site_hops(const Geom& g, const void* in, const void* links,
+                                               const void* dets, int par, int i, const int x[4],
+                                               int lex, cx<typename Traits<P>::real> acc[12])
+{
+    if constexpr (!PIPE) {
+        HopIn<P> A;
+#pragma unroll 1
+        for (int k = 2; k < 8; ++k) {
+            int ii = i, ll = lex, xx[4] = {x[0], x[1], x[2], x[3]};
+            asm volatile("" : "+v"(ii), "+v"(ll), "+v"(xx[0]), "+v"(xx[1]), "+v"(xx[2]), "+v"(xx[3]));
+            load_k<P>(k, g, in, links, dets, par, ii, xx, ll, A);
+            compute_k<P, DAG, true>(k, g, xx, A, acc);
+        }
+        return;
+    }
+    HopIn<P> A, B;
+    load_k<P>(2, g, in, links, dets, par, i, x, lex, A);
+#pragma unroll 1
+    for (int k = 2; k < 8; k += 2) {
+        int ii = i, ll = lex, xx[4] = {x[0], x[1], x[2], x[3]};
+        asm volatile("" : "+v"(ii), "+v"(ll), "+v"(xx[0]), "+v"(xx[1]), "+v"(xx[2]), "+v"(xx[3]));
+        load_k<P>(k + 1, g, in, links, dets, par, ii, xx, ll, B);
+        compute_k<P, DAG, true>(k, g, xx, A, acc);
+        if (k + 2 < 8) load_k<P>(k + 2, g, in, links, dets, par, ii, xx, ll, A);
+        compute_k<P, DAG, true>(k + 1, g, xx, B, acc);
+    }
+}
+
+// bytes of LDS for ts sites per parity: two slots of both half spinors of every lane
+template <class R>
+constexpr size_t hand_lds(int ts)
+{
+    return (size_t)2 * 2 * 12 * (2 * ts) * sizeof(R);
+}
+
+template <int P, bool DAG, bool PIPE, int EPI>
+__global__ __launch_bounds__(256)
+void dw_hand_kernel(Geom g, const void* __restrict__ links, const void* __restrict__ dets,
+                    const void* __restrict__ clover, Epi epi, RhsTable tab)
+{
+    using R = typename Traits<P>::real;
+    constexpr int SGF = DAG ? +1 : -1;  // projector of the +t hop: 1 + SGF gamma_0
+    constexpr int SGB = -SGF;           // of the -t hop
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    const int nl = blockDim.x;  // 2 ts lanes
+    R* hp = (R*)smem;           // [2 slots][12 reals][nl]: projected +t neighbours
+    R* pw = hp + 2 * 12 * nl;   // [2 slots][12 reals][nl]: transported -t neighbours
+    const int logical = xcd_tile(blockIdx.x, gridDim.x);
+    const int wg = logical / tab.nrhs;
+    const int rhs = logical - wg * tab.nrhs;
+    if (tab.gate && !tab.gate[(long)rhs * tab.gstride]) return;  // the whole workgroup
+    const void* __restrict__ in = tab.f[rhs].in;
+    void* __restrict__ out = tab.f[rhs].out;
+    const int c = wg / g.ntile, s = wg - c * g.ntile;
+    const int t0 = c * g.nt;
+    const int tid = threadIdx.x;
+    const int par = tid >= g.ts ? 1 : 0;
+    const int lane = tid - par * g.ts;
+    const int partner = tid + (par ? -g.ts : g.ts);
+    int k;
+    bool valid;
+    if (g.walk == 0) {
+        k = s * g.ts + lane;
+        valid = k < g.S;
+    } else {
+        const int b = s / g.L[1], x1 = s - b * g.L[1];
+        k = x1 * g.slab + b * g.ts + lane;
+        valid = b * g.ts + lane < g.slab;
+    }
+    auto put6 = [&](R* buf, int slot, int who, const cx<R> v[6]) {
+#pragma unroll
+        for (int q = 0; q < 6; ++q) {
+            buf[(slot * 12 + 2 * q) * nl + who] = v[q].re;
+            buf[(slot * 12 + 2 * q + 1) * nl + who] = v[q].im;
+        }
+    };
+    auto get6 = [&](const R* buf, int slot, cx<R> v[6]) {
+#pragma unroll
+        for (int q = 0; q < 6; ++q)
+            v[q] = {buf[(slot * 12 + 2 * q) * nl + tid], buf[(slot * 12 + 2 * q + 1) * nl + tid]};
+    };
+    // U_0(y)^+ (1 + SGB gamma_0) psi(y) for the partner's site one slice up (sign when the
+    // hop wraps from T-1 to 0)
+    auto push = [&](int t, int slot, const cx<R> sp[12], const cx<R> u[6], cx<R> d) {
+        cx<R> h[6], w[6];
+        project<R, 0, SGB>(sp, h);
+        if (g.bc_t < 0 && t == g.L[0] - 1) {
+#pragma unroll
+            for (int q = 0; q < 6; ++q) h[q] = {-h[q].re, -h[q].im};
+        }
+        su3_mul<R, true>(u, d, h, w);
+        put6(pw, slot, partner, w);
+    };
+    // A psi plus the six spatial hops (scaled by -1/2) of this lane's site at slice tt,
+    // whose spinor `sp` the lane holds
+    auto site_part = [&](int tt, const cx<R> sp[12], cx<R> acc[12]) {
+        const int i = tt * g.S + k;
+        int x[4], lex;
+        eo_coords(g, par, i, x, lex);
+        clover54_apply<P>(clover, g.Vh, par, i, (R)g.cdiag, sp, acc);
+        hand_site_hops<P, DAG, PIPE>(g, in, links, dets, par, i, x, lex, acc);
+    };
+    // the accumulator of the current slice was begun in the step before
+    cx<R> own[12], acc[12];
+    double sum = 0.0;
+    if (valid) {
+        const int tp = t0 == 0 ? g.L[0] - 1 : t0 - 1;
+        cx<R> u[6], d;
+        load_spinor<P>(in, g.Vh, par, tp * g.S + k, own);
+        load_link<P>(links, dets, g.Vh, par, tp * g.S + k, 0, u, d);
+        push(tp, t0 & 1, own, u, d);
+        load_spinor<P>(in, g.Vh, par, t0 * g.S + k, own);
+        site_part(t0, own, acc);
+    }
+    for (int step = 0; step < g.nt; ++step) {
+        const int t = t0 + step;
+        const int tn = t + 1 == g.L[0] ? 0 : t + 1;
+        // (1) the spinor this lane owns at t+1, projected for the partner's +t hop; slot
+        //     (t+1)&1 was last read two steps ago, before the previous barrier
+        cx<R> nxt[12];
+        if (valid) {
+            cx<R> h[6];
+            load_spinor<P>(in, g.Vh, par, tn * g.S + k, nxt);
+            project<R, 0, SGF>(nxt, h);
+            put6(hp, (t + 1) & 1, partner, h);
+        }
+        __syncthreads();
+        if (valid) {
+            const int i = t * g.S + k;
+            // the site's forward t link serves the +t hop and the hand-over below
+            cx<R> u0[6], d0;
+            load_link<P>(links, dets, g.Vh, par, i, 0, u0, d0);
+            // (2) the partner's -t hop at t+1; slot (t+1)&1 was read one step ago, before
+            //     this step's barrier
+            if (step + 1 < g.nt) push(t, (t + 1) & 1, own, u0, d0);
+            {
+                // +t: U_0(x) times the projected neighbour from the partner
+                cx<R> h[6], w[6];
+                get6(hp, (t + 1) & 1, h);
+                const R f = (g.bc_t < 0 && t == g.L[0] - 1) ? (R)0.5 : (R)-0.5;
+#pragma unroll
+                for (int q = 0; q < 6; ++q) h[q] = scale(h[q], f);
+                su3_mul<R, false>(u0, d0, h, w);
+                expand_add<R, 0, SGF>(w, acc);
+                // -t: already transported by the partner
+                get6(pw, t & 1, w);
+#pragma unroll
+                for (int q = 0; q < 6; ++q) w[q] = scale(w[q], (R)-0.5);
+                expand_add<R, 0, SGB>(w, acc);
+            }
+            store_out<P, EPI>(out, epi, g.Vh, par, i, acc, sum);
+            // (3) the next slice's clover term and spatial hops, on the spinors loaded in
+            //     this step
+            if (step + 1 < g.nt) {
+#pragma unroll
+                for (int q = 0; q < 12; ++q) own[q] = nxt[q];
+                site_part(tn, own, acc);
+            }
+        }
+    }
+    if constexpr (EPI != EPI_NONE) grid_sums<1>(&sum, epi.sums, blockIdx.x, gridDim.x);
+}
+
 // Even-odd reduced operator D^ = A_ee - D_eo A_oo^-1 D_oe on the even half of a field, in
 // two passes over one parity each (one lane per site):
 //   stage 1, odd sites:  t = A_oo^-1 (D_oe psi_e) = A_oo^-1 (-1/2 sum of the hops of psi_e)
@@ -814,6 +985,28 @@ inline bool split_form(int P, bool schur, long sites)
     return sites <= (schur ? kSchur[P] : kD[P]);
 }
 
+// Marching launches that take the form without the tile in LDS, by their 64-site units (two
+// waves each). That form needs nearly a wave's whole register file in FP64, so it is for
+// launches of one wave per SIMD (512 units; the tile form with the pipelined loop has one wave
+// per SIMD too and needs the launch to be nearly full); FP32 fits two waves per SIMD in either,
+// and the tile pays from a full round of them on, the pipelined loop on 64-site tiles in just
+// that round. FP16 conversions are folded into mixed-precision FMAs at every use of a value,
+// and a value read back from LDS is converted again, so FP16 has no tile form; nor has BF16
+// with the pipelined loop, where the two are even.
+// us, without the tile / with it: FP64 plain 14.7 / 17.7 at 320 units (20 x 12^2 x 14), 18.2 /
+// 20.8 at 512 (16^4), 505 / 552 at 512 (32^3 x 64, nt 32), 30 / 23 at 640 (20 x 16^3); FP64
+// pipelined 15.7 / 17.3 at 384, 30.5 / 31.8 at 768, even at 1024; FP32 pipelined 13.7 / 14.5 at
+// 768 (24 x 16^3), 16.7 / 16.5 at 1024 (32 x 16^3), 276 / 262 at 1024 (32^3 x 64), then 2 to 4 %
+// more; FP32 plain 14.7 / 15.5 at 768, 28.1 / 20.7 at 1196; BF16 plain 5 to 10 % more up to
+// 1024, 11 to 25 % less beyond; FP16 2 to 7 % more at any size.
+template <int P, bool PIPE>
+inline bool hand_over(int ts, long units)
+{
+    if (P == F64) return units <= (PIPE ? 960 : 512);
+    if (P == F32) return ts == 64 && (units <= 960 || (PIPE && units > 1024));
+    return P == F16S || PIPE || units <= 1024;
+}
+
 template <int P, bool DAG, int EPI>
 int schur_launch_t(qdw_op* op, const void* in, void* out, const Epi& epi, hipStream_t st)
 {
@@ -869,13 +1062,17 @@ int launch(qdw_op* op, const RhsTable& tab, const Epi& epi, hipStream_t st)
     if (op->dw_shape[P].march) {
         using R = typename Traits<P>::real;
         const int nblk = (g.L[0] / g.nt) * g.ntile * nrhs;
-        const size_t lds = march_lds<R>(g.ts);
-        if (pipe)
-            dw_march_kernel<P, DAG, true, EPI><<<nblk, 2 * g.ts, lds, st>>>(
-                g, op->links[P], op->det[P], op->clover54[P], epi, tab);
-        else
-            dw_march_kernel<P, DAG, false, EPI><<<nblk, 2 * g.ts, lds, st>>>(
-                g, op->links[P], op->det[P], op->clover54[P], epi, tab);
+        auto run = [&](auto pipe_c) {
+            constexpr bool PIPE = decltype(pipe_c)::value;
+            if (hand_over<P, PIPE>(g.ts, (long)nblk * (g.ts / 64)))
+                dw_hand_kernel<P, DAG, PIPE, EPI><<<nblk, 2 * g.ts, hand_lds<R>(g.ts), st>>>(
+                    g, op->links[P], op->det[P], op->clover54[P], epi, tab);
+            else if constexpr (P <= F32 || (P == BF16S && !PIPE))
+                dw_march_kernel<P, DAG, PIPE, EPI><<<nblk, 2 * g.ts, march_lds<R>(g.ts), st>>>(
+                    g, op->links[P], op->det[P], op->clover54[P], epi, tab);
+        };
+        if (pipe) run(std::true_type{});
+        else run(std::false_type{});
         QDW_LAUNCH_CHECK();
         return QDW_OK;
     }
