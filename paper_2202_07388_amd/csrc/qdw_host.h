@@ -56,17 +56,18 @@ inline size_t spinor_bytes(const Geom& g, int prec)
 }
 
 // The walk chunk and pipelining of the marching form on 64-site tiles. A workgroup walks nt
-// slices after loading one more (0.2 of a step: its neighbour in time has mostly just loaded
-// it), and the machine holds `room` workgroups at once: two waves per SIMD (FP64, and FP32 with
-// the pipelined hop loop) or three (FP32 without). A launch takes whole rounds and a rest; a
-// step of a rest that fills a share x of the machine is shorter than that of a full round, down
-// to the latency of one step. FP32 rounds of three waves are 1.5 times as long and 4 % slower
-// for the same work, so that form is for launches that would leave the other's last round
-// nearly empty. The choice with the smallest sum wins. Measured against the longest power of
-// two that gives 512 workgroups: FP64 24^3 x 48 175 instead of 230 us (nt 6 instead of 8), 32^3
-// x 40 334 instead of 397 us; FP32 32^3 x 64 262 instead of 315 us (nt 16 instead of 32); FP32
-// pipelined against not: 16.6 and 16.7 us at 20x14x18x22 (880 workgroups), 23.8 and 19.2 at
-// 24x20x18x16 (1080), 260 and 275 at 32^3 x 64.
+// slices after loading one more (0.3 of a step in FP64, 0.2 in FP32: its neighbour in time has
+// mostly just loaded it), and the machine holds `room` workgroups at once: two waves per SIMD
+// (FP64, and FP32 with the pipelined hop loop) or three (FP32 without). A launch takes whole
+// rounds and a rest; a step of a rest that fills a share x of the machine is shorter than that
+// of a full round, down to the latency of one step. FP32 rounds of three waves are 1.5 times as
+// long and 7 % slower for the same work, so that form is for launches that would leave the
+// other's last round nearly empty. The choice with the smallest sum wins. The constants are
+// fitted to the times of all chunks and hop loops on 280 lattices of 45,000 to 2.1 million
+// sites: the choice is 0.6 % (FP64) and 0.8 % (FP32) behind the fastest on average, and against
+// the longest power of two that gives 512 workgroups it is 3 % faster and on three of them more
+// than 2 % slower (at most 5 %). FP64 24^3 x 48 175 instead of 230 us (nt 6 instead of 8), 32^3
+// x 40 334 instead of 397 us; FP32 32^3 x 64 262 instead of 315 us (nt 16 instead of 32).
 // Several fields of one launch are that many times the workgroups. In one round they keep in
 // step, and the links and neighbours that they share stay in L2 (4 FP64 fields at 32^3 x 64:
 // 1483 us with nt 64 and the planes of x1 side by side, 1631 with nt 64 in index order, 1690
@@ -92,13 +93,13 @@ inline MarchShape march_shape(const Geom& g, int prec, int nrhs)
             const long last = one ? nwg : nwg % room;
             const double x = (double)last / room;
             double rounds = one ? 0.0 : (double)(nwg / room);
-            // (FP64 by the workgroups on the fullest of 256 CUs: one to four take 0.37, 0.54, 0.71
+            // (FP64 by the workgroups on the fullest of 256 CUs: one to four take 0.38, 0.56, 0.74
             // and 0.92 of a full round's step, so 588 workgroups as long as 768)
-            if (last && prec == F64) rounds += (one ? 0.2 : 0.28) + 0.18 * ((last + 255) / 256);
-            else if (last)
-                rounds += !three ? std::max(0.48, 0.2 + 0.8 * x) : several ? std::max(0.6, 0.3 + 0.7 * x) : std::max(0.5, x);
-            const double slower = three ? 1.56 : several && pipe ? 1.095 : 1.0;
-            const double steps = (nt + 0.2) * rounds * slower;
+            if (last && prec == F64) rounds += (one ? 0.2 : several ? 0.28 : 0.32) + 0.18 * ((last + 255) / 256);
+            else if (last && several) rounds += three ? std::max(0.6, 0.3 + 0.7 * x) : std::max(0.48, 0.2 + 0.8 * x);
+            else if (last) rounds += three ? std::max(0.6, x) : 0.4 + 0.6 * x;
+            const double slower = three ? (several ? 1.56 : 1.6) : several && pipe ? 1.095 : 1.0;
+            const double steps = (nt + (prec == F64 && !several ? 0.3 : 0.2)) * rounds * slower;
             if (!s.nt || steps < best) {
                 best = steps;
                 // (planes of x1 side by side: where they are whole tiles; chunks of fewer than

@@ -93,3 +93,18 @@ def test_default_form_is_not_slower_than_the_plain_one():
     qdw.set_dw_shape(op, "f64", 64, 1, 1, 0, 0)
     plain = best_us(lambda: qdw.dw_apply(op, x, y))
     assert default <= 1.03 * plain, (default, plain)
+
+
+@pytest.mark.parametrize("dims,prec,other,was", [
+    ((4, 60, 22, 54), "f64", (64, 4, 0, 0, 1), "75 against 90 us in chunks of one slice"),
+    ((50, 34, 12, 50), "f32", (64, 2, 1, 0, 1), "137 against 151 us in chunks of ten slices"),
+    ((38, 8, 32, 20), "f32", (64, 2, 1, 0, 1), "25.7 against 28.2 us with the plain hop loop")])
+def test_default_chunk_is_not_slower_than_another(dims, prec, other, was):
+    import torch
+    V = syn.volume(dims)
+    su3 = torch.eye(3, dtype=torch.complex128, device="cuda").expand(V, 4, 3, 3).contiguous()
+    op = qdw.Op(dims, su3, torch.zeros(V, 4, dtype=torch.float64, device="cuda"), -0.05, 1.7)
+    x, y = op.pack(torch.randn(V, 4, 3, dtype=torch.complex128, device="cuda"), prec), op.new_field(prec)
+    default = best_us(lambda: qdw.dw_apply(op, x, y, prec), 20)
+    qdw.set_dw_shape(op, prec, *other)
+    assert default <= 1.03 * best_us(lambda: qdw.dw_apply(op, x, y, prec), 20), (default, was)
