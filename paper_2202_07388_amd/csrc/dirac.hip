@@ -745,7 +745,7 @@ __global__ __launch_bounds__(256) void schur_kernel(Geom g, int ntile1, const vo
 
 // Small lattices: with one lane per site a lattice of some ten thousand sites leaves most of
 // the machine without work, and the launch lasts as long as one lane's chain of eight hops
-// (FP64 at 4^4: 9.7 us, whatever the shape). Here a workgroup of eight wavefronts owns 64
+// (FP64 at 4^4: 10.6 us, whatever the shape). Here a workgroup of eight wavefronts owns 64
 // consecutive sites of one parity, one hop direction per wavefront: the hops run side by side
 // and meet in LDS as half spinors, and then four wavefronts form one spin of the outputs
 // each, adding the diagonal term, whose loads they issue first. Any 64-site block is a
@@ -974,14 +974,14 @@ void dw_split_kernel(Geom g, const void* psi, const void* __restrict__ links,
 
 // Where the split form is used: up to the lattice size (times the fields of a launch) at which
 // the other forms have enough sites in flight to overtake it. Kernel times on either side, us,
-// split against the default shape: FP64 D 11.2 / 14.2 at 16 x 12^3, 22.8 / 19.7 at 16^4; FP32
-// 12.3 / 13.4 at 16^4, 19.0 / 16.9 at 20x14x18x22; FP16 10.1 / 12.0 and 15.1 / 13.5 at the
-// same; both stages of the reduced operator: FP64 27.5 / 33.5 at 16^4, 47.9 / 41.4 at
-// 20x14x18x22, FP32 15.6 / 23.6 and 25.9 / 26.6, FP16 13.0 / 21.2 and 18.6 / 20.1; at 4^4 5.1 /
-// 10.6 (FP64 D), 4.2 / 8.4 (FP32), 3.9 / 9.0 (FP16).
+// split against the other form: FP64 D 11.2 / 12.2 at 16 x 12^3, 22.8 / 18.2 at 16^4; FP32 12.3
+// / 13.1 at 16^4, 19.0 / 16.4 at 20x14x18x22; FP16 10.1 / 12.0 and 15.1 / 13.5 at the same; both
+// stages of the reduced operator: FP64 27.7 / 32.7 at 16^4 (512 workgroups, one round), 34.9 /
+// 33.4 at 18 x 16^3, FP32 15.6 / 23.6 at 16^4 and 24.9 / 25.8 at 20x14x18x22, FP16 11.5 / 18.5
+// and 17.4 / 19.7; at 4^4 5.1 / 10.6 (FP64 D), 4.2 / 8.4 (FP32), 3.9 / 9.0 (FP16).
 inline bool split_form(int P, bool schur, long sites)
 {
-    constexpr long kD[4] = {40000, 70000, 90000, 90000}, kSchur[4] = {85000, 120000, 200000, 200000};
+    constexpr long kD[4] = {40000, 70000, 90000, 90000}, kSchur[4] = {66000, 120000, 200000, 200000};
     return sites <= (schur ? kSchur[P] : kD[P]);
 }
 
