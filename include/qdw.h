@@ -164,9 +164,11 @@ size_t qdw_autotune_workspace_bytes(const qdw_op* op, qdw_prec prec, int nrhs);
  * loaded by nearby workgroups) and form (march 0: one workgroup per tile and slice; 1: a
  * workgroup marches through the chunk's slices of its tile and hands the time hops on
  * through LDS, so that they are read from memory once) -- for precision prec and nrhs
- * right-hand sides on the stream, keeps the fastest in op (used by dw_apply,
- * dw_apply_multi and the solvers from then on), and writes a one-line report (best shape,
- * then every candidate's time in ms as [ts,nt,pipe,walk,march]=ms) to report (host, may be
+ * right-hand sides on the stream, and the default below, and keeps the fastest in op (used by
+ * dw_apply, dw_apply_multi and the solvers from then on; the default stays, and goes on choosing
+ * by the launch, unless a shape is more than 2 % faster). Writes a one-line report (the chosen shape, marked where it is the
+ * default; the default's time; then every candidate's time in ms as
+ * [ts,nt,pipe,walk,march]=ms) to report (host, may be
  * NULL). Times on two scratch fields per right-hand side filled with a fixed non-zero
  * pattern, in work (device, qdw_autotune_workspace_bytes bytes, clobbered); the two timing
  * events it creates are destroyed before it returns; synchronises the stream. Results do

@@ -1441,8 +1441,8 @@ extern "C" int qdw_autotune(qdw_op* op, qdw_prec prec, int nrhs, void* work, siz
     for (int r = 0; r < nrhs; ++r) tab.f[r] = {buf + (size_t)r * fb, buf + (size_t)(nrhs + r) * fb};
     hipEvent_t e0 = nullptr, e1 = nullptr;
     const auto keep = op->dw_shape[prec];
-    const bool keep_auto = op->dw_auto[prec], split = split_form(prec, false, (long)g.V * nrhs);
-    float split_ms = 0.f;
+    const bool keep_auto = op->dw_auto[prec];
+    float default_ms = 0.f;
     struct Cand { int ts, nt, pipe, walk, march; float ms; };
     std::vector<Cand> cands;
     for (int march = 0; march < 2; ++march)
@@ -1476,10 +1476,8 @@ extern "C" int qdw_autotune(qdw_op* op, qdw_prec prec, int nrhs, void* work, siz
             return QDW_OK;
         };
         int r;
-        if (split) {
-            op->dw_auto[prec] = true;
-            if ((r = time_form(&split_ms))) return r;
-        }
+        default_dw_shape(op, prec);
+        if ((r = time_form(&default_ms))) return r;
         op->dw_auto[prec] = false;
         for (Cand& c : cands) {
             op->dw_shape[prec] = {c.ts, c.nt, c.pipe, c.walk, c.march};
@@ -1499,21 +1497,21 @@ extern "C" int qdw_autotune(qdw_op* op, qdw_prec prec, int nrhs, void* work, siz
     const Cand* best = &cands[0];
     for (const Cand& c : cands)
         if (c.ms < best->ms) best = &c;
-    op->dw_shape[prec] = {best->ts, best->nt, best->pipe, best->walk, best->march};
-    // a small lattice keeps the split form where no shape beats it
-    op->dw_auto[prec] = split && split_ms < best->ms;
+    // the default stays where no shape beats it by more than two runs differ: its chunks need not
+    // be powers of two, and it goes on choosing for launches of other sizes
+    const bool stays = default_ms <= 1.02f * best->ms;
+    if (stays) default_dw_shape(op, prec);
+    else op->dw_shape[prec] = {best->ts, best->nt, best->pipe, best->walk, best->march};
     if (report && report_len) {
         std::string s;
         char line[200];
+        const auto& c0 = op->dw_shape[prec];
         std::snprintf(line, sizeof line,
-                      "lattice %dx%dx%dx%d prec %d nrhs %d: best ts=%d nt=%d pipe=%d walk=%d march=%d %.4f ms;",
-                      g.L[0], g.L[1], g.L[2], g.L[3], (int)prec, nrhs, best->ts, best->nt,
-                      best->pipe, best->walk, best->march, best->ms);
+                      "lattice %dx%dx%dx%d prec %d nrhs %d: best ts=%d nt=%d pipe=%d walk=%d march=%d %.4f ms%s;"
+                      " default %.4f;",
+                      g.L[0], g.L[1], g.L[2], g.L[3], (int)prec, nrhs, c0.ts, c0.nt, c0.pipe, c0.walk,
+                      c0.march, stays ? default_ms : best->ms, stays ? " (default)" : "", default_ms);
         s += line;
-        if (split) {
-            std::snprintf(line, sizeof line, " split form %.4f;", split_ms);
-            s += line;
-        }
         for (const Cand& c : cands) {
             std::snprintf(line, sizeof line, " [%d,%d,%d,%d,%d]=%.4f", c.ts, c.nt, c.pipe, c.walk,
                           c.march, c.ms);

@@ -594,20 +594,7 @@ extern "C" int qdw_create(const qdw_lattice* lat, const double* su3, const doubl
             if (L[0] % d == 0) nt = d;
         set_walk(g, 128, nt, 0);
     }
-    {
-        // default D-kernel shapes (qdw_autotune or qdw_set_dw_shape may change them).
-        // FP64 and FP32: the marching form on 64-site tiles, with the walk chunk and
-        // pipelining that march_shape expects to be fastest
-        for (int p : {F64, F32}) {
-            const MarchShape s = march_shape(g, p, 1);
-            op->dw_shape[p] = {64, s.nt, s.pipe, 0, 1};
-        }
-        // half-precision storage: the plain form (one lane per site, four waves per SIMD)
-        // on 128-site tiles in chunks of two slices (T is even)
-        op->dw_shape[F16S] = {128, 2, 0, 0, 0};
-        op->dw_shape[BF16S] = {128, 2, 0, 0, 0};
-        for (int p = 0; p < 4; ++p) op->dw_auto[p] = true;
-    }
+    for (int p = 0; p < 4; ++p) default_dw_shape(op, p);
     op->m0 = m0;
     op->csw = csw;
     (void)hipGetDevice(&op->device);

@@ -110,6 +110,21 @@ inline MarchShape march_shape(const Geom& g, int prec, int nrhs)
     return s;
 }
 
+// The D kernel's shape at creation, and the default rule for it (dw_auto): launches of few
+// sites take the split form, several fields choose the chunk anew. FP64 and FP32 march on
+// 64-site tiles; half-precision storage takes the plain form (one lane per site, four waves per
+// SIMD) on 128-site tiles in chunks of two slices (T is even).
+inline void default_dw_shape(qdw_op* op, int prec)
+{
+    if (prec == F64 || prec == F32) {
+        const MarchShape s = march_shape(op->g, prec, 1);
+        op->dw_shape[prec] = {64, s.nt, s.pipe, 0, 1};
+    } else {
+        op->dw_shape[prec] = {128, 2, 0, 0, 0};
+    }
+    op->dw_auto[prec] = true;
+}
+
 }  // namespace qdw
 
 #define QDW_HIP(call)                                                                  \
