@@ -187,6 +187,12 @@ int qdw_autotune(qdw_op* op, qdw_prec prec, int nrhs, void* work, size_t work_by
  * march}); QDW_EINVAL for anything else. */
 int qdw_set_dw_shape(qdw_op* op, qdw_prec prec, int ts, int nt, int pipe, int walk, int march);
 int qdw_get_dw_shape(const qdw_op* op, qdw_prec prec, int* shape5);
+/* qdw_default_dw_shape: back to the default of qdw_create, which chooses by the launch; a shape
+ * set by hand, also one that qdw_get_dw_shape returned, is used for every launch instead.
+ * qdw_dw_shape_is_default: 1 while the default holds for prec, else 0 (QDW_EINVAL for a null
+ * operator or a bad precision). */
+int qdw_default_dw_shape(qdw_op* op, qdw_prec prec);
+int qdw_dw_shape_is_default(const qdw_op* op, qdw_prec prec);
 
 /* Fused BLAS-1 on eo-SoA fields of one precision (device), every reduction accumulated in
  * binary64 (Sec. 2.1: reduction variables in binary64 whatever the working type) in a

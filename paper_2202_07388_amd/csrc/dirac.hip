@@ -1417,6 +1417,21 @@ extern "C" int qdw_get_dw_shape(const qdw_op* op, qdw_prec prec, int* shape5)
     return QDW_OK;
 }
 
+extern "C" int qdw_default_dw_shape(qdw_op* op, qdw_prec prec)
+{
+    QDW_CHECK(op, QDW_EINVAL, "qdw_default_dw_shape: null operator");
+    QDW_CHECK(prec >= QDW_F64 && prec <= QDW_BF16S, QDW_EINVAL, "qdw_default_dw_shape: bad precision");
+    default_dw_shape(op, prec);
+    return QDW_OK;
+}
+
+extern "C" int qdw_dw_shape_is_default(const qdw_op* op, qdw_prec prec)
+{
+    QDW_CHECK(op, QDW_EINVAL, "qdw_dw_shape_is_default: null operator");
+    QDW_CHECK(prec >= QDW_F64 && prec <= QDW_BF16S, QDW_EINVAL, "qdw_dw_shape_is_default: bad precision");
+    return op->dw_auto[prec] ? 1 : 0;
+}
+
 extern "C" size_t qdw_autotune_workspace_bytes(const qdw_op* op, qdw_prec prec, int nrhs)
 {
     if (!op || prec < QDW_F64 || prec > QDW_BF16S || nrhs < 1 || nrhs > kMaxRhs) return 0;

@@ -141,6 +141,8 @@ _OPTIONAL: list = [
     ("qdw_set_dw_shape", [_P, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_int,
                           ctypes.c_int, ctypes.c_int], ctypes.c_int),
     ("qdw_get_dw_shape", [_P, ctypes.c_int, ctypes.POINTER(ctypes.c_int * 5)], ctypes.c_int),
+    ("qdw_default_dw_shape", [_P, ctypes.c_int], ctypes.c_int),
+    ("qdw_dw_shape_is_default", [_P, ctypes.c_int], ctypes.c_int),
     ("qdw_sap_gcr_batched_workspace_bytes", [_P, ctypes.c_int, ctypes.POINTER(SapGcrParams)],
      ctypes.c_size_t),
     ("sap_gcr_solve_batched", [_P, _P, _P, ctypes.c_int, ctypes.POINTER(SapGcrParams), _P,
@@ -449,7 +451,7 @@ def autotune(op: Op, prec: str = "f64", nrhs: int = 1) -> str:
 # D kernels themselves, so a cache entry is keyed by all five and a kernel source change
 # misses the cache.
 
-_TUNE_SOURCES = ("dirac.hip", "dirac_core.h", "qdw_internal.h")
+_TUNE_SOURCES = ("dirac.hip", "dirac_core.h", "qdw_internal.h", "qdw_host.h")
 
 
 def kernel_version() -> str:
@@ -470,35 +472,38 @@ def tune_key(dims, prec: str, nrhs: int, device: str, kernels: str) -> str:
                                    device, kernels)
 
 
-def read_tune_cache(path: str, key: str):
-    """The cached (ts, nt, pipe, walk, march) for key, or None (no file, no entry, or an
-    entry that is not five integers)."""
+def _tune_file(path: str) -> dict:
+    """A cache file's "entries" (key: shape) and "default" (keys whose choice is the default
+    form of D), each an empty dict where the file is missing or malformed."""
     import json
     try:
         with open(path) as fh:
-            entries = json.load(fh).get("entries", {})
-    except (OSError, ValueError, AttributeError):
-        return None
-    shape = entries.get(key) if isinstance(entries, dict) else None
+            data = json.load(fh)
+    except (OSError, ValueError):
+        data = None
+    data = data if isinstance(data, dict) else {}
+    return {k: data[k] if isinstance(data.get(k), dict) else {} for k in ("entries", "default")}
+
+
+def read_tune_cache(path: str, key: str):
+    """The cached (ts, nt, pipe, walk, march) for key, or None (no file, no entry, or an
+    entry that is not five integers)."""
+    shape = _tune_file(path)["entries"].get(key)
     if isinstance(shape, list) and len(shape) == 5 and all(isinstance(v, int) for v in shape):
         return tuple(shape)
     return None
 
 
-def write_tune_cache(path: str, key: str, shape) -> None:
-    """Add or replace one entry; the file is rewritten whole through a temporary file, so
-    a reader never sees a partial file; an entry that another process writes between this
-    call's read and its write is lost."""
+def write_tune_cache(path: str, key: str, shape, default: bool = False) -> None:
+    """Add or replace one entry (default: the choice is the default form, of this shape); the
+    file is rewritten whole through a temporary file, so a reader never sees a partial file; an
+    entry that another process writes between this call's read and its write is lost."""
     import json
-    data = {"version": 1, "entries": {}}
-    try:
-        with open(path) as fh:
-            old = json.load(fh)
-        if isinstance(old, dict) and isinstance(old.get("entries"), dict):
-            data["entries"] = old["entries"]
-    except (OSError, ValueError):
-        pass
+    data = {"version": 1, **_tune_file(path)}
     data["entries"][key] = [int(v) for v in shape]
+    data["default"].pop(key, None)
+    if default:
+        data["default"][key] = True
     tmp = "%s.tmp%d" % (path, os.getpid())
     with open(tmp, "w") as fh:
         json.dump(data, fh, indent=1, sort_keys=True)
@@ -508,17 +513,21 @@ def write_tune_cache(path: str, key: str, shape) -> None:
 def autotune_cached(op: Op, prec: str = "f64", nrhs: int = 1, path: str | None = None):
     """Set the D-kernel shape for this operator from the cache file when it holds one for
     this lattice, precision, field count, device and kernel version; otherwise run the
-    tuner and store its choice. Returns ("cached" or "tuned", shape)."""
+    tuner and store its choice. Where the tuner keeps the default form, the entry says so and
+    a later call restores it. Returns ("cached" or "tuned", shape)."""
     torch = _torch()
     path = path or os.path.join(_HERE, "dw_shapes.json")
     key = tune_key(op.dims, prec, nrhs, torch.cuda.get_device_name(op.device), kernel_version())
     shape = read_tune_cache(path, key)
     if shape is not None:
-        set_dw_shape(op, prec, *shape)
+        if _tune_file(path)["default"].get(key) is True:
+            default_dw_shape(op, prec)
+        else:
+            set_dw_shape(op, prec, *shape)
         return "cached", shape
     autotune(op, prec, nrhs)
     shape = get_dw_shape(op, prec)
-    write_tune_cache(path, key, shape)
+    write_tune_cache(path, key, shape, dw_shape_is_default(op, prec))
     return "tuned", shape
 
 
@@ -533,6 +542,18 @@ def get_dw_shape(op: Op, prec: str = "f64"):
     out = (ctypes.c_int * 5)()
     _check(load().qdw_get_dw_shape(op.handle, PREC[prec], ctypes.byref(out)), "qdw_get_dw_shape")
     return tuple(out)
+
+
+def default_dw_shape(op: Op, prec: str = "f64"):
+    """Back to the default form of D, which chooses by the launch (qdw_default_dw_shape)."""
+    _check(load().qdw_default_dw_shape(op.handle, PREC[prec]), "qdw_default_dw_shape")
+
+
+def dw_shape_is_default(op: Op, prec: str = "f64") -> bool:
+    """Whether the default form holds: no shape was set or tuned for this precision."""
+    rc = load().qdw_dw_shape_is_default(op.handle, PREC[prec])
+    _check(min(rc, 0), "qdw_dw_shape_is_default")
+    return rc == 1
 
 
 def sap_gcr_solve_batched(ops, etas, psis, res: float = 1e-10, nmx: int = 2000, nkv: int = 16,
