@@ -172,19 +172,21 @@ def _torch():
     return torch
 
 
-_raw_stream = _current_device = None
+_stream_calls = None
 
 
 def _stream() -> int:
     """The handle of torch's current stream on the current device. (Small lattices are bound
     by the calls themselves: a Stream object and a device check per call cost more than the
-    launch, so the device is looked for once and the handle is asked for directly.)"""
-    global _raw_stream, _current_device
-    if _raw_stream is None:
+    launch, so the device is looked for once and the handle is asked for directly. Both calls
+    are kept in one name: another thread finds either none or both.)"""
+    global _stream_calls
+    if _stream_calls is None:
         torch = _torch()
         torch.cuda.current_stream()  # initialises the runtime
-        _raw_stream, _current_device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
-    return _raw_stream(_current_device())
+        _stream_calls = (torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice)
+    raw, device = _stream_calls
+    return raw(device())
 
 
 def _ptr(t) -> int:
