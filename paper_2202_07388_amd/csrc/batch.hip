@@ -52,14 +52,14 @@ struct Group {
     double* sc;                             // nr * B_SIZE
     int* fl;                                // nr * F_SIZE (inside one array for all groups)
     double* part;                           // nr * kPartStride
-    uint64_t* tick;                         // nr * kTicketWords
+    unsigned* tick;                         // nr * kTicketWords
     hipStream_t s;
 };
 
 // ---------------------------------------------------------------- batched map / finalise
 
 template <class F>
-__global__ __launch_bounds__(256) void bmap_kernel(Runs runs, F f, double* partials, uint64_t* tickets,
+__global__ __launch_bounds__(256) void bmap_kernel(Runs runs, F f, double* partials, unsigned* tickets,
                                                    double* sc, int off, int fin, int k,
                                                    const int* fl, int gate)
 {
@@ -73,7 +73,7 @@ __global__ __launch_bounds__(256) void bmap_kernel(Runs runs, F f, double* parti
         if (runs.holds(u)) f(u, acc, r);
     }
     if constexpr (F::NS > 0)
-        grid_sums<F::NS>(acc, {partials + r * kPartStride, tickets + (long)r * kTicketWords, 0,
+        grid_sums<F::NS>(acc, {partials + r * kPartStride, tickets + (long)r * kTicketWords,
                                sc + (long)r * B_SIZE + off, fin, k, nullptr},
                          blockIdx.x, gridDim.x);
 }
@@ -92,9 +92,9 @@ int brun(const Group& G, const F& f, int gate, hipStream_t st, int off = 0, int 
 }
 
 // the arrival counters of a group's reductions, zero before its first one
-__global__ void zero_tickets_kernel(uint64_t* t, int n)
+__global__ void zero_tickets_kernel(unsigned* t, int n)
 {
-    for (int q = blockIdx.x * blockDim.x + threadIdx.x; q < n; q += gridDim.x * blockDim.x) t[q] = 0;
+    for (int q = blockIdx.x * blockDim.x + threadIdx.x; q < n; q += gridDim.x * blockDim.x) t[q] = 0u;
 }
 
 // ---------------------------------------------------------------- functors (right-hand side r)
@@ -557,7 +557,7 @@ int plan(qdw_op* const* ops, int n, const qdw_sap_gcr_params& p, char* base,
         G.delta = sap ? take((size_t)G.fbs * G.nr) : nullptr;
         G.sc = (double*)take(sizeof(double) * B_SIZE * G.nr);
         G.part = (double*)take(sizeof(double) * kPartStride * G.nr);
-        G.tick = (uint64_t*)take(sizeof(uint64_t) * kTicketWords * G.nr);
+        G.tick = (unsigned*)take(sizeof(unsigned) * kTicketWords * G.nr);
         G.fl = flags ? flags + fo : nullptr;
         fo += G.nr * F_SIZE;
         G.s = nullptr;

@@ -160,9 +160,7 @@ __device__ inline void scalar_program(const double* sums, int ns, double* out, i
 
 struct Sums {
     double* partials;   // sum j of workgroup b at [j * workgroups + b]
-    uint64_t* ticket;   // kTicketWords
-    uint64_t launch;    // next_sums, or 0: the counters are zero and stay so between launches
-                        // (a captured launch, which comes again with the same arguments)
+    unsigned* ticket;   // kTicketWords, zero between launches
     double* out;        // scalar program's block
     int fin, k;
     double* host;       // pinned host memory for the sums themselves, or nullptr
@@ -177,22 +175,25 @@ __device__ __forceinline__ void agent_store(double* p, double v)
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// one more arrival at a counter of a launch; true for the last of n
-__device__ __forceinline__ bool arrive(uint64_t* at, uint64_t launch, unsigned n)
+// Arrival `which` of n at a counter; true for the one that completes them. Arrival 0 adds
+// 2^32 - (n - 1) and the others one each: the last one's addition carries, whichever it is, and
+// the counter is zero again by itself. Nothing sets it back, so no arrival can be lost. (A
+// counter that the last workgroup zeroed could lose one to another launch's, when two reductions
+// ran at a time; they spoil each other's sums, but then no later sum was completed either.)
+__device__ __forceinline__ bool arrive(unsigned* at, unsigned which, unsigned n)
 {
-    if (launch) __hip_atomic_fetch_max(at, launch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const uint64_t before = __hip_atomic_fetch_add(at, (uint64_t)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (before != launch + n - 1) return false;
-    if (!launch) __hip_atomic_store(at, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return true;
+    if (n == 1) return true;
+    const unsigned mine = which == 0 ? 1u - n : 1u;
+    return __hip_atomic_fetch_add(at, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > ~mine;
 }
 
 // one lane per workgroup; true for the last of nblk
-__device__ __forceinline__ bool last_arrival(uint64_t* ticket, uint64_t launch, unsigned blk, unsigned nblk)
+__device__ __forceinline__ bool last_arrival(unsigned* ticket, unsigned blk, unsigned nblk)
 {
-    const unsigned ng = nblk < (unsigned)kTickets ? nblk : (unsigned)kTickets;
-    const unsigned gr = blk % ng, in_group = (nblk - gr + ng - 1) / ng;
-    return arrive(ticket + 16 * (1 + gr), launch, in_group) && arrive(ticket, launch, ng);
+    constexpr unsigned NG = kTickets;
+    if (nblk < NG) return arrive(ticket, blk, nblk);
+    const unsigned gr = blk % NG;
+    return arrive(ticket + 32 * (1 + gr), blk / NG, (nblk - gr + NG - 1) / NG) && arrive(ticket, gr, NG);
 }
 
 __device__ __forceinline__ double wave_sum(double v)
@@ -272,7 +273,7 @@ __device__ __forceinline__ void grid_sums(const double* acc, const Sums& s, unsi
         }
         // the workgroup's partial sums are in memory before its arrival is counted
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        if (lane == 0) last = last_arrival(s.ticket, s.launch, blk, nblk);
+        if (lane == 0) last = last_arrival(s.ticket, blk, nblk);
     }
     __syncthreads();
     if (!last) return;
@@ -337,7 +338,7 @@ int run_map(const qdw_op* op, const F& f, hipStream_t st, double* out = nullptr,
             double* host = nullptr)
 {
     const Runs r = runs_of(op->g, even_half, back);
-    const Sums s = {op->partials, op->tickets, F::NS > 0 ? next_sums(op) : 0, out ? out : op->scalars, fin, k, host};
+    const Sums s = {op->partials, op->tickets, out ? out : op->scalars, fin, k, host};
     map_kernel<F><<<map_blocks<F::NS>(r.nw), 256, 0, st>>>(r, f, s);
     QDW_LAUNCH_CHECK();
     return QDW_OK;

@@ -1238,7 +1238,7 @@ int schur_launch(qdw_op* op, const void* in, void* out, int prec, bool dag, hipS
 
 int cg_apply(qdw_op* op, const void* p, void* q, int prec, bool schur, int ring, hipStream_t st)
 {
-    const Epi e = {{op->partials, op->tickets, next_sums(op), op->scalars, FIN_CG_ALPHA, ring, nullptr}, nullptr, nullptr};
+    const Epi e = {{op->partials, op->tickets, op->scalars, FIN_CG_ALPHA, ring, nullptr}, nullptr, nullptr};
     const RhsTable tab = one_field(p, q);
     return by_precision(prec, [&](auto P) {
         return schur ? schur_launch_t<P.value, false, EPI_NORM>(op, p, q, e, st)
@@ -1249,7 +1249,7 @@ int cg_apply(qdw_op* op, const void* p, void* q, int prec, bool schur, int ring,
 int cg_apply_dag(qdw_op* op, const void* q, void* r, void* t, int prec, bool schur, double* host,
                  hipStream_t st)
 {
-    const Epi e = {{op->partials, op->tickets, next_sums(op), op->scalars, FIN_CG_BETA, 0, host}, r, op->scalars};
+    const Epi e = {{op->partials, op->tickets, op->scalars, FIN_CG_BETA, 0, host}, r, op->scalars};
     const RhsTable tab = one_field(q, r);
     return by_precision(prec, [&](auto P) {
         return schur ? schur_launch_t<P.value, true, EPI_STEP>(op, q, t, e, st)

@@ -96,10 +96,10 @@ __device__ inline long shifted(const Geom& g, const int x[4], int mu, int dmu, i
 
 // *p = 0 and the arrival counters of the reductions (a kernel, not a memset node, so the
 // set-up can be captured)
-__global__ void zero_scratch_kernel(unsigned long long* p, uint64_t* tickets)
+__global__ void zero_scratch_kernel(unsigned long long* p, unsigned* tickets)
 {
     if (threadIdx.x == 0) *p = 0ull;
-    for (int k = threadIdx.x; k < kTicketWords; k += blockDim.x) tickets[k] = 0;
+    for (int k = threadIdx.x; k < kTicketWords; k += blockDim.x) tickets[k] = 0u;
 }
 
 __global__ void unitarity_kernel(const double* su3, long nlinks, unsigned long long* worst)
@@ -515,7 +515,7 @@ OpLayout op_layout(int Vh, size_t max_blocks)
     const size_t c54[4] = {27 * 16, 14 * 16, 7 * 16, 7 * 16};  // compact clover, bytes per site
     for (int p = 0; p < 4; ++p) L.clover54[p] = take(ns * c54[p]);
     L.partials = take(sizeof(double) * std::max((size_t)kMaxPartials * kMaxScalars, max_blocks));
-    L.tickets = take(sizeof(uint64_t) * kTicketWords);
+    L.tickets = take(sizeof(unsigned) * kTicketWords);
     L.scalars = take(sizeof(double) * kMaxScalars);
     L.worst = take(sizeof(unsigned long long));
     L.total = off + 256;  // room to align the caller's pointer
@@ -609,7 +609,7 @@ extern "C" int qdw_create(const qdw_lattice* lat, const double* su3, const doubl
         op->clover54[p] = base + lay.clover54[p];
     }
     op->partials = (double*)(base + lay.partials);
-    op->tickets = (uint64_t*)(base + lay.tickets);
+    op->tickets = (unsigned*)(base + lay.tickets);
     op->scalars = (double*)(base + lay.scalars);
     op->host_scalars = (double*)host_mem;
     // reductions write what the host waits for straight into its block; a block that the

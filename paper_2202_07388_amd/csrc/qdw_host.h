@@ -27,11 +27,10 @@ struct qdw_op {
     // kernels use g
     struct { int ts, nt, pipe, walk, march; } dw_shape[4];
     bool dw_auto[4];       // per precision: the shape is the default one, not a caller's choice
-    // reduction scratch: per-workgroup partial sums, the arrival counters of the workgroups, the
-    // number of launches they have counted, and the final scalars
+    // reduction scratch: per-workgroup partial sums, the arrival counters of the workgroups
+    // (zero between launches) and the final scalars
     double* partials;      // device, kMaxPartials * kMaxScalars doubles, or one per site workgroup
-    uint64_t* tickets;     // device, kTicketWords words
-    mutable uint64_t nsums;
+    unsigned* tickets;     // device, kTicketWords words
     double* scalars;       // device, kMaxScalars doubles
     double* host_scalars;  // pinned host, kHostScalars doubles
     double* host_dev;      // the same block as kernels address it (nullptr: not mapped)
@@ -43,16 +42,7 @@ constexpr int kMaxPartials = 2048;  // workgroups of a reduction launch
 // arrivals are counted in two levels, kTickets counters (one per 128 bytes) and a top one,
 // so that thousands of workgroups do not meet on one address
 constexpr int kTickets = 32;
-constexpr int kTicketWords = (kTickets + 1) * 16;
-// A counter of an operator holds the number of the launch it counts for above kArrivalBits bits
-// of arrivals: whatever an earlier launch has left there, the first arrival of a later one
-// starts anew. (Zeroed by the last workgroup instead, counters that two launches at a time had
-// mixed up would have spoiled every later sum of the operator.)
-constexpr int kArrivalBits = 24;
-inline uint64_t next_sums(const qdw_op* op)
-{
-    return __atomic_add_fetch(&op->nsums, 1, __ATOMIC_RELAXED) << kArrivalBits;
-}
+constexpr int kTicketWords = (kTickets + 1) * 32;
 constexpr int kMaxScalars = 64;     // doubles produced by one fused reduction
 constexpr int kHostScalars = 1024;  // doubles the host can read back in one copy
 constexpr int kMaxRhs = 64;         // right-hand sides of one multi-right-hand-side launch
