@@ -145,7 +145,7 @@ __device__ __forceinline__ void hop_half(const Geom& g, const int x[4], const Ho
 #pragma unroll
         for (int c = 0; c < 6; ++c) h[c] = -h[c];
     }
-    su3_mul<R, !FWD>(b.u, b.d, h, w);
+    su3_mul<R, !FWD, true>(b.u, b.d, h, w);
 }
 
 // acc += U (1 -+ gamma) psi(x + mu)  or  U^+ (1 +- gamma) psi(x - mu), times the boundary
@@ -426,7 +426,7 @@ void dw_march_kernel(Geom g, const void* __restrict__ links, const void* __restr
 #pragma unroll
             for (int q = 0; q < 6; ++q) h[q] = {-h[q].re, -h[q].im};
         }
-        su3_mul<R, true>(u, d, h, w);
+        su3_mul<R, true, true>(u, d, h, w);
     };
     // A psi plus the six spatial hops (scaled by -1/2) of this lane's site at slice tt, the
     // slice in `tile`
@@ -486,7 +486,7 @@ void dw_march_kernel(Geom g, const void* __restrict__ links, const void* __restr
             const R f = (g.bc_t < 0 && t == g.L[0] - 1) ? (R)0.5 : (R)-0.5;
 #pragma unroll
             for (int q = 0; q < 6; ++q) h[q] = scale(h[q], f);
-            su3_mul<R, false>(u0, d0, h, w);
+            su3_mul<R, false, true>(u0, d0, h, w);
             expand_add<R, 0, SGF>(w, acc);
             // -t: already transported by the partner
 #pragma unroll
@@ -599,7 +599,7 @@ void dw_hand_kernel(Geom g, const void* __restrict__ links, const void* __restri
 #pragma unroll
             for (int q = 0; q < 6; ++q) h[q] = {-h[q].re, -h[q].im};
         }
-        su3_mul<R, true>(u, d, h, w);
+        su3_mul<R, true, true>(u, d, h, w);
         put6(pw, slot, partner, w);
     };
     // A psi plus the six spatial hops (scaled by -1/2) of this lane's site at slice tt,
@@ -651,7 +651,7 @@ void dw_hand_kernel(Geom g, const void* __restrict__ links, const void* __restri
                 const R f = (g.bc_t < 0 && t == g.L[0] - 1) ? (R)0.5 : (R)-0.5;
 #pragma unroll
                 for (int q = 0; q < 6; ++q) h[q] = scale(h[q], f);
-                su3_mul<R, false>(u0, d0, h, w);
+                su3_mul<R, false, true>(u0, d0, h, w);
                 expand_add<R, 0, SGF>(w, acc);
                 // -t: already transported by the partner
                 get6(pw, t & 1, w);

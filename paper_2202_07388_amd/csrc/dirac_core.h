@@ -122,14 +122,17 @@ __device__ __forceinline__ void load_link(const void* links, const void* dets, i
 }
 
 // w = U h (DAGGER: U^+ h) for both spin components of the half spinor h; row 2 of U is
-// rebuilt as d * conj(row0 x row1). Every fused operation is written out, so all kernels form
-// the same bits.
-template <typename R, bool DAGGER>
+// rebuilt as d * conj(row0 x row1). FIXED: with the fused operations of the products written
+// out, so that every kernel forms the same bits (the operator's kernels; the block solves are
+// at the limit of their registers, and the FP16 one spills with it).
+template <typename R, bool DAGGER, bool FIXED = false>
 __device__ __forceinline__ void su3_mul(const cx<R> u[6], cx<R> d, const cx<R> h[6], cx<R> w[6])
 {
-    const cx<R> r2[3] = {cprod(d, conj_(cmadd(cprod(u[1], u[5]), -u[2], u[4]))),
-                         cprod(d, conj_(cmadd(cprod(u[2], u[3]), -u[0], u[5]))),
-                         cprod(d, conj_(cmadd(cprod(u[0], u[4]), -u[1], u[3])))};
+    auto mul = [](cx<R> a, cx<R> b) { return FIXED ? cprod(a, b) : a * b; };
+    auto mul_conj = [](cx<R> a, cx<R> b) { return FIXED ? cprod_conj(a, b) : cmul_conj(a, b); };
+    const cx<R> r2[3] = {mul(d, conj_(cmadd(mul(u[1], u[5]), -u[2], u[4]))),
+                         mul(d, conj_(cmadd(mul(u[2], u[3]), -u[0], u[5]))),
+                         mul(d, conj_(cmadd(mul(u[0], u[4]), -u[1], u[3])))};
     const cx<R> m[9] = {u[0], u[1], u[2], u[3], u[4], u[5], r2[0], r2[1], r2[2]};
 #pragma unroll
     for (int a = 0; a < 2; ++a) {
@@ -137,9 +140,9 @@ __device__ __forceinline__ void su3_mul(const cx<R> u[6], cx<R> d, const cx<R> h
 #pragma unroll
         for (int r = 0; r < 3; ++r) {
             if (!DAGGER)
-                w[3 * a + r] = cmadd(cmadd(cprod(m[3 * r], h0), m[3 * r + 1], h1), m[3 * r + 2], h2);
+                w[3 * a + r] = cmadd(cmadd(mul(m[3 * r], h0), m[3 * r + 1], h1), m[3 * r + 2], h2);
             else
-                w[3 * a + r] = cmadd_conj(cmadd_conj(cprod_conj(m[r], h0), m[3 + r], h1), m[6 + r], h2);
+                w[3 * a + r] = cmadd_conj(cmadd_conj(mul_conj(m[r], h0), m[3 + r], h1), m[6 + r], h2);
         }
     }
 }

@@ -519,10 +519,11 @@ struct SiteDiag54 {
 // block's links (each read from HBM once) are in LDS, so a step needs two barriers (residuals
 // written; sums written) and a lane keeps only its residual, the correction and the compact
 // diagonal term in registers. That lets three 256-site blocks share a CU with 16-bit storage
-// (two with FP32). The form before it handed the backward hops over through LDS (48 KB more),
-// kept links and the full clover blocks in registers and took four barriers a step, at two
-// blocks per CU (one with FP32). One application at 24^3 x 48 (5 cycles, 4 steps, 4^4 blocks),
-// before and after: FP16 1729 -> 1480 us, BF16 1668 -> 1443, FP32 3426 -> 2400.
+// (two with FP32). One application at 24^3 x 48 (5 cycles, 4 steps, 4^4 blocks): FP16 1447 us,
+// BF16 1439, FP32 2386; 1729, 1668 and 3426 with the backward hops handed over through 48 KB
+// more of LDS, links and full clover blocks in registers and four barriers a step, at two
+// blocks per CU (one with FP32). At three waves per SIMD BF16, whose widening takes a register
+// more, keeps 11 of its registers in memory; at two it needs no memory and takes 1605 us.
 template <int SP>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SP == F32 ? 2 : 3)))
 void sap_mr_kernel(Geom g, BlockGeom B, int colour, int nmr, void* __restrict__ rs, void* __restrict__ psis,

@@ -28,7 +28,8 @@ def code_objects(data):
         at = data.find(MAGIC, at + 24)
 
 
-def test_operator_kernels_do_not_spill(tmp_path):
+def spills(tmp_path, pattern):
+    """How many kernels of the library match, and those of them that spill registers."""
     if not os.path.exists(qdw.LIB_PATH) or not os.path.exists(READELF):
         pytest.skip("needs the built library and llvm-readelf")
     seen, spilled = 0, []
@@ -40,9 +41,21 @@ def test_operator_kernels_do_not_spill(tmp_path):
         notes = subprocess.run([READELF, "--notes", str(path)], capture_output=True, text=True, check=True).stdout
         for kernel in notes.split(".agpr_count")[1:]:
             field = lambda k: re.search(r"\.%s: +(\S+)" % k, kernel).group(1)  # noqa: E731
-            if not re.search(r"\d+(dw_\w+?|schur)_kernelI", field("symbol")):
+            if not re.search(pattern, field("symbol")):
                 continue
             seen += 1
             if int(field("vgpr_spill_count")) or int(field("private_segment_fixed_size")):
                 spilled.append((field("symbol"), field("vgpr_spill_count")))
+    return seen, spilled
+
+
+def test_operator_kernels_do_not_spill(tmp_path):
+    seen, spilled = spills(tmp_path, r"\d+(dw_\w+?|schur)_kernelI")
     assert seen > 40 and not spilled, spilled
+
+
+def test_block_solves_do_not_spill(tmp_path):
+    """Storage in FP32 and FP16, and the reduced blocks in every type (the plain BF16 one keeps
+    11 registers in memory: three waves per SIMD are faster with them than two without)."""
+    seen, spilled = spills(tmp_path, r"\d+sap_mr_kernelILi[12]E|\d+sap_mr_eo_kernelI")
+    assert seen == 8 and not spilled, spilled
